@@ -4,15 +4,17 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libquasar.so")
-SOURCES = ["quasar_api.hip"]
-HEADERS = ["quasar_device.hpp", "stream_gemm.hpp", "stream_sequence.hpp", "stream_w8a8.hpp", "stream_w4.hpp", "drafter.hpp", "attention.hpp", "sample.hpp", "pack.hpp", "probe.hpp"]
+SOURCES = ["quasar_api.hip", "direct_int8.hip", "direct_bf16.hip"]
+HEADERS = ["quasar_device.hpp", "launch.hpp", "stream_gemm.hpp", "stream_direct.hpp", "stream_sequence.hpp", "stream_w8a8.hpp", "stream_w4.hpp", "drafter.hpp", "attention.hpp", "sample.hpp", "pack.hpp", "probe.hpp"]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed-fp32 vector instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # the whole-step kernel keeps rarely executed phase-entry code inside a fully unrolled round;
@@ -30,16 +32,28 @@ def hipcc() -> str:
 
 
 def build_library(verbose: bool = False, extra_flags=()) -> str:
-    cmd = [hipcc(), *HIPCC_FLAGS, *extra_flags, "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
+    """Compiles the sources side by side and links them."""
+    with tempfile.TemporaryDirectory() as tmp:
+        objects = [os.path.join(tmp, src + ".o") for src in SOURCES]
+        jobs = [[hipcc(), *HIPCC_FLAGS, *extra_flags, "-c", "-o", obj, os.path.join(CSRC, src)]
+                for src, obj in zip(SOURCES, objects)]
+        link = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objects]
+        with ThreadPoolExecutor(max_workers=len(jobs)) as pool:
+            for _ in pool.map(lambda cmd: _run(cmd, verbose), jobs):
+                pass
+        _run(link, verbose)
+    return LIB
+
+
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    lines = [l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l and l.strip()]
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout)
+    lines = [l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l and l.strip()]
     if verbose and lines:
-        print("\n".join(lines))
-    return LIB
+        print("\n".join(lines), flush=True)
 
 
 if __name__ == "__main__":

@@ -14,6 +14,7 @@
 
 #include "pack.hpp"
 #include "probe.hpp"
+#include "launch.hpp"
 #include "stream_gemm.hpp"
 #include "stream_sequence.hpp"
 #include "sample.hpp"
@@ -26,7 +27,6 @@ using namespace quasar;
 
 namespace {
 
-constexpr int kMaxLds = 160 * 1024;          // gfx950 LDS per compute unit
 constexpr int kSingleChunkX = 128 * 1024;    // activation bytes allowed when K needs no chunking
 constexpr int kMultiChunkX = 96 * 1024;      // activation bytes per chunk otherwise
 constexpr int kMinLds = 82 * 1024;           // > half the LDS: at most one workgroup per compute unit
@@ -130,29 +130,6 @@ Plan make_plan(int T, int S, int x_bytes_per_step, int unit_bytes, int NW, bool 
     return pl;
 }
 
-// Kernels that use more than the default dynamic LDS limit need a one-time opt-in per
-// function (and per device); remember which ones have had it.
-bool allow_large_lds(const void *fn) {
-    static std::mutex mu;
-    static std::vector<std::pair<const void *, int>> done;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    std::lock_guard<std::mutex> lock(mu);
-    for (const auto &e : done)
-        if (e.first == fn && e.second == dev) return true;
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess) return false;
-    done.emplace_back(fn, dev);
-    return true;
-}
-
-template <typename KernelT>
-int launch(KernelT kernel, int grid, int block, int lds_bytes, hipStream_t stream, const GemmParams &p) {
-    if (lds_bytes > kMaxLds) return QUASAR_ERR_SHAPE;
-    if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return QUASAR_ERR_HIP;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds_bytes, stream, p);
-    return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
-}
-
 // K split across workgroups for the bf16-activation linear: how many slices (1 = no split) and
 // steps per slice, such that the activations of one slice fit the LDS in one piece.
 void splitk_shape(int M, int S, bool w16, int &ksplit, int &slice_steps) {
@@ -179,6 +156,121 @@ void splitk_shape(int M, int S, bool w16, int &ksplit, int &slice_steps) {
 }
 size_t splitk_bytes(int M, int N, int ksplit) { return ksplit > 1 ? (size_t)ksplit * M * N * sizeof(float) : 0; }
 
+// ---- launches of the kernel that holds the activations in registers (stream_direct.hpp) ----
+
+// Register forms that are built: slots of 64 k per wave and tile.  What bounds them is the register file: a slot takes
+// 4, 8 or 16 registers at up to 8, 16 or 32 tokens.
+constexpr int kDirectSlots8[] = {1, 2, 3, 4, 5, 6, 8, 12};
+constexpr int kDirectSlots16[] = {1, 2, 3, 4, 5, 6, 8, 16, 20, 24};     // (16 and more: of eight waves)
+constexpr int kDirectSlots32[] = {2, 4, 6, 8, 10};
+
+// Smallest built form for `need` slots, at most `most` of them (0: none).
+int direct_form(int MP, int need, int most) {
+    auto pick = [&](const int *v, int n) {
+        for (int i = 0; i < n; ++i)
+            if (v[i] >= need && v[i] <= most) return v[i];
+        return 0;
+    };
+    if (MP == 8) return pick(kDirectSlots8, (int)(sizeof(kDirectSlots8) / sizeof(int)));
+    if (MP == 16) return pick(kDirectSlots16, (int)(sizeof(kDirectSlots16) / sizeof(int)));
+    return pick(kDirectSlots32, (int)(sizeof(kDirectSlots32) / sizeof(int)));
+}
+
+// The activations' rows are addressed with 32-bit byte offsets.
+bool direct_reach(int M, long long ldx) { return ldx * 2 * M < (1ll << 32); }
+
+// Plan for T tiles (handed out in units of TU) of S slots, K summed in C chunks of SC slots, split into ksplit slices
+// over workgroups.  keep_bytes: LDS behind the row scales (the kept gate tile), pre: LDS sums of the fused
+// normalisation.  False: no built form holds the activations, the LDS does not hold the partial tiles, or a chunk has
+// fewer steps than waves.
+bool plan_direct(int MP, int T, int TU, int S, int SC, int C, int ksplit, bool with_scales, int most_slots, int keep_bytes,
+                 bool pre, DirectPlan &d) {
+    if (g_tune_nw.load() != 16 || g_tune_wgs.load() != 1) return false;      // launch shapes asked for by hand
+    int NW = direct_waves(MP, 1);
+    // 16 tokens: the forms of eight waves where a slice is too long for those of sixteen
+    if (MP == 16 && C == 1 && most_slots > 8 && (S + ksplit - 1) / ksplit > 8 * 16) NW = 8;
+    d.ksplit = ksplit;
+    d.slice_steps = (S + ksplit - 1) / ksplit;
+    if (ksplit > 1) {
+        // whole multiples of the wave count where that costs no slice
+        const int up = (d.slice_steps + NW - 1) / NW * NW;
+        if ((S + up - 1) / up == ksplit) d.slice_steps = up;
+        if ((S + d.slice_steps - 1) / d.slice_steps != ksplit) return false;
+        SC = d.slice_steps;
+        C = 1;
+    }
+    if (C > 1 && (SC < NW || S - (C - 1) * SC < NW)) return false;
+    // the largest share of a wave: the ceiling of each chunk's steps over the waves
+    const int last = ksplit > 1 ? SC : S - (C - 1) * SC;
+    const int need = (C - 1) * ((SC + NW - 1) / NW) + (last + NW - 1) / NW;
+    d.XS = direct_form(MP, need, most_slots);
+    if (!d.XS || direct_waves(MP, d.XS) != NW) return false;
+    d.SC = SC;
+    d.C = C;
+    int groups = device_cus() / ksplit;
+    const int units = T / TU;
+    if (groups < 1) return false;
+    if (groups > units) groups = units;
+    const int least = (T + kMaxTilesPerWg - 1) / kMaxTilesPerWg;
+    if (groups < least) groups = least;
+    if ((long long)groups * ksplit > kMaxGrid) return false;
+    d.groups = groups;
+    const int tpw = TU * ((units + groups - 1) / groups);
+    d.sc_bytes = (with_scales ? ((tpw * kTileRows * 2 + 15) / 16) * 16 : 0) + keep_bytes;
+    d.lds_bytes = direct_region_bytes(MP, d.XS, C) + d.sc_bytes + (pre ? NW * MP * 4 : 0);
+    if (d.lds_bytes > kMaxLds) return false;
+    if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+    return true;
+}
+
+// How many slices a K that would otherwise be staged in chunks is split into: the cheapest of 1, 2, 4, .. by the bytes
+// that the busiest compute unit moves.  Measured rates: 25 KB/us of weights and 75 KB/us of activations per compute
+// unit; a split adds its partial sums (written, read and added by a second launch: 4 us and its bytes at 4 MB/us).
+bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t workspace_bytes, int most_slots, DirectPlan &best) {
+    double best_us = 0.0;
+    bool found = false;
+    for (int ks = 1; ks <= 16; ks *= 2) {
+        DirectPlan d{};
+        if (ks > 1 && splitk_bytes(M, N, ks) > workspace_bytes) break;
+        if (!plan_direct(MP, T, 1, S, S, 1, ks, !w16, most_slots, 0, false, d)) continue;
+        const int tpw = (T + d.groups - 1) / d.groups;
+        double us = (double)tpw * d.slice_steps * (w16 ? 2.0 : 1.0) / 25.0 + (double)MP * d.slice_steps * 0.125 / 75.0;
+        if (ks > 1) us += 4.0 + 8.0 * ks * M * N / 4.0e6;
+        if (!found || us < best_us) { best = d; best_us = us; found = true; }
+    }
+    return found;
+}
+
+// Plan of the ordered forms (linear without a workspace, argmax): the sum is taken in the order of the whole-step
+// launch, so K is summed in the chunks that it stages (SC, C in its own steps).  More than 16 tokens: that order is one
+// of 16 waves, which the 8-wave form does not have.
+bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, DirectPlan &d) {
+    if (MP == 32) return false;
+    const int per = w16 ? 2 : 1;                     // steps per slot; a wave's share must be whole slots
+    if (w16) {
+        const int last = 2 * S - (C - 1) * SC;
+        if (SC % 32 || last % 32) return false;
+    }
+    if (C > 1) {
+        // forms built: see launch_direct
+        if (!plan_direct(MP, T, 1, S, SC / per, C, 1, !w16, MP == 8 ? 12 : 8, 0, false, d)) return false;
+        if (MP == 8 && d.XS < 8) d.XS = 8;
+        if (MP == 16 && d.XS < 4) d.XS = 4;
+        d.lds_bytes = direct_region_bytes(MP, d.XS, C) + d.sc_bytes;
+        if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+        return d.lds_bytes <= kMaxLds;
+    }
+    return plan_direct(MP, T, 1, S, S, 1, 1, !w16, MP == 8 ? 12 : 8, 0, false, d);
+}
+
+template <bool W16>
+int launch_splitk_finalize(const GemmParams &p, int ksplit, int M, hipStream_t stream) {
+    const long long quads = (long long)M * (p.N / 4);
+    hipLaunchKernelGGL(splitk_finalize_kernel<W16>, dim3((unsigned int)((quads + 255) / 256)), dim3(256), 0, stream,
+                       p.part32, ksplit, M, p.N, p.scales, p.y, p.ldy);
+    return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
+}
+
 template <bool W16, int EPI>
 int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out, void *workspace = nullptr,
                 size_t workspace_bytes = 0) {
@@ -189,6 +281,22 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     const int NB = MP == 32 ? 2 : 1;
     const int NW = g_tune_nw.load();
     Plan pl = make_plan(p.T, p.S, (W16 ? 64 : 128) * MP, NB * 1024, NW, !W16);
+    {
+        // Activations in registers wherever a form holds them; with a workspace the order of the sum is free and a
+        // long K may be split across workgroups, without one it is that of the chunked kernel below.
+        const int slots = p.K / 64;
+        const bool free_order = EPI == EPI_LINEAR && workspace && aligned(workspace, 16) && (pl.C > 1 || MP == 32);
+        DirectPlan d{};
+        const bool ok = !direct_reach(M, p.ldx) ? false : free_order ? plan_direct_split(MP, M, p.T, slots, W16, p.N, workspace_bytes, MP == 8 ? 12 : (MP == 16 ? 24 : 10), d)
+                                   : plan_direct_ordered(MP, p.T, slots, W16, pl.SC, pl.C, d);
+        if (ok) {
+            if (d.ksplit > 1) p.part32 = static_cast<float *>(workspace);
+            if (grid_out) *grid_out = d.groups * d.ksplit;
+            const int rc = launch_direct(W16, EPI, PRE_NONE, false, p, MP, d, stream);
+            if (rc != QUASAR_OK || d.ksplit == 1) return rc;
+            return launch_splitk_finalize<W16>(p, d.ksplit, M, stream);
+        }
+    }
     int launch_grid = pl.grid;
     if (EPI == EPI_LINEAR && pl.C > 1 && NW == 16 && workspace && aligned(workspace, 16)) {
         int ksplit = 1, slice_steps = p.S;
@@ -223,10 +331,7 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     else rc = QUASAR_LAUNCH(32);
 #undef QUASAR_LAUNCH
     if (rc != QUASAR_OK || p.ksplit == 1) return rc;
-    const long long quads = (long long)M * (p.N / 4);
-    hipLaunchKernelGGL(splitk_finalize_kernel<W16>, dim3((unsigned int)((quads + 255) / 256)), dim3(256), 0, stream,
-                       p.part32, p.ksplit, M, p.N, p.scales, p.y, p.ldy);
-    return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
+    return launch_splitk_finalize<W16>(p, p.ksplit, M, stream);
 }
 
 int launch_valu(const GemmParams &base, int M, hipStream_t stream) {
@@ -550,6 +655,9 @@ int launch_logits(const GemmParams &base, int M, hipStream_t stream) {
     p.ksplit = 1;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NB = MP == 32 ? 2 : 1;
+    DirectPlan d{};
+    if (direct_reach(M, p.ldx) && plan_direct(MP, p.T, 1, p.S, p.S, 1, 1, true, MP == 8 ? 12 : (MP == 16 ? 24 : 10), 0, false, d))
+        return launch_direct(false, EPI_LOGITS, PRE_NONE, false, p, MP, d, stream);
     const Plan pl = make_plan(p.T, p.S, 128 * MP, NB * 1024, 16, true);
     if (pl.grid > kMaxGrid) return QUASAR_ERR_SHAPE;
     p.SC = pl.SC;
@@ -592,6 +700,15 @@ int launch_fused(const GemmParams &base, int M, hipStream_t stream) {
     p.ksplit = 1;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NB = MP == 32 ? 2 : 1;
+    {
+        // (with a normalisation its gamma takes registers beside the activations until they are scaled)
+        const int most = PRE == PRE_NONE ? (MP == 8 ? 12 : (MP == 16 ? 24 : 10)) : (MP == 8 ? 8 : (MP == 16 ? 5 : 6));
+        DirectPlan d{};
+        if (direct_reach(M, p.ldx) &&
+            plan_direct(MP, p.T, EPI == EPI_SWIGLU ? 2 : 1, p.S, p.S, 1, 1, true, most, EPI == EPI_SWIGLU ? NB * 1024 : 0,
+                        PRE != PRE_NONE, d))
+            return launch_direct(false, EPI, PRE, RES, p, MP, d, stream);
+    }
     Plan pl = make_plan(p.T, p.S, 128 * MP, NB * 1024, 16, true);
     int lds = pl.lds_bytes;
     int sc_bytes = pl.sc_bytes;
@@ -1326,8 +1443,7 @@ int quasar_w8_linear_fused(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
     if (gamma)
         return residual ? launch_fused<EPI_LINEAR, PRE_RMSNORM, true>(p, m, st)
                         : launch_fused<EPI_LINEAR, PRE_RMSNORM, false>(p, m, st);
-    return residual ? launch_fused<EPI_LINEAR, PRE_NONE, true>(p, m, st)
-                    : launch_fused<EPI_LINEAR, PRE_NONE, false>(p, m, st);
+    return residual ? launch_fused<EPI_LINEAR, PRE_NONE, true>(p, m, st) : launch_mfma<false, EPI_LINEAR>(p, m, st, nullptr);
 }
 
 int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,

@@ -1,0 +1,400 @@
+// Skinny-M weight streaming with the activations held in registers (gfx950).
+//
+// The 16 waves of a workgroup split K, so a wave meets the same activations at every weight tile: its K slice of all
+// M tokens.  That slice is M x K / 16 values - at M = 8, K = 4096 sixteen registers a lane - and this kernel loads it
+// once into the matrix instruction's B operand registers: no staging for the workgroup and no barrier in front of the
+// stream, no LDS reads in the main loop; the weight loads are requested in the same breath as the activations.  The kernel that stages x in LDS (stream_gemm.hpp) remains for shapes whose slice
+// does not fit the registers.
+//
+// At M <= 8 half of the B operand's 16 columns have no token.  A slot's 64 k of a token are two operands of 32; lanes
+// of columns 0 .. 7 load the first and lanes of columns 8 .. 15 the second, one full 1 KB load a slot, and the second
+// operand is the same register rotated by eight lanes (the unused columns multiply rubbish that nobody reads).
+//
+// What bounds it: a launch whose compute units read nothing but the 16 MB of a 4096 x 4096 matrix takes 3.9 us back to
+// back (48 MB: 8.6 us); the rest is the fetch of x (as many bytes per compute unit as its weights at M = 8) and the
+// tile end.  Back to back, HBM-cold, int8, us a launch, staged kernel -> this one:
+//     M = 8:  1024 x 1024 5.1 -> 3.5, 4096 x 4096 7.2 -> 5.7, 12288 x 4096 11.7 -> 10.6, 4096 x 12288 13.9 -> 11.5
+//     M = 16: 4096 x 4096 9.4 -> 6.5, 12288 x 4096 14.8 -> 11.3, 4096 x 8192 14.3 -> 9.9
+//     M = 32: 4096 x 4096 13.0 -> 7.9, 12288 x 4096 22.9 -> 12.6
+// Fetching x: straight into the registers, or, for more of it, in whole cache lines through the wave's own piece of LDS
+// (direct_pass).  Weights requested before x: 0.4 us slower; workgroups that start at different K slices, rows of x at
+// other strides: no difference.
+#pragma once
+
+#include "launch.hpp"
+
+namespace quasar {
+
+// lanes i of every row of 16 <- lanes (i + 8) mod 16
+__device__ __forceinline__ u32x4 rotate_half_row(const u32x4 v) {
+    u32x4 r;
+    r.x = __builtin_amdgcn_update_dpp(0, (int)v.x, 0x128, 0xf, 0xf, true);
+    r.y = __builtin_amdgcn_update_dpp(0, (int)v.y, 0x128, 0xf, 0xf, true);
+    r.z = __builtin_amdgcn_update_dpp(0, (int)v.z, 0x128, 0xf, 0xf, true);
+    r.w = __builtin_amdgcn_update_dpp(0, (int)v.w, 0x128, 0xf, 0xf, true);
+    return r;
+}
+
+// Slots in flight per wave: a compute unit accepts about 32 KB of outstanding loads, so three or four 1 KB loads in
+// each of 16 waves keep it full; up to eight where the registers allow.
+constexpr int direct_ring(int MP, int slots) {
+    return slots <= 6 ? slots : (slots == 8 ? (MP == 16 ? 4 : 8) : (slots % 5 == 0 ? 5 : (slots == 24 ? 6 : 4)));
+}
+
+// A slot is 64 k: one 1 KB load of int8 codes or two of bf16 weights.
+// XS: slots of a tile a wave may have (its activations are held in XS x (MP == 8 ? 4 : MP / 2) registers).
+// CH: K is summed in p.C chunks, each reduced over the waves by itself and added in chunk order (the bits of the
+//     kernels that stage x in chunks); otherwise one sum.
+// LDS: [a region per wave: activations on their way in, then 2 x C x NB partial tiles of 1 KB][row scales][kept gate tile (EPI_SWIGLU)][16 x MP sums (PRE)]
+template <int MP, bool W16, int EPI, int XS, bool CH = false, int PRE = PRE_NONE, bool RES = false>
+__global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kernel(const GemmParams p0) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int NW = direct_waves(MP, XS);
+    constexpr int NB = (MP == 32) ? 2 : 1;          // 16-token blocks
+    constexpr int XP = (MP == 8) ? 1 : 2;           // loads of x per slot and token block
+    constexpr int WL = W16 ? 2 : 1;                 // weight loads per slot
+    constexpr int U = XS >= 4 ? 1 : 4 / XS;         // tiles per round: at least four slots in flight
+    constexpr int RD = direct_ring(MP, XS * U);     // ring depth in slots
+    static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
+    constexpr int kSlotBytes = WL * kStepBytes;
+
+    GemmParams p = p0;
+    int G = gridDim.x, b = blockIdx.x, slice = 0;
+    if (p0.ksplit > 1) {
+        slice = b % p0.ksplit;
+        b = b / p0.ksplit;
+        G = G / p0.ksplit;
+        const int s0 = slice * p0.slice_steps;      // (all step counts here are in slots of 64 k)
+        p.S = min(p0.slice_steps, p0.S - s0);
+        p.w = p0.w + (long long)s0 * (64 * WL);
+        p.x = p0.x + (long long)s0 * 64;
+    }
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, mcol = lane & 15;
+
+    constexpr int TU = EPI == EPI_SWIGLU ? 2 : 1;   // tiles are handed out in units of TU
+    const int t0 = TU * tile_split(p.T / TU, b, G);
+    const int t1 = TU * tile_split(p.T / TU, b + 1, G);
+    const int ntiles = t1 - t0;
+    const int C = CH ? p.C : 1;
+
+    // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
+    constexpr int kPass = direct_pass(MP, XS);
+    const int region = max(kPass * MP * 128, 2 * C * NB * 1024);
+    unsigned char *own = lds + w * region;
+    uint16_t *sc_lds = reinterpret_cast<uint16_t *>(lds + NW * region);                // [tiles][16]
+    [[maybe_unused]] f32x4 *gate_keep = reinterpret_cast<f32x4 *>(lds + NW * region + p.sc_bytes - NB * 1024);
+
+    // ---- the wave's slots: slot i of a tile is step[i] of it.  Chunk c covers steps c * SC .., wave w takes the w-th of
+    // 16 shares of each.  Slots beyond the wave's last step repeat its first: their loads hit lines it has just
+    // requested, and they are not multiplied.
+    int n = 0, first = 0, bound0 = 0;
+    int step[XS];
+    if constexpr (CH) {
+        int c = 0, at = 0, left = 0;
+        first = (min(p.SC, p.S) * w) / NW;
+#pragma unroll
+        for (int i = 0; i < XS; ++i) {
+            if (left == 0 && c < C) {
+                const int scc = min(p.SC, p.S - c * p.SC);
+                at = c * p.SC + (scc * w) / NW;
+                left = (scc * (w + 1)) / NW - (scc * w) / NW;     // >= 1: chunks have at least 16 steps
+                if (c == 0) bound0 = left;
+                ++c;
+            }
+            step[i] = left > 0 ? at : first;
+            if (left > 0) { ++n; ++at; --left; }
+        }
+    } else {
+        first = (p.S * w) / NW;
+        n = (p.S * (w + 1)) / NW - first;
+#pragma unroll
+        for (int i = 0; i < XS; ++i) step[i] = i < n ? first + i : min(first, p.S - 1);
+    }
+
+    // ---- requests: activations, row scales, weight ring
+    const int tok = (MP == 8) ? (mcol & 7) : mcol;
+    u32x4 xr[XS][NB * XP];
+    const int kofs = W16 ? 8 * g + ((MP == 8) ? 32 * (mcol >> 3) : 0) : 16 * g + ((MP == 8) ? 8 * (mcol >> 3) : 0);
+    const uint16_t *xrow[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) xrow[nb] = p.x + (long long)min(tok + 16 * nb, p.M - 1) * p.ldx + kofs;
+    auto load_x = [&](int i) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int q = 0; q < XP; ++q)
+                xr[i][nb * XP + q] = *reinterpret_cast<const u32x4 *>(xrow[nb] + 64 * step[i] + (W16 ? 32 : 8) * q);
+    };
+    // through LDS: slots at .. at + kPass - 1, each instruction 128 bytes of eight tokens' rows, piece c of token t at
+    // position c ^ (t & 7) of its 128 bytes (the lanes that read one column of pieces meet different banks)
+    [[maybe_unused]] auto fetch_x = [&](int at) {
+        const unsigned int base = lds_address_of(lds) + (unsigned int)(w * region);
+        const unsigned long long xa = reinterpret_cast<unsigned long long>(p.x);
+#pragma unroll
+        for (int t8 = 0; t8 < MP / 8; ++t8) {
+            const int t = (lane >> 3) + 8 * t8;
+            const unsigned int off = (unsigned int)min(t, p.M - 1) * (unsigned int)(2 * p.ldx) + (unsigned int)(((lane & 7) ^ (t & 7)) * 16);
+#pragma unroll
+            for (int i = 0; i < kPass; ++i)
+                if (at + i < XS) load_to_lds_16(xa + 128ull * (unsigned int)step[at + i], off, base + (i * (MP / 8) + t8) * 1024);
+        }
+    };
+    [[maybe_unused]] auto read_x = [&](int at) {
+#pragma unroll
+        for (int i = 0; i < kPass; ++i)
+            if (at + i < XS)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int q = 0; q < XP; ++q) {
+                        const int t = tok + 16 * nb, half = MP == 8 ? mcol >> 3 : q;
+                        const int c = W16 ? 4 * half + g : 2 * g + half;
+                        xr[at + i][nb * XP + q] = *reinterpret_cast<const u32x4 *>(
+                            own + (i * (MP / 8) + (t >> 3)) * 1024 + (t & 7) * 128 + ((c ^ (t & 7)) * 16));
+                    }
+    };
+    if constexpr (kPass > 0) {
+        fetch_x(0);
+    } else {
+        // the slots of the first turn of the ring before the ring's loads, the others behind them
+#pragma unroll
+        for (int i = 0; i < (XS < RD || PRE != PRE_NONE ? XS : RD); ++i) load_x(i);
+    }
+    // gamma: requested with the activations where the registers hold both, else when the row sums are known
+    constexpr bool kGammaEarly = 4 * XS * (NB + 1) * XP + 4 * RD <= (MP == 32 ? 160 : 84);
+    [[maybe_unused]] u32x4 gm[PRE == PRE_RMSNORM ? XS : 1][XP];
+    [[maybe_unused]] auto load_gamma = [&](int i) {
+#pragma unroll
+        for (int q = 0; q < XP; ++q) gm[i][q] = *reinterpret_cast<const u32x4 *>(p.pre_arg + kofs + 64 * step[i] + 8 * q);
+    };
+    if constexpr (PRE == PRE_RMSNORM && kGammaEarly)
+#pragma unroll
+        for (int i = 0; i < XS; ++i) load_gamma(i);
+    [[maybe_unused]] unsigned int sc_first = 0;
+    if constexpr (!W16) {
+        if (2 * tid < ntiles * kTileRows)
+            sc_first = *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + 2 * tid);
+    }
+    u32x2 resid[NB];
+    load_residual<RES, NB>(p, t0 + min(w, ntiles - 1), lane, resid);
+
+    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w) + (unsigned long long)t0 * p.Srow * kSlotBytes;
+    const unsigned int tile_bytes = (unsigned int)p.Srow * (unsigned int)kSlotBytes;
+    u32x4 ring[RD][WL];
+    // refill of ring entry d with slot i of tile tl; beyond the workgroup's last tile every lane reads the same 16 bytes
+    auto refill = [&](int d, int tl, int i) {
+        const bool real = tl < ntiles;
+        const unsigned long long a = real ? wbase + (unsigned long long)tl * tile_bytes + (unsigned int)step[i] * (unsigned int)kSlotBytes
+                                          : reinterpret_cast<unsigned long long>(p.x);
+        unsigned int off = real ? 16u * lane : 0u;
+#pragma unroll
+        for (int j = 0; j < WL; ++j) ring[d][j] = ring_refill_at(a + (real ? j * kStepBytes : 0), off, ring[d][j]);
+    };
+#pragma unroll
+    for (int d = 0; d < RD; ++d) {
+#pragma unroll
+        for (int j = 0; j < WL; ++j) ring[d][j] = u32x4{0u, 0u, 0u, 0u};
+        refill(d, d / XS, d % XS);
+    }
+    if constexpr (kPass > 0) {
+        // the direct-to-LDS loads were issued first and loads return in order: once no more than the ring's are
+        // outstanding they are in LDS, where only this wave reads them
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RD * WL) : "memory");
+        read_x(0);
+#pragma unroll
+        for (int at = kPass; at < XS; at += kPass) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            fetch_x(at);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            read_x(at);
+        }
+    } else if constexpr (PRE == PRE_NONE) {
+#pragma unroll
+        for (int i = RD; i < XS; ++i) load_x(i);
+    }
+
+    // ---- what the activations need before they are operands
+    if constexpr (!W16) {
+        if (2 * tid < ntiles * kTileRows) reinterpret_cast<unsigned int *>(sc_lds)[tid] = sc_first;
+        for (int i = 2 * (tid + NW * 64); i < ntiles * kTileRows; i += 2 * NW * 64)
+            reinterpret_cast<unsigned int *>(sc_lds)[i >> 1] =
+                *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + i);
+    }
+    if constexpr (PRE == PRE_RMSNORM) {
+        // sum of squares per token: this lane's values, the lanes of the token, then the waves in order
+        float *red = reinterpret_cast<float *>(lds + NW * region + p.sc_bytes);    // [NW][MP]
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float ss = 0.f;
+#pragma unroll
+            for (int i = 0; i < XS; ++i)
+#pragma unroll
+                for (int q = 0; q < XP; ++q) {
+                    const float s = piece_sumsq(xr[i][nb * XP + q]);
+                    ss += i < n ? s : 0.f;
+                }
+            ss += __shfl_xor(ss, 16, 64);
+            ss += __shfl_xor(ss, 32, 64);
+            if constexpr (MP == 8) ss += __shfl_xor(ss, 8, 64);
+            if (lane < (MP == 8 ? 8 : 16)) red[w * MP + lane + 16 * nb] = ss;
+        }
+        lds_barrier();
+        float r[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float tot = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < NW; ++ww) tot += red[ww * MP + tok + 16 * nb];
+            r[nb] = __fdiv_rn(1.0f, __fsqrt_rn(__fdiv_rn(tot, (float)p.K) + p.eps));
+        }
+#pragma unroll
+        for (int i = 0; i < XS; ++i) {
+            if constexpr (!kGammaEarly) load_gamma(i);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int q = 0; q < XP; ++q) xr[i][nb * XP + q] = pre_rmsnorm_piece(xr[i][nb * XP + q], gm[i][q], r[nb]);
+        }
+    }
+
+    f32x4 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bestv[NB];
+    unsigned int besti[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) { bestv[nb] = -__builtin_inff(); besti[nb] = 0x7FFFFFFFu; }
+    int parity = 0;
+
+    // one slot: 64 k of a tile into the accumulators
+    auto slot = [&](int d, int i) {
+        bf16x8 a[2];
+        if constexpr (W16) {
+            a[0] = __builtin_bit_cast(bf16x8, ring[d][0]);
+            a[1] = __builtin_bit_cast(bf16x8, ring[d][WL - 1]);
+        } else {
+            a[0] = codes_to_bf16x8(ring[d][0].x, ring[d][0].y);
+            a[1] = codes_to_bf16x8(ring[d][0].z, ring[d][0].w);
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const u32x4 b0 = xr[i][nb * XP];
+            const u32x4 b1 = MP == 8 ? rotate_half_row(b0) : xr[i][nb * XP + XP - 1];
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], __builtin_bit_cast(bf16x8, b0), acc[nb], 0, 0, 0);
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], __builtin_bit_cast(bf16x8, b1), acc[nb], 0, 0, 0);
+        }
+    };
+    auto hand_over = [&](int c) {
+        f32x4 *st = reinterpret_cast<f32x4 *>(own) + (parity * C + c) * NB * 64;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            st[nb * 64 + lane] = acc[nb];
+            acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    // tile end: cross-wave sum through LDS, neighbouring waves in pairs, the pair sums in order, the chunks in order
+    auto tile_end = [&](int tl) {
+        lds_barrier();
+        if (w == (tl % NW)) {
+            f32x4 rsum[NB];
+            for (int c = 0; c < C; ++c) {
+                const unsigned char *st = lds + ((parity * C + c) * NB * 64 + lane) * 16;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb, st += 1024) {
+                    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int w0 = 0; w0 < NW; w0 += 8)         // (a loop: bounds the registers of the reads in flight)
+#pragma unroll
+                        for (int ww = w0; ww < w0 + 8; ww += 2)
+                            s += *reinterpret_cast<const f32x4 *>(st + ww * region) +
+                                 *reinterpret_cast<const f32x4 *>(st + (ww + 1) * region);
+                    rsum[nb] = c > 0 ? s + rsum[nb] : s;
+                }
+            }
+            finish_tile<W16, EPI, RES, NB>(p, rsum, t0 + tl, sc_lds + tl * kTileRows, resid, gate_keep, slice, lane, bestv, besti);
+            if (RES) load_residual<RES, NB>(p, t0 + min(tl + NW, ntiles - 1), lane, resid);      // of this wave's next tile
+        }
+        parity ^= 1;
+    };
+    auto round = [&](int tl0, auto last) {
+        constexpr bool kLast = decltype(last)::value;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int tl = tl0 + u;
+            int c = 0;
+            [[maybe_unused]] int bound = bound0;
+#pragma unroll
+            for (int i = 0; i < XS; ++i) {
+                constexpr int R = RD;
+                const int j = u * XS + i;
+                if (i < n && (U == 1 || tl < ntiles)) slot(j % R, i);
+                if (!kLast || j + R < U * XS) {
+                    const int jn = j + R;
+                    refill(j % R, tl0 + (jn / (U * XS)) * U + (jn % (U * XS)) / XS, jn % XS);
+                }
+                if constexpr (CH) {
+                    if (i + 1 == bound) {
+                        hand_over(c);
+                        ++c;
+                        if (c < C) {
+                            const int scc = min(p.SC, p.S - c * p.SC);
+                            bound += (scc * (w + 1)) / NW - (scc * w) / NW;
+                        }
+                    }
+                }
+            }
+            if (U == 1 || tl < ntiles) {
+                if constexpr (!CH) hand_over(0);
+                tile_end(tl);
+            }
+        }
+    };
+    int tl0 = 0;
+    for (; tl0 + U < ntiles; tl0 += U) round(tl0, std::false_type{});
+    round(tl0, std::true_type{});
+
+    if constexpr (EPI == EPI_ARGMAX) publish_argmax<MP, NB, NW>(bestv, besti, lds, p.partial + (long long)b * MP);
+}
+
+// ---- dispatch over the built forms ----
+
+template <int MP, bool W16, int EPI, bool CH, int PRE, bool RES, int... XS>
+int launch_direct_forms(int xs, int grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
+    int rc = QUASAR_ERR_SHAPE;
+    ((xs == XS ? (void)(rc = launch(stream_direct_kernel<MP, W16, EPI, XS, CH, PRE, RES>, grid, direct_waves(MP, XS) * 64, lds_bytes,
+                                    stream, p))
+               : (void)0), ...);
+    return rc;
+}
+template <bool W16, int EPI, int PRE, bool RES>
+int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStream_t stream) {
+    GemmParams p = base;
+    p.S = p.Srow = p.K / 64;
+    p.SC = d.SC;
+    p.C = d.C;
+    p.ksplit = d.ksplit;
+    p.slice_steps = d.slice_steps;
+    p.sc_bytes = d.sc_bytes;
+    p.xs_bytes = 0;
+    const int grid = d.groups * d.ksplit;
+    if constexpr (PRE == PRE_NONE && !RES && (EPI == EPI_LINEAR || EPI == EPI_ARGMAX)) {
+        if (d.C > 1) {
+            if (MP == 8) return launch_direct_forms<8, W16, EPI, true, PRE, RES, 8, 12>(d.XS, grid, d.lds_bytes, stream, p);
+            return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
+        }
+    }
+    if constexpr (PRE != PRE_NONE) {
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
+    } else {
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 12>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 16, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
+    }
+}
+
+}  // namespace quasar

@@ -156,6 +156,120 @@ struct WaveWalk {
     }
 };
 
+template <bool RES, int NB>
+__device__ __forceinline__ void load_residual(const GemmParams &p, int tile, int lane, u32x2 (&resid)[NB]) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        resid[nb] = u32x2{0u, 0u};
+        if constexpr (RES) {
+            const int m = (lane & 15) + 16 * nb;
+            if (m < p.M) resid[nb] = *reinterpret_cast<const u32x2 *>(p.resid + m * p.ldr + tile * kTileRows + 4 * (lane >> 4));
+        }
+    }
+}
+
+// Epilogue of one 16-row tile, run by the one wave that holds its finished sums: rsum[nb] lane l = 16 g + i is
+// rows 4 g .. 4 g + 3 of token i + 16 nb.  row_scales: the tile's 16 step sizes in LDS; resid: the residual's values
+// of these rows and tokens (RES, load_residual).
+template <bool W16, int EPI, bool RES, int NB>
+__device__ __forceinline__ void finish_tile(const GemmParams &p, const f32x4 (&rsum)[NB], int tile, const uint16_t *row_scales,
+                                            const u32x2 (&resid)[NB], f32x4 *gate_keep, int slice, int lane,
+                                            float (&bestv)[NB], unsigned int (&besti)[NB]) {
+    const int g = lane >> 4, mcol = lane & 15;
+    const int n0 = tile * kTileRows + 4 * g;
+    float s4[4] = {1.f, 1.f, 1.f, 1.f};
+    if constexpr (!W16) {
+        const u32x2 sb = *reinterpret_cast<const u32x2 *>(row_scales + 4 * g);
+        s4[0] = bf16_bits_to_float(sb.x & 0xFFFFu);
+        s4[1] = bf16_bits_to_float(sb.x >> 16);
+        s4[2] = bf16_bits_to_float(sb.y & 0xFFFFu);
+        s4[3] = bf16_bits_to_float(sb.y >> 16);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int m = mcol + 16 * nb;
+        const float v0 = rsum[nb].x * s4[0], v1 = rsum[nb].y * s4[1];
+        const float v2 = rsum[nb].z * s4[2], v3 = rsum[nb].w * s4[3];
+        if constexpr (EPI == EPI_SWIGLU) {
+            // both projections are rounded to bf16 as separate linears would be
+            const f32x4 r = {bf16_bits_to_float(float_to_bf16_bits(v0)),
+                             bf16_bits_to_float(float_to_bf16_bits(v1)),
+                             bf16_bits_to_float(float_to_bf16_bits(v2)),
+                             bf16_bits_to_float(float_to_bf16_bits(v3))};
+            if ((tile & 1) == 0) {
+                gate_keep[nb * 64 + lane] = r;      // read by the next tile's reducer, after a barrier
+            } else if (m < p.M) {
+                const f32x4 gt = gate_keep[nb * 64 + lane];
+                u32x2 o;
+                o.x = float_to_bf16_bits(silu_bf16(gt.x) * r.x) | (float_to_bf16_bits(silu_bf16(gt.y) * r.y) << 16);
+                o.y = float_to_bf16_bits(silu_bf16(gt.z) * r.z) | (float_to_bf16_bits(silu_bf16(gt.w) * r.w) << 16);
+                *reinterpret_cast<u32x2 *>(p.y + m * p.ldy + (tile >> 1) * kTileRows + 4 * g) = o;
+            }
+        } else if constexpr (EPI == EPI_LOGITS) {
+            if (m < p.M)
+                *reinterpret_cast<f32x4 *>(p.part32 + (long long)m * p.N + n0) =
+                    f32x4{v0, v1, v2, v3};
+        } else if constexpr (EPI == EPI_LINEAR) {
+            if (m < p.M) {
+                if (p.ksplit > 1) {
+                    *reinterpret_cast<f32x4 *>(p.part32 + ((long long)slice * p.M + m) * p.N + n0) =
+                        rsum[nb];
+                } else if constexpr (RES) {
+                    // y = bf16( bf16(linear) + residual ), as a bf16 block computes it
+                    const u32x2 rr = resid[nb];
+                    const float r0 = bf16_bits_to_float(float_to_bf16_bits(v0)) + bf16_bits_to_float(rr.x & 0xFFFFu);
+                    const float r1 = bf16_bits_to_float(float_to_bf16_bits(v1)) + __uint_as_float(rr.x & 0xFFFF0000u);
+                    const float r2 = bf16_bits_to_float(float_to_bf16_bits(v2)) + bf16_bits_to_float(rr.y & 0xFFFFu);
+                    const float r3 = bf16_bits_to_float(float_to_bf16_bits(v3)) + __uint_as_float(rr.y & 0xFFFF0000u);
+                    u32x2 o;
+                    o.x = float_to_bf16_bits(r0) | (float_to_bf16_bits(r1) << 16);
+                    o.y = float_to_bf16_bits(r2) | (float_to_bf16_bits(r3) << 16);
+                    *reinterpret_cast<u32x2 *>(p.y + m * p.ldy + n0) = o;
+                } else {
+                    u32x2 o;
+                    o.x = float_to_bf16_bits(v0) | (float_to_bf16_bits(v1) << 16);
+                    o.y = float_to_bf16_bits(v2) | (float_to_bf16_bits(v3) << 16);
+                    *reinterpret_cast<u32x2 *>(p.y + m * p.ldy + n0) = o;
+                }
+            }
+        } else {
+            // strictly greater keeps the lowest index inside a lane
+            if (v0 > bestv[nb]) { bestv[nb] = v0; besti[nb] = n0; }
+            if (v1 > bestv[nb]) { bestv[nb] = v1; besti[nb] = n0 + 1; }
+            if (v2 > bestv[nb]) { bestv[nb] = v2; besti[nb] = n0 + 2; }
+            if (v3 > bestv[nb]) { bestv[nb] = v3; besti[nb] = n0 + 3; }
+        }
+    }
+}
+
+// The workgroup's (value, index) keys of its MP tokens from its waves' running maxima: combine the four k-groups' row
+// subsets in each wave, then the waves, then publish.  scratch: NW x MP keys of LDS (any region all waves are done with).
+template <int MP, int NB, int NW>
+__device__ __forceinline__ void publish_argmax(const float (&bestv)[NB], const unsigned int (&besti)[NB],
+                                               unsigned char *scratch, unsigned long long *out) {
+    unsigned long long *red = reinterpret_cast<unsigned long long *>(scratch);   // [NW][MP]
+    const int tid = threadIdx.x, w = tid >> 6, g = (tid & 63) >> 4, mcol = tid & 15;
+    lds_barrier();   // all tile-end reads of the staging area are done
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        unsigned long long key = argmax_key(bestv[nb], besti[nb]);
+        unsigned long long o = shfl_xor_u64(key, 16);
+        key = o > key ? o : key;
+        o = shfl_xor_u64(key, 32);
+        key = o > key ? o : key;
+        if (g == 0 && (MP != 8 || mcol < 8)) red[w * MP + mcol + 16 * nb] = key;
+    }
+    lds_barrier();
+    if (tid < MP) {
+        unsigned long long key = red[tid];
+        for (int ww = 1; ww < NW; ++ww) {
+            const unsigned long long o = red[ww * MP + tid];
+            key = o > key ? o : key;
+        }
+        out[tid] = key;
+    }
+}
+
 // ------------------------------------------------------------------------------------
 // MFMA variant.  A operand = 16 weight rows x 32 k (bf16, converted in registers from the
 // int8 codes), B operand = 32 k x 16 tokens from LDS, D = 16 rows x 16 tokens fp32.
@@ -491,70 +605,10 @@ __global__ __launch_bounds__(NW * 64) void stream_mfma_kernel(const GemmParams p
                             }
                         }
                         if (c == p.C - 1) {
-                            const int n0 = (t0 + tl) * kTileRows + 4 * g;
-                            float s4[4] = {1.f, 1.f, 1.f, 1.f};
-                            if constexpr (!W16) {
-                                const u32x2 sb = *reinterpret_cast<const u32x2 *>(sc_lds + tl * kTileRows + 4 * g);
-                                s4[0] = bf16_bits_to_float(sb.x & 0xFFFFu);
-                                s4[1] = bf16_bits_to_float(sb.x >> 16);
-                                s4[2] = bf16_bits_to_float(sb.y & 0xFFFFu);
-                                s4[3] = bf16_bits_to_float(sb.y >> 16);
-                            }
-#pragma unroll
-                            for (int nb = 0; nb < NB; ++nb) {
-                                const int m = mcol + 16 * nb;
-                                const float v0 = rsum[nb].x * s4[0], v1 = rsum[nb].y * s4[1];
-                                const float v2 = rsum[nb].z * s4[2], v3 = rsum[nb].w * s4[3];
-                                if constexpr (EPI == EPI_SWIGLU) {
-                                    // both projections are rounded to bf16 as separate linears would be
-                                    const f32x4 r = {bf16_bits_to_float(float_to_bf16_bits(v0)),
-                                                     bf16_bits_to_float(float_to_bf16_bits(v1)),
-                                                     bf16_bits_to_float(float_to_bf16_bits(v2)),
-                                                     bf16_bits_to_float(float_to_bf16_bits(v3))};
-                                    if (((t0 + tl) & 1) == 0) {
-                                        gate_keep[nb * 64 + lane] = r;      // read by the next tile's reducer, after a barrier
-                                    } else if (m < p.M) {
-                                        const f32x4 gt = gate_keep[nb * 64 + lane];
-                                        u32x2 o;
-                                        o.x = float_to_bf16_bits(silu_bf16(gt.x) * r.x) | (float_to_bf16_bits(silu_bf16(gt.y) * r.y) << 16);
-                                        o.y = float_to_bf16_bits(silu_bf16(gt.z) * r.z) | (float_to_bf16_bits(silu_bf16(gt.w) * r.w) << 16);
-                                        *reinterpret_cast<u32x2 *>(p.y + m * p.ldy + ((t0 + tl) >> 1) * kTileRows + 4 * g) = o;
-                                    }
-                                } else if constexpr (EPI == EPI_LOGITS) {
-                                    if (m < p.M)
-                                        *reinterpret_cast<f32x4 *>(p0.part32 + (long long)m * p.N + n0) =
-                                            f32x4{v0, v1, v2, v3};
-                                } else if constexpr (EPI == EPI_LINEAR) {
-                                    if (m < p.M) {
-                                        if (p0.ksplit > 1) {
-                                            *reinterpret_cast<f32x4 *>(p0.part32 + ((long long)slice * p.M + m) * p.N + n0) =
-                                                rsum[nb];
-                                        } else if constexpr (RES) {
-                                            // y = bf16( bf16(linear) + residual ), as a bf16 block computes it
-                                            const u32x2 rr = *reinterpret_cast<const u32x2 *>(p.resid + m * p.ldr + n0);
-                                            const float r0 = bf16_bits_to_float(float_to_bf16_bits(v0)) + bf16_bits_to_float(rr.x & 0xFFFFu);
-                                            const float r1 = bf16_bits_to_float(float_to_bf16_bits(v1)) + __uint_as_float(rr.x & 0xFFFF0000u);
-                                            const float r2 = bf16_bits_to_float(float_to_bf16_bits(v2)) + bf16_bits_to_float(rr.y & 0xFFFFu);
-                                            const float r3 = bf16_bits_to_float(float_to_bf16_bits(v3)) + __uint_as_float(rr.y & 0xFFFF0000u);
-                                            u32x2 o;
-                                            o.x = float_to_bf16_bits(r0) | (float_to_bf16_bits(r1) << 16);
-                                            o.y = float_to_bf16_bits(r2) | (float_to_bf16_bits(r3) << 16);
-                                            *reinterpret_cast<u32x2 *>(p.y + m * p.ldy + n0) = o;
-                                        } else {
-                                            u32x2 o;
-                                            o.x = float_to_bf16_bits(v0) | (float_to_bf16_bits(v1) << 16);
-                                            o.y = float_to_bf16_bits(v2) | (float_to_bf16_bits(v3) << 16);
-                                            *reinterpret_cast<u32x2 *>(p.y + m * p.ldy + n0) = o;
-                                        }
-                                    }
-                                } else {
-                                    // strictly greater keeps the lowest index inside a lane
-                                    if (v0 > bestv[nb]) { bestv[nb] = v0; besti[nb] = n0; }
-                                    if (v1 > bestv[nb]) { bestv[nb] = v1; besti[nb] = n0 + 1; }
-                                    if (v2 > bestv[nb]) { bestv[nb] = v2; besti[nb] = n0 + 2; }
-                                    if (v3 > bestv[nb]) { bestv[nb] = v3; besti[nb] = n0 + 3; }
-                                }
-                            }
+                            u32x2 resid[NB];
+                            load_residual<RES, NB>(p, t0 + tl, lane, resid);
+                            finish_tile<W16, EPI, RES, NB>(p0, rsum, t0 + tl, sc_lds + tl * kTileRows, resid, gate_keep, slice, lane,
+                                                           bestv, besti);
                         }
                     }
                     parity ^= 1;
@@ -568,27 +622,7 @@ __global__ __launch_bounds__(NW * 64) void stream_mfma_kernel(const GemmParams p
     }
 
     if constexpr (EPI == EPI_ARGMAX) {
-        // per wave: combine the four k-groups' row subsets, then combine waves, then publish
-        unsigned long long *red = reinterpret_cast<unsigned long long *>(stage);   // [NW][MP]
-        lds_barrier();   // all tile-end reads of the staging area are done
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            unsigned long long key = argmax_key(bestv[nb], besti[nb]);
-            unsigned long long o = shfl_xor_u64(key, 16);
-            key = o > key ? o : key;
-            o = shfl_xor_u64(key, 32);
-            key = o > key ? o : key;
-            if (g == 0 && (MP != 8 || mcol < 8)) red[w * MP + mcol + 16 * nb] = key;
-        }
-        lds_barrier();
-        if (tid < MP) {
-            unsigned long long key = red[tid];
-            for (int ww = 1; ww < NW; ++ww) {
-                const unsigned long long o = red[ww * MP + tid];
-                key = o > key ? o : key;
-            }
-            p.partial[(long long)b * MP + tid] = key;
-        }
+        publish_argmax<MP, NB, NW>(bestv, besti, lds + p.xs_bytes + p.sc_bytes, p.partial + (long long)b * MP);
     }
 }
 
@@ -769,7 +803,7 @@ __global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part3
     *reinterpret_cast<u32x2 *>(y + m * ldy + n0) = o;
 }
 
-__global__ __launch_bounds__(1024) void verify_finalize_kernel(const unsigned long long *partial, int nparts,
+[[maybe_unused]] static __global__ __launch_bounds__(1024) void verify_finalize_kernel(const unsigned long long *partial, int nparts,
                                                                int MP, int M, int V, const int32_t *draft,
                                                                int n_draft, int32_t *out_argmax,
                                                                int32_t *out_accept) {

@@ -1,0 +1,79 @@
+"""The streaming kernel that holds its activations in registers: every register form (slots of 64 k per wave), ragged shares
+of K over the waves, tile remainders, both weight types.  Without a workspace its sums are taken in the order of the kernel
+that stages the activations in LDS, so the two must agree bit for bit; with one, and for the fused forms, the outputs are held
+to the bar of the linear (one bf16 rounding of an fp32 sum: 4e-3 of max|y|) against a 64-bit product of the same codes."""
+import pytest
+import torch
+
+from paper_2603_01399_amd import synth
+from gpu_util import bf16_to_dev, f32_to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def qb():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2603_01399_amd import binding
+    return binding
+
+
+def bits(t):
+    return t.contiguous().view(torch.int16)
+
+
+def rel(y, want):
+    return float((y.double() - want).abs().max() / want.abs().max())
+
+
+def make(qb, M, N, K):
+    x = bf16_to_dev(synth.activations_bf16(M, K, seed=synth.seed_for(20, M, K)))
+    w = f32_to_dev(synth.normal_weights(N, K, seed=synth.seed_for(21, M, K)))
+    wq, sc = qb.quantize_weights(w)
+    what = qb.unpack_weights(wq, N, K).double() * sc.double()[:, None]
+    return x, w, wq, sc, what
+
+
+# K: one step; fewer steps than waves; 17, 33, 49, 65, 81 steps (two to six slots, ragged); eight slots; two chunks
+KS = [64, 960, 1088, 2112, 3136, 4160, 5184, 6208, 7680, 8192, 12288]
+
+
+@pytest.mark.parametrize("K", KS)
+@pytest.mark.parametrize("M,N", [(1, 16), (8, 16 * 261), (9, 16 * 261), (16, 16 * 40), (17, 16 * 261), (32, 16 * 40)])
+def test_linear_forms(qb, M, N, K):
+    print("direct linear", M, N, K, flush=True)
+    x, w, wq, sc, what = make(qb, M, N, K)
+    want = x.double() @ what.t()
+    wp = qb.pack_bf16_weights(w)
+    want16 = x.double() @ w.to(torch.bfloat16).double().t()
+    ws = qb.make_workspace(M, N, K)
+    ws.fill_(0xFF)
+    plain, plain16 = qb.w8_linear(x, wq, sc, N), qb.bf16_linear(x, wp, N)
+    free, free16 = qb.w8_linear(x, wq, sc, N, workspace=ws), qb.bf16_linear(x, wp, N, workspace=ws)
+    for y, ref in ((plain, want), (free, want), (plain16, want16), (free16, want16)):
+        assert rel(y, ref) <= 4e-3
+    qb.set_tuning(16, 2, 4)                    # two workgroups per compute unit: the staged kernel
+    try:
+        staged, staged16 = qb.w8_linear(x, wq, sc, N), qb.bf16_linear(x, wp, N)
+    finally:
+        qb.set_tuning(16, 1, 4)
+    assert torch.equal(bits(plain), bits(staged)) and torch.equal(bits(plain16), bits(staged16))
+
+
+@pytest.mark.parametrize("K", [64, 1088, 3136, 4160, 6208, 12288])
+@pytest.mark.parametrize("M", [3, 8, 16, 32])
+def test_fused_forms(qb, M, K):
+    N = 16 * 22
+    print("direct fused", M, N, K, flush=True)
+    x, _, wq, sc, what = make(qb, M, N, K)
+    gamma = bf16_to_dev(synth.activations_bf16(1, K, seed=synth.seed_for(22, M, K)))[0].contiguous()
+    res = bf16_to_dev(synth.activations_bf16(M, N, seed=synth.seed_for(23, M, K)))
+    xd = x.double()
+    norm = ((xd * torch.rsqrt((xd * xd).mean(1, keepdim=True) + 1e-6)).bfloat16().double() * gamma.double()).bfloat16().double()
+    lin = norm @ what.t()
+    assert rel(qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, eps=1e-6), lin) <= 6e-3
+    assert rel(qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, eps=1e-6, residual=res), lin.bfloat16().double() + res.double()) <= 6e-3
+    assert rel(qb.w8_linear_fused(x, wq, sc, N, residual=res), (xd @ what.t()).bfloat16().double() + res.double()) <= 6e-3
+    gu = lin.bfloat16().double().view(M, N // 32, 2, 16)
+    act = (torch.nn.functional.silu(gu[:, :, 0]).bfloat16().double() * gu[:, :, 1]).reshape(M, N // 2)
+    assert rel(qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, eps=1e-6), act) <= 1e-2
