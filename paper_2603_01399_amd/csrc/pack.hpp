@@ -20,67 +20,190 @@ __device__ __forceinline__ float load_w(const void *w, long long idx) {
     else
         return reinterpret_cast<const float *>(w)[idx];
 }
-// element k of a row, with the offline side of the smoothing transformation applied
-// (W diag(s)^-1, one fp32 division) when a smoothing vector is given
-template <bool SRC_BF16>
-__device__ __forceinline__ float load_w_smoothed(const void *w, long long row_base, int k, const float *smooth) {
-    const float v = load_w<SRC_BF16>(w, row_base + k);
-    return smooth ? __fdiv_rn(v, smooth[k]) : v;
+
+// rint(v / s) of the quotient of one IEEE division.  v * inv, inv the rounded reciprocal, is within 2^-23 of the quotient
+// relatively, the rounded quotient within 2^-24: below 256 that is 4.6e-5, so both round alike unless the product lies closer
+// than that to a half (one element in ten thousand), where the division is made.  Not-finite products make it too.
+__device__ __forceinline__ float rounded_ratio(float v, float s, float inv) {
+    const float q = v * inv;
+    float r = rintf(q);
+    if (!(fabsf(q - r) < 0.49995f)) r = rintf(__fdiv_rn(v, s));
+    return r;
 }
 
-// One workgroup (256 threads) per 16-row tile.
-template <bool SRC_BF16>
-__global__ __launch_bounds__(256) void quantize_pack_kernel(const void *w, long long ldw, int N, int K,
-                                                            const float *smooth, u32x4 *packed, uint16_t *scales) {
-    __shared__ float row_scale[kTileRows];
-    const int tid = threadIdx.x;
+// One workgroup of 8 waves per 16-row tile; a wave owns two rows.  Bound by memory (4 or 2 bytes in, 1 out per weight), so
+// a row is read once, 16 bytes a lane and load, and kept in registers (NJ loads a lane) from its maximum to its codes; of
+// longer rows the maximum is taken first and the row read again.  The tile's codes meet in LDS in packed order - slots of
+// 16 rows x 16 k, 16 bytes further apart than their length, so that the lanes of a store meet different banks - and leave in
+// contiguous 16-byte pieces.  Up to K = 4096 two workgroups share a compute unit: one converts while the other's rows
+// arrive.  With scalar loads, two passes and 16-byte
+// pieces stored row by row -> now, us: 12288 x 4096 fp32 240 -> 47 (5.4 TB/s), bf16 165 -> 33, fp32 smoothed 209 -> 67;
+// 25600 x 5120 fp32 632 -> 162, bf16 (read twice) 432 -> 135; 1024 x 1024 fp32 15.6 -> 8.5.
+// VEC: rows (and smooth) start on 16 bytes; otherwise the same elements are read one by one.
+constexpr int kQuantWaves = 8;
+constexpr int kQuantSlotBytes = kTileRows * 16 + 16;
+
+template <bool SRC_BF16, bool SMOOTH, bool VEC, int NJ>
+__global__ __launch_bounds__(kQuantWaves * 64, NJ > 16 ? 2 : 4) void quantize_pack_kernel(const void *w, long long ldw, int K,
+                                                                                        const float *smooth, u32x4 *packed,
+                                                                                        uint16_t *scales) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int VE = SRC_BF16 ? 8 : 4;              // elements per lane and load
+    constexpr int kSpan = NJ * 64 * VE;               // k of a row that a wave holds
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t = blockIdx.x;
-    const int S = K / kStepK8;
 
-    // pass 1: row maxima.  16 threads per row.
-    {
-        const int r = tid >> 4, c = tid & 15;
-        const long long base = (long long)(t * kTileRows + r) * ldw;
-        float amax = 0.f;
-        for (int k = c; k < K; k += 16) amax = fmaxf(amax, fabsf(load_w_smoothed<SRC_BF16>(w, base, k, smooth)));
+    u32x4 raw[NJ];
+    auto load_row = [&](int row, int k0) {
+        // (a wave-uniform address and the lane's offset: no address registers per load)
+        const long long base = (long long)(t * kTileRows + row) * ldw + k0;
+        const unsigned long long at = reinterpret_cast<unsigned long long>(w) + base * (SRC_BF16 ? 2 : 4);
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-        if (c == 0) {
-            const float step = __fdiv_rn(amax, 127.0f);
-            unsigned int sb = float_to_bf16_bits(step);
-            float s = bf16_bits_to_float(sb);
-            if (!(s > 0.f)) { sb = 0; s = 0.f; }
-            row_scale[r] = s;
-            scales[t * kTileRows + r] = (uint16_t)sb;
-        }
-    }
-    __syncthreads();
-
-    // pass 2: each thread produces one 16-byte lane slot of one step at a time
-    for (int slot = tid; slot < S * 64; slot += 256) {
-        const int s = slot >> 6, l = slot & 63;
-        const int g = l >> 4, i = l & 15;
-        const float sc = row_scale[i];
-        const long long base = (long long)(t * kTileRows + i) * ldw;
-        const int k0 = s * kStepK8 + 16 * g;
-        unsigned int out[4];
+        for (int j = 0; j < NJ; ++j) {
+            raw[j] = u32x4{0u, 0u, 0u, 0u};
+            if (lane * VE < K - k0 - 64 * j * VE) {
+                if constexpr (VEC) {
+                    typedef const __attribute__((address_space(1))) u32x4 *vec_ptr;
+                    raw[j] = __builtin_nontemporal_load(reinterpret_cast<vec_ptr>(at + 1024u * j + 16u * (unsigned int)lane));
+                } else {
+                    const int k = (64 * j + lane) * VE;
+                    unsigned int u[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            unsigned int word = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                int code = 0;
-                if (sc > 0.f) {
-                    const float ratio = __fdiv_rn(load_w_smoothed<SRC_BF16>(w, base, k0 + 4 * q + e, smooth), sc);
-                    float r = rintf(ratio);                 // round half to even
-                    r = fminf(fmaxf(r, -127.f), 127.f);
-                    code = (int)r;
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (SRC_BF16) {
+                            const uint16_t *p = reinterpret_cast<const uint16_t *>(w) + base + k + 2 * e;
+                            u[e] = p[0] | ((unsigned int)p[1] << 16);
+                        } else {
+                            u[e] = reinterpret_cast<const unsigned int *>(w)[base + k + e];
+                        }
+                    }
+                    raw[j] = u32x4{u[0], u[1], u[2], u[3]};
                 }
-                word |= ((unsigned int)code & 0xffu) << (8 * e);
             }
-            out[q] = word;
         }
-        packed[((long long)t * S + s) * 64 + l] = u32x4{out[0], out[1], out[2], out[3]};
+    };
+    // the VE values of raw[j] with the offline side of the smoothing transformation (W diag(s)^-1, one fp32 division)
+    auto values = [&](int j, int k, float (&v)[VE]) {
+        const unsigned int u[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
+#pragma unroll
+        for (int e = 0; e < VE; ++e)
+            v[e] = !SRC_BF16 ? __uint_as_float(u[e & 3])
+                             : ((e & 1) ? __uint_as_float(u[e >> 1] & 0xFFFF0000u) : __uint_as_float(u[e >> 1] << 16));
+        if constexpr (SMOOTH) {
+            if (k < K) {
+                float sm[VE];
+                if constexpr (VEC) {
+#pragma unroll
+                    for (int e = 0; e < VE; e += 4) {
+                        const f32x4 s4 = *reinterpret_cast<const f32x4 *>(smooth + k + e);
+                        sm[e] = s4.x; sm[e + 1] = s4.y; sm[e + 2] = s4.z; sm[e + 3] = s4.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < VE; ++e) sm[e] = smooth[k + e];
+                }
+#pragma unroll
+                for (int e = 0; e < VE; ++e) v[e] = __fdiv_rn(v[e], sm[e]);
+            }
+        }
+    };
+    // largest magnitude of the held span; fp32 values are kept smoothed
+    auto held_amax = [&](int k0, float amax) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            float v[VE];
+            values(j, k0 + (64 * j + lane) * VE, v);
+            if constexpr (SMOOTH && !SRC_BF16)
+                raw[j] = u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+#pragma unroll
+            for (int e = 0; e < VE; ++e) amax = fmaxf(amax, fabsf(v[e]));
+            if constexpr (SMOOTH) __builtin_amdgcn_sched_barrier(0);       // one load's quotients at a time
+        }
+        return amax;
+    };
+    // the row's step size (stored), 0 for a row without one
+    auto step_size = [&](int row, float amax) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+        unsigned int sb = float_to_bf16_bits(__fdiv_rn(amax, 127.0f));
+        float s = bf16_bits_to_float(sb);
+        if (!(s > 0.f)) { sb = 0; s = 0.f; }
+        if (lane == 0) scales[t * kTileRows + row] = (uint16_t)sb;
+        return s;
+    };
+    auto codes_to_lds = [&](int row, int k0, float s, bool smoothed) {
+        const float inv = __fdiv_rn(1.0f, s);
+        // bf16, smoothed: the quotients are formed again from the held words (kept from the maximum they spill)
+        if constexpr (SRC_BF16 && SMOOTH) asm volatile("" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int kk = (64 * j + lane) * VE;
+            if constexpr (SRC_BF16 && SMOOTH) asm volatile("" : "+v"(raw[j].x), "+v"(raw[j].y), "+v"(raw[j].z), "+v"(raw[j].w));
+            float v[VE];
+            if (SMOOTH && !SRC_BF16 && smoothed) {
+                v[0] = __uint_as_float(raw[j].x); v[1] = __uint_as_float(raw[j].y);
+                v[2] = __uint_as_float(raw[j].z); v[3] = __uint_as_float(raw[j].w);
+            } else {
+                values(j, k0 + kk, v);
+            }
+            unsigned int word[VE / 4];
+#pragma unroll
+            for (int q = 0; q < VE / 4; ++q) {
+                word[q] = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float r = fminf(fmaxf(rounded_ratio(v[4 * q + e], s, inv), -127.f), 127.f);
+                    word[q] |= ((unsigned int)(int)r & 0xffu) << (8 * e);
+                }
+                if (!(s > 0.f)) word[q] = 0;
+            }
+            if (lane * VE < K - k0 - 64 * j * VE) {
+                unsigned char *dst = lds + j * (4 * VE * kQuantSlotBytes) + row * 16 + ((lane * VE) >> 4) * kQuantSlotBytes + ((lane * VE) & 15);
+                if constexpr (VE == 4) *reinterpret_cast<unsigned int *>(dst) = word[0];
+                else *reinterpret_cast<u32x2 *>(dst) = u32x2{word[0], word[VE / 4 - 1]};
+            }
+            __builtin_amdgcn_sched_barrier(0);               // (bounds the registers of codes in the making)
+        }
+    };
+    auto store_span = [&](int k0) {
+        u32x4 *out = packed + ((long long)t * K + k0);               // 16 rows x 1 k per 16 bytes
+        const int n = min(kSpan, K - k0);
+        for (int q = tid; q < n; q += kQuantWaves * 64)
+            out[q] = *reinterpret_cast<const u32x4 *>(lds + (q >> 4) * kQuantSlotBytes + (q & 15) * 16);
+    };
+
+    if (K <= kSpan) {
+#pragma unroll 1
+        for (int row = 2 * wv; row < 2 * wv + 2; ++row) {
+            load_row(row, 0);
+            codes_to_lds(row, 0, step_size(row, held_amax(0, 0.f)), true);
+        }
+        __syncthreads();
+        store_span(0);
+        return;
+    }
+    float s[2];
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) {
+        float amax = 0.f;
+#pragma unroll 1
+        for (int k0 = 0; k0 < K; k0 += kSpan) {
+            load_row(2 * wv + rr, k0);
+            amax = held_amax(k0, amax);
+        }
+        s[rr] = step_size(2 * wv + rr, amax);
+    }
+#pragma unroll 1
+    for (int k0 = 0; k0 < K; k0 += kSpan) {
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr) {
+            load_row(2 * wv + rr, k0);
+            codes_to_lds(2 * wv + rr, k0, s[rr], false);
+        }
+        __syncthreads();
+        store_span(k0);
+        __syncthreads();
     }
 }
 

@@ -398,6 +398,43 @@ int verify_impl(const uint16_t *h, int64_t M, int64_t K, int64_t ldh, const void
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
+struct QuantArgs {
+    const void *w;
+    long long ldw;
+    int N, K;
+    const float *smooth;
+    u32x4 *packed;
+    uint16_t *scales;
+    hipStream_t st;
+};
+template <bool SRC_BF16, bool SMOOTH, bool VEC, int NJ>
+int launch_quantize_as(const QuantArgs &q) {
+    constexpr int kSpan = NJ * 64 * (SRC_BF16 ? 8 : 4);
+    auto kernel = quantize_pack_kernel<SRC_BF16, SMOOTH, VEC, NJ>;
+    if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return QUASAR_ERR_HIP;
+    const int lds = (q.K < kSpan ? q.K : kSpan) / 16 * kQuantSlotBytes;
+    hipLaunchKernelGGL(kernel, dim3(q.N / kTileRows), dim3(kQuantWaves * 64), lds, q.st, q.w, q.ldw, q.K, q.smooth, q.packed, q.scales);
+    return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
+}
+// Registers that hold the row: the fewest loads a lane that do; longer rows are read twice in spans of 4096 (holding bf16
+// rows of 8192 took 186 us for 25600 x 5120: the values double in the registers).
+template <bool SRC_BF16, bool SMOOTH, bool VEC>
+int launch_quantize_form(const QuantArgs &q) {
+    if constexpr (SRC_BF16) {
+        return launch_quantize_as<true, SMOOTH, VEC, 8>(q);
+    } else {
+        if (q.K <= 2048) return launch_quantize_as<false, SMOOTH, VEC, 8>(q);
+        if (q.K <= 4096 || q.K > 8192) return launch_quantize_as<false, SMOOTH, VEC, 16>(q);
+        return launch_quantize_as<false, SMOOTH, VEC, 32>(q);
+    }
+}
+template <bool SRC_BF16>
+int launch_quantize(const QuantArgs &q) {
+    const bool vec = aligned(q.w, 16) && q.ldw % (SRC_BF16 ? 8 : 4) == 0 && aligned(q.smooth, 16);
+    if (q.smooth) return vec ? launch_quantize_form<SRC_BF16, true, true>(q) : launch_quantize_form<SRC_BF16, true, false>(q);
+    return vec ? launch_quantize_form<SRC_BF16, false, true>(q) : launch_quantize_form<SRC_BF16, false, false>(q);
+}
+
 // Argmax partials of quasar_lmhead_verify_static: part of the device image, one copy per GPU.
 constexpr size_t kStaticPartialWords = (size_t)kMaxGrid * 32u;
 static __device__ __align__(256) unsigned long long g_verify_scratch[kStaticPartialWords];
@@ -488,15 +525,9 @@ int quasar_quantize_weights_smoothed(const void *w, int w_dtype, int64_t N, int6
     if (!aligned(wq_packed, 16) || !aligned(scales_bf16, 2) || !aligned(w, w_dtype == QUASAR_F32 ? 4 : 2) ||
         !aligned(smooth, 4))
         return QUASAR_ERR_ALIGN;
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const int T = (int)(N / kTileRows);
-    if (w_dtype == QUASAR_F32)
-        hipLaunchKernelGGL(quantize_pack_kernel<false>, dim3(T), dim3(256), 0, st, w, (long long)ldw, (int)N, (int)K,
-                           smooth, reinterpret_cast<u32x4 *>(wq_packed), scales_bf16);
-    else
-        hipLaunchKernelGGL(quantize_pack_kernel<true>, dim3(T), dim3(256), 0, st, w, (long long)ldw, (int)N, (int)K,
-                           smooth, reinterpret_cast<u32x4 *>(wq_packed), scales_bf16);
-    return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
+    const QuantArgs q{w, (long long)ldw, (int)N, (int)K, smooth, reinterpret_cast<u32x4 *>(wq_packed), scales_bf16,
+                      static_cast<hipStream_t>(hip_stream)};
+    return w_dtype == QUASAR_F32 ? launch_quantize<false>(q) : launch_quantize<true>(q);
 }
 
 int quasar_quantize_weights(const void *w, int w_dtype, int64_t N, int64_t K, int64_t ldw, int8_t *wq_packed,

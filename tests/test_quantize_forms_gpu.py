@@ -1,0 +1,41 @@
+"""The int8 quantiser over its forms: rows held in registers (one span, several loads a lane), rows read twice, rows that do not
+start on 16 bytes, both sources, with and without smoothing; codes and step sizes equal the stated rule in plain torch (IEEE
+divisions, ties to even) bit for bit, ties and quotients next to them included."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def rule(w, smooth):
+    w = w.float() / smooth if smooth is not None else w.float()
+    d = (w.abs().amax(1) / 127.0).to(torch.bfloat16)
+    q = torch.clamp(torch.round(w / d.float()[:, None]), -127, 127)
+    return torch.where(d.float()[:, None] > 0, q, torch.zeros_like(q)).to(torch.int8), d
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("smoothed", [False, True])
+@pytest.mark.parametrize("N,K,offset", [(16, 64, 0), (48, 1088, 0), (32, 2112, 0), (32, 4096, 0), (32, 4160, 0), (16, 8192, 0),
+                                        (16, 8256, 0), (32, 12288, 0), (32, 2112, 1), (16, 8256, 1)])
+def test_quantize_forms(dtype, smoothed, N, K, offset):
+    from paper_2603_01399_amd import binding as qb
+    print("quantize", dtype, smoothed, N, K, offset, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N * 7919 + K)
+    flat = torch.zeros(N * (K + 8) + offset, device="cuda", dtype=dtype)
+    w = flat[offset:].view(N, K + 8)[:, :K]                 # a row stride of its own
+    v = torch.randn(N, K, generator=gen, device="cuda") * 0.02
+    v[1] = 0.0
+    v[2] = torch.randint(-254, 255, (K,), generator=gen, device="cuda").float() * 0.5     # ties (the maximum set to 127)
+    v[2, 0] = 127.0
+    v[3] *= 2.0 ** -120
+    # quotients within an ulp or two of a half
+    v[4] = (torch.randint(-126, 126, (K,), generator=gen, device="cuda").float() + 0.5) * 0.013671875
+    v[4] *= 1.0 + torch.randint(-2, 3, (K,), generator=gen, device="cuda").float() * 2.0 ** -24
+    v[4, 0] = 127 * 0.013671875
+    w.copy_(v)
+    smooth = torch.exp2(torch.rand(K, generator=gen, device="cuda") * 2 - 1) if smoothed else None
+    q, d = rule(w, smooth)
+    packed, scales = qb.quantize_weights_smoothed(w, smooth) if smoothed else qb.quantize_weights(w)
+    assert torch.equal(scales.view(torch.int16), d.view(torch.int16))
+    assert torch.equal(qb.unpack_weights(packed, N, K), q)
