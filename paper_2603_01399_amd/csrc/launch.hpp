@@ -67,6 +67,8 @@ struct DirectPlan {
 int launch_direct_int8(int epi, int pre, bool resid, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 int launch_direct_bf16(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 
+int launch_direct_w8a8(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
+
 inline int launch_direct(bool w16, int epi, int pre, bool resid, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream) {
     return w16 ? launch_direct_bf16(epi, p, MP, d, stream) : launch_direct_int8(epi, pre, resid, p, MP, d, stream);
 }

@@ -700,6 +700,27 @@ int launch_logits(const GemmParams &base, int M, hipStream_t stream) {
     return launch(stream_mfma_kernel<32, false, EPI_LOGITS, 16, 4>, pl.grid, 1024, pl.lds_bytes, stream, p);
 }
 
+// Plan of the W8A8 kernel that keeps its activation codes in registers (stream_direct_a8.hpp): integer sums, so no order to
+// keep; 16 waves, the smallest built form that holds a wave's slots.
+bool plan_direct_w8a8(int MP, int T, int S, bool smooth, DirectPlan &d) {
+    constexpr int kSlots[] = {1, 2, 3, 4, 5, 6, 8, 12};
+    if (g_tune_nw.load() != 16 || g_tune_wgs.load() != 1) return false;
+    const int need = (S + 15) / 16, NB = MP == 32 ? 2 : 1;
+    d.XS = 0;
+    for (int xs : kSlots)
+        if (!d.XS && xs >= need && !(MP == 32 && xs > 8)) d.XS = xs;
+    if (!d.XS) return false;
+    d.groups = device_cus() < T ? device_cus() : T;
+    const int least = (T + kMaxTilesPerWg - 1) / kMaxTilesPerWg;
+    if (d.groups < least) d.groups = least;
+    if (d.groups > kMaxGrid) return false;
+    const int tpw = (T + d.groups - 1) / d.groups;
+    d.sc_bytes = ((tpw * kTileRows * 2 + 15) / 16) * 16;
+    d.lds_bytes = 2 * 16 * NB * 1024 + d.sc_bytes + 16 * MP * 4 + (smooth ? 16 * d.XS * 256 : 0);
+    if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+    return d.lds_bytes <= kMaxLds;
+}
+
 template <int EPI>
 int launch_w8a8(const GemmParams &base, int M, hipStream_t stream, int *grid_out) {
     GemmParams p = base;
@@ -707,6 +728,11 @@ int launch_w8a8(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     p.ksplit = 1;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NB = MP == 32 ? 2 : 1;
+    DirectPlan d{};
+    if (plan_direct_w8a8(MP, p.T, p.S, p.smooth != nullptr, d)) {
+        if (grid_out) *grid_out = d.groups;
+        return launch_direct_w8a8(EPI, p, MP, d, stream);
+    }
     // int8 codes: 64 bytes of LDS per token and step; 256 bytes more for the per-token steps
     Plan pl = make_plan(p.T, p.S, 64 * MP, NB * 1024, 16, true);
     if (pl.grid > kMaxGrid) return QUASAR_ERR_SHAPE;

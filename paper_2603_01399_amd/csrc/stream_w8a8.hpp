@@ -67,7 +67,7 @@ __device__ __forceinline__ float inverse_step_of(float amax) { return amax > 0.f
 // One workgroup (256 threads) per token.  The fused kernels below run the same three
 // device functions; this entry makes the codes observable.
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void quantize_activations_kernel(const uint16_t *x, long long ldx, int K,
+[[maybe_unused]] static __global__ __launch_bounds__(256) void quantize_activations_kernel(const uint16_t *x, long long ldx, int K,
                                                                    const float *smooth, int8_t *xq, float *dx) {
     __shared__ float red[4];
     const int m = blockIdx.x, tid = threadIdx.x;
