@@ -151,20 +151,28 @@ def _check(fn: str, status: int) -> None:
         raise QuasarError(fn, status, _lib.quasar_status_string(status).decode())
 
 
+# A call costs about as much here as its kernel takes on the GPU, so these three do no more than they must: addresses and the
+# stream go to ctypes as plain integers (the declared argument types convert them), the stream is torch's current one without
+# a Stream object around it.  One linear through the binding: 8.9 -> 5.8 us of host time.
+_Tensor = torch.Tensor
+_current_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _current_raw_stream(_current_device())
 
 
 def _dev(t, name, dtype=None):
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if isinstance(t, _Tensor) and t.is_cuda and (dtype is None or t.dtype == dtype):
+        return t
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA tensor")
-    if dtype is not None and t.dtype != dtype:
-        raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
-    return t
+    raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
 
 
 def status_string(status: int) -> str:
@@ -299,7 +307,7 @@ def w8a8_lmhead_verify(hidden: torch.Tensor, wq_packed: torch.Tensor, scales: to
                                           _ptr(wq_packed), _ptr(scales), V,
                                           _ptr(draft_ids) if n_draft else None, n_draft, _ptr(out_argmax),
                                           _ptr(out_accept), _ptr(workspace),
-                                          workspace.numel() * workspace.element_size(), _stream()))
+                                          workspace.nbytes, _stream()))
     return out_argmax, out_accept
 
 
@@ -331,7 +339,7 @@ def lmhead_verify_sample(hidden: torch.Tensor, wq_packed: torch.Tensor, scales: 
            _lib.quasar_lmhead_verify_sample(_ptr(hidden), M, K, hidden.stride(0), _ptr(wq_packed), _ptr(scales), V,
                                             _ptr(draft_ids) if n_draft else None, n_draft, float(temperature),
                                             _ptr(u_accept) if n_draft else None, _ptr(u_sample), _ptr(acc), _ptr(tok),
-                                            _ptr(pd), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                            _ptr(pd), _ptr(workspace), workspace.nbytes,
                                             _stream()))
     return acc, tok, pd[:n_draft]
 
@@ -351,7 +359,7 @@ def w8_linear(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, N:
     M, K = x.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check("quasar_w8_linear",
            _lib.quasar_w8_linear(_ptr(x), M, K, x.stride(0), _ptr(wq_packed), _ptr(scales), N,
                                  _ptr(y), y.stride(0), _ptr(workspace), ws_bytes, _stream()))
@@ -422,7 +430,7 @@ def w4_lmhead_verify(hidden: torch.Tensor, w4_packed: torch.Tensor, V: int, draf
            _lib.quasar_w4_lmhead_verify(_ptr(hidden), M, K, hidden.stride(0), _ptr(w4_packed), V,
                                         _ptr(draft_ids) if n_draft else None, n_draft, _ptr(out_argmax),
                                         _ptr(out_accept), _ptr(workspace),
-                                        workspace.numel() * workspace.element_size(), _stream()))
+                                        workspace.nbytes, _stream()))
     return out_argmax, out_accept
 
 
@@ -536,7 +544,7 @@ def verify_attention(q: torch.Tensor, n_q_heads: int, cache: KvCache, L_total: i
     _check("quasar_verify_attention",
            _lib.quasar_verify_attention(_ptr(q), M, q.stride(0), n_q_heads, cache.n_kv_heads, _ptr(cache.buf),
                                         cache.max_len, L_total, _ptr(out), out.stride(0), _ptr(workspace),
-                                        workspace.numel() * workspace.element_size(), _stream()))
+                                        workspace.nbytes, _stream()))
     return out
 
 
@@ -599,7 +607,7 @@ def lmhead_verify(hidden: torch.Tensor, wq_packed: torch.Tensor, scales: torch.T
            _lib.quasar_lmhead_verify(_ptr(hidden), M, K, hidden.stride(0), _ptr(wq_packed), _ptr(scales), V,
                                      _ptr(draft_ids) if n_draft else None, n_draft, _ptr(out_argmax),
                                      _ptr(out_accept), _ptr(workspace),
-                                     workspace.numel() * workspace.element_size(), _stream()))
+                                     workspace.nbytes, _stream()))
     return out_argmax, out_accept
 
 
@@ -646,7 +654,7 @@ def bf16_linear(x: torch.Tensor, w_packed: torch.Tensor, N: int, y: torch.Tensor
     M, K = x.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check("quasar_bf16_linear",
            _lib.quasar_bf16_linear(_ptr(x), M, K, x.stride(0), _ptr(w_packed), N, _ptr(y), y.stride(0),
                                    _ptr(workspace), ws_bytes, _stream()))
@@ -667,7 +675,7 @@ def bf16_lmhead_verify(hidden: torch.Tensor, w_packed: torch.Tensor, V: int, dra
            _lib.quasar_bf16_lmhead_verify(_ptr(hidden), M, K, hidden.stride(0), _ptr(w_packed), V,
                                           _ptr(draft_ids) if n_draft else None, n_draft, _ptr(out_argmax),
                                           _ptr(out_accept), _ptr(workspace),
-                                          workspace.numel() * workspace.element_size(), _stream()))
+                                          workspace.nbytes, _stream()))
     return out_argmax, out_accept
 
 
