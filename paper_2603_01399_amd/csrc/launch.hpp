@@ -38,7 +38,18 @@ int launch(KernelT kernel, int grid, int block, int lds_bytes, hipStream_t strea
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
-// ---- the kernel that holds the activations in registers (stream_direct.hpp) ----
+// ---- the kernels that hold the activations in registers (stream_direct*.hpp) ----
+
+// lanes i of every row of 16 <- lanes (i + 8) mod 16
+__device__ __forceinline__ u32x4 rotate_half_row(const u32x4 v) {
+    u32x4 r;
+    r.x = __builtin_amdgcn_update_dpp(0, (int)v.x, 0x128, 0xf, 0xf, true);
+    r.y = __builtin_amdgcn_update_dpp(0, (int)v.y, 0x128, 0xf, 0xf, true);
+    r.z = __builtin_amdgcn_update_dpp(0, (int)v.z, 0x128, 0xf, 0xf, true);
+    r.w = __builtin_amdgcn_update_dpp(0, (int)v.w, 0x128, 0xf, 0xf, true);
+    return r;
+}
+
 
 // Waves of a workgroup by form (XS slots of 64 k per wave): where the activations take more than about half of a wave's
 // 128 registers, eight waves of 256 - the ring, the accumulators and the addresses are then paid for half as often.
@@ -58,6 +69,18 @@ constexpr int direct_region_bytes(int MP, int XS, int C) {
     return direct_waves(MP, XS) * (x > tiles ? x : tiles);
 }
 
+// The same for the 4-bit kernel (slots of 128 k): its waves, the slots that pass through LDS at a time, the regions.
+constexpr int w4_waves(int MP, int XS) { return MP == 32 || (MP == 16 && XS > 4) ? 8 : 16; }
+constexpr int w4_pass(int MP, int XS) {
+    if (MP == 8 && XS <= 2) return 0;
+    const int fit = 512 / (w4_waves(MP, XS) * MP);
+    return XS < fit ? XS : fit;
+}
+constexpr int w4_region_bytes(int MP, int XS) {
+    const int x = w4_pass(MP, XS) * MP * 256, tiles = 2 * (MP == 32 ? 2 : 1) * 1024;
+    return w4_waves(MP, XS) * (x > tiles ? x : tiles);
+}
+
 struct DirectPlan {
     int XS, SC, C, ksplit, slice_steps, groups, sc_bytes, lds_bytes;
 };
@@ -68,6 +91,8 @@ int launch_direct_int8(int epi, int pre, bool resid, const GemmParams &p, int MP
 int launch_direct_bf16(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 
 int launch_direct_w8a8(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
+
+int launch_direct_w4(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 
 inline int launch_direct(bool w16, int epi, int pre, bool resid, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream) {
     return w16 ? launch_direct_bf16(epi, p, MP, d, stream) : launch_direct_int8(epi, pre, resid, p, MP, d, stream);

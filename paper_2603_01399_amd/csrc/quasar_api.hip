@@ -840,6 +840,24 @@ bool plan_w4(int T, int S, int MP, int NW, PlanW4 &pl) {
     return true;
 }
 
+// Plan of the 4-bit kernel that keeps its activations in registers (stream_direct_w4.hpp); S steps of 128 k.
+bool plan_direct_w4(int MP, int T, int S, DirectPlan &d) {
+    constexpr int kSlots8[] = {1, 2, 3, 4, 6}, kSlots16[] = {1, 2, 3, 4, 6, 8, 12}, kSlots32[] = {1, 2, 3, 4, 5};
+    auto pick = [&](const int *v, int count) {
+        for (int i = 0; i < count; ++i) {
+            const int NW = w4_waves(MP, v[i]);
+            if (v[i] >= (S + NW - 1) / NW) return v[i];
+        }
+        return 0;
+    };
+    d.XS = MP == 8 ? pick(kSlots8, 5) : (MP == 16 ? pick(kSlots16, 7) : pick(kSlots32, 5));
+    if (!d.XS) return false;
+    d.groups = device_cus() < T ? device_cus() : T;
+    d.lds_bytes = w4_region_bytes(MP, d.XS);
+    if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+    return d.groups <= kMaxGrid && d.lds_bytes <= kMaxLds;
+}
+
 template <int EPI>
 int launch_w4(const GemmParams &base, int M, hipStream_t stream, int *grid_out) {
     GemmParams p = base;
@@ -847,6 +865,11 @@ int launch_w4(const GemmParams &base, int M, hipStream_t stream, int *grid_out) 
     p.ksplit = 1;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NW = g_w4_nw.load(), DD = g_w4_d.load();
+    DirectPlan d{};
+    if (NW == 16 && DD == 2 && direct_reach(M, p.ldx) && plan_direct_w4(MP, p.T, p.S, d)) {
+        if (grid_out) *grid_out = d.groups;
+        return launch_direct_w4(EPI, p, MP, d, stream);
+    }
     PlanW4 pl{};
     if (!plan_w4(p.T, p.S, MP, NW, pl) || pl.grid > kMaxGrid) return QUASAR_ERR_SHAPE;
     p.SC = pl.SC;

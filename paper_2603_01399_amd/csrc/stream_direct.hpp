@@ -25,16 +25,6 @@
 
 namespace quasar {
 
-// lanes i of every row of 16 <- lanes (i + 8) mod 16
-__device__ __forceinline__ u32x4 rotate_half_row(const u32x4 v) {
-    u32x4 r;
-    r.x = __builtin_amdgcn_update_dpp(0, (int)v.x, 0x128, 0xf, 0xf, true);
-    r.y = __builtin_amdgcn_update_dpp(0, (int)v.y, 0x128, 0xf, 0xf, true);
-    r.z = __builtin_amdgcn_update_dpp(0, (int)v.z, 0x128, 0xf, 0xf, true);
-    r.w = __builtin_amdgcn_update_dpp(0, (int)v.w, 0x128, 0xf, 0xf, true);
-    return r;
-}
-
 // Slots in flight per wave: a compute unit accepts about 32 KB of outstanding loads, so three or four 1 KB loads in
 // each of 16 waves keep it full; up to eight where the registers allow.
 constexpr int direct_ring(int MP, int slots) {
