@@ -679,16 +679,22 @@ bool plan_phase(SeqPhase &ph, int MP, bool w16, bool a8, int G, int &xs_bytes, i
 }
 
 // The vocabulary projection with fp32 outputs (input of the stochastic verification): the
-// int8-weight streaming kernel in its default shape, logits to part32[m][n].
-int launch_logits(const GemmParams &base, int M, hipStream_t stream) {
+// int8-weight streaming kernel in its default shape, logits to part32[m][n].  stats: room for `most` blocks of softmax
+// statistics per position; nblk: the blocks that were taken while streaming (0: none).
+int launch_logits(const GemmParams &base, int M, float inv_t, float *stats, size_t most, int &nblk, hipStream_t stream) {
     GemmParams p = base;
     p.Srow = p.S;
     p.ksplit = 1;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NB = MP == 32 ? 2 : 1;
     DirectPlan d{};
-    if (direct_reach(M, p.ldx) && plan_direct(MP, p.T, 1, p.S, p.S, 1, 1, true, MP == 8 ? 12 : (MP == 16 ? 24 : 10), 0, false, d))
+    if (direct_reach(M, p.ldx) && plan_direct(MP, p.T, 1, p.S, p.S, 1, 1, true, MP == 8 ? 12 : (MP == 16 ? 24 : 10), 0, false, d)) {
+        nblk = (size_t)d.groups <= most ? d.groups : 0;
+        p.soft_stats = nblk ? stats : nullptr;
+        p.inv_t = inv_t;
         return launch_direct(false, EPI_LOGITS, PRE_NONE, false, p, MP, d, stream);
+    }
+    nblk = 0;
     const Plan pl = make_plan(p.T, p.S, 128 * MP, NB * 1024, 16, true);
     if (pl.grid > kMaxGrid) return QUASAR_ERR_SHAPE;
     p.SC = pl.SC;
@@ -1367,10 +1373,14 @@ int quasar_w8a8_lmhead_verify(const uint16_t *hidden, int64_t M, int64_t K, int6
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
+// logits, per-(position, vocabulary block) softmax statistics of kSampleBlocks blocks: what a call needs.  With the room that
+// quasar_sample_workspace_bytes asks for beyond it the statistics are taken while streaming, one block per workgroup.
+static size_t sample_least_bytes(int64_t M, int64_t V) {
+    return (size_t)M * (size_t)V * sizeof(float) + 32u * (size_t)kSampleBlocks * 2u * sizeof(float);
+}
 size_t quasar_sample_workspace_bytes(int64_t M, int64_t V) {
     if (M < 1 || M > 32 || V < 16 || V % 16 || V > 0x7FFFFFF0ll) return 0;
-    // logits, per-(position, vocabulary block) softmax statistics
-    return (size_t)M * (size_t)V * sizeof(float) + 32u * (size_t)kSampleBlocks * 2u * sizeof(float);
+    return sample_least_bytes(M, V) + (size_t)M * (size_t)kMaxGrid / 8u * 2u * sizeof(float);
 }
 
 int quasar_lmhead_verify_sample(const uint16_t *hidden, int64_t M, int64_t K, int64_t ldh, const int8_t *wq_packed,
@@ -1389,7 +1399,7 @@ int quasar_lmhead_verify_sample(const uint16_t *hidden, int64_t M, int64_t K, in
     if (!aligned(hidden, 16) || !aligned(wq_packed, 16) || !aligned(scales_bf16, 8) || !aligned(u_accept, 4) ||
         !aligned(u_sample, 4) || !aligned(out_p_draft, 4))
         return QUASAR_ERR_ALIGN;
-    if (!workspace || workspace_bytes < quasar_sample_workspace_bytes(M, V)) return QUASAR_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < sample_least_bytes(M, V)) return QUASAR_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return QUASAR_ERR_ALIGN;
     float *logits = static_cast<float *>(workspace);
     float *stats = logits + (size_t)M * (size_t)V;
@@ -1400,11 +1410,16 @@ int quasar_lmhead_verify_sample(const uint16_t *hidden, int64_t M, int64_t K, in
     p.T = (int)(V / kTileRows);
     p.S = (int)(K / kStepK8);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (const int e = launch_logits(p, (int)M, st)) return e;
     const float inv_t = 1.0f / temperature;
-    hipLaunchKernelGGL(softmax_partial_kernel, dim3(kSampleBlocks, (unsigned int)M), dim3(256), 0, st, logits, (int)V,
-                       inv_t, stats);
-    hipLaunchKernelGGL(speculative_sample_kernel, dim3(1), dim3(1024), 0, st, logits, (int)V, (int)M, inv_t, draft_ids,
+    const size_t most = (workspace_bytes - (size_t)M * (size_t)V * sizeof(float)) / ((size_t)M * 2u * sizeof(float));
+    int nblk = 0;
+    if (const int e = launch_logits(p, (int)M, inv_t, stats, most, nblk, st)) return e;
+    if (!nblk) {
+        nblk = kSampleBlocks;
+        hipLaunchKernelGGL(softmax_partial_kernel, dim3(kSampleBlocks, (unsigned int)M), dim3(256), 0, st, logits, (int)V,
+                           inv_t, stats);
+    }
+    hipLaunchKernelGGL(speculative_sample_kernel, dim3(1), dim3(1024), 0, st, logits, (int)V, (int)M, inv_t, nblk, draft_ids,
                        (int)n_draft, u_accept, u_sample, stats, out_accept_len, out_next_token, out_p_draft);
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }

@@ -257,6 +257,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     unsigned int besti[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) { bestv[nb] = -__builtin_inff(); besti[nb] = 0x7FFFFFFFu; }
+    [[maybe_unused]] float sume[NB] = {};            // EPI_LOGITS: sum of exp(z - bestv)
     int parity = 0;
 
     // one slot: 64 k of a tile into the accumulators
@@ -305,6 +306,18 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                 }
             }
             finish_tile<W16, EPI, RES, NB>(p, rsum, t0 + tl, sc_lds + tl * kTileRows, resid, gate_keep, slice, lane, bestv, besti);
+            if constexpr (EPI == EPI_LOGITS) {
+                if (p.soft_stats) {
+                    // the logits of finish_tile once more: a running (max, sum) per lane and token
+                    const u32x2 sb = *reinterpret_cast<const u32x2 *>(sc_lds + tl * kTileRows + 4 * g);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        softmax_add(bestv[nb], sume[nb], rsum[nb].x * bf16_bits_to_float(sb.x & 0xFFFFu) * p.inv_t,
+                                    rsum[nb].y * bf16_bits_to_float(sb.x >> 16) * p.inv_t,
+                                    rsum[nb].z * bf16_bits_to_float(sb.y & 0xFFFFu) * p.inv_t,
+                                    rsum[nb].w * bf16_bits_to_float(sb.y >> 16) * p.inv_t);
+                }
+            }
             if (RES) load_residual<RES, NB>(p, t0 + min(tl + NW, ntiles - 1), lane, resid);      // of this wave's next tile
         }
         parity ^= 1;
@@ -347,6 +360,31 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     round(tl0, std::true_type{});
 
     if constexpr (EPI == EPI_ARGMAX) publish_argmax<MP, NB, NW>(bestv, besti, lds, p.partial + (long long)b * MP);
+    if constexpr (EPI == EPI_LOGITS) {
+        if (p.soft_stats) {
+            float *red = reinterpret_cast<float *>(lds);             // [NW][MP] (max, sum)
+            lds_barrier();   // all tile-end reads of the partial tiles are done
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+                for (int off = 16; off <= 32; off <<= 1) {
+                    const float m2 = __shfl_xor(bestv[nb], off, 64), s2 = __shfl_xor(sume[nb], off, 64);
+                    softmax_merge(bestv[nb], sume[nb], m2, s2);
+                }
+                if (g == 0 && (MP != 8 || mcol < 8)) {
+                    red[(w * MP + mcol + 16 * nb) * 2] = bestv[nb];
+                    red[(w * MP + mcol + 16 * nb) * 2 + 1] = sume[nb];
+                }
+            }
+            lds_barrier();
+            if (tid < p.M) {
+                float m = red[2 * tid], s = red[2 * tid + 1];
+                for (int ww = 1; ww < NW; ++ww) softmax_merge(m, s, red[(ww * MP + tid) * 2], red[(ww * MP + tid) * 2 + 1]);
+                p.soft_stats[((long long)tid * G + b) * 2] = m;
+                p.soft_stats[((long long)tid * G + b) * 2 + 1] = s;
+            }
+        }
+    }
 }
 
 // ---- dispatch over the built forms ----

@@ -41,6 +41,10 @@ struct GemmParams {
     float eps;                 // PRE_RMSNORM
     const uint16_t *resid;     // RES: residual [M, N] bf16, row stride ldr (may be y itself)
     long long ldr;
+    // softmax statistics of the workgroup's rows beside the logits (EPI_LOGITS of the kernel with register activations):
+    // [M][workgroups] (max, sum of exp(z - max)), z = logit * inv_t; nullptr: none
+    float *soft_stats;
+    float inv_t;
 };
 
 // Operation applied to the activations while they are staged (the normalisation in front of
@@ -74,6 +78,23 @@ __device__ __forceinline__ float piece_sumsq(const u32x4 x) {
         s = __builtin_fmaf(hi, hi, s);
     }
     return s;
+}
+
+// (max, sum of exp(z - max)) pairs combine associatively
+__device__ __forceinline__ void softmax_merge(float &m, float &s, float m2, float s2) {
+    if (!(m2 > -__builtin_inff())) return;
+    const float mm = fmaxf(m, m2);
+    s = s * expf(m - mm) + s2 * expf(m2 - mm);
+    m = mm;
+}
+// four more values of a running pair
+__device__ __forceinline__ void softmax_add(float &m, float &s, float z0, float z1, float z2, float z3) {
+    const float zm = fmaxf(fmaxf(z0, z1), fmaxf(z2, z3));
+    if (zm > m) {
+        s = s * expf(m - zm);
+        m = zm;
+    }
+    if (zm > -__builtin_inff()) s += (expf(z0 - m) + expf(z1 - m)) + (expf(z2 - m) + expf(z3 - m));
 }
 
 // EPI_LOGITS: the linear epilogue with fp32 outputs, part32[m][n] (row stride N): the input of

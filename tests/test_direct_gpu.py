@@ -77,3 +77,23 @@ def test_fused_forms(qb, M, K):
     gu = lin.bfloat16().double().view(M, N // 32, 2, 16)
     act = (torch.nn.functional.silu(gu[:, :, 0]).bfloat16().double() * gu[:, :, 1]).reshape(M, N // 2)
     assert rel(qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, eps=1e-6), act) <= 1e-2
+
+
+@pytest.mark.parametrize("M", [2, 9, 17])
+def test_sampling_statistics_taken_while_streaming(qb, M):
+    """Softmax statistics per workgroup of the streaming kernel against those taken from the finished logits (a workspace with
+    room for no more): the same decisions and token, probabilities within a few fp32 roundings of sums of 4800 terms."""
+    V, K = 16 * 300, 512
+    print("direct sampling", M, V, K, flush=True)
+    x, _, wq, sc, what = make(qb, M, V, K)
+    p = torch.softmax(x.double() @ what.t() / 0.8, 1)
+    draft = p.argmax(1).int()[:-1].contiguous()
+    ua = (p.max(1).values * 0.9).float()
+    ua[M // 2] = 0.999
+    us = torch.rand(M, device="cuda")
+    full = qb.lmhead_verify_sample(x, wq, sc, V, draft, 0.8, ua, us)
+    least = torch.empty(M * V * 4 + 32 * 32 * 2 * 4, dtype=torch.uint8, device="cuda")
+    small = qb.lmhead_verify_sample(x, wq, sc, V, draft, 0.8, ua, us, workspace=least)
+    assert int(full[0]) == int(small[0]) and int(full[1]) == int(small[1])
+    assert torch.allclose(full[2], small[2], rtol=1e-5, atol=0)
+    assert torch.allclose(full[2].double(), p[:-1].gather(1, draft.long()[:, None])[:, 0], rtol=1e-3, atol=0)
