@@ -87,7 +87,9 @@ __global__ __launch_bounds__(64) void attn_prepare_kernel(const uint16_t *qkv, l
                                                            bf16_bits_to_float(gamma[lane + 64])));
     // angle = pos * theta^(-2 i / 128) in double: positions reach tens of thousands of radians
     const double angle = (double)pos * exp2(-(2.0 * lane / kHeadDim) * log2_theta);
-    const float c = (float)cos(angle), s = (float)sin(angle);
+    double sd, cd;
+    sincos(angle, &sd, &cd);                               // (one reduction of the argument)
+    const float c = (float)cd, s = (float)sd;
     const uint16_t o1 = (uint16_t)float_to_bf16_bits(n1 * c - n2 * s);
     const uint16_t o2 = (uint16_t)float_to_bf16_bits(n2 * c + n1 * s);
     if (h < Hq) {
@@ -168,17 +170,12 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) { mrow[qt] = -__builtin_inff(); lrow[qt] = 0.f; }
 
-    // One block of prefetch.  The loads are issued unconditionally (the last iteration fetches its
-    // own block once more, a cache hit) so that the compiler can count them: with a conditional
-    // prefetch it has to assume the shorter queue and waits for the prefetched block before the
-    // current one is used.
+    // One block of prefetch, the last block of a wave without one: both loads counts are known to the compiler (a conditional
+    // prefetch would make it wait for the prefetched block before the current one is used), and a wave whose share is one
+    // or two blocks - a short context - does not read a block it has already read.
     u32x4 kc[8], vc[8];
     int b = b0 + w;
-    load_block(min(b, b1 - 1), kc, vc);
-    for (; b < b1; b += NW) {
-        u32x4 kn[8], vn[8];
-        load_block(min(b + NW, b1 - 1), kn, vn);
-
+    auto process = [&](int b) {
         const int pos0 = b * kKvBlock;
         const bool edge = pos0 + kKvBlock - 1 > p.L_total - p.M;      // some position may be hidden from some query
         if (edge) {
@@ -262,8 +259,17 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
                 oacc[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vc[dt]),
                                                                        __builtin_bit_cast(bf16x8, pb16), oacc[dt][qt], 0, 0, 0);
         }
+    };
+    if (b < b1) {
+        load_block(b, kc, vc);
+        for (; b + NW < b1; b += NW) {
+            u32x4 kn[8], vn[8];
+            load_block(b + NW, kn, vn);
+            process(b);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { kc[i] = kn[i]; vc[i] = vn[i]; }
+            for (int i = 0; i < 8; ++i) { kc[i] = kn[i]; vc[i] = vn[i]; }
+        }
+        process(b);
     }
     // the four lanes of a query column hold partial row sums; the maxima go on in log2 units
 #pragma unroll
@@ -311,9 +317,10 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
     }
 }
 
-// Combine the splits: one workgroup of 512 threads per (kv head, query tile, 16-d output tile);
-// the 8 waves share the splits (wave g takes splits g, g + 8, ...) and meet twice in LDS: for
-// the maximum over all splits, then for the sums (added in wave order: a fixed order).
+// Combine the splits: one workgroup of 512 threads per (kv head, query tile, 16-d output tile); the 8 waves share the
+// splits (wave g takes splits g, g + 8, ...), four of them requested at a time, statistics and outputs together: the only
+// wait of the kernel is one round trip to memory (a pass for the maximum ahead of the outputs cost a second one: 4.6 us a
+// launch, now 3.3).  A wave keeps its outputs against its own maximum; they meet once in LDS and are added in wave order.
 __global__ __launch_bounds__(512) void attention_merge_kernel(const AttnParams p, int NQT) {
     __shared__ float smax[8][16];
     __shared__ float slsum[8][16];
@@ -322,30 +329,49 @@ __global__ __launch_bounds__(512) void attention_merge_kernel(const AttnParams p
     const int sg = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g4 = lane >> 4, col = lane & 15;
     const int r = p.row0 + 16 * qt + col;
-    float lmax = -__builtin_inff();
-    for (int s = sg; s < p.nsplit; s += 8)
-        lmax = fmaxf(lmax, p.part_ml[((((long long)h * p.nsplit + s) * NQT + qt) * 16 + col) * 2]);
-    if (g4 == 0) smax[sg][col] = lmax;
+    float mw = -__builtin_inff(), lsum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = sg; s0 < p.nsplit; s0 += 32) {
+        f32x4 o[4];
+        u32x2 ml[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const long long pb = ((long long)h * p.nsplit + min(s0 + 8 * i, p.nsplit - 1)) * NQT + qt;
+            ml[i] = reinterpret_cast<const u32x2 *>(p.part_ml)[pb * 16 + col];
+            o[i] = reinterpret_cast<const f32x4 *>(p.part_o)[(pb * 8 + dt) * 64 + lane];
+        }
+        float m_new = mw;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (s0 + 8 * i < p.nsplit) m_new = fmaxf(m_new, __uint_as_float(ml[i].x));
+        const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;        // nothing visible in these splits
+        const float keep = exp2f(mw - m_use);
+        acc *= keep;
+        lsum *= keep;
+        mw = m_new;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (s0 + 8 * i < p.nsplit) {
+                const float f = exp2f(__uint_as_float(ml[i].x) - m_use);
+                lsum += f * __uint_as_float(ml[i].y);
+                acc += o[i] * f;
+            }
+        }
+    }
+    sacc[sg][lane] = acc;
+    if (g4 == 0) { smax[sg][col] = mw; slsum[sg][col] = lsum; }
     __syncthreads();
+    if (sg != 0 || r >= p.M * p.G) return;
     float mstar = smax[0][col];
 #pragma unroll
     for (int i = 1; i < 8; ++i) mstar = fmaxf(mstar, smax[i][col]);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float lsum = 0.f;
-    for (int s = sg; s < p.nsplit; s += 8) {
-        const long long pb = ((long long)h * p.nsplit + s) * NQT + qt;
-        const float f = exp2f(p.part_ml[(pb * 16 + col) * 2] - mstar);
-        lsum += f * p.part_ml[(pb * 16 + col) * 2 + 1];
-        acc += reinterpret_cast<const f32x4 *>(p.part_o)[(pb * 8 + dt) * 64 + lane] * f;
-    }
-    sacc[sg][lane] = acc;
-    if (g4 == 0) slsum[sg][col] = lsum;
-    __syncthreads();
-    if (sg != 0 || r >= p.M * p.G) return;
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    lsum = 0.f;
 #pragma unroll
-    for (int i = 1; i < 8; ++i) {
-        acc += sacc[i][lane];
-        lsum += slsum[i][col];
+    for (int i = 0; i < 8; ++i) {
+        const float f = exp2f(smax[i][col] - mstar);
+        acc += sacc[i][lane] * f;
+        lsum += slsum[i][col] * f;
     }
     const float inv = __fdiv_rn(1.0f, lsum);
     const int m = r / p.G, g = r % p.G;
