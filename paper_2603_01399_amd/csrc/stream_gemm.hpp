@@ -58,10 +58,9 @@ __device__ __forceinline__ u32x4 pre_rmsnorm_piece(const u32x4 x, const u32x4 ga
     unsigned int o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float lo = bf16_bits_to_float(float_to_bf16_bits(bf16_bits_to_float(xw[i] & 0xFFFFu) * r));
-        const float hi = bf16_bits_to_float(float_to_bf16_bits(__uint_as_float(xw[i] & 0xFFFF0000u) * r));
-        o[i] = float_to_bf16_bits(lo * bf16_bits_to_float(gw[i] & 0xFFFFu)) |
-               (float_to_bf16_bits(hi * __uint_as_float(gw[i] & 0xFFFF0000u)) << 16);
+        const unsigned int n = float2_to_bf16_pair(__uint_as_float(xw[i] << 16) * r, __uint_as_float(xw[i] & 0xFFFF0000u) * r);
+        o[i] = float2_to_bf16_pair(__uint_as_float(n << 16) * __uint_as_float(gw[i] << 16),
+                                   __uint_as_float(n & 0xFFFF0000u) * __uint_as_float(gw[i] & 0xFFFF0000u));
     }
     return u32x4{o[0], o[1], o[2], o[3]};
 }
