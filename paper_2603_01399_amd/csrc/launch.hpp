@@ -81,6 +81,18 @@ constexpr int w4_region_bytes(int MP, int XS) {
     return w4_waves(MP, XS) * (x > tiles ? x : tiles);
 }
 
+// The W8A8 kernel (16 waves): whether the raw activations of a form stay in registers between the maximum and the codes (else
+// they are read again), the slots that pass through LDS at a time on their way there, the regions.
+constexpr bool a8_hold(int MP, int XS) { return XS * MP <= (MP == 8 ? 96 : 80) && MP != 32; }
+constexpr int a8_pass(int MP, int XS) {
+    if (!a8_hold(MP, XS) || (MP == 8 && XS <= 4)) return 0;
+    return XS <= (MP == 8 ? 6 : 4) ? XS : (XS + 1) / 2;
+}
+constexpr int a8_region_bytes(int MP, int XS) {
+    const int x = a8_pass(MP, XS) * MP * 128, tiles = 2 * (MP == 32 ? 2 : 1) * 1024;
+    return 16 * (x > tiles ? x : tiles);
+}
+
 struct DirectPlan {
     int XS, SC, C, ksplit, slice_steps, groups, sc_bytes, lds_bytes;
 };

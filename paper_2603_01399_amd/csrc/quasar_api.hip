@@ -711,7 +711,7 @@ int launch_logits(const GemmParams &base, int M, float inv_t, float *stats, size
 bool plan_direct_w8a8(int MP, int T, int S, bool smooth, DirectPlan &d) {
     constexpr int kSlots[] = {1, 2, 3, 4, 5, 6, 8, 12};
     if (g_tune_nw.load() != 16 || g_tune_wgs.load() != 1) return false;
-    const int need = (S + 15) / 16, NB = MP == 32 ? 2 : 1;
+    const int need = (S + 15) / 16;
     d.XS = 0;
     for (int xs : kSlots)
         if (!d.XS && xs >= need && !(MP == 32 && xs > 8)) d.XS = xs;
@@ -722,7 +722,7 @@ bool plan_direct_w8a8(int MP, int T, int S, bool smooth, DirectPlan &d) {
     if (d.groups > kMaxGrid) return false;
     const int tpw = (T + d.groups - 1) / d.groups;
     d.sc_bytes = ((tpw * kTileRows * 2 + 15) / 16) * 16;
-    d.lds_bytes = 2 * 16 * NB * 1024 + d.sc_bytes + 16 * MP * 4 + (smooth ? 16 * d.XS * 256 : 0);
+    d.lds_bytes = a8_region_bytes(MP, d.XS) + d.sc_bytes + 16 * MP * 4 + (smooth ? 16 * d.XS * 256 : 0);
     if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
     return d.lds_bytes <= kMaxLds;
 }
@@ -735,7 +735,7 @@ int launch_w8a8(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NB = MP == 32 ? 2 : 1;
     DirectPlan d{};
-    if (plan_direct_w8a8(MP, p.T, p.S, p.smooth != nullptr, d)) {
+    if (direct_reach(M, p.ldx) && plan_direct_w8a8(MP, p.T, p.S, p.smooth != nullptr, d)) {
         if (grid_out) *grid_out = d.groups;
         return launch_direct_w8a8(EPI, p, MP, d, stream);
     }

@@ -9,8 +9,9 @@
 //
 // What bounds it: the quantiser's vector instructions (about eight per element and workgroup, 1.3 us at M = 8, K = 4096)
 // while the first weights are on their way; then the weight stream.  Back to back, HBM-cold, us a launch, staged -> this:
-//     M = 8:  4096 x 4096 11.8 -> 7.1, 12288 x 4096 17.2 -> 11.4, 4096 x 12288 28.4 -> 20.5 (12 slots: every workgroup
-//             quantises 98304 values);  M = 16: 17.8 -> 9.3, 23.1 -> 13.2, 45.2 -> 29.2;  M = 32: 31.6 -> 22.3, 36.0 -> 28.8
+//     M = 8:  4096 x 4096 11.8 -> 7.1, 12288 x 4096 17.2 -> 11.4, 4096 x 12288 28.4 -> 17.9 (12 slots: every workgroup
+//             quantises 98304 values; 20.7 with x gathered);  M = 16: 17.8 -> 8.7, 23.1 -> 12.5, 45.2 -> 29.3;  M = 32: 31.6 -> 21.5,
+//             36.0 -> 27.6
 #pragma once
 
 #include "launch.hpp"
@@ -31,11 +32,9 @@ __device__ __forceinline__ unsigned int quantize_quad(float x0, float x1, float 
     return lo | (hi << 16);
 }
 
-// Whether the raw activations of a form stay in registers between the maximum and the codes (else they are read again).
-constexpr bool a8_hold(int MP, int XS) { return XS * MP <= (MP == 8 ? 96 : 80) && MP != 32; }
-
 // A slot is 64 k of one tile: one 1 KB load, one v_mfma_i32_16x16x64_i8 per 16 tokens.
-// LDS: [2 x 16 x NB partial tiles of 1 KB][row scales][16 x MP maxima][smoothing factors: 16 waves x XS x 256 B]
+// LDS: [a region per wave: activations on their way in, then 2 x NB partial tiles of 1 KB][row scales][16 x MP maxima]
+//      [smoothing factors: 16 waves x XS x 256 B]
 template <int MP, int EPI, int XS, bool SMOOTH>
 __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams p) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -55,10 +54,12 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     const int t0 = tile_split(p.T, b, G);
     const int ntiles = tile_split(p.T, b + 1, G) - t0;
 
-    i32x4 *stage = reinterpret_cast<i32x4 *>(lds);                                   // [2][NW][NB][64]
-    uint16_t *sc_lds = reinterpret_cast<uint16_t *>(lds + 2 * NW * NB * 1024);       // [tiles][16]
-    float *maxima = reinterpret_cast<float *>(lds + 2 * NW * NB * 1024 + p.sc_bytes);              // [NW][MP]
-    const unsigned int sm_ofs = (unsigned int)(2 * NW * NB * 1024 + p.sc_bytes + NW * MP * 4 + w * (XS * 256));
+    constexpr int kPass = a8_pass(MP, XS);
+    constexpr int region = a8_region_bytes(MP, XS) / NW;
+    unsigned char *own = lds + w * region;
+    uint16_t *sc_lds = reinterpret_cast<uint16_t *>(lds + NW * region);              // [tiles][16]
+    float *maxima = reinterpret_cast<float *>(lds + NW * region + p.sc_bytes);       // [NW][MP]
+    const unsigned int sm_ofs = (unsigned int)(NW * region + p.sc_bytes + NW * MP * 4 + w * (XS * 256));
 
     const int first = (p.S * w) / NW;
     const int n = (p.S * (w + 1)) / NW - first;
@@ -84,7 +85,34 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     for (int nb = 0; nb < NB; ++nb) xrow[nb] = p.x + (long long)min(tok + 16 * nb, p.M - 1) * p.ldx + 16 * g + 8 * half8;
     auto load_x = [&](int i, int j) { return *reinterpret_cast<const u32x4 *>(xrow[j / XP] + 64 * step[i] + 8 * (j % XP)); };
     u32x4 raw[HOLD ? XS : 1][NB * XP];
-    if constexpr (HOLD)
+    static_assert(HOLD || kPass == 0, "activations that are read twice come straight from memory");
+    // through LDS in whole cache lines, as in stream_direct.hpp
+    [[maybe_unused]] auto fetch_x = [&](int at) {
+        const unsigned int base = lds_address_of(lds) + (unsigned int)(w * region);
+#pragma unroll
+        for (int t8 = 0; t8 < MP / 8; ++t8) {
+            const int t = (lane >> 3) + 8 * t8;
+            const unsigned int off = (unsigned int)min(t, p.M - 1) * (unsigned int)(2 * p.ldx) + (unsigned int)(((lane & 7) ^ (t & 7)) * 16);
+#pragma unroll
+            for (int i = 0; i < kPass; ++i)
+                if (at + i < XS)
+                    load_to_lds_16(reinterpret_cast<unsigned long long>(p.x) + 128ull * (unsigned int)step[at + i], off,
+                                   base + (i * (MP / 8) + t8) * 1024);
+        }
+    };
+    [[maybe_unused]] auto read_x = [&](int at) {
+#pragma unroll
+        for (int i = 0; i < kPass; ++i)
+            if (at + i < XS)
+#pragma unroll
+                for (int j = 0; j < NB * XP; ++j) {
+                    const int t = tok + 16 * (j / XP), c = 2 * g + half8 + j % XP;
+                    raw[HOLD ? at + i : 0][j] =
+                        *reinterpret_cast<const u32x4 *>(own + (i * (MP / 8) + (t >> 3)) * 1024 + (t & 7) * 128 + ((c ^ (t & 7)) * 16));
+                }
+    };
+    if constexpr (kPass > 0) fetch_x(0);
+    else if constexpr (HOLD)
 #pragma unroll
         for (int i = 0; i < XS; ++i)
 #pragma unroll
@@ -113,7 +141,17 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
         reinterpret_cast<unsigned int *>(sc_lds)[i >> 1] =
             *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + i);
     // (the loads into LDS are older than the ring's and loads return in order)
-    if constexpr (SMOOTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RD) : "memory");
+    if constexpr (SMOOTH || kPass > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RD) : "memory");
+    if constexpr (kPass > 0) {
+        read_x(0);
+#pragma unroll
+        for (int at = kPass; at < XS; at += kPass) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            fetch_x(at);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            read_x(at);
+        }
+    }
 
     // the eight smoothed values of piece j of slot i
     auto smoothed = [&](const u32x4 &v, int i, int j, float (&xt)[8]) {
@@ -198,10 +236,10 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
 
     // tile end: exact integer sum over the waves, Eq. 10 as fp32(acc) * (dx * dw), each one fp32 operation
     auto tile_end = [&](int tl) {
-        i32x4 *st = stage + parity * NW * NB * 64;
+        const int at = (parity * NB * 64 + lane) * 16;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            st[(w * NB + nb) * 64 + lane] = acc[nb];
+            *reinterpret_cast<i32x4 *>(own + at + nb * 1024) = acc[nb];
             acc[nb] = i32x4{0, 0, 0, 0};
         }
         lds_barrier();
@@ -216,7 +254,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
 #pragma unroll 1
                 for (int w0 = 0; w0 < NW; w0 += 8)             // (a loop: bounds the registers of the reads in flight)
 #pragma unroll
-                    for (int ww = w0; ww < w0 + 8; ++ww) r += st[(ww * NB + nb) * 64 + lane];
+                    for (int ww = w0; ww < w0 + 8; ++ww) r += *reinterpret_cast<const i32x4 *>(lds + ww * region + at + nb * 1024);
                 const int m = mcol + 16 * nb;
                 const float dxm = dx[nb];
                 const float v0 = (float)r.x * (dxm * dw0), v1 = (float)r.y * (dxm * dw1);
