@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kQuantWaves * 64, NJ > 16 ? 2 : 4) void quantize_pa
         u32x4 *out = packed + ((long long)t * K + k0);               // 16 rows x 1 k per 16 bytes
         const int n = min(kSpan, K - k0);
         for (int q = tid; q < n; q += kQuantWaves * 64)
-            out[q] = *reinterpret_cast<const u32x4 *>(lds + (q >> 4) * kQuantSlotBytes + (q & 15) * 16);
+            __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(lds + (q >> 4) * kQuantSlotBytes + (q & 15) * 16), out + q);
     };
 
     if (K <= kSpan) {
