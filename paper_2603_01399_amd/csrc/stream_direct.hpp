@@ -417,7 +417,7 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
     if constexpr (PRE != PRE_NONE) {
         if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
         if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5>(d.XS, grid, d.lds_bytes, stream, p);
-        return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     } else {
         if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 12>(d.XS, grid, d.lds_bytes, stream, p);
         if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 16, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);

@@ -79,6 +79,24 @@ def test_fused_forms(qb, M, K):
     assert rel(qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, eps=1e-6), act) <= 1e-2
 
 
+@pytest.mark.parametrize("M,N,K", [(32, 16 * 22, 4096), (32, 16 * 1026, 5120), (27, 16 * 1026, 4160)])
+def test_fused_norm_of_many_tokens(qb, M, N, K):
+    """The normalised forms of 17 to 32 tokens: eight slots a wave, and ten where there are many tiles."""
+    print("direct fused norm", M, N, K, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    gamma = (1 + 0.2 * torch.randn(K, generator=gen, device="cuda")).bfloat16()
+    wq, sc = qb.quantize_weights(torch.randn(N, K, generator=gen, device="cuda") * 0.02)
+    what = qb.unpack_weights(wq, N, K).float() * sc.float()[:, None]
+    xd = x.double()
+    norm = ((xd * torch.rsqrt((xd * xd).mean(1, keepdim=True) + 1e-6)).bfloat16().double() * gamma.double()).bfloat16()
+    lin = torch.cat([norm.double() @ what[i:i + 4096].double().t() for i in range(0, N, 4096)], 1)
+    assert rel(qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, eps=1e-6), lin) <= 6e-3
+    gu = lin.bfloat16().double().view(M, N // 32, 2, 16)
+    act = (torch.nn.functional.silu(gu[:, :, 0]).bfloat16().double() * gu[:, :, 1]).reshape(M, N // 2)
+    assert rel(qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, eps=1e-6), act) <= 1e-2
+
+
 @pytest.mark.parametrize("M", [2, 9, 17])
 def test_sampling_statistics_taken_while_streaming(qb, M):
     """Softmax statistics per workgroup of the streaming kernel against those taken from the finished logits (a workspace with
