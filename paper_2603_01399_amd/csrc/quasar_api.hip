@@ -1421,9 +1421,9 @@ int quasar_lmhead_verify_sample(const uint16_t *hidden, int64_t M, int64_t K, in
     if (!nblk) {
         nblk = kSampleBlocks;
         hipLaunchKernelGGL(softmax_partial_kernel, dim3(kSampleBlocks, (unsigned int)M), dim3(256), 0, st, logits, (int)V,
-                           inv_t, stats);
+                           SampleBlocks((int)V, kSampleBlocks), inv_t, stats);
     }
-    hipLaunchKernelGGL(speculative_sample_kernel, dim3(1), dim3(1024), 0, st, logits, (int)V, (int)M, inv_t, nblk, draft_ids,
+    hipLaunchKernelGGL(speculative_sample_kernel, dim3(1), dim3(1024), 0, st, logits, (int)V, (int)M, inv_t, SampleBlocks((int)V, nblk), draft_ids,
                        (int)n_draft, u_accept, u_sample, stats, out_accept_len, out_next_token, out_p_draft);
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }

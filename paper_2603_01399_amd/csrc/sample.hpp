@@ -15,6 +15,7 @@
 // two launches of 5.5 and 14 us before, now one of 6.6 us.
 #pragma once
 
+#include "draw.hpp"
 #include "quasar_device.hpp"
 #include "stream_gemm.hpp"
 
@@ -22,18 +23,34 @@ namespace quasar {
 
 constexpr int kSampleBlocks = 32;
 
-// first quad of block b of nblk
-__device__ __forceinline__ int sample_block_begin(int V, int b, int nblk) { return 4 * tile_split(V / kTileRows, b, nblk); }
+// The vocabulary's blocks of whole tiles, cut where the workgroups of the streaming kernel are (tile_split): of n blocks of T
+// tiles, block b begins at tile floor(T b / n) = (T / n) b + floor((T mod n) b / n).  n is at most 4096, so the second product is below
+// 2^24: its quotient is taken in fp32, one off at most, and put right.  (The general integer divisions cost the one
+// workgroup that draws 0.6 us.)
+struct SampleBlocks {
+    int n, each, rest;
+    float inv_n;
+    SampleBlocks(int V, int n_) : n(n_), each((V / kTileRows) / n_), rest((V / kTileRows) % n_), inv_n(1.0f / (float)n_) {}
+    __device__ __forceinline__ int tile(int b) const {
+        const int x = rest * b;
+        int q = (int)((float)x * inv_n);
+        const int left = x - q * n;
+        q += left >= n ? 1 : 0;
+        q -= left < 0 ? 1 : 0;
+        return each * b + q;
+    }
+    __device__ __forceinline__ int quad(int b) const { return kTileRows / 4 * tile(b); }
+};
 
 // grid (kSampleBlocks, M), 256 threads.  partial[(m * kSampleBlocks + b) * 2] = max of z over the
 // block, [.. + 1] = sum of exp(z - max); z = logit * inv_t.  V is a multiple of 16: rows are read
 // as 16-byte quads.
-__global__ __launch_bounds__(256) void softmax_partial_kernel(const float *logits, int V, float inv_t,
+__global__ __launch_bounds__(256) void softmax_partial_kernel(const float *logits, int V, SampleBlocks blocks, float inv_t,
                                                              float *partial) {
     __shared__ float sm[4], ss[4];
     const int b = blockIdx.x, m = blockIdx.y, tid = threadIdx.x;
     const f32x4 *row4 = reinterpret_cast<const f32x4 *>(logits + (long long)m * V);
-    const int q_lo = sample_block_begin(V, b, kSampleBlocks), q_hi = sample_block_begin(V, b + 1, kSampleBlocks);
+    const int q_lo = blocks.quad(b), q_hi = blocks.quad(b + 1);
     float mx = -__builtin_inff(), s = 0.f;
     for (int q0 = q_lo + tid; q0 < q_hi; q0 += 256 * 4) {
         f32x4 v[4];
@@ -62,8 +79,11 @@ __global__ __launch_bounds__(256) void softmax_partial_kernel(const float *logit
     }
 }
 
-// Inclusive prefix sum over the workgroup's 1024 threads (fixed order); total: the sum over all.
-__device__ __forceinline__ float block_scan(float v, float *wave_tot, float &total) {
+// Prefix sum over the workgroup's 1024 threads (fixed order): incl, this thread's inclusive sum; before, the sum of the waves in
+// front of its own; behind, that and its own wave; total.  wave_tot: 16 floats, another 16 in the next call (the barrier
+// of that call is behind the reads of this one).
+struct BlockSums { float incl, before, behind, total; };
+__device__ __forceinline__ BlockSums block_scan(float v, float *wave_tot) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -72,30 +92,39 @@ __device__ __forceinline__ float block_scan(float v, float *wave_tot, float &tot
     }
     if (lane == 63) wave_tot[wv] = v;
     __syncthreads();
-    float base = 0.f;
-    total = 0.f;
+    BlockSums s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        if (i < wv) base += wave_tot[i];
-        total += wave_tot[i];
+        if (i == wv) s.before = s.total;
+        s.total += wave_tot[i];
+        if (i == wv) s.behind = s.total;
     }
-    __syncthreads();
-    return base + v;
+    s.incl = s.before + v;
+    return s;
+}
+
+// Whether this thread owns the draw at the target (draw.hpp), and the sum in front of it.
+__device__ __forceinline__ bool draw_mine(float sum, const BlockSums &s, float target, float &run) {
+    const int lane = threadIdx.x & 63;
+    run = __shfl_up(s.incl, 1, 64);
+    if (lane == 0) run = s.before;
+    const unsigned long long mass = __builtin_amdgcn_ballot_w64(sum > 0.f);
+    const unsigned long long reach = __builtin_amdgcn_ballot_w64(sum > 0.f && s.incl > target);
+    return draw_in_wave(s.before, s.behind, target) && lane == draw_lane(reach, mass);
 }
 
 // One workgroup of 1024 threads.  partial: [M][nblk] (max, sum of exp(z - max)).
-__global__ __launch_bounds__(1024) void speculative_sample_kernel(const float *logits, int V, int M, float inv_t, int nblk,
+__global__ __launch_bounds__(1024) void speculative_sample_kernel(const float *logits, int V, int M, float inv_t, SampleBlocks blocks,
                                                                  const int32_t *draft, int n_draft,
                                                                  const float *u_accept, const float *u_sample,
                                                                  const float *partial, int32_t *out_accept,
                                                                  int32_t *out_token, float *out_p_draft) {
     __shared__ float pos_max[32], pos_pd[32], pos_zd[32], pos_ua[32], pos_us[32];
     __shared__ int pos_draft[32];
-    __shared__ float part[1024];
-    __shared__ float wave_tot[16];
-    __shared__ int blk_s, chunk_s;
+    __shared__ float wave_tot[2][16];
+    __shared__ int blk_s, thin_s;
     __shared__ float target_s;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, nblk = blocks.n;
     // per position: 32 lanes merge the block statistics; p of the proposed token
     {
         const int m = tid >> 5, j = tid & 31;
@@ -141,6 +170,7 @@ __global__ __launch_bounds__(1024) void speculative_sample_kernel(const float *l
             pos_max[m] = mx;
             pos_pd[m] = pd;
         }
+        if (tid == 0) blk_s = 0, thin_s = -1, target_s = 0.f;
     }
     __syncthreads();
     // leading accepted candidates (every wave for itself): q(x~) = 1
@@ -148,102 +178,90 @@ __global__ __launch_bounds__(1024) void speculative_sample_kernel(const float *l
     const int pos = __builtin_ctzll(~__builtin_amdgcn_ballot_w64(ok));
     const float mx = pos_max[pos];
     const int banned = pos < n_draft ? pos_draft[pos] : -1;
+    if (tid == 0) out_accept[0] = pos;
+    const float *row = logits + (long long)pos * V;
+    const f32x4 *row4 = reinterpret_cast<const f32x4 *>(row);
+    auto quad_mass = [&](int q) {
+        const f32x4 v = row4[q];
+        return f32x4{4 * q != banned ? expf(v.x * inv_t - mx) : 0.f, 4 * q + 1 != banned ? expf(v.y * inv_t - mx) : 0.f,
+                     4 * q + 2 != banned ? expf(v.z * inv_t - mx) : 0.f, 4 * q + 3 != banned ? expf(v.w * inv_t - mx) : 0.f};
+    };
+    // quads a0 .. a1 - 1 of the row: this thread's stretch of quads q_lo .. q_hi - 1, and its mass (first quad's kept in `head`)
+    auto stretch = [&](int q_lo, int q_hi, int &a0, int &a1, f32x4 &head) {
+        const int per = (q_hi - q_lo + 1023) / 1024;
+        a0 = min(q_hi, q_lo + tid * per);
+        a1 = min(q_hi, a0 + per);
+        float sum = 0.f;
+        for (int q = a0; q < a1; ++q) {
+            const f32x4 e = quad_mass(q);
+            if (q == a0) head = e;
+            sum += (e.x + e.y) + (e.z + e.w);
+        }
+        return sum;
+    };
+    // A block among all, each thread with a stretch of neighbouring ones; the rejected token's mass is removed (max(0, p - q) is 0
+    // on the proposed token and p elsewhere).
     {
-        // the draw at that position: masses of the blocks, the rejected token's mass removed (max(0, p - q) is 0 on the
-        // proposed token and p elsewhere); each thread owns `per` neighbouring blocks
         const bool ban = banned >= 0 && banned < V;
+        const int ban_tile = ban ? banned / kTileRows : -1;
         const float ban_mass = ban ? expf(pos_zd[pos] - mx) : 0.f;
+        const u32x2 *stats = reinterpret_cast<const u32x2 *>(partial) + (long long)pos * nblk;
         const int per = (nblk + 1023) / 1024;
         const int b0 = min(nblk, tid * per), b1 = min(nblk, b0 + per);
+        int ban_blk = -1;                        // the rejected token's block, if it is this thread's, and its other mass
+        float ban_left = -1.f;
         auto mass = [&](int b) {
-            const float pm = partial[((long long)pos * nblk + b) * 2];
-            float v = pm > -__builtin_inff() ? partial[((long long)pos * nblk + b) * 2 + 1] * expf(pm - mx) : 0.f;
-            if (ban && banned / 4 >= sample_block_begin(V, b, nblk) && banned / 4 < sample_block_begin(V, b + 1, nblk))
-                v = fmaxf(0.f, v - ban_mass);
-            return v;
+            if (b == ban_blk) return ban_left;
+            const u32x2 st = stats[b];
+            const float pm = __uint_as_float(st.x);
+            const float v = pm > -__builtin_inff() ? __uint_as_float(st.y) * expf(pm - mx) : 0.f;
+            if (!ban || ban_tile < blocks.tile(b) || ban_tile >= blocks.tile(b + 1)) return v;
+            // where the token is nearly all of its block the difference is rounding: the other tokens are added up below
+            ban_blk = b;
+            ban_left = fmaxf(0.f, v - ban_mass);
+            if (!(ban_left > v * (1.f / 1024.f))) thin_s = b;
+            return ban_left;
         };
         float sum = 0.f;
         for (int b = b0; b < b1; ++b) sum += mass(b);
-        float total;
-        const float incl = block_scan(sum, wave_tot, total);
-        part[tid] = incl;
-        if (tid == 0) {
-            out_accept[0] = pos;
-            blk_s = -1;
-            chunk_s = 1023;
-        }
-        __syncthreads();
-        float target = pos_us[pos] * total;
-        if (!(target < total)) target = total * (1.f - 1.f / 16777216.f);     // u * total rounded up to the total
-        const float before = tid > 0 ? part[tid - 1] : 0.f;
-        // the first thread whose blocks reach beyond the target; past them all through rounding: the last with mass
-        if (incl > target && (tid == 0 || !(before > target))) {
-            float run = before;
-            int blk = b0;
-            for (; blk + 1 < b1; ++blk) {
-                const float v = mass(blk);
-                if (run + v > target) break;
-                run += v;
+        BlockSums s = block_scan(sum, wave_tot[0]);
+        const int thin = thin_s;                 // (set ahead of the scan's barrier, if at all)
+        if (thin >= 0) {
+            int a0, a1;
+            f32x4 head;
+            const float left = block_scan(stretch(blocks.quad(thin), blocks.quad(thin + 1), a0, a1, head), wave_tot[1]).total;
+            if (ban_blk == thin) {
+                ban_left = left;
+                sum = 0.f;
+                for (int b = b0; b < b1; ++b) sum += mass(b);
             }
-            blk_s = blk;
-            target_s = target - run;            // what is left to cover inside the block
+            s = block_scan(sum, wave_tot[0]);
         }
+        const float target = draw_point(pos_us[pos], s.total);
+        float run;
+        if (draw_mine(sum, s, target, run)) {
+            blk_s = b1 - b0 == 1 ? b0 : max(b0, draw_walk(b0, b1, target, run, mass));
+            target_s = fmaxf(0.f, target - run);                     // what is left to cover inside the block
+        }
+        if (tid == 0) out_accept[0] = pos;
         __syncthreads();
-        const bool none = blk_s < 0;
-        __syncthreads();
-        if (none) {
-            if (sum > 0.f) atomicMax(&blk_s, b1 - 1);
-            __syncthreads();
-            if (tid == 0) {
-                if (blk_s < 0) blk_s = 0;
-                target_s = total;
-            }
-            __syncthreads();
-        }
     }
-    const int blk = blk_s;
-    const float *row = logits + (long long)pos * V;
-    // inside the block: contiguous stretches of quads per thread, prefix sums in vocabulary order
-    const int q_lo = sample_block_begin(V, blk, nblk), q_hi = sample_block_begin(V, blk + 1, nblk);
-    const int per = (q_hi - q_lo + 1023) / 1024;                  // quads per thread
-    const int a0 = min(q_hi, q_lo + tid * per), a1 = min(q_hi, a0 + per);
-    const f32x4 *row4 = reinterpret_cast<const f32x4 *>(row);
-    float sum = 0.f;
-    const f32x4 head = a0 < a1 ? row4[a0] : f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int q = a0; q < a1; ++q) {
-        const f32x4 v = q == a0 ? head : row4[q];
-        const float z4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * q + e != banned) sum += expf(z4[e] * inv_t - mx);
+    // a token of that block, each thread with a stretch of its quads, in vocabulary order
+    int a0, a1;
+    f32x4 head = {0.f, 0.f, 0.f, 0.f};
+    const float sum = stretch(blocks.quad(blk_s), blocks.quad(blk_s + 1), a0, a1, head);
+    const BlockSums s = block_scan(sum, wave_tot[1]);
+    // (block mass and the sum inside the block differ by rounding)
+    const float target = target_s < s.total ? target_s : draw_point(1.f, s.total);
+    float run;
+    if (draw_mine(sum, s, target, run)) {
+        const int tok = draw_walk(4 * a0, 4 * a1, target, run, [&](int i) {
+            const f32x4 e = (i >> 2) == a0 ? head : quad_mass(i >> 2);
+            return (i & 2) ? ((i & 1) ? e.w : e.z) : ((i & 1) ? e.y : e.x);
+        });
+        out_token[0] = max(tok, 4 * a0);
     }
-    float total;
-    const float incl = block_scan(sum, wave_tot, total);
-    part[tid] = incl;
-    float target = target_s;
-    if (!(target < total)) target = total * (1.f - 1.f / 16777216.f);   // block mass and in-block sum differ by rounding
-    if (target < 0.f) target = 0.f;
-    __syncthreads();
-    if (incl > target && (tid == 0 || !(part[tid - 1] > target))) chunk_s = tid;
-    __syncthreads();
-    if (tid == chunk_s) {
-        float run = tid > 0 ? part[tid - 1] : 0.f;
-        int tok = -1, last = -1;
-        for (int q = a0; q < a1 && tok < 0; ++q) {
-            const f32x4 v = q == a0 ? head : row4[q];
-            const float z4[4] = {v.x, v.y, v.z, v.w};
-            for (int e = 0; e < 4; ++e) {
-                if (4 * q + e == banned) continue;
-                const float ex = expf(z4[e] * inv_t - mx);
-                if (ex > 0.f) last = 4 * q + e;
-                run += ex;
-                if (run > target) { tok = 4 * q + e; break; }
-            }
-        }
-        if (tok < 0) tok = last;            // rounding at the very end of the stretch
-        if (tok < 0) tok = a1 > a0 ? 4 * a1 - 1 : V - 1;
-        out_token[0] = tok;
-    }
+    if (tid == 0 && !(target < s.total)) out_token[0] = V - 1;          // (no mass in the row: not finite)
 }
 
 }  // namespace quasar

@@ -153,3 +153,62 @@ def test_sample_argument_errors(qb):
     small = torch.empty(64, dtype=torch.uint8, device="cuda")
     with pytest.raises(qb.QuasarError):
         qb.lmhead_verify_sample(h, wq, sc, 64, d4[:3], 1.0, u4, u4, workspace=small)
+
+
+def stepped_head(qb, logits, step=0.125):
+    """Hidden state and int8 vocabulary matrix whose logits are exactly `logits` (multiples of `step` within 127 steps)."""
+    V = len(logits)
+    w = np.zeros((V, 64), dtype=np.float32)
+    w[:, 0] = logits
+    w[:, 1] = 127 * step                                         # sets the row's step size; its input is zero
+    h = np.zeros((1, 64), dtype=np.float32)
+    h[0, 0] = 1.0
+    wq, sc = qb.quantize_weights(f32_to_dev(w))
+    return synth.to_bf16_bits(h), wq, sc
+
+
+# 20, 100 and 256 blocks, and with room for the least workspace only 32 blocks where the vocabulary has more than 128 tiles
+@pytest.mark.parametrize("least", [False, True])
+@pytest.mark.parametrize("T", [1.0, 0.02])
+@pytest.mark.parametrize("V", [320, 1600, 4096, 40000])
+def test_draw_at_the_ends_of_the_distribution(qb, V, T, least):
+    """The largest uniform numbers, also where most blocks of the vocabulary have no mass in fp32."""
+    say("sample verify, ends", V, T, least)
+    M = 8
+    rng = np.random.Generator(np.random.Philox(V))
+    logits = rng.integers(-127, 128, size=V) * 0.125
+    h, wq, sc = stepped_head(qb, logits)
+    h = bf16_to_dev(np.repeat(h, M, axis=0))
+    p = sp.softmax(logits[None], T)[0]
+    ws = torch.full((M * V * 4 + 32 * 32 * 2 * 4,), 0xFF, dtype=torch.uint8, device="cuda") if least else None
+    us = torch.zeros(M, dtype=torch.float32, device="cuda")
+    for u in [0.0] + [1.0 - j * 2.0 ** -24 for j in range(1, 17)] + list(np.float32(rng.random(8)).astype(float)):
+        us[0] = u
+        acc, tok, _ = qb.lmhead_verify_sample(h, wq, sc, V, None, T, None, us, workspace=ws)
+        assert int(acc) == 0
+        tok = int(tok)
+        assert 0 <= tok < V and np.float32(p[tok] / p.max()) > 0, (u, tok)
+        check_draw(tok, p, u, *sp.inverse_cdf(p, u))
+
+
+@pytest.mark.parametrize("V", [320, 4096, 40000])
+def test_draw_without_a_token_that_was_nearly_certain(qb, V):
+    """The rejected token holds all but 1e-4 or less of the mass: what is left of its block must not be the rounding of a
+    difference."""
+    say("sample verify, nearly certain token rejected", V)
+    M = 2
+    rng = np.random.Generator(np.random.Philox(V + 1))
+    logits = rng.integers(-127, -20, size=V) * 0.125
+    top = V // 3
+    logits[top] = 127 * 0.125
+    h, wq, sc = stepped_head(qb, logits)
+    h = np.repeat(h, M, axis=0)
+    p = sp.softmax(logits[None], 1.0)[0]
+    assert 1.2e-7 < 1 - p[top] < 1e-4
+    mass = p.copy()
+    mass[top] = 0.0
+    ua = np.array([1.0 - 2.0 ** -24], dtype=np.float32)          # above the probability: rejected
+    for u in [0.0, 1.0 - 2.0 ** -24] + list(np.float32(rng.random(24)).astype(float)):
+        n_acc, tok, _ = run(qb, h, wq, sc, V, np.array([top], np.int32), 1.0, ua, np.array([u, 0], np.float32))
+        assert n_acc == 0 and tok != top
+        check_draw(tok, mass, u, *sp.inverse_cdf(mass, u))
