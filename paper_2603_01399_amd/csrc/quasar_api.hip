@@ -223,19 +223,23 @@ bool plan_direct(int MP, int T, int TU, int S, int SC, int C, int ksplit, bool w
     return true;
 }
 
-// How many slices a K that would otherwise be staged in chunks is split into: the cheapest of 1, 2, 4, .. by the bytes
-// that the busiest compute unit moves.  Measured rates: 25 KB/us of weights and 75 KB/us of activations per compute
-// unit; a split adds its partial sums (written, read and added by a second launch: 4 us and its bytes at 4 MB/us).
+// How many slices a K that would otherwise be staged in chunks is split into: the cheapest of 1 .. 8 by what the busiest
+// compute unit does.  Fitted to the times of 676 shapes (M 1 .. 32, K 2048 .. 25600, N 256 .. 16384, both weight types) with every
+// number of slices: 62 KB/us of weights, half of that for the loads of slots that only fill a form, 60 KB/us of
+// activations; a split adds a second launch (1 us and 0.6 us a slice, which it reads one after the other) and 0.7 us per MB of
+// partial sums.  Over those shapes the choice is 1 % slower than the best one on average.  (Rates of 25 and 75 KB/us and 4 us for
+// a split, the first estimate, chose up to half too many or too few slices where tiles are few: M = 16, 1024 x 12288
+// 12.7 us, now 8.5.)
 bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t workspace_bytes, int most_slots, DirectPlan &best) {
     double best_us = 0.0;
     bool found = false;
-    for (int ks = 1; ks <= 16; ks *= 2) {
+    for (int ks = 1; ks <= 8; ++ks) {
         DirectPlan d{};
         if (ks > 1 && splitk_bytes(M, N, ks) > workspace_bytes) break;
         if (!plan_direct(MP, T, 1, S, S, 1, ks, !w16, most_slots, 0, false, d)) continue;
-        const int tpw = (T + d.groups - 1) / d.groups;
-        double us = (double)tpw * d.slice_steps * (w16 ? 2.0 : 1.0) / 25.0 + (double)MP * d.slice_steps * 0.125 / 75.0;
-        if (ks > 1) us += 4.0 + 8.0 * ks * M * N / 4.0e6;
+        const int tpw = (T + d.groups - 1) / d.groups, fill = d.XS * direct_waves(MP, d.XS) - d.slice_steps;
+        double us = tpw * (w16 ? 2.0 : 1.0) * (d.slice_steps / 62.0 + fill / 30.0) + MP * 0.125 * d.slice_steps / 60.0;
+        if (ks > 1) us += 1.0 + 0.6 * ks + 0.7e-6 * (double)splitk_bytes(M, N, ks);
         if (!found || us < best_us) { best = d; best_us = us; found = true; }
     }
     return found;
@@ -287,7 +291,8 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
         const int slots = p.K / 64;
         const bool free_order = EPI == EPI_LINEAR && workspace && aligned(workspace, 16) && (pl.C > 1 || MP == 32);
         DirectPlan d{};
-        const bool ok = !direct_reach(M, p.ldx) ? false : free_order ? plan_direct_split(MP, M, p.T, slots, W16, p.N, workspace_bytes, MP == 8 ? 12 : (MP == 16 ? 24 : 10), d)
+        const bool ok = !direct_reach(M, p.ldx) ? false : free_order ? plan_direct_split(MP, M, p.T, slots, W16, p.N, workspace_bytes,
+                                                                                              MP == 8 ? 12 : (MP == 16 ? (W16 ? 20 : 24) : 10), d)
                                    : plan_direct_ordered(MP, p.T, slots, W16, pl.SC, pl.C, d);
         if (ok) {
             if (d.ksplit > 1) p.part32 = static_cast<float *>(workspace);
