@@ -95,6 +95,7 @@ constexpr int a8_region_bytes(int MP, int XS) {
 
 struct DirectPlan {
     int XS, SC, C, ksplit, slice_steps, groups, sc_bytes, lds_bytes;
+    bool pair;       // 32 tokens in the order of sixteen waves
 };
 
 // p: as for the other kernels (its step counts are replaced by slots of 64 k).  epi, pre, resid: EPI_*, PRE_* and whether a

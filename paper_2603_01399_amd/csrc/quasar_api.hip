@@ -246,11 +246,21 @@ bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t work
 }
 
 // Plan of the ordered forms (linear without a workspace, argmax): the sum is taken in the order of the whole-step
-// launch, so K is summed in the chunks that it stages (SC, C in its own steps).  More than 16 tokens: that order is one
-// of 16 waves, which the 8-wave form does not have.
+// launch, so K is summed in the chunks that it stages (SC, C in its own steps).  More than 16 tokens: K in one piece only
+// (22 slots at most), by waves that hold two neighbouring shares each.
 bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, DirectPlan &d) {
-    if (MP == 32) return false;
-    const int per = w16 ? 2 : 1;                     // steps per slot; a wave's share must be whole slots
+    const int per = w16 ? 2 : 1;                     // steps per slot
+    if (MP == 32) {
+        if (C > 1) return false;
+        const int share = (per * S + 15) / 16;       // steps of the largest of sixteen shares
+        if (share > (w16 ? 3 : 2) || !plan_direct(MP, T, 1, S, S, 1, 1, !w16, 4, 0, false, d)) return false;
+        d.XS = 2 * share;
+        d.pair = true;
+        d.lds_bytes = direct_region_bytes(MP, d.XS, 1) + d.sc_bytes;
+        if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+        return d.lds_bytes <= kMaxLds;
+    }
+    // up to 16 tokens a wave's share must be whole slots
     if (w16) {
         const int last = 2 * S - (C - 1) * SC;
         if (SC % 32 || last % 32) return false;
@@ -286,10 +296,14 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     const int NW = g_tune_nw.load();
     Plan pl = make_plan(p.T, p.S, (W16 ? 64 : 128) * MP, NB * 1024, NW, !W16);
     {
-        // Activations in registers wherever a form holds them; with a workspace the order of the sum is free and a
-        // long K may be split across workgroups, without one it is that of the chunked kernel below.
+        // Activations in registers wherever a form holds them.  Where they do not fit the LDS in one piece and the workspace
+        // holds the partial sums, the order of the sum is free and K may be split across workgroups; otherwise it
+        // is that of the chunked kernel below.
         const int slots = p.K / 64;
-        const bool free_order = EPI == EPI_LINEAR && workspace && aligned(workspace, 16) && (pl.C > 1 || MP == 32);
+        int ksplit = 1, slice_steps = p.S;
+        splitk_shape(M, p.S, W16, ksplit, slice_steps);
+        const bool free_order = EPI == EPI_LINEAR && pl.C > 1 && workspace && aligned(workspace, 16) &&
+                                workspace_bytes >= splitk_bytes(M, p.N, ksplit);
         DirectPlan d{};
         const bool ok = !direct_reach(M, p.ldx) ? false : free_order ? plan_direct_split(MP, M, p.T, slots, W16, p.N, workspace_bytes,
                                                                                               MP == 8 ? 12 : (MP == 16 ? (W16 ? 20 : 24) : 10), d)

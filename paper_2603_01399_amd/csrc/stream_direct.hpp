@@ -33,18 +33,23 @@ constexpr int direct_ring(int MP, int slots) {
 
 // A slot is 64 k: one 1 KB load of int8 codes or two of bf16 weights.
 // XS: slots of a tile a wave may have (its activations are held in XS x (MP == 8 ? 4 : MP / 2) registers).
-// CH: K is summed in p.C chunks, each reduced over the waves by itself and added in chunk order (the bits of the
-//     kernels that stage x in chunks); otherwise one sum.
+// CH: the bits of the kernels that stage x, whose order of the sum is one of 16 waves.  Up to 16 tokens: K is summed in p.C
+//     chunks, each reduced over the waves by itself and added in chunk order.  32 tokens (PAIR): a wave of the eight takes two
+//     neighbouring shares of sixteen, each in its half of the slots and with an accumulator of its own, and hands over
+//     their sum, which is what that order adds first; slots of bf16 weights are 32 k there, as the shares are.
+//     Otherwise one sum a wave.
 // LDS: [a region per wave: activations on their way in, then 2 x C x NB partial tiles of 1 KB][row scales][kept gate tile (EPI_SWIGLU)][16 x MP sums (PRE)]
 template <int MP, bool W16, int EPI, int XS, bool CH = false, int PRE = PRE_NONE, bool RES = false>
 __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kernel(const GemmParams p0) {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int NW = direct_waves(MP, XS);
     constexpr int NB = (MP == 32) ? 2 : 1;          // 16-token blocks
-    constexpr int XP = (MP == 8) ? 1 : 2;           // loads of x per slot and token block
-    constexpr int WL = W16 ? 2 : 1;                 // weight loads per slot
-    constexpr int U = XS >= 4 ? 1 : 4 / XS;         // tiles per round: at least four slots in flight
-    constexpr int RD = direct_ring(MP, XS * U);     // ring depth in slots
+    constexpr bool PAIR = CH && MP == 32;
+    constexpr int KS = PAIR && W16 ? 32 : 64;       // k of a slot
+    constexpr int XP = (MP == 8 || KS == 32) ? 1 : 2;   // loads of x per slot and token block
+    constexpr int WL = W16 && KS == 64 ? 2 : 1;     // weight loads per slot
+    constexpr int U = KS == 32 ? (XS == 6 ? 1 : 2) : (XS >= 4 ? 1 : 4 / XS);    // tiles per round: at least four slots in flight
+    constexpr int RD = KS == 32 ? XS * U : direct_ring(MP, XS * U);                  // ring depth in slots
     static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
     constexpr int kSlotBytes = WL * kStepBytes;
 
@@ -68,10 +73,11 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     const int t0 = TU * tile_split(p.T / TU, b, G);
     const int t1 = TU * tile_split(p.T / TU, b + 1, G);
     const int ntiles = t1 - t0;
-    const int C = CH ? p.C : 1;
+    const int C = CH && !PAIR ? p.C : 1;
 
     // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
     constexpr int kPass = direct_pass(MP, XS);
+    static_assert(KS == 64 || XS / 2 + 1 <= kPass, "slots of 32 k come in one pass of whole lines");
     const int region = max(kPass * MP * 128, 2 * C * NB * 1024);
     unsigned char *own = lds + w * region;
     uint16_t *sc_lds = reinterpret_cast<uint16_t *>(lds + NW * region);                // [tiles][16]
@@ -82,7 +88,18 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     // requested, and they are not multiplied.
     int n = 0, first = 0, bound0 = 0;
     int step[XS];
-    if constexpr (CH) {
+    [[maybe_unused]] int n1 = 0;                    // PAIR: slots of the second share (n: of the first)
+    if constexpr (PAIR) {
+        first = (p.S * (2 * w)) / 16;
+        const int mid = (p.S * (2 * w + 1)) / 16;
+        n = mid - first;
+        n1 = (p.S * (2 * w + 2)) / 16 - mid;
+#pragma unroll
+        for (int i = 0; i < XS; ++i) {
+            const bool mine = i < XS / 2 ? i < n : i - XS / 2 < n1;
+            step[i] = mine ? (i < XS / 2 ? first + i : mid + i - XS / 2) : min(first, p.S - 1);
+        }
+    } else if constexpr (CH) {
         int c = 0, at = 0, left = 0;
         first = (min(p.SC, p.S) * w) / NW;
 #pragma unroll
@@ -116,7 +133,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int q = 0; q < XP; ++q)
-                xr[i][nb * XP + q] = *reinterpret_cast<const u32x4 *>(xrow[nb] + 64 * step[i] + (W16 ? 32 : 8) * q);
+                xr[i][nb * XP + q] = *reinterpret_cast<const u32x4 *>(xrow[nb] + KS * step[i] + (W16 ? 32 : 8) * q);
     };
     // through LDS: slots at .. at + kPass - 1, each instruction 128 bytes of eight tokens' rows, piece c of token t at
     // position c ^ (t & 7) of its 128 bytes (the lanes that read one column of pieces meet different banks)
@@ -128,11 +145,26 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
             const int t = (lane >> 3) + 8 * t8;
             const unsigned int off = (unsigned int)min(t, p.M - 1) * (unsigned int)(2 * p.ldx) + (unsigned int)(((lane & 7) ^ (t & 7)) * 16);
 #pragma unroll
-            for (int i = 0; i < kPass; ++i)
-                if (at + i < XS) load_to_lds_16(xa + 128ull * (unsigned int)step[at + i], off, base + (i * (MP / 8) + t8) * 1024);
+            for (int i = 0; i < kPass; ++i) {
+                // (slots of 32 k: the lines of 64 that hold them)
+                const int s64 = KS == 64 ? step[min(at + i, XS - 1)] : min((min(first, p.S - 1) >> 1) + i, (p.S - 1) >> 1);
+                if (KS == 64 ? at + i < XS : i <= XS / 2)
+                    load_to_lds_16(xa + 128ull * (unsigned int)s64, off, base + (i * (MP / 8) + t8) * 1024);
+            }
         }
     };
     [[maybe_unused]] auto read_x = [&](int at) {
+        if constexpr (KS == 32) {
+#pragma unroll
+            for (int i = 0; i < XS; ++i)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int t = tok + 16 * nb, c = 4 * (step[i] & 1) + g;
+                    xr[i][nb] = *reinterpret_cast<const u32x4 *>(own + (((step[i] >> 1) - (min(first, p.S - 1) >> 1)) * (MP / 8) + (t >> 3)) * 1024 +
+                                                                 (t & 7) * 128 + ((c ^ (t & 7)) * 16));
+                }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < kPass; ++i)
             if (at + i < XS)
@@ -195,7 +227,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RD * WL) : "memory");
         read_x(0);
 #pragma unroll
-        for (int at = kPass; at < XS; at += kPass) {
+        for (int at = kPass; KS == 64 && at < XS; at += kPass) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             fetch_x(at);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -260,6 +292,10 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     [[maybe_unused]] float sume[NB] = {};            // EPI_LOGITS: sum of exp(z - bestv)
     int parity = 0;
 
+    [[maybe_unused]] f32x4 share1[NB];               // PAIR: the second of the two shares
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) share1[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mine = [&](int i) { return PAIR && i >= XS / 2 ? i - XS / 2 < n1 : i < n; };
     // one slot: 64 k of a tile into the accumulators
     auto slot = [&](int d, int i) {
         bf16x8 a[2];
@@ -274,16 +310,18 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
         for (int nb = 0; nb < NB; ++nb) {
             const u32x4 b0 = xr[i][nb * XP];
             const u32x4 b1 = MP == 8 ? rotate_half_row(b0) : xr[i][nb * XP + XP - 1];
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], __builtin_bit_cast(bf16x8, b0), acc[nb], 0, 0, 0);
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], __builtin_bit_cast(bf16x8, b1), acc[nb], 0, 0, 0);
+            f32x4 &to = PAIR && i >= XS / 2 ? share1[nb] : acc[nb];
+            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], __builtin_bit_cast(bf16x8, b0), to, 0, 0, 0);
+            if constexpr (KS == 64) to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], __builtin_bit_cast(bf16x8, b1), to, 0, 0, 0);
         }
     };
     auto hand_over = [&](int c) {
         f32x4 *st = reinterpret_cast<f32x4 *>(own) + (parity * C + c) * NB * 64;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            st[nb * 64 + lane] = acc[nb];
+            st[nb * 64 + lane] = PAIR ? acc[nb] + share1[nb] : acc[nb];
             acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (PAIR) share1[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
     // tile end: cross-wave sum through LDS, neighbouring waves in pairs, the pair sums in order, the chunks in order
@@ -299,9 +337,12 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
 #pragma unroll 1
                     for (int w0 = 0; w0 < NW; w0 += 8)         // (a loop: bounds the registers of the reads in flight)
 #pragma unroll
-                        for (int ww = w0; ww < w0 + 8; ww += 2)
-                            s += *reinterpret_cast<const f32x4 *>(st + ww * region) +
-                                 *reinterpret_cast<const f32x4 *>(st + (ww + 1) * region);
+                        for (int ww = w0; ww < w0 + 8; ww += 2) {
+                            const f32x4 s0 = *reinterpret_cast<const f32x4 *>(st + ww * region);
+                            const f32x4 s1 = *reinterpret_cast<const f32x4 *>(st + (ww + 1) * region);
+                            if constexpr (PAIR) s = (s + s0) + s1;           // (each the sum of a pair already)
+                            else s += s0 + s1;
+                        }
                     rsum[nb] = c > 0 ? s + rsum[nb] : s;
                 }
             }
@@ -333,12 +374,12 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
             for (int i = 0; i < XS; ++i) {
                 constexpr int R = RD;
                 const int j = u * XS + i;
-                if (i < n && (U == 1 || tl < ntiles)) slot(j % R, i);
+                if (mine(i) && (U == 1 || tl < ntiles)) slot(j % R, i);
                 if (!kLast || j + R < U * XS) {
                     const int jn = j + R;
                     refill(j % R, tl0 + (jn / (U * XS)) * U + (jn % (U * XS)) / XS, jn % XS);
                 }
-                if constexpr (CH) {
+                if constexpr (CH && !PAIR) {
                     if (i + 1 == bound) {
                         hand_over(c);
                         ++c;
@@ -350,7 +391,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                 }
             }
             if (U == 1 || tl < ntiles) {
-                if constexpr (!CH) hand_over(0);
+                if constexpr (!CH || PAIR) hand_over(0);
                 tile_end(tl);
             }
         }
@@ -409,6 +450,14 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
     p.xs_bytes = 0;
     const int grid = d.groups * d.ksplit;
     if constexpr (PRE == PRE_NONE && !RES && (EPI == EPI_LINEAR || EPI == EPI_ARGMAX)) {
+        if (d.pair) {
+            if constexpr (W16) {
+                p.S = p.Srow = p.K / 32;
+                return launch_direct_forms<32, W16, EPI, true, PRE, RES, 2, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
+            } else {
+                return launch_direct_forms<32, W16, EPI, true, PRE, RES, 2, 4>(d.XS, grid, d.lds_bytes, stream, p);
+            }
+        }
         if (d.C > 1) {
             if (MP == 8) return launch_direct_forms<8, W16, EPI, true, PRE, RES, 8, 12>(d.XS, grid, d.lds_bytes, stream, p);
             return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);

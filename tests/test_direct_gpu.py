@@ -115,3 +115,40 @@ def test_sampling_statistics_taken_while_streaming(qb, M):
     assert int(full[0]) == int(small[0]) and int(full[1]) == int(small[1])
     assert torch.allclose(full[2], small[2], rtol=1e-5, atol=0)
     assert torch.allclose(full[2].double(), p[:-1].gather(1, draft.long()[:, None])[:, 0], rtol=1e-3, atol=0)
+
+
+# K: one step; one slot a wave; pairs of shares that begin in the middle of a slot (bf16), up to the longest K in one piece
+@pytest.mark.parametrize("K", [64, 512, 576, 960, 1024, 1088, 1216, 1344, 1408])
+@pytest.mark.parametrize("M,N", [(17, 16), (17, 16 * 261), (32, 16 * 600)])
+def test_order_of_many_tokens(qb, M, N, K):
+    """More than 16 tokens, K in one piece: a workspace changes nothing, and the sums are those of the staged kernel."""
+    print("direct order", M, N, K, flush=True)
+    x, w, wq, sc, _ = make(qb, M, N, K)
+    wp = qb.pack_bf16_weights(w)
+    ws = qb.make_workspace(M, N, K)
+    plain, plain16 = qb.w8_linear(x, wq, sc, N), qb.bf16_linear(x, wp, N)
+    assert torch.equal(bits(plain), bits(qb.w8_linear(x, wq, sc, N, workspace=ws)))
+    assert torch.equal(bits(plain16), bits(qb.bf16_linear(x, wp, N, workspace=ws)))
+    am, am16 = (f(None, ws)[0] for f in (lambda d, s: qb.lmhead_verify(x, wq, sc, N, d, s),
+                                         lambda d, s: qb.bf16_lmhead_verify(x, wp, N, d, s)))
+    qb.set_tuning(16, 2, 4)
+    try:
+        assert torch.equal(bits(plain), bits(qb.w8_linear(x, wq, sc, N)))
+        assert torch.equal(bits(plain16), bits(qb.bf16_linear(x, wp, N)))
+        assert torch.equal(am, qb.lmhead_verify(x, wq, sc, N, None, ws)[0])
+        assert torch.equal(am16, qb.bf16_lmhead_verify(x, wp, N, None, ws)[0])
+    finally:
+        qb.set_tuning(16, 1, 4)
+
+
+@pytest.mark.parametrize("M,K", [(1, 12288), (16, 8192), (32, 4096)])
+def test_a_workspace_too_small_changes_nothing(qb, M, K):
+    """K in several pieces, but no room for the partial sums: the order of the call without a workspace."""
+    N = 16 * 4400
+    print("direct small workspace", M, N, K, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    wq = torch.randint(-127, 128, (N * K,), generator=gen, device="cuda", dtype=torch.int8)
+    sc = torch.full((N,), 0.01, dtype=torch.bfloat16, device="cuda")
+    small = torch.empty(4 * M * N, dtype=torch.uint8, device="cuda")
+    assert torch.equal(bits(qb.w8_linear(x, wq, sc, N)), bits(qb.w8_linear(x, wq, sc, N, workspace=small)))
