@@ -160,7 +160,7 @@ size_t splitk_bytes(int M, int N, int ksplit) { return ksplit > 1 ? (size_t)kspl
 
 // Register forms that are built: slots of 64 k per wave and tile.  What bounds them is the register file: a slot takes
 // 4, 8 or 16 registers at up to 8, 16 or 32 tokens.
-constexpr int kDirectSlots8[] = {1, 2, 3, 4, 5, 6, 8, 12};
+constexpr int kDirectSlots8[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12};
 constexpr int kDirectSlots16[] = {1, 2, 3, 4, 5, 6, 8, 16, 20, 24};     // (16 and more: of eight waves)
 constexpr int kDirectSlots32[] = {2, 4, 6, 8, 10};
 
@@ -268,8 +268,10 @@ bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, DirectPl
     if (C > 1) {
         // forms built: see launch_direct
         if (!plan_direct(MP, T, 1, S, SC / per, C, 1, !w16, MP == 8 ? 12 : 8, 0, false, d)) return false;
-        if (MP == 8 && d.XS < 8) d.XS = 8;
         if (MP == 16 && d.XS < 4) d.XS = 4;
+        // slots that only fill the form cost like the others where many tiles are streamed (16384 x 8256, 129 slots of 160,
+        // M = 8: staged 30.6 us, in registers 33.5; 12288 x 8256 22.0 and 22.7; 4096 x 8256 12.0 and 10.8)
+        if (MP == 8 && 16 * d.XS - S > S / 6 && T >= 3 * device_cus()) return false;
         d.lds_bytes = direct_region_bytes(MP, d.XS, C) + d.sc_bytes;
         if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
         return d.lds_bytes <= kMaxLds;
@@ -728,12 +730,16 @@ int launch_logits(const GemmParams &base, int M, float inv_t, float *stats, size
 // Plan of the W8A8 kernel that keeps its activation codes in registers (stream_direct_a8.hpp): integer sums, so no order to
 // keep; 16 waves, the smallest built form that holds a wave's slots.
 bool plan_direct_w8a8(int MP, int T, int S, bool smooth, DirectPlan &d) {
-    constexpr int kSlots[] = {1, 2, 3, 4, 5, 6, 8, 12};
+    constexpr int kSlots[] = {1, 2, 3, 4, 5, 6, 8, 10, 12};
     if (g_tune_nw.load() != 16 || g_tune_wgs.load() != 1) return false;
     const int need = (S + 15) / 16;
+    // More than 16 tokens: at most 8 slots, and with smoothing 5, beyond which the codes, the values on their way and the factors
+    // spill 80 to 160 registers: M = 32, 12288 x 6144 staged 52.4 us, in registers 61.2, 4096 x 8192 60.0 and 83.3; 4096 x 5120
+    // 42.1 and 39.8.
+    const int most = MP == 32 ? (smooth ? 5 : 8) : 12;
     d.XS = 0;
     for (int xs : kSlots)
-        if (!d.XS && xs >= need && !(MP == 32 && xs > 8)) d.XS = xs;
+        if (!d.XS && xs >= need && xs <= most) d.XS = xs;
     if (!d.XS) return false;
     d.groups = device_cus() < T ? device_cus() : T;
     const int least = (T + kMaxTilesPerWg - 1) / kMaxTilesPerWg;

@@ -28,7 +28,7 @@ namespace quasar {
 // Slots in flight per wave: a compute unit accepts about 32 KB of outstanding loads, so three or four 1 KB loads in
 // each of 16 waves keep it full; up to eight where the registers allow.
 constexpr int direct_ring(int MP, int slots) {
-    return slots <= 6 ? slots : (slots == 8 ? (MP == 16 ? 4 : 8) : (slots % 5 == 0 ? 5 : (slots == 24 ? 6 : 4)));
+    return slots <= 7 ? slots : (slots == 8 ? (MP == 16 ? 4 : 8) : (slots % 5 == 0 ? 5 : (slots == 24 ? 6 : 4)));
 }
 
 // A slot is 64 k: one 1 KB load of int8 codes or two of bf16 weights.
@@ -459,16 +459,16 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
             }
         }
         if (d.C > 1) {
-            if (MP == 8) return launch_direct_forms<8, W16, EPI, true, PRE, RES, 8, 12>(d.XS, grid, d.lds_bytes, stream, p);
+            if (MP == 8) return launch_direct_forms<8, W16, EPI, true, PRE, RES, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
             return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
         }
     }
     if constexpr (PRE != PRE_NONE) {
-        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
         if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5>(d.XS, grid, d.lds_bytes, stream, p);
         return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     } else {
-        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 12>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
         if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 16, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);
         return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     }

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     constexpr int NB = (MP == 32) ? 2 : 1;
     constexpr int XP = (MP == 8) ? 1 : 2;           // 8-value pieces per lane, slot and token block
     constexpr int U = XS >= 4 ? 1 : 4 / XS;
-    constexpr int RD = XS * U <= 6 ? XS * U : (XS == 8 && MP == 8 ? 8 : 4);
+    constexpr int RD = XS * U <= 6 ? XS * U : (XS == 10 ? 5 : (XS == 8 && MP == 8 ? 8 : 4));
     static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
     constexpr bool HOLD = a8_hold(MP, XS);
 
@@ -312,9 +312,10 @@ int launch_a8_forms(int xs, int grid, int lds_bytes, hipStream_t stream, const G
 }
 template <int EPI, bool SMOOTH>
 int launch_a8_as(const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream) {
-    if (MP == 8) return launch_a8_forms<8, EPI, SMOOTH, 1, 2, 3, 4, 5, 6, 8, 12>(d.XS, d.groups, d.lds_bytes, stream, p);
-    if (MP == 16) return launch_a8_forms<16, EPI, SMOOTH, 1, 2, 3, 4, 5, 6, 8, 12>(d.XS, d.groups, d.lds_bytes, stream, p);
-    return launch_a8_forms<32, EPI, SMOOTH, 1, 2, 3, 4, 5, 6, 8>(d.XS, d.groups, d.lds_bytes, stream, p);
+    if (MP == 8) return launch_a8_forms<8, EPI, SMOOTH, 1, 2, 3, 4, 5, 6, 8, 10, 12>(d.XS, d.groups, d.lds_bytes, stream, p);
+    if (MP == 16) return launch_a8_forms<16, EPI, SMOOTH, 1, 2, 3, 4, 5, 6, 8, 10, 12>(d.XS, d.groups, d.lds_bytes, stream, p);
+    if constexpr (SMOOTH) return launch_a8_forms<32, EPI, SMOOTH, 1, 2, 3, 4, 5>(d.XS, d.groups, d.lds_bytes, stream, p);
+    else return launch_a8_forms<32, EPI, SMOOTH, 1, 2, 3, 4, 5, 6, 8>(d.XS, d.groups, d.lds_bytes, stream, p);
 }
 
 }  // namespace quasar
