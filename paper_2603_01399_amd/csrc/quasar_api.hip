@@ -790,11 +790,13 @@ int launch_fused(const GemmParams &base, int M, hipStream_t stream) {
     const int NB = MP == 32 ? 2 : 1;
     {
         // With a normalisation its gamma takes registers beside the activations until they are scaled.  32 tokens: the form of
-        // 8 slots spills at its start and is still the faster one (6144 x 4096 34.2 -> 30.9 us, 24576 x 4096 53.7 -> 40.8);
-        // that of 10 loses 6 us there, which only the streaming of many tiles wins back (7168 x 5120 40.2 -> 46.1, 51200 x
-        // 5120 109 -> 81).
+        // 8 slots spills 81 to 90 registers at its start and is still the faster one (6144 x 4096 34.2 -> 30.9 us, 24576 x
+        // 4096 53.7 -> 40.8).  That of 10 spills 145 to 158 and starts 10 us later; it is ahead from five tiles a compute unit on
+        // (K = 5120, M = 32, staged and in registers: N = 16384 50.4 and 52.5, 20480 63.2 and
+        // 55.8, 32768 73.6 and 65.0, 51200 110 and 81; M = 17 with a residual: 16384 44.7 and 55.8, 20480 58.2 and 59.1,
+        // 32768 69.0 and 68.3).
         const int most = PRE == PRE_NONE ? (MP == 8 ? 12 : (MP == 16 ? 24 : 10))
-                                         : (MP == 8 ? 8 : (MP == 16 ? 5 : (p.T >= 4 * device_cus() ? 10 : 8)));
+                                         : (MP == 8 ? 8 : (MP == 16 ? 5 : (p.T > 4 * device_cus() ? 10 : 8)));
         DirectPlan d{};
         if (direct_reach(M, p.ldx) &&
             plan_direct(MP, p.T, EPI == EPI_SWIGLU ? 2 : 1, p.S, p.S, 1, 1, true, most, EPI == EPI_SWIGLU ? NB * 1024 : 0,
