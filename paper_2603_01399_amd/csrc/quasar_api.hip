@@ -161,7 +161,7 @@ size_t splitk_bytes(int M, int N, int ksplit) { return ksplit > 1 ? (size_t)kspl
 // Register forms that are built: slots of 64 k per wave and tile.  What bounds them is the register file: a slot takes
 // 4, 8 or 16 registers at up to 8, 16 or 32 tokens.
 constexpr int kDirectSlots8[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12};
-constexpr int kDirectSlots16[] = {1, 2, 3, 4, 5, 6, 8, 16, 20, 24};     // (16 and more: of eight waves)
+constexpr int kDirectSlots16[] = {1, 2, 3, 4, 5, 6, 8, 20, 24};     // (20 and 24: of eight waves, shares of 129 slots and more)
 constexpr int kDirectSlots32[] = {2, 4, 6, 8, 10};
 
 // Smallest built form for `need` slots, at most `most` of them (0: none).
@@ -879,7 +879,7 @@ bool plan_w4(int T, int S, int MP, int NW, PlanW4 &pl) {
 
 // Plan of the 4-bit kernel that keeps its activations in registers (stream_direct_w4.hpp); S steps of 128 k.
 bool plan_direct_w4(int MP, int T, int S, DirectPlan &d) {
-    constexpr int kSlots8[] = {1, 2, 3, 4, 6}, kSlots16[] = {1, 2, 3, 4, 6, 8, 12}, kSlots32[] = {1, 2, 3, 4, 5};
+    constexpr int kSlots8[] = {1, 2, 3, 4, 6}, kSlots16[] = {1, 2, 3, 4, 12}, kSlots32[] = {1, 2, 3, 4, 5};
     auto pick = [&](const int *v, int count) {
         for (int i = 0; i < count; ++i) {
             const int NW = w4_waves(MP, v[i]);
@@ -887,7 +887,7 @@ bool plan_direct_w4(int MP, int T, int S, DirectPlan &d) {
         }
         return 0;
     };
-    d.XS = MP == 8 ? pick(kSlots8, 5) : (MP == 16 ? pick(kSlots16, 7) : pick(kSlots32, 5));
+    d.XS = MP == 8 ? pick(kSlots8, 5) : (MP == 16 ? pick(kSlots16, 5) : pick(kSlots32, 5));
     if (!d.XS) return false;
     d.groups = device_cus() < T ? device_cus() : T;
     d.lds_bytes = w4_region_bytes(MP, d.XS);

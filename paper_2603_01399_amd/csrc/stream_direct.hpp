@@ -460,16 +460,25 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
         }
         if (d.C > 1) {
             if (MP == 8) return launch_direct_forms<8, W16, EPI, true, PRE, RES, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
-            return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
+            // (bf16 weights: chunks of whole slots for every wave, K = 4096 and 6144)
+            if constexpr (W16) return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
+            else return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
         }
     }
-    if constexpr (PRE != PRE_NONE) {
+    if constexpr (EPI == EPI_ARGMAX) {
+        // the order of the staged kernel: K in one piece is 120 slots at 8 tokens, 60 at 16
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4>(d.XS, grid, d.lds_bytes, stream, p);
+    } else if constexpr (PRE != PRE_NONE) {
         if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
         if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5>(d.XS, grid, d.lds_bytes, stream, p);
         return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     } else {
         if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
-        if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 16, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 16) {
+            if constexpr (W16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 20>(d.XS, grid, d.lds_bytes, stream, p);
+            else return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);
+        }
         return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     }
 }

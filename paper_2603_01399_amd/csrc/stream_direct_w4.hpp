@@ -232,7 +232,7 @@ int launch_w4_forms(int xs, int grid, int lds_bytes, hipStream_t stream, const G
 template <int EPI>
 int launch_w4_as(const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream) {
     if (MP == 8) return launch_w4_forms<8, EPI, 1, 2, 3, 4, 6>(d.XS, d.groups, d.lds_bytes, stream, p);
-    if (MP == 16) return launch_w4_forms<16, EPI, 1, 2, 3, 4, 6, 8, 12>(d.XS, d.groups, d.lds_bytes, stream, p);
+    if (MP == 16) return launch_w4_forms<16, EPI, 1, 2, 3, 4, 12>(d.XS, d.groups, d.lds_bytes, stream, p);
     return launch_w4_forms<32, EPI, 1, 2, 3, 4, 5>(d.XS, d.groups, d.lds_bytes, stream, p);
 }
 
