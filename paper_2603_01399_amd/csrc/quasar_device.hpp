@@ -28,8 +28,9 @@ __device__ __forceinline__ unsigned int float_to_bf16_bits(float f) {
     return u >> 16;
 }
 
-// two fp32 -> a pair of bf16 (lo in the low half) by the hardware's conversion: the same values as float_to_bf16_bits
-// (checked over every exponent and rounding case; NaN keeps its payload) in one instruction instead of a dozen
+// two fp32 -> a pair of bf16 (lo in the low half) by the hardware's conversion, in one instruction instead of a dozen: to
+// nearest, ties to even, as float_to_bf16_bits (test_rounding_of_the_normalised_activations runs all products of 8-bit
+// significands over the exponents); a NaN keeps its payload here, so the two may differ in its bits
 __device__ __forceinline__ unsigned int float2_to_bf16_pair(float lo, float hi) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));

@@ -34,8 +34,9 @@ def make(qb, M, N, K):
     return x, w, wq, sc, what
 
 
-# K: one step; fewer steps than waves; 17, 33, 49, 65, 81 steps (two to six slots, ragged); eight slots; two chunks
-KS = [64, 960, 1088, 2112, 3136, 4160, 5184, 6208, 7680, 8192, 12288]
+# K: one step; fewer steps than waves; 17, 33, 49, 65, 81 steps (two to six slots, ragged); seven and eight slots; two chunks of
+# them; 129 and 160 steps (ten slots, and the twenty of eight waves at 9 to 16 tokens, ragged and full); twelve and 24
+KS = [64, 960, 1088, 2112, 3136, 4160, 5184, 6208, 7168, 7680, 8192, 8256, 10240, 12288]
 
 
 @pytest.mark.parametrize("K", KS)
@@ -60,7 +61,7 @@ def test_linear_forms(qb, M, N, K):
     assert torch.equal(bits(plain), bits(staged)) and torch.equal(bits(plain16), bits(staged16))
 
 
-@pytest.mark.parametrize("K", [64, 1088, 3136, 4160, 6208, 12288])
+@pytest.mark.parametrize("K", [64, 1088, 3136, 4160, 6208, 7168, 8256, 10240, 12288])
 @pytest.mark.parametrize("M", [3, 8, 16, 32])
 def test_fused_forms(qb, M, K):
     N = 16 * 22
@@ -152,3 +153,85 @@ def test_a_workspace_too_small_changes_nothing(qb, M, K):
     sc = torch.full((N,), 0.01, dtype=torch.bfloat16, device="cuda")
     small = torch.empty(4 * M * N, dtype=torch.uint8, device="cuda")
     assert torch.equal(bits(qb.w8_linear(x, wq, sc, N)), bits(qb.w8_linear(x, wq, sc, N, workspace=small)))
+
+
+@pytest.mark.parametrize("M,V,K", [(9, 16 * 256 * 17, 1024), (16, 16 * 256 * 17, 4096), (16, 16 * 600, 8256), (16, 16 * 600, 12288),
+                                   (32, 16 * 256 * 17, 1024), (32, 16 * 600, 4096), (32, 16 * 600, 5120)])
+def test_sampling_statistics_over_many_tiles(qb, M, V, K):
+    """The running softmax statistics over several tiles of a wave (17 tiles a workgroup of 16 or 8 waves), two blocks of
+    tokens and the longer forms."""
+    print("direct sampling, many tiles", M, V, K, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(V + K)
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    wq, sc = qb.quantize_weights(torch.randn(V, K, generator=gen, device="cuda") * (2.0 / K ** 0.5))
+    what = qb.unpack_weights(wq, V, K).float() * sc.float()[:, None]
+    logits = torch.cat([x.double() @ what[i:i + 4096].double().t() for i in range(0, V, 4096)], 1)
+    p = torch.softmax(logits / 0.8, 1)
+    draft = p.argmax(1).int()[:-1].contiguous()
+    ua = (p.max(1).values * 0.9).float()
+    ua[M // 2] = 0.999
+    us = torch.rand(M, generator=gen, device="cuda") * 0.98 + 0.01
+    full = qb.lmhead_verify_sample(x, wq, sc, V, draft, 0.8, ua, us)
+    least = torch.empty(M * V * 4 + 32 * 32 * 2 * 4, dtype=torch.uint8, device="cuda")
+    small = qb.lmhead_verify_sample(x, wq, sc, V, draft, 0.8, ua, us, workspace=least)
+    assert int(full[0]) == int(small[0]) == M // 2
+    assert torch.allclose(full[2], small[2], rtol=1e-5, atol=0)
+    assert torch.allclose(full[2].double(), p[:-1].gather(1, draft.long()[:, None])[:, 0], rtol=1e-3, atol=0)
+    # either token covers the drawn point as the 64-bit sums have it, within 1e-4 of the mass (fp32 logits and sums)
+    mass = p[M // 2].clone()
+    mass[int(draft[M // 2])] = 0.0
+    c = torch.cumsum(mass, 0)
+    for tok in (int(full[1]), int(small[1])):
+        point = float(us[M // 2]) * float(c[-1])
+        assert 0 <= tok < V and float(c[tok] - mass[tok]) - 1e-4 * float(c[-1]) <= point < float(c[tok]) + 1e-4 * float(c[-1])
+
+
+def test_rounding_of_the_normalised_activations(qb):
+    """The pair conversion of the fused normalisation rounds to nearest, ties to even, over the exponents of bf16: the products
+    of all pairs of 8-bit significands, read back through a weight matrix that picks one channel per row.
+
+    x are whole numbers whose squares have the mean 2^14 exactly, so the normalised x are x / 128 exactly and gamma's product with
+    them is the only rounding.  Row n has code 1 at channel n and 127 at a channel whose input is zero (its step size is
+    1), so y[m, n] is that channel's operand itself."""
+    print("rounding of normalised activations", flush=True)
+    K, live = 256, 128                                            # channels 128 .. 255 are zero
+    w = torch.zeros(live, K, device="cuda")
+    w[:, :live] = torch.eye(live, device="cuda")
+    w[:, K - 1] = 127.0
+    wq, sc = qb.quantize_weights(w)
+    assert bool((sc == 1).all())
+    gen = torch.Generator().manual_seed(3)
+    for trial in range(8):
+        # 124 numbers of 8 bits, then four squares that complete the sum of 256 x 2^14 = 128 x 32768 (Lagrange)
+        v = torch.randint(128, 232, (live - 4,), generator=gen)
+        left = K * 2 ** 14 - int((v * v).sum())
+        while not 20000 <= left <= 150000:
+            i = int(torch.randint(live - 4, (1,), generator=gen))
+            v[i] = min(255, max(128, int(v[i]) + (8 if left > 85000 else -8)))
+            left = K * 2 ** 14 - int((v * v).sum())
+        four = four_squares(left)
+        x = torch.zeros(1, K)
+        x[0, :live] = torch.cat([v, torch.tensor(four)]).float()
+        sign = torch.where(torch.rand(K, generator=gen) < 0.5, -1.0, 1.0)
+        x = (x * sign).bfloat16()
+        assert int((x.double() ** 2).sum()) == K * 2 ** 14
+        for e in (-100, -30, -1, 0, 7, 60, 110):
+            gamma = (torch.randint(128, 256, (K,), generator=gen).float() * 2.0 ** (e - 7)).bfloat16()
+            exact = x.double() / 128 * gamma.double()
+            want = exact.float().bfloat16()                       # 16-bit products: exact in fp32, rounded once, ties to even
+            y = qb.w8_linear_fused(x.cuda(), wq, sc, live, gamma=gamma.cuda(), eps=0.0)
+            assert torch.equal(bits(y.cpu()), bits(want[:, :live])), (trial, e)
+
+
+def four_squares(n):
+    """Four whole numbers up to 255 whose squares add up to n."""
+    for a in range(min(255, int(n ** 0.5)), -1, -1):
+        for b in range(min(255, int((n - a * a) ** 0.5)), -1, -1):
+            r = n - a * a - b * b
+            if r > 2 * 255 ** 2:
+                break
+            for c in range(min(255, int(r ** 0.5)), -1, -1):
+                d = int(round((r - c * c) ** 0.5))
+                if c * c + d * d == r and d <= 255:
+                    return [a, b, c, d]
+    raise AssertionError(n)
