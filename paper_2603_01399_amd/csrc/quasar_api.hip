@@ -437,13 +437,16 @@ int launch_quantize_as(const QuantArgs &q) {
     hipLaunchKernelGGL(kernel, dim3(q.N / kTileRows), dim3(kQuantWaves * 64), lds, q.st, q.w, q.ldw, q.K, q.smooth, q.packed, q.scales);
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
-// Registers that hold the row: the fewest loads a lane that do; longer rows are read twice in spans of 4096 (holding bf16
+// Registers that hold the row: the fewest loads a lane that do (a form's loads beyond a short row cost their arithmetic all the
+// same: 25600 x 64 bf16 30.8 us with eight, 11.3 with one); longer rows are read twice in spans of 4096 (holding bf16
 // rows of 8192 took 186 us for 25600 x 5120: the values double in the registers).
 template <bool SRC_BF16, bool SMOOTH, bool VEC>
 int launch_quantize_form(const QuantArgs &q) {
     if constexpr (SRC_BF16) {
+        if (q.K <= 512) return launch_quantize_as<true, SMOOTH, VEC, 1>(q);
         return launch_quantize_as<true, SMOOTH, VEC, 8>(q);
     } else {
+        if (q.K <= 256) return launch_quantize_as<false, SMOOTH, VEC, 1>(q);
         if (q.K <= 2048) return launch_quantize_as<false, SMOOTH, VEC, 8>(q);
         if (q.K <= 4096 || q.K > 8192) return launch_quantize_as<false, SMOOTH, VEC, 16>(q);
         return launch_quantize_as<false, SMOOTH, VEC, 32>(q);

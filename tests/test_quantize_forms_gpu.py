@@ -17,7 +17,8 @@ def rule(w, smooth):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("smoothed", [False, True])
 @pytest.mark.parametrize("N,K,offset", [(16, 64, 0), (48, 1088, 0), (32, 2112, 0), (32, 4096, 0), (32, 4160, 0), (16, 8192, 0),
-                                        (16, 8256, 0), (32, 12288, 0), (32, 2112, 1), (16, 8256, 1)])
+                                        (16, 8256, 0), (32, 12288, 0), (32, 2112, 1), (16, 8256, 1),
+                                        (32, 256, 0), (16, 320, 1), (48, 512, 0), (32, 512, 1), (16, 576, 0)])
 def test_quantize_forms(dtype, smoothed, N, K, offset):
     from paper_2603_01399_amd import binding as qb
     print("quantize", dtype, smoothed, N, K, offset, flush=True)
