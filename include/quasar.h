@@ -68,10 +68,13 @@ int quasar_get_path(void);
 /* Development knobs (no passage of the paper stands behind them; process-wide, not thread-safe,
  * meant for launch-shape sweeps in the benchmark, never needed for correct results):
  *   quasar_set_tuning      waves per workgroup (8 or 16), workgroups per compute unit (1..8) and
- *                          load-ring depth (4 or 8) of the single-call int8 / bf16 kernels; the
- *                          first two can also be preset through the environment variables
- *                          QUASAR_TUNE_NW and QUASAR_TUNE_WGS, read when the library is loaded;
- *   quasar_set_tuning_w4   waves per workgroup and ring depth of the 4-bit kernel;
+ *                          load-ring depth (4 or 8) of the single-call int8 / bf16 kernels that stage the
+ *                          activations; the first two can also be preset through the environment variables
+ *                          QUASAR_TUNE_NW and QUASAR_TUNE_WGS, read when the library is loaded.  Anything
+ *                          but 16 waves and one workgroup switches the kernels that hold the activations
+ *                          in registers off; their ring has a depth of its own;
+ *   quasar_set_tuning_w4   waves per workgroup and ring depth of the 4-bit kernel; anything but (16, 2)
+ *                          runs the one that stages the activations;
  *   quasar_set_sequence_form   workgroups per compute unit of the whole-step launch for sequences
  *                          prepared afterwards: 0 lets quasar_sequence_prepare choose (two alternating
  *                          workgroups of 8 waves when at most a quarter of the phases wait for an
@@ -94,7 +97,8 @@ size_t quasar_packed_bytes_bf16(int64_t N, int64_t K);
  * one of at least this size, shapes whose activations do not fit the on-chip memory in one
  * piece (large M x K) split K across workgroups through fp32 partial sums in the workspace
  * instead of re-reading the activations chunk by chunk - same result up to fp32 summation
- * order, several times faster.  The workspace is scratch: undefined on entry and on exit. */
+ * order, several times faster.  Elsewhere, and where it has no room for the partial sums, a
+ * workspace changes no bit.  It is scratch: undefined on entry and on exit. */
 size_t quasar_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /*
@@ -341,9 +345,14 @@ int quasar_sequence_prepare_w8a8(const quasar_linear_desc *linears, int64_t n_li
  *   out_accept_len  device [1]: number of leading accepted candidates
  *   out_next_token  device [1]: corrective or bonus token
  *   out_p_draft     device [n_draft] fp32 or NULL: p_i(x~_i)
- *   workspace       quasar_sample_workspace_bytes(M, V) bytes (the [M, V] fp32 logits live there)
- * Three launches: the weight stream with fp32 outputs, softmax statistics per position, the
- * decision.  int8 weights with bf16 activations only.
+ *   workspace       quasar_sample_workspace_bytes(M, V) bytes (the [M, V] fp32 logits live there);
+ *                   4 M V + 8192 bytes are the least that is accepted
+ * Two launches: the weight stream with fp32 outputs, whose workgroups leave the softmax statistics
+ * of their rows beside the logits, and the decision.  A workspace that has no room for statistics of
+ * every workgroup (the least size at M > 4), or a K whose activations the streaming kernel does not
+ * hold in registers (beyond 12288, 5120 at M > 16), takes a third launch between them, with statistics of 32
+ * blocks of the vocabulary: the fp32 sums are then taken over other blocks, and a draw that falls within
+ * rounding of the border between two tokens may give the other one.  int8 weights with bf16 activations only.
  */
 size_t quasar_sample_workspace_bytes(int64_t M, int64_t V);
 int quasar_lmhead_verify_sample(const uint16_t *hidden, int64_t M, int64_t K, int64_t ldh,
