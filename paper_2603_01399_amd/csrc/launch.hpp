@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -93,6 +94,22 @@ constexpr int a8_region_bytes(int MP, int XS) {
     return 16 * (x > tiles ? x : tiles);
 }
 
+// formats of weights and activations
+enum { FMT_INT8 = 0, FMT_BF16 = 1, FMT_W4 = 2, FMT_A8 = 3 };
+// ---- the kernel with K outermost (stream_outer.hpp): FMT_A8 and FMT_W4 ----
+constexpr int kOuterTiles = 8;                                              // tiles a workgroup walks side by side, at most
+constexpr int outer_waves(int MP) { return MP == 32 ? 8 : 16; }             // (32 tokens: 256 registers a wave)
+constexpr int outer_slot_k(int fmt) { return fmt == FMT_W4 ? 128 : 64; }    // k of a slot
+// 16-byte loads of activations a lane and slot
+constexpr int outer_x_loads(int fmt, int MP) { return fmt == FMT_A8 ? (MP == 32 ? 2 : 1) : MP / 4; }
+// passes the weights are requested ahead: six to ten slots in flight a wave, in powers of two so that shares of 4 and 8 slots
+// are whole rounds
+constexpr int outer_depth(int fmt, int MP, int NT) {
+    if (fmt == FMT_W4) return NT == 1 ? (MP == 32 ? 4 : 2) : (NT <= 3 ? 2 : 1);
+    return NT <= 2 ? 4 : (NT <= (MP == 32 ? 6 : 4) ? 2 : 1);
+}
+constexpr int outer_lds_bytes(int MP, int NT) { return outer_waves(MP) * NT * (MP == 32 ? 2 : 1) * 1024; }
+
 struct DirectPlan {
     int XS, SC, C, ksplit, slice_steps, groups, sc_bytes, lds_bytes;
     bool pair;       // 32 tokens in the order of sixteen waves
@@ -104,6 +121,10 @@ int launch_direct_int8(int epi, int pre, bool resid, const GemmParams &p, int MP
 int launch_direct_bf16(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 
 int launch_direct_w8a8(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
+
+int launch_outer_w4(const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
+int launch_quantize_operand(const GemmParams &p, int MP, unsigned char *codes, float *dx, hipStream_t stream);
+int launch_outer_w8a8(const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 
 int launch_direct_w4(int epi, const GemmParams &p, int MP, const DirectPlan &d, hipStream_t stream);
 

@@ -20,6 +20,7 @@
 #include "sample.hpp"
 #include "stream_w8a8.hpp"
 #include "stream_w4.hpp"
+#include "stream_outer.hpp"
 #include "drafter.hpp"
 #include "attention.hpp"
 
@@ -279,12 +280,58 @@ bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, DirectPl
     return plan_direct(MP, T, 1, S, S, 1, 1, !w16, MP == 8 ? 12 : 8, 0, false, d);
 }
 
-template <bool W16>
-int launch_splitk_finalize(const GemmParams &p, int ksplit, int M, hipStream_t stream) {
-    const long long quads = (long long)M * (p.N / 4);
-    hipLaunchKernelGGL(splitk_finalize_kernel<W16>, dim3((unsigned int)((quads + 255) / 256)), dim3(256), 0, stream,
-                       p.part32, ksplit, M, p.N, p.scales, p.y, p.ldy);
+template <int FMT>
+int launch_splitk_finalize(const GemmParams &p, int ksplit, const float *dx, hipStream_t stream) {
+    hipLaunchKernelGGL(splitk_finalize_kernel<FMT>, dim3((unsigned int)((p.N / 4 + 255) / 256), (unsigned int)p.M), dim3(256), 0, stream,
+                       p.part32, ksplit, p.M, p.N, p.scales, dx, p.y, p.ldy);
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
+}
+
+// ---- launches of the kernel with K outermost (stream_outer.hpp) ----
+
+// Plan for T tiles of S slots, split into ksplit slices of K.
+bool plan_outer(int MP, int T, int S, int ksplit, DirectPlan &d) {
+    const int NW = outer_waves(MP);
+    d = DirectPlan{};
+    d.ksplit = ksplit;
+    d.slice_steps = (S + ksplit - 1) / ksplit;
+    if (ksplit > 1) {
+        // whole multiples of the wave count where that costs no slice
+        const int up = (d.slice_steps + NW - 1) / NW * NW;
+        if ((S + up - 1) / up == ksplit) d.slice_steps = up;
+        if ((S + d.slice_steps - 1) / d.slice_steps != ksplit) return false;
+    }
+    d.groups = device_cus() / ksplit;
+    if (d.groups > T) d.groups = T;
+    // more tiles than the workgroups of one round walk side by side: more rounds
+    if (ksplit == 1 && d.groups < (T + kOuterTiles - 1) / kOuterTiles) d.groups = (T + kOuterTiles - 1) / kOuterTiles;
+    if (d.groups < 1) return false;
+    d.XS = (T + d.groups - 1) / d.groups;
+    if (d.XS > kOuterTiles) return false;
+    d.sc_bytes = d.XS * kTileRows * 2;
+    d.lds_bytes = outer_lds_bytes(MP, d.XS) + d.sc_bytes;
+    if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+    return true;
+}
+
+// The number of K slices, 1 .. 8, by what the busiest compute unit does and what a split costs: its weights at 45 KB/us (beyond
+// the average share, which all divisions have in common), its activations at 52, 2.8 us for a second launch and 0.7 us per MB of
+// partial sums.  Fitted to W8A8 times of 1, 2, 3 and 4 slices (us, quantiser included): 5120 x 25600, M = 32 46, 38, 35, 34.5
+// and M = 8 35, 33, 32, 33; 4096 x 12288, M = 32 21.8, 20.3, 19.9, 18.9 and M = 8 15.8, 18.4, 18.4, 17.6; 12288 x 4096, M = 32
+// 15.6, 19.9.  slot_kb: weights of a slot, x_kb: activations of a slot.
+bool plan_outer_split(int MP, int M, int T, int S, int N, double slot_kb, double x_kb, size_t room, DirectPlan &best) {
+    if (g_tune_nw.load() != 16 || g_tune_wgs.load() != 1) return false;      // launch shapes asked for by hand
+    double best_us = 0.0;
+    bool found = false;
+    for (int ks = 1; ks <= 8; ++ks) {
+        DirectPlan d{};
+        if (ks > 1 && splitk_bytes(M, N, ks) > room) break;
+        if (!plan_outer(MP, T, S, ks, d)) continue;
+        double us = d.slice_steps * (d.XS * slot_kb / 45.0 + x_kb / 52.0);
+        if (ks > 1) us += 2.8 + 0.7e-6 * (double)splitk_bytes(M, N, ks);
+        if (!found || us < best_us) { best = d; best_us = us; found = true; }
+    }
+    return found;
 }
 
 template <bool W16, int EPI>
@@ -315,7 +362,7 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
             if (grid_out) *grid_out = d.groups * d.ksplit;
             const int rc = launch_direct(W16, EPI, PRE_NONE, false, p, MP, d, stream);
             if (rc != QUASAR_OK || d.ksplit == 1) return rc;
-            return launch_splitk_finalize<W16>(p, d.ksplit, M, stream);
+            return launch_splitk_finalize<W16 ? FMT_BF16 : FMT_INT8>(p, d.ksplit, nullptr, stream);
         }
     }
     int launch_grid = pl.grid;
@@ -352,7 +399,7 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     else rc = QUASAR_LAUNCH(32);
 #undef QUASAR_LAUNCH
     if (rc != QUASAR_OK || p.ksplit == 1) return rc;
-    return launch_splitk_finalize<W16>(p, p.ksplit, M, stream);
+    return launch_splitk_finalize<W16 ? FMT_BF16 : FMT_INT8>(p, p.ksplit, nullptr, stream);
 }
 
 int launch_valu(const GemmParams &base, int M, hipStream_t stream) {
@@ -753,6 +800,22 @@ bool plan_direct_w8a8(int MP, int T, int S, bool smooth, DirectPlan &d) {
     d.lds_bytes = a8_region_bytes(MP, d.XS) + d.sc_bytes + 16 * MP * 4 + (smooth ? 16 * d.XS * 256 : 0);
     if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
     return d.lds_bytes <= kMaxLds;
+}
+
+// W8A8 linear with the activations quantised by a launch of their own (stream_outer.hpp): codes, 32 step sizes and the partial
+// sums of a K split lie in the workspace one after the other.
+size_t a8_code_bytes(int MP, int S) { return (size_t)S * 64u * (size_t)MP; }
+
+// Whether that is the faster way, and its plan for a workspace of `room` bytes.  Quantising in every workgroup costs by M x K
+// (and by the registers that hold the codes), the launch 2.8 us; us of a call, in every workgroup -> apart:
+//   M <= 8:   4096 x 4096 7.9 -> 9.1, 12288 x 4096 12.5 -> 14.1, 5120 x 8192 14.1 -> 16.2, 4096 x 12288 19.0 -> 15.9
+//   M <= 16:  4096 x 4096 9.1 -> 9.6, 25600 x 5120 27.3 -> 28.2, 4096 x 6144 18.6 -> 13, 5120 x 8192 25.4 -> 17.2, 4096 x 12288 32.5 -> 16.7
+//   M <= 32:  1024 x 1024 7.9 -> 7.1, 4096 x 4096 22.5 -> 11.6, 12288 x 4096 29.7 -> 15.5, 25600 x 5120 56 -> 28.7
+bool plan_w8a8_apart(int M, int N, int K, size_t room, DirectPlan &d) {
+    const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32), S = K / kStepK8;
+    if (S <= (MP == 8 ? 128 : (MP == 16 ? 80 : 15))) return false;
+    const size_t head = a8_code_bytes(MP, S) + 128;
+    return room >= head && plan_outer_split(MP, M, N / kTileRows, S, N, 1.0, MP / 16.0, room - head, d);
 }
 
 template <int EPI>
@@ -1359,10 +1422,16 @@ int quasar_quantize_activations(const uint16_t *x, int64_t M, int64_t K, int64_t
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
+size_t quasar_w8a8_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    DirectPlan d{};
+    if (check_mnk(M, N, K) || !plan_w8a8_apart((int)M, (int)N, (int)K, (size_t)-1, d)) return 0;
+    const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
+    return a8_code_bytes(MP, (int)(K / kStepK8)) + 128 + splitk_bytes((int)M, (int)N, d.ksplit);
+}
+
 int quasar_w8a8_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const float *smooth,
                        const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, uint16_t *y, int64_t ldy,
                        void *workspace, size_t workspace_bytes, void *hip_stream) {
-    (void)workspace; (void)workspace_bytes;
     if (!x || !wq_packed || !scales_bf16 || !y) return QUASAR_ERR_NULL;
     if (const int e = check_mnk(M, N, K)) return e;
     if (ldx < K || ldy < N || ldx % 8 || ldy % 8) return QUASAR_ERR_SHAPE;
@@ -1375,6 +1444,20 @@ int quasar_w8a8_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, con
     p.M = (int)M; p.N = (int)N; p.K = (int)K;
     p.T = (int)(N / kTileRows);
     p.S = (int)(K / kStepK8);
+    DirectPlan d{};
+    if (workspace && aligned(workspace, 16) && plan_w8a8_apart((int)M, (int)N, (int)K, workspace_bytes, d)) {
+        const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
+        unsigned char *codes = static_cast<unsigned char *>(workspace);
+        float *dx = reinterpret_cast<float *>(codes + a8_code_bytes(MP, p.S));
+        hipStream_t st = static_cast<hipStream_t>(hip_stream);
+        if (const int e = launch_quantize_operand(p, MP, codes, dx, st)) return e;
+        p.x = reinterpret_cast<const uint16_t *>(codes);
+        p.dx = dx;
+        if (d.ksplit > 1) p.part32 = dx + 32;
+        const int rc = launch_outer_w8a8(p, MP, d, st);
+        if (rc != QUASAR_OK || d.ksplit == 1) return rc;
+        return launch_splitk_finalize<FMT_A8>(p, d.ksplit, dx, st);
+    }
     return launch_w8a8<EPI_LINEAR>(p, (int)M, static_cast<hipStream_t>(hip_stream), nullptr);
 }
 

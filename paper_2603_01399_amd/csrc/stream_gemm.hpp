@@ -45,6 +45,7 @@ struct GemmParams {
     // [M][workgroups] (max, sum of exp(z - max)), z = logit * inv_t; nullptr: none
     float *soft_stats;
     float inv_t;
+    const float *dx;           // step sizes of the activation codes (stream_outer.hpp), [M]
 };
 
 // Operation applied to the activations while they are staged (the normalisation in front of
@@ -800,32 +801,6 @@ __global__ __launch_bounds__(NW * 64) void stream_valu_kernel(const GemmParams p
 // Second stage of the fused verify: combine the per-workgroup keys, then count leading
 // draft matches.  One workgroup of 1024 threads, 32 threads per token position.
 // ------------------------------------------------------------------------------------
-// y[m, n] = bf16( (sum over K slices, in slice order, of part32[slice][m][n]) * delta_n ).
-// One thread per four consecutive outputs of a token.
-template <bool W16>
-__global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part32, int ksplit, int M, int N,
-                                                              const uint16_t *scales, uint16_t *y, long long ldy) {
-    const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-    const int nq = N / 4;
-    if (q >= (long long)M * nq) return;
-    const int m = (int)(q / nq), n0 = (int)(q % nq) * 4;
-    f32x4 acc = *reinterpret_cast<const f32x4 *>(part32 + (long long)m * N + n0);
-    for (int sl = 1; sl < ksplit; ++sl)
-        acc += *reinterpret_cast<const f32x4 *>(part32 + ((long long)sl * M + m) * N + n0);
-    float s4[4] = {1.f, 1.f, 1.f, 1.f};
-    if constexpr (!W16) {
-        const u32x2 sb = *reinterpret_cast<const u32x2 *>(scales + n0);
-        s4[0] = bf16_bits_to_float(sb.x & 0xFFFFu);
-        s4[1] = bf16_bits_to_float(sb.x >> 16);
-        s4[2] = bf16_bits_to_float(sb.y & 0xFFFFu);
-        s4[3] = bf16_bits_to_float(sb.y >> 16);
-    }
-    u32x2 o;
-    o.x = float_to_bf16_bits(acc.x * s4[0]) | (float_to_bf16_bits(acc.y * s4[1]) << 16);
-    o.y = float_to_bf16_bits(acc.z * s4[2]) | (float_to_bf16_bits(acc.w * s4[3]) << 16);
-    *reinterpret_cast<u32x2 *>(y + m * ldy + n0) = o;
-}
-
 [[maybe_unused]] static __global__ __launch_bounds__(1024) void verify_finalize_kernel(const unsigned long long *partial, int nparts,
                                                                int MP, int M, int V, const int32_t *draft,
                                                                int n_draft, int32_t *out_argmax,

@@ -62,6 +62,13 @@ __device__ __forceinline__ u32x2 quantize_piece(const float (&xt)[8], float inv)
 __device__ __forceinline__ float step_of(float amax) { return amax > 0.f ? __fdiv_rn(amax, 127.0f) : 0.f; }
 __device__ __forceinline__ float inverse_step_of(float amax) { return amax > 0.f ? __fdiv_rn(127.0f, amax) : 0.f; }
 
+// Eq. 10 for four rows (bf16 step sizes rows) of a token: fp32(acc) * (dx * dw), each one fp32 operation, as bf16
+__device__ __forceinline__ u32x2 a8_outputs(const i32x4 acc, const u32x2 rows, float dx) {
+    const float v0 = (float)acc.x * (dx * bf16_bits_to_float(rows.x & 0xFFFFu)), v1 = (float)acc.y * (dx * bf16_bits_to_float(rows.x >> 16));
+    const float v2 = (float)acc.z * (dx * bf16_bits_to_float(rows.y & 0xFFFFu)), v3 = (float)acc.w * (dx * bf16_bits_to_float(rows.y >> 16));
+    return u32x2{float_to_bf16_bits(v0) | (float_to_bf16_bits(v1) << 16), float_to_bf16_bits(v2) | (float_to_bf16_bits(v3) << 16)};
+}
+
 // ------------------------------------------------------------------------------------
 // Stand-alone activation quantiser: x[M, K] bf16 -> codes[M, K] int8 row-major, dx[M] fp32.
 // One workgroup (256 threads) per token.  The fused kernels below run the same three
