@@ -401,6 +401,14 @@ int quasar_w4_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
                      const void *w4_packed, int64_t N,
                      uint16_t *y, int64_t ldy, void *hip_stream);
 
+/* quasar_w4_linear with a workspace (may be NULL): where M x K is large, one of quasar_w4_workspace_bytes (0: none is
+ * used for this shape) lets K be split across workgroups through fp32 partial sums, which are then added in another
+ * order than without.  It is scratch: undefined on entry and on exit. */
+size_t quasar_w4_workspace_bytes(int64_t M, int64_t N, int64_t K);
+int quasar_w4_linear_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
+                           const void *w4_packed, int64_t N, uint16_t *y, int64_t ldy,
+                           void *workspace, size_t workspace_bytes, void *hip_stream);
+
 /* Vocabulary projection with 4-bit weights fused with the greedy acceptance decision (Eq. 2 at
  * temperature 0); arguments and workspace as quasar_lmhead_verify. */
 int quasar_w4_lmhead_verify(const uint16_t *hidden, int64_t M, int64_t K, int64_t ldh,

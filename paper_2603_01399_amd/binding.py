@@ -32,7 +32,7 @@ EXPORTS = (
     "quasar_w8a8_lmhead_verify", "quasar_sequence_prepare_w8a8",
     "quasar_sample_workspace_bytes", "quasar_lmhead_verify_sample",
     "quasar_w4_packed_bytes", "quasar_quantize_weights_w4", "quasar_unpack_weights_w4", "quasar_w4_linear",
-    "quasar_w4_lmhead_verify",
+    "quasar_w4_workspace_bytes", "quasar_w4_linear_split", "quasar_w4_lmhead_verify",
     "quasar_drafter_create", "quasar_drafter_destroy", "quasar_drafter_append", "quasar_drafter_length",
     "quasar_drafter_propose",
     "quasar_w8_linear_fused", "quasar_w8_gateup_swiglu",
@@ -114,6 +114,9 @@ def _load() -> ctypes.CDLL:
     lib.quasar_quantize_weights_w4.argtypes = [vp, ci, i64, i64, i64, vp, vp]
     lib.quasar_unpack_weights_w4.argtypes = [vp, i64, i64, vp, vp, vp]
     lib.quasar_w4_linear.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, vp]
+    lib.quasar_w4_workspace_bytes.argtypes = [i64, i64, i64]
+    lib.quasar_w4_workspace_bytes.restype = sz
+    lib.quasar_w4_linear_split.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, vp, sz, vp]
     lib.quasar_w4_lmhead_verify.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, vp, vp, vp, sz, vp]
     lib.quasar_w8_linear_fused.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp, i64, vp]
     lib.quasar_w8_gateup_swiglu.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp]
@@ -412,8 +415,12 @@ def w4_linear(x: torch.Tensor, w4_packed: torch.Tensor, N: int, y: torch.Tensor 
         raise ValueError("w4_packed is smaller than quasar_w4_packed_bytes(N, K)")
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
+    # scratch of the call, from the allocator of the stream it runs on (small shapes never use any: not asked for)
+    need = _lib.quasar_w4_workspace_bytes(M, N, K) if M * K > 65536 else 0
+    ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
     _check("quasar_w4_linear",
-           _lib.quasar_w4_linear(_ptr(x), M, K, x.stride(0), _ptr(w4_packed), N, _ptr(y), y.stride(0), _stream()))
+           _lib.quasar_w4_linear_split(_ptr(x), M, K, x.stride(0), _ptr(w4_packed), N, _ptr(y), y.stride(0), _ptr(ws), need,
+                                       _stream()))
     return y
 
 

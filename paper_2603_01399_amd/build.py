@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libquasar.so")
 SOURCES = ["quasar_api.hip", "direct_int8.hip", "direct_bf16.hip", "direct_w8a8.hip", "direct_w4.hip",
-           "outer_w8a8.hip"]
+           "outer_w8a8.hip", "outer_w4.hip"]
 HEADERS = ["quasar_device.hpp", "launch.hpp", "stream_gemm.hpp", "stream_direct.hpp", "stream_direct_a8.hpp", "stream_direct_w4.hpp", "stream_outer.hpp", "stream_sequence.hpp", "stream_w8a8.hpp", "stream_w4.hpp", "drafter.hpp", "attention.hpp", "sample.hpp", "draw.hpp", "pack.hpp", "probe.hpp"]
 
 HIPCC_FLAGS = [

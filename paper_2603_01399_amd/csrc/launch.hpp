@@ -97,7 +97,8 @@ constexpr int a8_region_bytes(int MP, int XS) {
 // formats of weights and activations
 enum { FMT_INT8 = 0, FMT_BF16 = 1, FMT_W4 = 2, FMT_A8 = 3 };
 // ---- the kernel with K outermost (stream_outer.hpp): FMT_A8 and FMT_W4 ----
-constexpr int kOuterTiles = 8;                                              // tiles a workgroup walks side by side, at most
+// tiles a workgroup walks side by side, at most (4-bit weights, 9 to 16 tokens: seven spill 44 registers)
+constexpr int outer_tiles(int fmt, int MP) { return fmt == FMT_W4 && MP == 16 ? 6 : 8; }
 constexpr int outer_waves(int MP) { return MP == 32 ? 8 : 16; }             // (32 tokens: 256 registers a wave)
 constexpr int outer_slot_k(int fmt) { return fmt == FMT_W4 ? 128 : 64; }    // k of a slot
 // 16-byte loads of activations a lane and slot

@@ -290,8 +290,8 @@ int launch_splitk_finalize(const GemmParams &p, int ksplit, const float *dx, hip
 // ---- launches of the kernel with K outermost (stream_outer.hpp) ----
 
 // Plan for T tiles of S slots, split into ksplit slices of K.
-bool plan_outer(int MP, int T, int S, int ksplit, DirectPlan &d) {
-    const int NW = outer_waves(MP);
+bool plan_outer(int fmt, int MP, int T, int S, int ksplit, DirectPlan &d) {
+    const int NW = outer_waves(MP), most = outer_tiles(fmt, MP);
     d = DirectPlan{};
     d.ksplit = ksplit;
     d.slice_steps = (S + ksplit - 1) / ksplit;
@@ -304,10 +304,10 @@ bool plan_outer(int MP, int T, int S, int ksplit, DirectPlan &d) {
     d.groups = device_cus() / ksplit;
     if (d.groups > T) d.groups = T;
     // more tiles than the workgroups of one round walk side by side: more rounds
-    if (ksplit == 1 && d.groups < (T + kOuterTiles - 1) / kOuterTiles) d.groups = (T + kOuterTiles - 1) / kOuterTiles;
+    if (ksplit == 1 && d.groups < (T + most - 1) / most) d.groups = (T + most - 1) / most;
     if (d.groups < 1) return false;
     d.XS = (T + d.groups - 1) / d.groups;
-    if (d.XS > kOuterTiles) return false;
+    if (d.XS > most) return false;
     d.sc_bytes = d.XS * kTileRows * 2;
     d.lds_bytes = outer_lds_bytes(MP, d.XS) + d.sc_bytes;
     if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
@@ -315,20 +315,23 @@ bool plan_outer(int MP, int T, int S, int ksplit, DirectPlan &d) {
 }
 
 // The number of K slices, 1 .. 8, by what the busiest compute unit does and what a split costs: its weights at 45 KB/us (beyond
-// the average share, which all divisions have in common), its activations at 52, 2.8 us for a second launch and 0.7 us per MB of
-// partial sums.  Fitted to W8A8 times of 1, 2, 3 and 4 slices (us, quantiser included): 5120 x 25600, M = 32 46, 38, 35, 34.5
-// and M = 8 35, 33, 32, 33; 4096 x 12288, M = 32 21.8, 20.3, 19.9, 18.9 and M = 8 15.8, 18.4, 18.4, 17.6; 12288 x 4096, M = 32
-// 15.6, 19.9.  slot_kb: weights of a slot, x_kb: activations of a slot.
-bool plan_outer_split(int MP, int M, int T, int S, int N, double slot_kb, double x_kb, size_t room, DirectPlan &best) {
+// the average share, which all divisions have in common), its activations at 50, 2.8 us (W8A8; 4-bit 2.0) for a second launch
+// and 0.7 us per MB of partial sums.  Fitted to times of 1 to 8 slices; us:
+//   W8A8 (quantiser included), 1, 2, 3, 4 slices: 5120 x 25600, M = 32 46, 38, 35, 34.5 and M = 8 35, 33, 32, 33; 4096 x 12288, M = 32
+//     21.8, 20.3, 19.9, 18.9 and M = 8 15.8, 18.4, 18.4, 17.6; 12288 x 4096, M = 32 15.6, 19.9
+//   4-bit, 1, 2, 3, 4, 6 slices: 5120 x 25600, M = 32 57, 39, 33, 31, 28; 4096 x 12288, M = 32 29, 20, 18, 17, 17 and M = 16 17.5, 15.3,
+//     14.5, 13.5, 16.3 (seven tiles); 25600 x 5120, M = 32 25.6
+bool plan_outer_split(int fmt, int MP, int M, int T, int S, int N, size_t room, DirectPlan &best) {
     if (g_tune_nw.load() != 16 || g_tune_wgs.load() != 1) return false;      // launch shapes asked for by hand
+    const double x_kb = fmt == FMT_W4 ? M / 4.0 : MP / 16.0;                 // of a slot (rows beyond M are a row of x again)
     double best_us = 0.0;
     bool found = false;
     for (int ks = 1; ks <= 8; ++ks) {
         DirectPlan d{};
         if (ks > 1 && splitk_bytes(M, N, ks) > room) break;
-        if (!plan_outer(MP, T, S, ks, d)) continue;
-        double us = d.slice_steps * (d.XS * slot_kb / 45.0 + x_kb / 52.0);
-        if (ks > 1) us += 2.8 + 0.7e-6 * (double)splitk_bytes(M, N, ks);
+        if (!plan_outer(fmt, MP, T, S, ks, d)) continue;
+        double us = d.slice_steps * (d.XS / 45.0 + x_kb / 50.0);
+        if (ks > 1) us += (fmt == FMT_W4 ? 2.0 : 2.8) + 0.7e-6 * (double)splitk_bytes(M, N, ks);
         if (!found || us < best_us) { best = d; best_us = us; found = true; }
     }
     return found;
@@ -815,7 +818,7 @@ bool plan_w8a8_apart(int M, int N, int K, size_t room, DirectPlan &d) {
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32), S = K / kStepK8;
     if (S <= (MP == 8 ? 128 : (MP == 16 ? 80 : 15))) return false;
     const size_t head = a8_code_bytes(MP, S) + 128;
-    return room >= head && plan_outer_split(MP, M, N / kTileRows, S, N, 1.0, MP / 16.0, room - head, d);
+    return room >= head && plan_outer_split(FMT_A8, MP, M, N / kTileRows, S, N, room - head, d);
 }
 
 template <int EPI>
@@ -959,6 +962,21 @@ bool plan_direct_w4(int MP, int T, int S, DirectPlan &d) {
     d.lds_bytes = w4_region_bytes(MP, d.XS);
     if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
     return d.groups <= kMaxGrid && d.lds_bytes <= kMaxLds;
+}
+
+// Whether a 4-bit linear walks its tiles with K outermost (stream_outer.hpp), and its plan for a workspace of `room` bytes:
+// where the kernel that holds the activations has no form (it stages them then) or one of many slots.  us a call, without -> with:
+//   M <= 8:   5120 x 25600 34.1 -> 22.6 (4096 x 12288, six slots: 10.0 -> 12.0)
+//   M <= 16:  4096 x 9216 16.9 -> 12.1, 4096 x 12288 18.8 -> 13.5, 5120 x 25600 50 -> 26 (5120 x 8192, four slots: 11.7 -> 12.5)
+//   M <= 32:  8192 x 5120 16.6 -> 14.9, 25600 x 5120 39.5 -> 25.6, 5120 x 8192 36.4 -> 15.1, 4096 x 12288 48.6 -> 17.2, 5120 x 25600
+//             101 -> 28.4 (12288 x 4096, four slots: 11.6 -> 14.9)
+bool plan_w4_outer(int M, int N, int K, size_t room, DirectPlan &d) {
+    if (g_w4_nw.load() != 16 || g_w4_d.load() != 2) return false;            // launch shapes asked for by hand
+    const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32), S = K / kStepK4, T = N / kTileRows;
+    if (S <= (MP == 8 ? 96 : (MP == 16 ? 64 : 32))) return false;
+    if (!plan_outer_split(FMT_W4, MP, M, T, S, N, room, d)) return false;
+    // (five slots, one tile a workgroup and K in one piece: 4096 x 5120 at M = 32 11.3 held, 14.9 so)
+    return !(MP == 32 && S <= 40 && d.ksplit == 1 && d.XS == 1);
 }
 
 template <int EPI>
@@ -1587,8 +1605,14 @@ int quasar_unpack_weights_w4(const void *w4_packed, int64_t N, int64_t K, int8_t
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
-int quasar_w4_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const void *w4_packed, int64_t N,
-                     uint16_t *y, int64_t ldy, void *hip_stream) {
+size_t quasar_w4_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    DirectPlan d{};
+    if (check_mnk_w4(M, N, K) || !plan_w4_outer((int)M, (int)N, (int)K, (size_t)-1, d)) return 0;
+    return splitk_bytes((int)M, (int)N, d.ksplit);
+}
+
+int quasar_w4_linear_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const void *w4_packed, int64_t N,
+                           uint16_t *y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream) {
     if (!x || !w4_packed || !y) return QUASAR_ERR_NULL;
     if (const int e = check_mnk_w4(M, N, K)) return e;
     if (ldx < K || ldy < N || ldx % 8 || ldy % 8) return QUASAR_ERR_SHAPE;
@@ -1599,7 +1623,21 @@ int quasar_w4_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const
     p.M = (int)M; p.N = (int)N; p.K = (int)K;
     p.T = (int)(N / kTileRows);
     p.S = (int)(K / kStepK4);
-    return launch_w4<EPI_LINEAR>(p, (int)M, static_cast<hipStream_t>(hip_stream), nullptr);
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    DirectPlan d{};
+    const size_t room = workspace && aligned(workspace, 16) ? workspace_bytes : 0;
+    if (direct_reach((int)M, ldx) && plan_w4_outer((int)M, (int)N, (int)K, room, d)) {
+        if (d.ksplit > 1) p.part32 = static_cast<float *>(workspace);
+        const int rc = launch_outer_w4(p, M <= 8 ? 8 : (M <= 16 ? 16 : 32), d, st);
+        if (rc != QUASAR_OK || d.ksplit == 1) return rc;
+        return launch_splitk_finalize<FMT_W4>(p, d.ksplit, nullptr, st);
+    }
+    return launch_w4<EPI_LINEAR>(p, (int)M, st, nullptr);
+}
+
+int quasar_w4_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const void *w4_packed, int64_t N,
+                     uint16_t *y, int64_t ldy, void *hip_stream) {
+    return quasar_w4_linear_split(x, M, K, ldx, w4_packed, N, y, ldy, nullptr, 0, hip_stream);
 }
 
 int quasar_w4_lmhead_verify(const uint16_t *hidden, int64_t M, int64_t K, int64_t ldh, const void *w4_packed,

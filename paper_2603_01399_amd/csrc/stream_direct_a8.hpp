@@ -11,7 +11,7 @@
 // while the first weights are on their way; then the weight stream.  Back to back, HBM-cold, us a launch, staged -> this:
 //     M = 8:  4096 x 4096 11.8 -> 7.1, 12288 x 4096 17.2 -> 11.4, 4096 x 12288 28.4 -> 17.9 (12 slots: every workgroup
 //             quantises 98304 values; 20.7 with x gathered);  M = 16: 17.8 -> 8.7, 23.1 -> 12.5, 45.2 -> 29.3;  M = 32: 31.6 -> 21.5,
-//             36.0 -> 27.6
+//             36.0 -> 27.6.  Linears of large M x K with a workspace: stream_outer.hpp
 #pragma once
 
 #include "launch.hpp"

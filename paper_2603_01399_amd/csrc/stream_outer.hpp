@@ -11,7 +11,14 @@
 //
 // W8A8: the activations come as int8 codes in operand order from a launch of their own (quantize_operand_kernel), 64 bytes
 // a token and slot in contiguous KB.  Quantising in every workgroup costs eight vector instructions an element, 256
-// times over; the launch costs 2.8 us once.  What bounds it: the weight stream, and x at about 50 KB/us a compute unit.
+// times over; the launch costs 2.8 us once.
+//
+// 4-bit weights: x is read in place, eight tokens' 128 bytes an instruction; an eight-lane rotation with a bank mask turns the
+// two halves of 16 tokens into two operands, and the group's offset is a matrix product a pass (stream_direct_w4.hpp).
+//
+// What bounds it: the weight stream and, in the same in-order queue of the compute unit, x at about 50 KB/us; nothing of x is
+// hidden behind the weights (int8 weights with bf16 activations were slower so: 12288 x 4096, M = 32 13.9 -> 16.3 us).
+// us a call against the kernels that hold x: at the rules that choose between them (plan_w8a8_apart, plan_w4_outer).
 #pragma once
 
 #include "launch.hpp"
@@ -307,7 +314,10 @@ int launch_outer_as(const GemmParams &base, int MP, const DirectPlan &d, hipStre
     p.slice_steps = d.slice_steps;
     const int grid = d.groups * d.ksplit;
     if (MP == 8) return launch_outer_forms<FMT, 8, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
-    if (MP == 16) return launch_outer_forms<FMT, 16, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
+    if (MP == 16) {
+        if constexpr (outer_tiles(FMT, 16) == 6) return launch_outer_forms<FMT, 16, 1, 2, 3, 4, 5, 6>(d.XS, grid, d.lds_bytes, stream, p);
+        else return launch_outer_forms<FMT, 16, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
+    }
     return launch_outer_forms<FMT, 32, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
 }
 

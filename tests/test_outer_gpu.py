@@ -57,3 +57,33 @@ def test_w8a8_apart(M, N, K, smoothed):
         same = y2.view(torch.int16) == want.view(torch.int16)
         assert bool((same | (y2.isnan() & want.isnan())).all())
         assert bool((ws[room:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 16, 12416), (8, 16 * 320, 25600), (5, 16 * 1300, 12416), (8, 16 * 2049, 12416),
+                                   (9, 16, 8320), (16, 16 * 256, 12288), (13, 16 * 700, 8320), (16, 16 * 1500, 8320), (16, 16 * 1537, 8320),
+                                   (17, 16 * 40, 5120), (32, 16 * 257, 5120), (24, 16 * 700, 4224), (32, 16 * 1000, 4224),
+                                   (31, 16 * 1200, 4224), (32, 16 * 1600, 5120), (32, 16 * 2049, 4224), (32, 16 * 320, 25600), (20, 16 * 16, 33024)])
+def test_w4_outer(M, N, K):
+    """Outputs against a 64-bit product with the dequantised codes: 4e-3 of max|y|, as for the kernel that holds x."""
+    from paper_2603_01399_amd import binding as qb
+    print("w4 outer", M, N, K, flush=True)
+    x = _activations(M, K)
+    x[M // 2] = x[M // 2].abs()                                    # all positive: the largest offset
+    w = torch.randn(N, K, device="cuda", generator=torch.Generator("cuda").manual_seed(30 + K)) * 0.02
+    packed = qb.quantize_weights_w4(w)
+    codes, steps = qb.unpack_weights_w4(packed, N, K)
+    what = (codes.double().view(N, -1, 128) * steps.double()[..., None]).view(N, K)
+    want = x.double() @ what.t()
+    y = torch.full((M, N + 24), 7.0, dtype=torch.bfloat16, device="cuda")
+    qb.w4_linear(x, packed, N, y=y[:, :N])
+    assert float((y[:, :N].double() - want).abs().max() / want.abs().max()) <= 4e-3
+    assert bool((y[:, N:] == 7.0).all())
+    assert torch.equal(y[:, :N].view(torch.int16), qb.w4_linear(x, packed, N).view(torch.int16))
+    need = qb.lib().quasar_w4_workspace_bytes(M, N, K)
+    for room in (0, need, need - 1):                               # no scratch, and scratch of exactly one plan or less
+        ws = torch.full((max(need, 0) + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        y2 = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        qb._check("w4", qb.lib().quasar_w4_linear_split(x.data_ptr(), M, K, x.stride(0), packed.data_ptr(), N, y2.data_ptr(), N,
+                                                        ws.data_ptr(), max(room, 0), qb._stream()))
+        assert float((y2.double() - want).abs().max() / want.abs().max()) <= 4e-3
+        assert bool((ws[max(room, 0):] == 0xA5).all())
