@@ -288,7 +288,7 @@ def w8a8_linear(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, 
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     # scratch of the call, from the allocator of the stream it runs on (small shapes never use any: not asked for)
-    need = _lib.quasar_w8a8_workspace_bytes(M, N, K) if M > 16 or K > 5120 else 0
+    need = _lib.quasar_w8a8_workspace_bytes(M, N, K) if M > 16 or K > (8192 if M <= 8 else 5120) else 0
     ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
     _check("quasar_w8a8_linear",
            _lib.quasar_w8a8_linear(_ptr(x), M, K, x.stride(0), _smooth_arg(smooth, K), _ptr(wq_packed), _ptr(scales),
@@ -416,7 +416,7 @@ def w4_linear(x: torch.Tensor, w4_packed: torch.Tensor, N: int, y: torch.Tensor 
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     # scratch of the call, from the allocator of the stream it runs on (small shapes never use any: not asked for)
-    need = _lib.quasar_w4_workspace_bytes(M, N, K) if M * K > 65536 else 0
+    need = _lib.quasar_w4_workspace_bytes(M, N, K) if K > (12288 if M <= 8 else 8192 if M <= 16 else 4096) else 0
     ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
     _check("quasar_w4_linear",
            _lib.quasar_w4_linear_split(_ptr(x), M, K, x.stride(0), _ptr(w4_packed), N, _ptr(y), y.stride(0), _ptr(ws), need,

@@ -70,6 +70,12 @@ constexpr int direct_region_bytes(int MP, int XS, int C) {
     return direct_waves(MP, XS) * (x > tiles ? x : tiles);
 }
 
+// LDS of the waves' regions in the pair form of several chunks (32 tokens)
+constexpr int direct_pair_bytes(int XS, int C, bool w16) {
+    const int x = w16 ? 0 : direct_pass(32, XS) * 32 * 128, tiles = (C > 4 ? 1 : 2) * C * 2048;
+    return 8 * (x > tiles ? x : tiles);
+}
+
 // The same for the 4-bit kernel (slots of 128 k): its waves, the slots that pass through LDS at a time, the regions.
 constexpr int w4_waves(int MP, int XS) { return MP == 32 || (MP == 16 && XS > 4) ? 8 : 16; }
 constexpr int w4_pass(int MP, int XS) {

@@ -247,12 +247,23 @@ bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t work
 }
 
 // Plan of the ordered forms (linear without a workspace, argmax): the sum is taken in the order of the whole-step
-// launch, so K is summed in the chunks that it stages (SC, C in its own steps).  More than 16 tokens: K in one piece only
-// (22 slots at most), by waves that hold two neighbouring shares each.
-bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, DirectPlan &d) {
+// launch, so K is summed in the chunks that it stages (SC, C in its own steps).  More than 16 tokens: by waves that hold
+// two neighbouring shares each.
+bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, bool argmax, DirectPlan &d) {
     const int per = w16 ? 2 : 1;                     // steps per slot
     if (MP == 32) {
-        if (C > 1) return false;
+        if (C > 1) {
+            // shares of at most one step of 64 k, two of 32; two sets of the chunks' partial tiles, of five chunks one (linears
+            // have a workspace where it matters; their forms of four and five chunks spill 70 to 370 registers)
+            if (!argmax || SC > (w16 ? 32 : 16) || C > 5 || !plan_direct(MP, T, 1, S, S, 1, 1, !w16, 10, 0, false, d)) return false;
+            d.XS = (w16 ? 4 : 2) * C;
+            d.SC = SC;
+            d.C = C;
+            d.pair = true;
+            d.lds_bytes = direct_pair_bytes(d.XS, C, w16) + d.sc_bytes;
+            if (d.lds_bytes < kMinLds) d.lds_bytes = kMinLds;
+            return d.lds_bytes <= kMaxLds;
+        }
         const int share = (per * S + 15) / 16;       // steps of the largest of sixteen shares
         if (share > (w16 ? 3 : 2) || !plan_direct(MP, T, 1, S, S, 1, 1, !w16, 4, 0, false, d)) return false;
         d.XS = 2 * share;
@@ -359,7 +370,7 @@ int launch_mfma(const GemmParams &base, int M, hipStream_t stream, int *grid_out
         DirectPlan d{};
         const bool ok = !direct_reach(M, p.ldx) ? false : free_order ? plan_direct_split(MP, M, p.T, slots, W16, p.N, workspace_bytes,
                                                                                               MP == 8 ? 12 : (MP == 16 ? (W16 ? 20 : 24) : 10), d)
-                                   : plan_direct_ordered(MP, p.T, slots, W16, pl.SC, pl.C, d);
+                                   : plan_direct_ordered(MP, p.T, slots, W16, pl.SC, pl.C, EPI == EPI_ARGMAX, d);
         if (ok) {
             if (d.ksplit > 1) p.part32 = static_cast<float *>(workspace);
             if (grid_out) *grid_out = d.groups * d.ksplit;

@@ -35,21 +35,24 @@ constexpr int direct_ring(int MP, int slots) {
 // XS: slots of a tile a wave may have (its activations are held in XS x (MP == 8 ? 4 : MP / 2) registers).
 // CH: the bits of the kernels that stage x, whose order of the sum is one of 16 waves.  Up to 16 tokens: K is summed in p.C
 //     chunks, each reduced over the waves by itself and added in chunk order.  32 tokens (PAIR): a wave of the eight takes two
-//     neighbouring shares of sixteen, each in its half of the slots and with an accumulator of its own, and hands over
-//     their sum, which is what that order adds first; slots of bf16 weights are 32 k there, as the shares are.
-//     Otherwise one sum a wave.
+//     neighbouring shares of sixteen of each chunk, CH slots each, and hands over the sum of the two, which is what that order adds
+//     first; slots of bf16 weights are 32 k there, as the shares are.  The chunks are XS / (2 CH), as many as p.C; slots that a
+//     share does not have read one line and are not multiplied.  0: one sum a wave.
+// 32 tokens in chunks, V = 151936, staged -> so: int8 K = 4096 255 -> 109 us, K = 5120 314 -> 190; bf16 K = 4096 290 -> 196, K = 5120 359 -> 256
 // LDS: [a region per wave: activations on their way in, then 2 x C x NB partial tiles of 1 KB][row scales][kept gate tile (EPI_SWIGLU)][16 x MP sums (PRE)]
-template <int MP, bool W16, int EPI, int XS, bool CH = false, int PRE = PRE_NONE, bool RES = false>
+template <int MP, bool W16, int EPI, int XS, int CH = 0, int PRE = PRE_NONE, bool RES = false>
 __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kernel(const GemmParams p0) {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int NW = direct_waves(MP, XS);
     constexpr int NB = (MP == 32) ? 2 : 1;          // 16-token blocks
-    constexpr bool PAIR = CH && MP == 32;
+    constexpr bool PAIR = CH > 0 && MP == 32;
+    constexpr int CC = PAIR ? XS / (2 * CH) : 1;    // chunks of the pair form
+    constexpr int PARS = CC > 4 ? 1 : 2;            // sets of partial tiles (five chunks: two sets do not fit the LDS)
     constexpr int KS = PAIR && W16 ? 32 : 64;       // k of a slot
     constexpr int XP = (MP == 8 || KS == 32) ? 1 : 2;   // loads of x per slot and token block
     constexpr int WL = W16 && KS == 64 ? 2 : 1;     // weight loads per slot
-    constexpr int U = KS == 32 ? (XS == 6 ? 1 : 2) : (XS >= 4 ? 1 : 4 / XS);    // tiles per round: at least four slots in flight
-    constexpr int RD = KS == 32 ? XS * U : direct_ring(MP, XS * U);                  // ring depth in slots
+    constexpr int U = KS == 32 ? (XS >= 6 ? 1 : 2) : (XS >= 4 ? 1 : 4 / XS);    // tiles per round: at least four slots in flight
+    constexpr int RD = KS == 32 ? (CC == 1 ? XS * U : (XS == 12 ? 6 : (XS == 20 ? 10 : 8))) : direct_ring(MP, XS * U);                  // ring depth in slots
     static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
     constexpr int kSlotBytes = WL * kStepBytes;
 
@@ -73,12 +76,12 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     const int t0 = TU * tile_split(p.T / TU, b, G);
     const int t1 = TU * tile_split(p.T / TU, b + 1, G);
     const int ntiles = t1 - t0;
-    const int C = CH && !PAIR ? p.C : 1;
+    const int C = PAIR ? CC : (CH ? p.C : 1);
 
     // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
-    constexpr int kPass = direct_pass(MP, XS);
-    static_assert(KS == 64 || XS / 2 + 1 <= kPass, "slots of 32 k come in one pass of whole lines");
-    const int region = max(kPass * MP * 128, 2 * C * NB * 1024);
+    constexpr int kPass = KS == 32 && CC > 1 ? 0 : direct_pass(MP, XS);
+    static_assert(KS == 64 || CC > 1 || XS / 2 + 1 <= kPass, "slots of 32 k come in one pass of whole lines");
+    const int region = max(kPass * MP * 128, PARS * C * NB * 1024);
     unsigned char *own = lds + w * region;
     uint16_t *sc_lds = reinterpret_cast<uint16_t *>(lds + NW * region);                // [tiles][16]
     [[maybe_unused]] f32x4 *gate_keep = reinterpret_cast<f32x4 *>(lds + NW * region + p.sc_bytes - NB * 1024);
@@ -88,16 +91,22 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     // requested, and they are not multiplied.
     int n = 0, first = 0, bound0 = 0;
     int step[XS];
-    [[maybe_unused]] int n1 = 0;                    // PAIR: slots of the second share (n: of the first)
+    [[maybe_unused]] unsigned int have = 0;         // PAIR: the slots that carry a step
     if constexpr (PAIR) {
-        first = (p.S * (2 * w)) / 16;
-        const int mid = (p.S * (2 * w + 1)) / 16;
-        n = mid - first;
-        n1 = (p.S * (2 * w + 2)) / 16 - mid;
 #pragma unroll
-        for (int i = 0; i < XS; ++i) {
-            const bool mine = i < XS / 2 ? i < n : i - XS / 2 < n1;
-            step[i] = mine ? (i < XS / 2 ? first + i : mid + i - XS / 2) : min(first, p.S - 1);
+        for (int c = 0; c < CC; ++c) {
+            const int scc = CC == 1 ? p.S : min(p.SC, p.S - c * p.SC);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int lo = (scc * (2 * w + h)) / 16, count = (scc * (2 * w + h + 1)) / 16 - lo;
+                if (c == 0 && h == 0) first = lo;
+#pragma unroll
+                for (int j = 0; j < CH; ++j) {
+                    const int i = (2 * c + h) * CH + j;
+                    if (j < count) have |= 1u << i;
+                    step[i] = j < count ? (CC == 1 ? lo : c * p.SC + lo) + j : min(first, p.S - 1);
+                }
+            }
         }
     } else if constexpr (CH) {
         int c = 0, at = 0, left = 0;
@@ -205,10 +214,11 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
 
     const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w) + (unsigned long long)t0 * p.Srow * kSlotBytes;
     const unsigned int tile_bytes = (unsigned int)p.Srow * (unsigned int)kSlotBytes;
+    auto mine = [&](int i) { return PAIR ? (have >> i & 1u) != 0u : i < n; };
     u32x4 ring[RD][WL];
     // refill of ring entry d with slot i of tile tl; beyond the workgroup's last tile every lane reads the same 16 bytes
     auto refill = [&](int d, int tl, int i) {
-        const bool real = tl < ntiles;
+        const bool real = tl < ntiles && (CC == 1 || mine(i));
         const unsigned long long a = real ? wbase + (unsigned long long)tl * tile_bytes + (unsigned int)step[i] * (unsigned int)kSlotBytes
                                           : reinterpret_cast<unsigned long long>(p.x);
         unsigned int off = real ? 16u * lane : 0u;
@@ -295,7 +305,6 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     [[maybe_unused]] f32x4 share1[NB];               // PAIR: the second of the two shares
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) share1[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto mine = [&](int i) { return PAIR && i >= XS / 2 ? i - XS / 2 < n1 : i < n; };
     // one slot: 64 k of a tile into the accumulators
     auto slot = [&](int d, int i) {
         bf16x8 a[2];
@@ -310,7 +319,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
         for (int nb = 0; nb < NB; ++nb) {
             const u32x4 b0 = xr[i][nb * XP];
             const u32x4 b1 = MP == 8 ? rotate_half_row(b0) : xr[i][nb * XP + XP - 1];
-            f32x4 &to = PAIR && i >= XS / 2 ? share1[nb] : acc[nb];
+            f32x4 &to = PAIR && (i / (PAIR ? CH : 1)) % 2 == 1 ? share1[nb] : acc[nb];
             to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], __builtin_bit_cast(bf16x8, b0), to, 0, 0, 0);
             if constexpr (KS == 64) to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], __builtin_bit_cast(bf16x8, b1), to, 0, 0, 0);
         }
@@ -346,6 +355,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                     rsum[nb] = c > 0 ? s + rsum[nb] : s;
                 }
             }
+            if constexpr (PARS == 1) lds_barrier();          // (the others wait below: the one set of partial tiles is free again)
             finish_tile<W16, EPI, RES, NB>(p, rsum, t0 + tl, sc_lds + tl * kTileRows, resid, gate_keep, slice, lane, bestv, besti);
             if constexpr (EPI == EPI_LOGITS) {
                 if (p.soft_stats) {
@@ -360,8 +370,10 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                 }
             }
             if (RES) load_residual<RES, NB>(p, t0 + min(tl + NW, ntiles - 1), lane, resid);      // of this wave's next tile
+        } else if constexpr (PARS == 1) {
+            lds_barrier();
         }
-        parity ^= 1;
+        if constexpr (PARS == 2) parity ^= 1;
     };
     auto round = [&](int tl0, auto last) {
         constexpr bool kLast = decltype(last)::value;
@@ -379,6 +391,9 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                     const int jn = j + R;
                     refill(j % R, tl0 + (jn / (U * XS)) * U + (jn % (U * XS)) / XS, jn % XS);
                 }
+                if constexpr (CC > 1) {
+                    if ((i + 1) % (2 * CH) == 0) hand_over(i / (2 * CH));
+                }
                 if constexpr (CH && !PAIR) {
                     if (i + 1 == bound) {
                         hand_over(c);
@@ -391,7 +406,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                 }
             }
             if (U == 1 || tl < ntiles) {
-                if constexpr (!CH || PAIR) hand_over(0);
+                if constexpr (!CH || (PAIR && CC == 1)) hand_over(0);
                 tile_end(tl);
             }
         }
@@ -430,7 +445,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
 
 // ---- dispatch over the built forms ----
 
-template <int MP, bool W16, int EPI, bool CH, int PRE, bool RES, int... XS>
+template <int MP, bool W16, int EPI, int CH, int PRE, bool RES, int... XS>
 int launch_direct_forms(int xs, int grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
     int rc = QUASAR_ERR_SHAPE;
     ((xs == XS ? (void)(rc = launch(stream_direct_kernel<MP, W16, EPI, XS, CH, PRE, RES>, grid, direct_waves(MP, XS) * 64, lds_bytes,
@@ -450,36 +465,44 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
     p.xs_bytes = 0;
     const int grid = d.groups * d.ksplit;
     if constexpr (PRE == PRE_NONE && !RES && (EPI == EPI_LINEAR || EPI == EPI_ARGMAX)) {
+        // (CH: slots of a share)
         if (d.pair) {
             if constexpr (W16) {
                 p.S = p.Srow = p.K / 32;
-                return launch_direct_forms<32, W16, EPI, true, PRE, RES, 2, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
+                if constexpr (EPI == EPI_ARGMAX)
+                    if (d.C > 1) return launch_direct_forms<32, W16, EPI, 2, PRE, RES, 8, 12, 16, 20>(d.XS, grid, d.lds_bytes, stream, p);
+                if (d.XS == 2) return launch_direct_forms<32, W16, EPI, 1, PRE, RES, 2>(d.XS, grid, d.lds_bytes, stream, p);
+                if (d.XS == 4) return launch_direct_forms<32, W16, EPI, 2, PRE, RES, 4>(d.XS, grid, d.lds_bytes, stream, p);
+                return launch_direct_forms<32, W16, EPI, 3, PRE, RES, 6>(d.XS, grid, d.lds_bytes, stream, p);
             } else {
-                return launch_direct_forms<32, W16, EPI, true, PRE, RES, 2, 4>(d.XS, grid, d.lds_bytes, stream, p);
+                if constexpr (EPI == EPI_ARGMAX)
+                    if (d.C > 1) return launch_direct_forms<32, W16, EPI, 1, PRE, RES, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
+                if (d.XS == 2) return launch_direct_forms<32, W16, EPI, 1, PRE, RES, 2>(d.XS, grid, d.lds_bytes, stream, p);
+                return launch_direct_forms<32, W16, EPI, 2, PRE, RES, 4>(d.XS, grid, d.lds_bytes, stream, p);
             }
         }
         if (d.C > 1) {
-            if (MP == 8) return launch_direct_forms<8, W16, EPI, true, PRE, RES, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
+            if (MP == 8) return launch_direct_forms<8, W16, EPI, 1, PRE, RES, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
             // (bf16 weights: chunks of whole slots for every wave, K = 4096 and 6144)
-            if constexpr (W16) return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
-            else return launch_direct_forms<16, W16, EPI, true, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
+            if constexpr (W16) return launch_direct_forms<16, W16, EPI, 1, PRE, RES, 4, 6>(d.XS, grid, d.lds_bytes, stream, p);
+            else return launch_direct_forms<16, W16, EPI, 1, PRE, RES, 4, 5, 6, 8>(d.XS, grid, d.lds_bytes, stream, p);
         }
     }
     if constexpr (EPI == EPI_ARGMAX) {
         // the order of the staged kernel: K in one piece is 120 slots at 8 tokens, 60 at 16
-        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
-        return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, 0, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<16, W16, EPI, 0, PRE, RES, 1, 2, 3, 4>(d.XS, grid, d.lds_bytes, stream, p);
     } else if constexpr (PRE != PRE_NONE) {
-        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
-        if (MP == 16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5>(d.XS, grid, d.lds_bytes, stream, p);
-        return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, 0, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 16) return launch_direct_forms<16, W16, EPI, 0, PRE, RES, 1, 2, 3, 4, 5>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<32, W16, EPI, 0, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     } else {
-        if (MP == 8) return launch_direct_forms<8, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
+        if (MP == 8) return launch_direct_forms<8, W16, EPI, 0, PRE, RES, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12>(d.XS, grid, d.lds_bytes, stream, p);
         if (MP == 16) {
-            if constexpr (W16) return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 20>(d.XS, grid, d.lds_bytes, stream, p);
-            else return launch_direct_forms<16, W16, EPI, false, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);
+            if constexpr (W16) return launch_direct_forms<16, W16, EPI, 0, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 20>(d.XS, grid, d.lds_bytes, stream, p);
+            else return launch_direct_forms<16, W16, EPI, 0, PRE, RES, 1, 2, 3, 4, 5, 6, 8, 20, 24>(d.XS, grid, d.lds_bytes, stream, p);
         }
-        return launch_direct_forms<32, W16, EPI, false, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
+        return launch_direct_forms<32, W16, EPI, 0, PRE, RES, 2, 4, 6, 8, 10>(d.XS, grid, d.lds_bytes, stream, p);
     }
 }
 

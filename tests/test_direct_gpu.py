@@ -235,3 +235,32 @@ def four_squares(n):
                 if c * c + d * d == r and d <= 255:
                     return [a, b, c, d]
     raise AssertionError(n)
+
+
+# K: two to five chunks, of 12 to 16 steps, a short last one; tiles: one, several a workgroup and a remainder
+@pytest.mark.parametrize("K", [1472, 1536, 2048, 2560, 3072, 3136, 4096, 4160, 5120])
+@pytest.mark.parametrize("M,V", [(17, 16), (32, 16 * 261), (24, 16 * 1100)])
+def test_order_of_many_tokens_in_chunks(qb, M, V, K):
+    """More than 16 tokens, K in chunks: argmax and accepted length of rows whose exact logits are equal (the winner is the row
+    whose sum rounds up most, so it shows the order of the sum) are those of the staged kernel."""
+    print("direct chunks", M, V, K, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(K + V)
+    half = torch.randn(M, K // 2, generator=gen, device="cuda").bfloat16()
+    x = torch.cat([half, half], 1).contiguous()
+    codes = torch.randint(-127, 128, (K,), generator=gen, device="cuda").float()
+    codes[0] = 127.0
+    swap = torch.rand(V, K // 2, generator=gen, device="cuda") < 0.5
+    lo, hi = codes[:K // 2].expand(V, -1), codes[K // 2:].expand(V, -1)
+    w = torch.cat([torch.where(swap, hi, lo), torch.where(swap, lo, hi)], 1) / 128.0
+    wq, sc = qb.quantize_weights(w)
+    wp = qb.pack_bf16_weights(w)
+    ws = qb.make_workspace(M, V, K)
+    draft = torch.zeros(M - 1, dtype=torch.int32, device="cuda")
+    now = [t.clone() for f in (lambda: qb.lmhead_verify(x, wq, sc, V, draft, ws), lambda: qb.bf16_lmhead_verify(x, wp, V, draft, ws)) for t in f()]
+    qb.set_tuning(16, 2, 4)
+    try:
+        staged = [t.clone() for f in (lambda: qb.lmhead_verify(x, wq, sc, V, draft, ws), lambda: qb.bf16_lmhead_verify(x, wp, V, draft, ws)) for t in f()]
+    finally:
+        qb.set_tuning(16, 1, 4)
+    assert all(torch.equal(a, b) for a, b in zip(now, staged))
+    assert V == 16 or len(set(now[0].tolist())) > M // 2
