@@ -451,6 +451,22 @@ int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx
                             const int8_t *wq_packed_interleaved, const uint16_t *scales_bf16_interleaved,
                             int64_t I, uint16_t *y, int64_t ldy, void *hip_stream);
 
+/* The same with a workspace (may be NULL).  One of quasar_w8_fused_workspace_bytes (0: none is used for this shape; N is 2 I for
+ * the gate/up form, which has no residual) lets the normalisation be a launch of its own where every workgroup's is dearer, and
+ * K be split across workgroups through fp32 partial sums; sums are then taken in another order than without.  It is scratch:
+ * undefined on entry and on exit. */
+size_t quasar_w8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int has_gamma, int has_residual);
+int quasar_w8_linear_fused_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
+                                 const uint16_t *gamma, float eps,
+                                 const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N,
+                                 const uint16_t *residual, int64_t ldr,
+                                 uint16_t *y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream);
+int quasar_w8_gateup_swiglu_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
+                                  const uint16_t *gamma, float eps,
+                                  const int8_t *wq_packed_interleaved, const uint16_t *scales_bf16_interleaved,
+                                  int64_t I, uint16_t *y, int64_t ldy, void *workspace, size_t workspace_bytes,
+                                  void *hip_stream);
+
 /*
  * ---- Attention of a verification step (Sec. 3.1: the gamma + 1 positions are verified in one
  * forward pass; the attention of that pass is the target model's own: grouped-query attention

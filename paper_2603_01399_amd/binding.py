@@ -35,7 +35,8 @@ EXPORTS = (
     "quasar_w4_workspace_bytes", "quasar_w4_linear_split", "quasar_w4_lmhead_verify",
     "quasar_drafter_create", "quasar_drafter_destroy", "quasar_drafter_append", "quasar_drafter_length",
     "quasar_drafter_propose",
-    "quasar_w8_linear_fused", "quasar_w8_gateup_swiglu",
+    "quasar_w8_linear_fused", "quasar_w8_gateup_swiglu", "quasar_w8_fused_workspace_bytes", "quasar_w8_linear_fused_split",
+    "quasar_w8_gateup_swiglu_split",
     "quasar_kv_cache_bytes", "quasar_kv_cache_fill", "quasar_attn_prepare", "quasar_attention_workspace_bytes",
     "quasar_verify_attention",
 )
@@ -120,6 +121,10 @@ def _load() -> ctypes.CDLL:
     lib.quasar_w4_lmhead_verify.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, vp, vp, vp, sz, vp]
     lib.quasar_w8_linear_fused.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp, i64, vp]
     lib.quasar_w8_gateup_swiglu.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp]
+    lib.quasar_w8_fused_workspace_bytes.argtypes = [i64, i64, i64, ci, ci]
+    lib.quasar_w8_fused_workspace_bytes.restype = sz
+    lib.quasar_w8_linear_fused_split.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp, i64, vp, sz, vp]
+    lib.quasar_w8_gateup_swiglu_split.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp, sz, vp]
     lib.quasar_kv_cache_bytes.argtypes = [i64, i64]
     lib.quasar_kv_cache_bytes.restype = sz
     lib.quasar_kv_cache_fill.argtypes = [vp, vp, i64, i64, i64, vp, i64, vp]
@@ -455,6 +460,14 @@ def _gamma_arg(gamma, K):
     return gamma
 
 
+def _fused_scratch(x, M, N, K, gamma, residual):
+    """Scratch of a fused call, from the allocator of the stream it runs on (small shapes never use any: not asked for)."""
+    if K <= (8192 if M <= 8 else 4096 if M <= 16 else 2048):
+        return None, 0
+    need = _lib.quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None)
+    return (torch.empty(need, dtype=torch.uint8, device=x.device) if need else None), need
+
+
 def w8_linear_fused(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, N: int, *, gamma: torch.Tensor = None,
                     eps: float = 1e-6, residual: torch.Tensor = None, y: torch.Tensor = None) -> torch.Tensor:
     """y = [residual +] W8([RMSNorm](x)); the normalisation (gamma, eps) and the residual are optional."""
@@ -469,10 +482,11 @@ def w8_linear_fused(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tens
             raise ValueError("residual must be [M, N] with a contiguous last dimension")
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
+    ws, need = _fused_scratch(x, M, N, K, gamma, residual)
     _check("quasar_w8_linear_fused",
-           _lib.quasar_w8_linear_fused(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), N,
-                                       _ptr(residual), 0 if residual is None else residual.stride(0),
-                                       _ptr(y), y.stride(0), _stream()))
+           _lib.quasar_w8_linear_fused_split(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), N,
+                                             _ptr(residual), 0 if residual is None else residual.stride(0),
+                                             _ptr(y), y.stride(0), _ptr(ws), need, _stream()))
     return y
 
 
@@ -495,9 +509,10 @@ def w8_gateup_swiglu(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Ten
     gamma = _gamma_arg(gamma, K)
     if y is None:
         y = torch.empty((M, I), dtype=torch.bfloat16, device=x.device)
+    ws, need = _fused_scratch(x, M, 2 * I, K, gamma, None)
     _check("quasar_w8_gateup_swiglu",
-           _lib.quasar_w8_gateup_swiglu(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), I,
-                                        _ptr(y), y.stride(0), _stream()))
+           _lib.quasar_w8_gateup_swiglu_split(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), I,
+                                              _ptr(y), y.stride(0), _ptr(ws), need, _stream()))
     return y
 
 

@@ -21,6 +21,7 @@
 #include "stream_w8a8.hpp"
 #include "stream_w4.hpp"
 #include "stream_outer.hpp"
+#include "norm.hpp"
 #include "drafter.hpp"
 #include "attention.hpp"
 
@@ -294,7 +295,7 @@ bool plan_direct_ordered(int MP, int T, int S, bool w16, int SC, int C, bool arg
 template <int FMT>
 int launch_splitk_finalize(const GemmParams &p, int ksplit, const float *dx, hipStream_t stream) {
     hipLaunchKernelGGL(splitk_finalize_kernel<FMT>, dim3((unsigned int)((p.N / 4 + 255) / 256), (unsigned int)p.M), dim3(256), 0, stream,
-                       p.part32, ksplit, p.M, p.N, p.scales, dx, p.y, p.ldy);
+                       p.part32, ksplit, p.M, p.N, p.scales, dx, p.resid, p.ldr, p.y, p.ldy);
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
@@ -905,6 +906,72 @@ int launch_fused(const GemmParams &base, int M, hipStream_t stream) {
     if (MP == 16)
         return launch(stream_mfma_kernel<16, false, EPI, 16, 4, PRE, RES>, pl.grid, 1024, lds, stream, p);
     return launch(stream_mfma_kernel<32, false, EPI, 16, 4, PRE, RES>, pl.grid, 1024, lds, stream, p);
+}
+
+// Scratch of a call, handed out from the front in pieces of 16 bytes.
+struct Scratch {
+    unsigned char *at;
+    size_t room;
+    Scratch(void *p, size_t bytes) : at(static_cast<unsigned char *>(p)), room(p && aligned(p, 16) ? bytes / 16 * 16 : 0) {}
+    void *take(size_t bytes) {               // nullptr: no room
+        bytes = (bytes + 15) / 16 * 16;
+        if (bytes == 0 || bytes > room) return nullptr;
+        void *p = at;
+        at += bytes;
+        room -= bytes;
+        return p;
+    }
+};
+
+// Bytes of normalised activations that a fused linear takes from its workspace (0: the normalisation stays in the kernel).  A
+// launch of its own costs 2.6 us; in the kernel every workgroup scans and scales its waves' slices, in registers that long K
+// and many tokens do not leave.  us a call, in the kernel -> apart:
+//   M <= 8:   6144 x 4096 10.3 -> 11.0, 51200 x 5120 gated 45.8 -> 46.6 (K beyond 8192: x staged)
+//   M <= 16:  24576 x 4096 gated 22.2 -> 22.6, 10240 x 5120 18.6 -> 16.5, 51200 x 5120 gated 52.0 -> 47.1
+//   M <= 32:  16384 x 2048 gated 13.5 -> 14.1, 6144 x 4096 31.7 -> 14.0, 24576 x 4096 gated 41.3 -> 24.6, 51200 x 5120 gated 81 -> 51
+size_t fused_norm_bytes(int M, int K, bool gamma) {
+    return gamma && K > (M <= 8 ? 8192 : (M <= 16 ? 4096 : 2048)) ? (size_t)M * K * 2 : 0;
+}
+
+// Normalises x into the workspace where that is the faster way; the linear then has no normalisation left (pre_arg).
+int norm_apart(GemmParams &p, int M, Scratch &ws, hipStream_t stream) {
+    const size_t bytes = fused_norm_bytes(M, p.K, p.pre_arg != nullptr);
+    uint16_t *xn = bytes ? static_cast<uint16_t *>(ws.take(bytes)) : nullptr;
+    if (!xn) return QUASAR_OK;
+    hipLaunchKernelGGL(rmsnorm_rows_kernel, dim3(M), dim3(1024), 0, stream, p.x, p.ldx, p.K, p.pre_arg, p.eps, xn);
+    if (hipGetLastError() != hipSuccess) return QUASAR_ERR_HIP;
+    p.x = xn;
+    p.ldx = p.K;
+    p.pre_arg = nullptr;
+    return QUASAR_OK;
+}
+
+// Most slots of the forms that hold x for a linear without normalisation.
+constexpr int direct_most(int MP) { return MP == 8 ? 12 : (MP == 16 ? 24 : 10); }
+
+// The int8 linear, with a residual or without, whose sum has no order to keep: K split over workgroups where the forms for all of K
+// are long ones or none, and the workspace holds the partial sums.  us a call, K in one piece -> split: 5120 x 25600
+// M = 8 / 16 / 32 43 / 54 / 107 -> 27 / 27 / 30, 4096 x 12288 M = 32 45 -> 15.8, 5120 x 8192 M = 32 37 -> 14.9; up to the limits
+// below one piece is as fast (2048 x 8192 M = 2 6.8 against 7.3, 4096 x 5120 M = 32 9.8 against 10.0).
+bool plan_free(int M, int N, int K, size_t room, DirectPlan &d) {
+    const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
+    if (K <= (MP == 32 ? 5120 : 8192)) return false;
+    return plan_direct_split(MP, M, N / kTileRows, K / kStepK8, false, N, room, direct_most(MP), d);
+}
+size_t free_split_bytes(int M, int N, int K) {
+    DirectPlan d{};
+    return plan_free(M, N, K, (size_t)-1, d) ? splitk_bytes(M, N, d.ksplit) : 0;
+}
+int launch_free(const GemmParams &p0, int M, Scratch &ws, hipStream_t stream) {
+    DirectPlan d{};
+    if (ws.room && direct_reach(M, p0.ldx) && plan_free(M, p0.N, p0.K, ws.room, d) && d.ksplit > 1) {
+        GemmParams p = p0;
+        p.Srow = p.S;
+        p.part32 = static_cast<float *>(ws.take(splitk_bytes(M, p.N, d.ksplit)));
+        if (const int e = launch_direct(false, EPI_LINEAR, PRE_NONE, false, p, M <= 8 ? 8 : (M <= 16 ? 16 : 32), d, stream)) return e;
+        return launch_splitk_finalize<FMT_INT8>(p, d.ksplit, nullptr, stream);
+    }
+    return p0.resid ? launch_fused<EPI_LINEAR, PRE_NONE, true>(p0, M, stream) : launch_fused<EPI_LINEAR, PRE_NONE, false>(p0, M, stream);
 }
 
 std::atomic<int> g_w4_nw{16};
@@ -1681,9 +1748,16 @@ int quasar_w4_lmhead_verify(const uint16_t *hidden, int64_t M, int64_t K, int64_
 
 /* ---- int8 linears with the decoder block's surrounding operations fused in ---- */
 
-int quasar_w8_linear_fused(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
-                           const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, const uint16_t *residual,
-                           int64_t ldr, uint16_t *y, int64_t ldy, void *hip_stream) {
+size_t quasar_w8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int has_gamma, int has_residual) {
+    if (check_mnk(M, N, K)) return 0;
+    const size_t norm = fused_norm_bytes((int)M, (int)K, has_gamma != 0);
+    return norm + (norm || (has_residual && !has_gamma) ? free_split_bytes((int)M, (int)N, (int)K) : 0);
+}
+
+int quasar_w8_linear_fused_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
+                                 const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, const uint16_t *residual,
+                                 int64_t ldr, uint16_t *y, int64_t ldy, void *workspace, size_t workspace_bytes,
+                                 void *hip_stream) {
     if (!x || !wq_packed || !scales_bf16 || !y) return QUASAR_ERR_NULL;
     if (const int e = check_mnk(M, N, K)) return e;
     if (ldx < K || ldy < N || ldx % 8 || ldy % 8) return QUASAR_ERR_SHAPE;
@@ -1701,15 +1775,25 @@ int quasar_w8_linear_fused(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
     p.pre_arg = gamma; p.eps = eps; p.resid = residual; p.ldr = ldr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const int m = (int)M;
-    if (gamma)
+    Scratch ws(workspace, workspace_bytes);
+    if (const int e = norm_apart(p, m, ws, st)) return e;
+    if (!p.pre_arg && (gamma || residual)) return launch_free(p, m, ws, st);
+    if (p.pre_arg)
         return residual ? launch_fused<EPI_LINEAR, PRE_RMSNORM, true>(p, m, st)
                         : launch_fused<EPI_LINEAR, PRE_RMSNORM, false>(p, m, st);
-    return residual ? launch_fused<EPI_LINEAR, PRE_NONE, true>(p, m, st) : launch_mfma<false, EPI_LINEAR>(p, m, st, nullptr);
+    return launch_mfma<false, EPI_LINEAR>(p, m, st, nullptr);      // the plain linear, its bits
 }
 
-int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
-                            const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t I, uint16_t *y, int64_t ldy,
-                            void *hip_stream) {
+int quasar_w8_linear_fused(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
+                           const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, const uint16_t *residual,
+                           int64_t ldr, uint16_t *y, int64_t ldy, void *hip_stream) {
+    return quasar_w8_linear_fused_split(x, M, K, ldx, gamma, eps, wq_packed, scales_bf16, N, residual, ldr, y, ldy, nullptr, 0, hip_stream);
+}
+
+
+int quasar_w8_gateup_swiglu_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
+                                  const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t I, uint16_t *y, int64_t ldy,
+                                  void *workspace, size_t workspace_bytes, void *hip_stream) {
     if (!x || !wq_packed || !scales_bf16 || !y) return QUASAR_ERR_NULL;
     if (I < 16 || I % 16 || I > (1 << 25)) return QUASAR_ERR_SHAPE;
     if (const int e = check_mnk(M, 2 * I, K)) return e;
@@ -1725,8 +1809,16 @@ int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx
     p.S = (int)(K / kStepK8);
     p.pre_arg = gamma; p.eps = eps;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    return gamma ? launch_fused<EPI_SWIGLU, PRE_RMSNORM, false>(p, (int)M, st)
-                 : launch_fused<EPI_SWIGLU, PRE_NONE, false>(p, (int)M, st);
+    Scratch ws(workspace, workspace_bytes);
+    if (const int e = norm_apart(p, (int)M, ws, st)) return e;
+    return p.pre_arg ? launch_fused<EPI_SWIGLU, PRE_RMSNORM, false>(p, (int)M, st)
+                     : launch_fused<EPI_SWIGLU, PRE_NONE, false>(p, (int)M, st);
+}
+
+int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
+                            const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t I, uint16_t *y, int64_t ldy,
+                            void *hip_stream) {
+    return quasar_w8_gateup_swiglu_split(x, M, K, ldx, gamma, eps, wq_packed, scales_bf16, I, y, ldy, nullptr, 0, hip_stream);
 }
 
 /* ---- attention of a verification step ---- */

@@ -265,7 +265,8 @@ __global__ __launch_bounds__(outer_waves(MP) * 64) void stream_outer_kernel(cons
 // trip to memory, so the slices are requested eight at a time and added in order (one after the other they cost 0.6 us each).
 template <int FMT>
 __global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part, int ksplit, int M, int N, const uint16_t *scales,
-                                                              const float *dx, uint16_t *y, long long ldy) {
+                                                              const float *dx, const uint16_t *resid, long long ldr, uint16_t *y,
+                                                              long long ldy) {
     typedef std::conditional_t<FMT == FMT_A8, i32x4, f32x4> sum_t;
     const int n0 = 4 * (blockIdx.x * 256 + threadIdx.x), m = blockIdx.y;
     if (n0 >= N) return;
@@ -294,6 +295,17 @@ __global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part,
         }
         o.x = float_to_bf16_bits(acc.x * s4[0]) | (float_to_bf16_bits(acc.y * s4[1]) << 16);
         o.y = float_to_bf16_bits(acc.z * s4[2]) | (float_to_bf16_bits(acc.w * s4[3]) << 16);
+    }
+    if constexpr (FMT == FMT_INT8) {
+        if (resid) {                                         // (may be y itself: read here, by the thread that writes)
+            const u32x2 rr = *reinterpret_cast<const u32x2 *>(resid + m * ldr + n0);
+            const float r0 = bf16_bits_to_float(o.x & 0xFFFFu) + bf16_bits_to_float(rr.x & 0xFFFFu);
+            const float r1 = __uint_as_float(o.x & 0xFFFF0000u) + __uint_as_float(rr.x & 0xFFFF0000u);
+            const float r2 = bf16_bits_to_float(o.y & 0xFFFFu) + bf16_bits_to_float(rr.y & 0xFFFFu);
+            const float r3 = __uint_as_float(o.y & 0xFFFF0000u) + __uint_as_float(rr.y & 0xFFFF0000u);
+            o.x = float_to_bf16_bits(r0) | (float_to_bf16_bits(r1) << 16);
+            o.y = float_to_bf16_bits(r2) | (float_to_bf16_bits(r3) << 16);
+        }
     }
     *reinterpret_cast<u32x2 *>(y + m * ldy + n0) = o;
 }
