@@ -14,7 +14,7 @@
 // so that a lane owns ONE query column in every accumulator: the running maximum, the rescaling
 // of the output and the probabilities (B operand of the second product) never cross lanes.
 //
-// Work split: grid (splits, kv heads); the waves of a workgroup take the split's 32-position
+// Work split: grid (splits, kv heads, groups of query rows); the waves of a workgroup take the split's 32-position
 // blocks in turn with private online-softmax state, merge through LDS, and the workgroup writes
 // one partial (max, sum, output) per split; attention_merge_kernel combines the splits.
 #pragma once
@@ -34,10 +34,10 @@ struct AttnParams {
     long long head_stride;    // bytes between kv heads in one cache
     uint16_t *out;            // [M, Hq * 128] bf16
     long long ldo;
-    float *part_o;            // [Hkv][nsplit][NQT][8][64] f32x4
-    float *part_ml;           // [Hkv][nsplit][NQT][16][2]
+    float *part_o;            // [row groups][Hkv][nsplit][NQT][8][64] f32x4
+    float *part_ml;           // [row groups][Hkv][nsplit][NQT][16][2]
     int M, G, Hkv, L_total, nblk, nsplit;
-    int row0;                 // first query row (m * G + g) of this launch; rows row0 .. row0 + 16 NQT - 1
+    int row0;                 // first query row (m * G + g) of this launch; group z has rows row0 + 16 NQT z .. + 16 NQT - 1
     float scale_log2;         // log2(e) / sqrt(128)
 };
 
@@ -117,10 +117,14 @@ __global__ __launch_bounds__(256) void kv_cache_fill_kernel(const uint16_t *src,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Main kernel.  NQT = number of 16-row query tiles of one launch (rows r = m * G + g, starting at
-// row0; rows at or beyond M * G are padding).  More than 64 rows take several launches.
+// Main kernel.  NQT = number of 16-row query tiles of one workgroup (rows r = m * G + g; rows at or
+// beyond M * G are padding): as many as the rows need, each costs its share of the arithmetic, of the merges and
+// 8 KB of partial sums a split.  More than 64 rows are several groups, side by side in the grid (SHARED): groups of the same
+// positions are a multiple of eight workgroups apart, so they meet in one XCD's L2 and the cache comes from memory once.
+// One launch a group, one after the other: 32 tokens of 32 / 8 heads over 4096 positions 33.8 us, now 19.9; 30011 70.3, now 52.
+// 1 to 4 tokens (one tile instead of two) over 4096 positions 12.4, now 9.8; 12 tokens (three instead of four) 17.5, now 14.4.
 // ---------------------------------------------------------------------------------------------
-template <int NQT, int NW>
+template <int NQT, int NW, bool SHARED>
 __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x;
@@ -128,17 +132,31 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g4 = lane >> 4, col = lane & 15;
     const int h = blockIdx.y, split = blockIdx.x;
-    const int R = p.M * p.G;
+    const int R = p.M * p.G, row0 = p.row0 + 16 * NQT * (int)blockIdx.z;
 
     const int b0 = (int)(((long long)p.nblk * split) / p.nsplit);
     const int b1 = (int)(((long long)p.nblk * (split + 1)) / p.nsplit);
+
+    const u32x4 *kbase = reinterpret_cast<const u32x4 *>(p.kcache + h * p.head_stride) + lane;
+    const u32x4 *vbase = reinterpret_cast<const u32x4 *>(p.vcache + h * p.head_stride) + lane;
+    auto load_block = [&](const u32x4 *base, int b, u32x4 (&to)[8]) {
+        const u32x4 *from = base + (long long)b * (kKvBlockBytes / 16);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) to[i] = SHARED ? from[64 * i] : __builtin_nontemporal_load(from + 64 * i);
+    };
+
+    // the wave's first keys are requested ahead of the queries, whose addresses take divisions, the values behind them (loads
+    // return in order)
+    u32x4 kc[8], vc[8];
+    int b = b0 + w;
+    if (b < b1) load_block(kbase, b, kc);
 
     // queries as B operands: lane (query column col, k group g4) holds d = 32 ks + 8 g4 .. + 7
     bf16x8 qb[NQT][4];
     int limit[NQT];                       // last visible position of this lane's query column
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
-        const int r = p.row0 + 16 * qt + col;
+        const int r = row0 + 16 * qt + col;
         const int m = r < R ? r / p.G : p.M - 1, g = r < R ? r % p.G : 0;
         limit[qt] = p.L_total - p.M + m;
 #pragma unroll
@@ -149,17 +167,6 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
             qb[qt][ks] = __builtin_bit_cast(bf16x8, v);
         }
     }
-
-    const u32x4 *kbase = reinterpret_cast<const u32x4 *>(p.kcache + h * p.head_stride) + lane;
-    const u32x4 *vbase = reinterpret_cast<const u32x4 *>(p.vcache + h * p.head_stride) + lane;
-    auto load_block = [&](int b, u32x4 (&kk)[8], u32x4 (&vv)[8]) {
-        const u32x4 *kp = kbase + (long long)b * (kKvBlockBytes / 16);
-        const u32x4 *vp = vbase + (long long)b * (kKvBlockBytes / 16);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) kk[i] = __builtin_nontemporal_load(kp + 64 * i);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) vv[i] = __builtin_nontemporal_load(vp + 64 * i);
-    };
 
     f32x4 oacc[8][NQT];
 #pragma unroll
@@ -173,8 +180,6 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
     // One block of prefetch, the last block of a wave without one: both loads counts are known to the compiler (a conditional
     // prefetch would make it wait for the prefetched block before the current one is used), and a wave whose share is one
     // or two blocks - a short context - does not read a block it has already read.
-    u32x4 kc[8], vc[8];
-    int b = b0 + w;
     auto process = [&](int b) {
         const int pos0 = b * kKvBlock;
         const bool edge = pos0 + kKvBlock - 1 > p.L_total - p.M;      // some position may be hidden from some query
@@ -195,76 +200,102 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
                 vc[dt].w &= keep[3];
             }
         }
+        // step by step over two or three query tiles: a tile's chain of matrix products, lane exchanges and exponentials is long, and
+        // with one wave a SIMD only other tiles' chains can fill it (8 tokens of 32 / 8 heads, 30011 positions 28.8 -> 27.7 us).
+        // Four tiles one by one, their values do not fit: 16 tokens 36.3 us, 39.8 by twos, 44.8 all at once
+        constexpr int QG = NQT == 4 ? 1 : NQT;
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) {
-            f32x4 s[2];
+        for (int q0 = 0; q0 < NQT; q0 += QG) {
+            f32x4 s[QG][2];
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                s[sub] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int qt = 0; qt < QG; ++qt)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                    s[sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kc[sub * 4 + ks]), qb[qt][ks],
-                                                                     s[sub], 0, 0, 0);
-            }
+                for (int sub = 0; sub < 2; ++sub) s[qt][sub] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int qt = 0; qt < QG; ++qt)
+#pragma unroll
+                    for (int sub = 0; sub < 2; ++sub)
+                        s[qt][sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kc[sub * 4 + ks]), qb[q0 + qt][ks],
+                                                                             s[qt][sub], 0, 0, 0);
             if (edge) {
 #pragma unroll
-                for (int sub = 0; sub < 2; ++sub) {
-                    const int pb = pos0 + 16 * sub + 4 * g4;
-                    if (pb + 0 > limit[qt]) s[sub].x = -__builtin_inff();
-                    if (pb + 1 > limit[qt]) s[sub].y = -__builtin_inff();
-                    if (pb + 2 > limit[qt]) s[sub].z = -__builtin_inff();
-                    if (pb + 3 > limit[qt]) s[sub].w = -__builtin_inff();
-                }
+                for (int qt = 0; qt < QG; ++qt)
+#pragma unroll
+                    for (int sub = 0; sub < 2; ++sub) {
+                        const int pb = pos0 + 16 * sub + 4 * g4;
+                        if (pb + 0 > limit[q0 + qt]) s[qt][sub].x = -__builtin_inff();
+                        if (pb + 1 > limit[q0 + qt]) s[qt][sub].y = -__builtin_inff();
+                        if (pb + 2 > limit[q0 + qt]) s[qt][sub].z = -__builtin_inff();
+                        if (pb + 3 > limit[q0 + qt]) s[qt][sub].w = -__builtin_inff();
+                    }
             }
             // running maximum in units of the raw scores; exponentials as exp2(raw * c - max * c) in one
             // fused multiply-add each (c = log2(e) / sqrt(128) > 0 keeps the order)
-            float mx = fmaxf(fmaxf(fmaxf(s[0].x, s[0].y), fmaxf(s[0].z, s[0].w)),
-                             fmaxf(fmaxf(s[1].x, s[1].y), fmaxf(s[1].z, s[1].w)));
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            const float m_new = fmaxf(mrow[qt], mx);
-            const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;     // nothing visible yet
-            const float mc = -m_use * p.scale_log2;
-            const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(mrow[qt], p.scale_log2, mc));   // 0 while mrow is -inf
-            mrow[qt] = m_new;
-            float pr[8];
-            pr[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0].x, p.scale_log2, mc));
-            pr[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0].y, p.scale_log2, mc));
-            pr[2] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0].z, p.scale_log2, mc));
-            pr[3] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0].w, p.scale_log2, mc));
-            pr[4] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1].x, p.scale_log2, mc));
-            pr[5] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1].y, p.scale_log2, mc));
-            pr[6] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1].z, p.scale_log2, mc));
-            pr[7] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1].w, p.scale_log2, mc));
-            // the probabilities enter the second product as bf16 (hardware conversion, nearest even);
-            // the row sum uses the same rounded values so that the weights that are applied sum to one
-            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-            typedef float f32x2 __attribute__((ext_vector_type(2)));
-            unsigned int pk[4];
-            float psum = 0.f;
+            float mx[QG], alpha[QG];
+            u32x4 pb16[QG];
+            bool moved = false;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const bf16x2 h2 = __builtin_convertvector(f32x2{pr[2 * i], pr[2 * i + 1]}, bf16x2);
-                pk[i] = __builtin_bit_cast(unsigned int, h2);
-                psum += __uint_as_float(pk[i] << 16) + __uint_as_float(pk[i] & 0xFFFF0000u);
+            for (int qt = 0; qt < QG; ++qt)
+                mx[qt] = fmaxf(fmaxf(fmaxf(s[qt][0].x, s[qt][0].y), fmaxf(s[qt][0].z, s[qt][0].w)),
+                               fmaxf(fmaxf(s[qt][1].x, s[qt][1].y), fmaxf(s[qt][1].z, s[qt][1].w)));
+#pragma unroll
+            for (int qt = 0; qt < QG; ++qt) mx[qt] = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
+#pragma unroll
+            for (int qt = 0; qt < QG; ++qt) mx[qt] = fmaxf(mx[qt], __shfl_xor(mx[qt], 32, 64));
+#pragma unroll
+            for (int qt = 0; qt < QG; ++qt) {
+                const float m_new = fmaxf(mrow[q0 + qt], mx[qt]);
+                const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;     // nothing visible yet
+                const float mc = -m_use * p.scale_log2;
+                alpha[qt] = __builtin_amdgcn_exp2f(__builtin_fmaf(mrow[q0 + qt], p.scale_log2, mc));   // 0 while mrow is -inf
+                mrow[q0 + qt] = m_new;
+                float pr[8];
+                pr[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0].x, p.scale_log2, mc));
+                pr[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0].y, p.scale_log2, mc));
+                pr[2] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0].z, p.scale_log2, mc));
+                pr[3] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0].w, p.scale_log2, mc));
+                pr[4] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1].x, p.scale_log2, mc));
+                pr[5] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1].y, p.scale_log2, mc));
+                pr[6] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1].z, p.scale_log2, mc));
+                pr[7] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1].w, p.scale_log2, mc));
+                // the probabilities enter the second product as bf16 (hardware conversion, nearest even);
+                // the row sum uses the same rounded values so that the weights that are applied sum to one
+                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                unsigned int pk[4];
+                float psum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bf16x2 h2 = __builtin_convertvector(f32x2{pr[2 * i], pr[2 * i + 1]}, bf16x2);
+                    pk[i] = __builtin_bit_cast(unsigned int, h2);
+                    psum += __uint_as_float(pk[i] << 16) + __uint_as_float(pk[i] & 0xFFFF0000u);
+                }
+                pb16[qt] = u32x4{pk[0], pk[1], pk[2], pk[3]};
+                lrow[q0 + qt] = lrow[q0 + qt] * alpha[qt] + psum;
+                moved |= alpha[qt] != 1.0f;
             }
-            const u32x4 pb16 = {pk[0], pk[1], pk[2], pk[3]};
-            lrow[qt] = lrow[qt] * alpha + psum;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0ull) {        // some row's maximum moved
+            if (__builtin_amdgcn_ballot_w64(moved) != 0ull) {                    // some row's maximum moved
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt) oacc[dt][qt] *= alpha;
+                for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+                    for (int qt = 0; qt < QG; ++qt) oacc[dt][q0 + qt] *= alpha[qt];
             }
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt)
-                oacc[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vc[dt]),
-                                                                       __builtin_bit_cast(bf16x8, pb16), oacc[dt][qt], 0, 0, 0);
+#pragma unroll
+                for (int qt = 0; qt < QG; ++qt)
+                    oacc[dt][q0 + qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vc[dt]),
+                                                                           __builtin_bit_cast(bf16x8, pb16[qt]), oacc[dt][q0 + qt], 0, 0, 0);
         }
     };
     if (b < b1) {
-        load_block(b, kc, vc);
+        load_block(vbase, b, vc);
         for (; b + NW < b1; b += NW) {
             u32x4 kn[8], vn[8];
-            load_block(b + NW, kn, vn);
+            load_block(kbase, b + NW, kn);
+            load_block(vbase, b + NW, vn);
             process(b);
 #pragma unroll
             for (int i = 0; i < 8; ++i) { kc[i] = kn[i]; vc[i] = vn[i]; }
@@ -293,7 +324,7 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
     }
     __syncthreads();
     // wave w merges the output tiles dt = w, w + NW, ...; wave 0 also the (max, sum) pairs
-    const long long pbase = ((long long)h * p.nsplit + split) * NQT;
+    const long long pbase = (((long long)blockIdx.z * p.Hkv + h) * p.nsplit + split) * NQT;
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
         float mstar = -__builtin_inff();
@@ -317,7 +348,7 @@ __global__ __launch_bounds__(NW * 64) void verify_attention_kernel(const AttnPar
     }
 }
 
-// Combine the splits: one workgroup of 512 threads per (kv head, query tile, 16-d output tile); the 8 waves share the
+// Combine the splits: one workgroup of 512 threads per (kv head, query tile, 16-d output tile) and row group; the 8 waves share the
 // splits (wave g takes splits g, g + 8, ...), four of them requested at a time, statistics and outputs together: the only
 // wait of the kernel is one round trip to memory (a pass for the maximum ahead of the outputs cost a second one: 4.6 us a
 // launch, now 3.3).  A wave keeps its outputs against its own maximum; they meet once in LDS and are added in wave order.
@@ -328,7 +359,7 @@ __global__ __launch_bounds__(512) void attention_merge_kernel(const AttnParams p
     const int dt = blockIdx.x & 7, qt = (blockIdx.x >> 3) % NQT, h = (blockIdx.x >> 3) / NQT;
     const int sg = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g4 = lane >> 4, col = lane & 15;
-    const int r = p.row0 + 16 * qt + col;
+    const int r = p.row0 + 16 * (NQT * (int)blockIdx.y + qt) + col;
     float mw = -__builtin_inff(), lsum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = sg; s0 < p.nsplit; s0 += 32) {
@@ -336,7 +367,7 @@ __global__ __launch_bounds__(512) void attention_merge_kernel(const AttnParams p
         u32x2 ml[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const long long pb = ((long long)h * p.nsplit + min(s0 + 8 * i, p.nsplit - 1)) * NQT + qt;
+            const long long pb = (((long long)blockIdx.y * p.Hkv + h) * p.nsplit + min(s0 + 8 * i, p.nsplit - 1)) * NQT + qt;
             ml[i] = reinterpret_cast<const u32x2 *>(p.part_ml)[pb * 16 + col];
             o[i] = reinterpret_cast<const f32x4 *>(p.part_o)[(pb * 8 + dt) * 64 + lane];
         }

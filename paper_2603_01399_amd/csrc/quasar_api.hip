@@ -974,6 +974,16 @@ int launch_free(const GemmParams &p0, int M, Scratch &ws, hipStream_t stream) {
     return p0.resid ? launch_fused<EPI_LINEAR, PRE_NONE, true>(p0, M, stream) : launch_fused<EPI_LINEAR, PRE_NONE, false>(p0, M, stream);
 }
 
+constexpr int kAttnWaves = 4;
+template <int NQT, bool SHARED>
+int launch_attention(const AttnParams &p, int groups, hipStream_t stream) {
+    auto kern = verify_attention_kernel<NQT, kAttnWaves, SHARED>;
+    if (!allow_large_lds(reinterpret_cast<const void *>(kern))) return QUASAR_ERR_HIP;
+    const int lds = kAttnWaves * NQT * (8 * 64 * 16 + 16 * 2 * 4);
+    hipLaunchKernelGGL(kern, dim3((unsigned int)p.nsplit, (unsigned int)p.Hkv, (unsigned int)groups), dim3(kAttnWaves * 64), lds, stream, p);
+    return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
+}
+
 std::atomic<int> g_w4_nw{16};
 std::atomic<int> g_w4_d{2};
 
@@ -1824,20 +1834,24 @@ int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx
 /* ---- attention of a verification step ---- */
 
 namespace {
-constexpr int kAttnWaves = 4;
-struct AttnShape { int NQT, nblk, nsplit; };
+struct AttnShape {
+    int NQT, groups, nblk, nsplit;       // query tiles of a workgroup, groups of query rows, cache blocks, splits
+    size_t group_bytes;                  // partial sums of a row group
+};
 bool attn_shape(int64_t M, int64_t Hq, int64_t Hkv, int64_t L_total, AttnShape &a) {
     if (M < 1 || M > 32 || Hkv < 1 || Hkv > 1024 || Hq < Hkv || Hq % Hkv || Hq > 4096) return false;
     if (L_total < M || L_total > (1 << 24)) return false;
     const int64_t R = M * (Hq / Hkv);
     if (R > 1024) return false;
-    a.NQT = R <= 32 ? 2 : 4;                                       // rows per launch: 32 or 64
+    a.NQT = R >= 64 ? 4 : (int)((R + 15) / 16);
+    a.groups = (int)((R + 63) / 64);
     a.nblk = (int)((L_total + kKvBlock - 1) / kKvBlock);
-    int64_t cap = (int64_t)device_cus() / Hkv;                     // one workgroup per compute unit in total
+    int64_t cap = (int64_t)device_cus() / (Hkv * a.groups);        // one workgroup per compute unit in total
     if (cap < 1) cap = 1;
     int64_t ns = a.nblk / kAttnWaves;
     if (ns < 1) ns = 1;
     a.nsplit = (int)(ns < cap ? ns : cap);
+    a.group_bytes = (size_t)Hkv * a.nsplit * a.NQT * (8 * 64 * 16 + 16 * 2 * 4);
     return true;
 }
 int64_t cache_blocks(int64_t max_len) { return (max_len + kKvBlock - 1) / kKvBlock; }
@@ -1885,7 +1899,7 @@ int quasar_attn_prepare(const uint16_t *qkv, int64_t M, int64_t ld, int64_t n_q_
 size_t quasar_attention_workspace_bytes(int64_t M, int64_t n_q_heads, int64_t n_kv_heads, int64_t L_total) {
     AttnShape a{};
     if (!attn_shape(M, n_q_heads, n_kv_heads, L_total, a)) return 0;
-    return (size_t)n_kv_heads * a.nsplit * a.NQT * (8 * 64 * 16 + 16 * 2 * 4);
+    return a.groups * a.group_bytes;
 }
 
 int quasar_verify_attention(const uint16_t *q, int64_t M, int64_t ldq, int64_t n_q_heads, int64_t n_kv_heads,
@@ -1897,8 +1911,7 @@ int quasar_verify_attention(const uint16_t *q, int64_t M, int64_t ldq, int64_t n
     if (!quasar_kv_cache_bytes(n_kv_heads, max_len) || L_total > max_len) return QUASAR_ERR_SHAPE;
     if (ldq < n_q_heads * kHeadDim || ldo < n_q_heads * kHeadDim || ldq % 8 || ldo % 4) return QUASAR_ERR_SHAPE;
     if (!aligned(q, 16) || !aligned(out, 8) || !aligned(kv_cache, 16)) return QUASAR_ERR_ALIGN;
-    if (!workspace || workspace_bytes < quasar_attention_workspace_bytes(M, n_q_heads, n_kv_heads, L_total))
-        return QUASAR_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < a.group_bytes) return QUASAR_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return QUASAR_ERR_ALIGN;
     AttnParams p{};
     const long long head_stride = (long long)cache_blocks(max_len) * kKvBlockBytes;
@@ -1908,27 +1921,24 @@ int quasar_verify_attention(const uint16_t *q, int64_t M, int64_t ldq, int64_t n
     p.head_stride = head_stride;
     p.out = out; p.ldo = ldo;
     p.part_o = static_cast<float *>(workspace);
-    p.part_ml = p.part_o + (size_t)n_kv_heads * a.nsplit * a.NQT * 8 * 64 * 4;
     p.M = (int)M; p.G = (int)(n_q_heads / n_kv_heads); p.Hkv = (int)n_kv_heads;
     p.L_total = (int)L_total; p.nblk = a.nblk; p.nsplit = a.nsplit;
     p.scale_log2 = 1.4426950408889634f / 11.313708498984761f;      // log2(e) / sqrt(128)
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const int lds = kAttnWaves * a.NQT * (8 * 64 * 16 + 16 * 2 * 4);
-    const dim3 grid((unsigned int)a.nsplit, (unsigned int)n_kv_heads);
-    const int R = (int)(M * (n_q_heads / n_kv_heads));
-    for (int row0 = 0; row0 < R; row0 += 16 * a.NQT) {             // 64 query rows per pass over the cache
-        p.row0 = row0;
-        if (a.NQT == 2) {
-            auto kern = verify_attention_kernel<2, kAttnWaves>;
-            if (!allow_large_lds(reinterpret_cast<const void *>(kern))) return QUASAR_ERR_HIP;
-            hipLaunchKernelGGL(kern, grid, dim3(kAttnWaves * 64), lds, st, p);
-        } else {
-            auto kern = verify_attention_kernel<4, kAttnWaves>;
-            if (!allow_large_lds(reinterpret_cast<const void *>(kern))) return QUASAR_ERR_HIP;
-            hipLaunchKernelGGL(kern, grid, dim3(kAttnWaves * 64), lds, st, p);
-        }
-        if (hipGetLastError() != hipSuccess) return QUASAR_ERR_HIP;
-        hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned int)(n_kv_heads * a.NQT * 8)), dim3(512), 0, st, p, a.NQT);
+    // (a workspace that does not hold all row groups: as many at a time as it does)
+    const size_t fit = workspace_bytes / a.group_bytes;
+    const int at_once = fit < (size_t)a.groups ? (int)fit : a.groups;
+    p.part_ml = p.part_o + (size_t)at_once * n_kv_heads * a.nsplit * a.NQT * 8 * 64 * 4;
+    for (int z0 = 0; z0 < a.groups; z0 += at_once) {
+        const int nz = a.groups - z0 < at_once ? a.groups - z0 : at_once;
+        p.row0 = 64 * z0;
+        const int rc = nz > 1          ? launch_attention<4, true>(p, nz, st)
+                       : a.NQT == 1    ? launch_attention<1, false>(p, 1, st)
+                       : a.NQT == 2    ? launch_attention<2, false>(p, 1, st)
+                       : a.NQT == 3    ? launch_attention<3, false>(p, 1, st)
+                                       : launch_attention<4, false>(p, 1, st);
+        if (rc != QUASAR_OK) return rc;
+        hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned int)(n_kv_heads * a.NQT * 8), (unsigned int)nz), dim3(512), 0, st, p, a.NQT);
         if (hipGetLastError() != hipSuccess) return QUASAR_ERR_HIP;
     }
     return QUASAR_OK;

@@ -172,3 +172,36 @@ def test_attention_argument_errors(qb):
     big = torch.zeros((33, 32 * 128), dtype=torch.bfloat16, device="cuda")
     with pytest.raises(qb.QuasarError):
         qb.verify_attention(big, 32, cache, 64)                              # M > 32
+
+
+@pytest.mark.parametrize("M,Hq,Hkv,Lt", [(1, 8, 8, 33), (4, 16, 4, 1000), (5, 16, 4, 4100), (6, 32, 4, 700), (12, 8, 2, 2049), (17, 16, 4, 5000),
+                                         (32, 16, 4, 300), (32, 8, 1, 4500), (31, 32, 2, 64)])
+def test_row_groups_and_workspace(qb, M, Hq, Hkv, Lt):
+    """One to four query tiles a workgroup and up to eight groups of rows in one launch: outputs against a 64-bit softmax over
+    the same cache; a workspace that holds one group (the groups then run one after the other) gives the same bits, a smaller one
+    is refused, and none is written beyond its end."""
+    say("attention row groups", M, Hq, Hkv, Lt)
+    gen = torch.Generator(device="cuda").manual_seed(M * 1000 + Lt)
+    q = (torch.randn(M, Hq * D, generator=gen, device="cuda") * 1.5).bfloat16()
+    k, v = (torch.randn(Lt, Hkv, D, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    cache = qb.KvCache(Hkv, Lt)
+    cache.buf.fill_(0xFF)                                          # NaN wherever nothing is written
+    cache.fill(k, v)
+    need = qb.lib().quasar_attention_workspace_bytes(M, Hq, Hkv, Lt)
+    groups = -(-M * (Hq // Hkv) // 64)
+    assert need % groups == 0
+    G, outs = Hq // Hkv, []
+    for room in (need, need // groups):
+        ws = torch.full((room + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        outs.append(qb.verify_attention(q, Hq, cache, Lt, workspace=ws[:room]).clone())
+        assert bool((ws[room:] == 0xA5).all())
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    with pytest.raises(qb.QuasarError):
+        qb.verify_attention(q, Hq, cache, Lt, workspace=ws[:need // groups - 16])
+    qd = q.double().view(M, Hkv, G, D)
+    hidden = torch.arange(Lt, device="cuda")[None] > torch.arange(Lt - M, Lt, device="cuda")[:, None]
+    for h in range(Hkv):
+        s = (qd[:, h].reshape(M * G, D) @ k[:, h].double().t().contiguous() / D ** 0.5).view(M, G, Lt).masked_fill(hidden[:, None], float("-inf"))
+        want = (torch.softmax(s, -1).view(M * G, Lt) @ v[:, h].double()).view(M, G, D)
+        got = outs[0].view(M, Hkv, G, D)[:, h].double()
+        assert float((got - want).abs().max() / want.abs().max()) <= 8e-3        # bf16 weights and output, as for the oracle above
