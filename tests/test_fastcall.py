@@ -1,0 +1,66 @@
+"""The linears' native marshalling: only calls of plain CUDA tensors are taken, every other one is left to the Python path, which
+raises as it did (CPU), and the ordinary calls give the same bits and the same errors (GPU)."""
+import pytest
+import torch
+
+
+@pytest.fixture(scope="module")
+def qb():
+    from paper_2603_01399_amd import binding
+    return binding
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def test_what_is_not_an_ordinary_call(qb):
+    f = qb._fast
+    x, w, s, y = torch.zeros(2, 128).bfloat16(), torch.zeros(4096, dtype=torch.int8), torch.zeros(16).bfloat16(), torch.zeros(2, 16).bfloat16()
+    assert f.w8_linear(x, w, s, 16, y, None) == -1                               # not on a GPU
+    assert f.w8_linear(x, w, s, 16, y) == -1 and f.w4_linear() == -1             # arguments missing
+    assert f.w8_linear(None, w, s, 16, y, None) == -1
+    assert f.w8_linear(x.as_subclass(_Sub), w, s, 16, y, None) == -1
+    assert f.bf16_linear(x, s, 2 ** 80, y, None) == -1 and f.bf16_linear(x, s, 16.0, y, None) == -1
+    assert f.w8a8_linear(x, w, s, 16, None, y) == -1 and f.w4_linear(x, w, 16, y) == -1
+    with pytest.raises(TypeError):
+        qb.w8_linear(x, w, s, 16, y=y)                                           # what the Python path says of it
+    with pytest.raises(TypeError):
+        qb.w4_linear(x, w, 16, y=y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["int8", "bf16", "w8a8", "smoothed", "int4"])
+def test_ordinary_calls(qb, kind):
+    M, N, K = 5, 48, 256
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(M, K + 8, generator=gen, device="cuda").bfloat16()[:, :K]
+    w = torch.randn(N, K, generator=gen, device="cuda") * 0.02
+    smooth = torch.rand(K, generator=gen, device="cuda") + 0.5
+    wq, sc = qb.quantize_weights(w)
+    packed = {"bf16": qb.pack_bf16_weights(w), "int4": qb.quantize_weights_w4(w)}.get(kind, wq)
+    calls = {"int8": lambda x, N, y: qb.w8_linear(x, wq, sc, N, y=y), "bf16": lambda x, N, y: qb.bf16_linear(x, packed, N, y=y),
+             "w8a8": lambda x, N, y: qb.w8a8_linear(x, wq, sc, N, y=y), "smoothed": lambda x, N, y: qb.w8a8_linear(x, wq, sc, N, smooth=smooth, y=y),
+             "int4": lambda x, N, y: qb.w4_linear(x, packed, N, y=y)}
+    call = calls[kind]
+    want = call(x, N, None)                                                      # without an output: the Python path
+    y = torch.full((M, N + 16), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = y[:, :N]
+    assert call(x, N, out) is out and torch.equal(out.view(torch.int16), want.view(torch.int16)) and bool((y[:, N:] == 7.0).all())
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):                                                # torch's current stream is the one that is used
+        y2 = torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")
+        call(x, N, y2)
+        got = y2.clone()
+    side.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    for bad in (lambda: call(x, N + 8, out), lambda: call(x[:, 8:K // 2 + 8 - 4], N, out), lambda: call(x[:, 1:129], N, out),
+                lambda: call(x[0], N, out), lambda: call(x.float(), N, out), lambda: call(x.cpu(), N, out)):
+        with pytest.raises((qb.QuasarError, TypeError, ValueError)):
+            bad()
+    param = torch.nn.Parameter(x.contiguous(), requires_grad=False)
+    assert torch.equal(call(param, N, out.contiguous()).view(torch.int16), want.view(torch.int16))
+    meta = torch.empty(M, K, dtype=torch.bfloat16, device="meta")
+    with pytest.raises(TypeError):
+        call(meta, N, out)
