@@ -52,15 +52,51 @@ __device__ __forceinline__ u32x4 rotate_half_row(const u32x4 v) {
 }
 
 
+// A wave's range of K, `cnt` slots from `first` on, of MP token rows into its LDS region, in whole cache lines and as many of them in
+// a row as a power of two allows: with one line of each of eight rows an instruction's lines, some KB apart, meet in one cache
+// channel (4096 x 4096 at M = 8 6.5 -> 5.8 us, 1024 x 4096 5.1 -> 4.7, at M = 16 4096 x 12288 15.6 -> 14.7).  The addresses take one
+// multiplication a wave and four additions a load (a division a load, for row segments as long as the range, cost 4096 x 6144
+// 0.2 us).  Piece c of slot i of row t lies at piece c ^ (t & 7) of its slot: the lanes that read one column of pieces meet
+// different banks.  Slots beyond `last` repeat it.
+template <int SLOT>
+constexpr int fetch_segment(int cnt) {               // slots of a row that an instruction takes
+    int seg = 1;
+    while (cnt % (2 * seg) == 0 && 2 * seg * SLOT <= 1024) seg *= 2;
+    return seg;
+}
+template <int MP, int SLOT>
+__device__ __forceinline__ void fetch_rows(const uint16_t *x, long long ldx, int M, int first, int last, int cnt, unsigned int lds_base, int lane) {
+    constexpr int PS = SLOT / 16;
+    const int seg = fetch_segment<SLOT>(cnt), rows = 64 / (PS * seg);
+    const unsigned long long xa = reinterpret_cast<unsigned long long>(x);
+    const unsigned int ld2 = (unsigned int)(2 * ldx), end = (unsigned int)(M - 1) * ld2;
+    const int t0 = lane / (PS * seg), sl = (lane / PS) % seg;
+    const unsigned int row0 = (unsigned int)t0 * ld2, c16 = (unsigned int)(((lane % PS) ^ t0) * 16);
+#pragma unroll
+    for (int i = 0; i < cnt / seg; ++i) {
+        const unsigned int slot = (unsigned int)(min(first + i * seg + sl, last) * SLOT);
+#pragma unroll
+        for (int j = 0; j < MP / rows; ++j)
+            load_to_lds_16(xa, min(row0 + (unsigned int)(j * rows) * ld2, end) + slot + (c16 ^ (unsigned int)(((j * rows) & 7) * 16)),
+                           lds_base + 1024 * (i * (MP / rows) + j));
+    }
+}
+// where piece c of slot i of row t lies, in bytes
+template <int MP, int SLOT>
+__device__ __forceinline__ int row_piece(int t, int i, int c, int cnt) {
+    const int seg = fetch_segment<SLOT>(cnt), rows = 1024 / (SLOT * seg);
+    return 1024 * ((i / seg) * (MP / rows) + t / rows) + ((t % rows) * seg + i % seg) * SLOT + ((c ^ (t & 7)) * 16);
+}
+
 // Waves of a workgroup by form (XS slots of 64 k per wave): where the activations take more than about half of a wave's
 // 128 registers, eight waves of 256 - the ring, the accumulators and the addresses are then paid for half as often.
 constexpr int direct_waves(int MP, int XS) { return MP == 32 || (MP == 16 && XS > 8) ? 8 : 16; }
 
-// Slots of activations that pass through a wave's LDS region at a time (0: straight into registers).  Up to 64 KB of x a
+// Slots of activations that pass through a wave's LDS region at a time (0: straight into registers).  Up to 48 KB of x a
 // workgroup the gather of 16-byte pieces is as fast; beyond that the direct-to-LDS path, whose instructions read whole
-// cache lines, is: 6.0 -> 5.5 us for 4096 x 3072 at M = 16, 7.6 -> 7.1 for 4096 x 6144 at M = 8.  128 KB a workgroup at most.
+// cache lines (fetch_rows), is.  128 KB a workgroup at most.
 constexpr int direct_pass(int MP, int XS) {
-    if (MP == 8 && XS <= 4) return 0;
+    if (MP == 8 && XS <= 3) return 0;
     const int fit = 1024 / (direct_waves(MP, XS) * MP);
     return XS < fit ? XS : fit;
 }
@@ -79,7 +115,7 @@ constexpr int direct_pair_bytes(int XS, int C, bool w16) {
 // The same for the 4-bit kernel (slots of 128 k): its waves, the slots that pass through LDS at a time, the regions.
 constexpr int w4_waves(int MP, int XS) { return MP == 32 || (MP == 16 && XS > 4) ? 8 : 16; }
 constexpr int w4_pass(int MP, int XS) {
-    if (MP == 8 && XS <= 2) return 0;
+    if (MP == 8 && XS <= 1) return 0;
     const int fit = 512 / (w4_waves(MP, XS) * MP);
     return XS < fit ? XS : fit;
 }
@@ -92,7 +128,7 @@ constexpr int w4_region_bytes(int MP, int XS) {
 // they are read again), the slots that pass through LDS at a time on their way there, the regions.
 constexpr bool a8_hold(int MP, int XS) { return XS * MP <= (MP == 8 ? 96 : 80) && MP != 32; }
 constexpr int a8_pass(int MP, int XS) {
-    if (!a8_hold(MP, XS) || (MP == 8 && XS <= 4)) return 0;
+    if (!a8_hold(MP, XS) || (MP == 8 && XS <= 3)) return 0;
     return XS <= (MP == 8 ? 6 : 4) ? XS : (XS + 1) / 2;
 }
 constexpr int a8_region_bytes(int MP, int XS) {

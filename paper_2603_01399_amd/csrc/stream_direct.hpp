@@ -13,7 +13,7 @@
 // What bounds it: a launch whose compute units read nothing but the 16 MB of a 4096 x 4096 matrix takes 3.9 us back to
 // back (48 MB: 8.6 us); the rest is the fetch of x (as many bytes per compute unit as its weights at M = 8) and the
 // tile end.  Back to back, HBM-cold, int8, us a launch, staged kernel -> this one:
-//     M = 8:  1024 x 1024 5.1 -> 3.5, 4096 x 4096 7.2 -> 5.7, 12288 x 4096 11.7 -> 10.6, 4096 x 12288 13.9 -> 11.5
+//     M = 8:  1024 x 1024 5.1 -> 3.5, 4096 x 4096 7.2 -> 5.2, 12288 x 4096 11.7 -> 10.2, 4096 x 12288 13.9 -> 11.5
 //     M = 16: 4096 x 4096 9.4 -> 6.5, 12288 x 4096 14.8 -> 11.3, 4096 x 8192 14.3 -> 9.9
 //     M = 32: 4096 x 4096 13.0 -> 7.9, 12288 x 4096 22.9 -> 12.6
 // Fetching x: straight into the registers, or, for more of it, in whole cache lines through the wave's own piece of LDS
@@ -79,7 +79,8 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     const int C = PAIR ? CC : (CH ? p.C : 1);
 
     // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
-    constexpr int kPass = KS == 32 && CC > 1 ? 0 : direct_pass(MP, XS);
+    // (bf16 weights keep the gather at four slots: seven linears of an 8B layer, 5 tokens, 79.4 us, 79.9 through LDS)
+    constexpr int kPass = (KS == 32 && CC > 1) || (W16 && MP == 8 && XS == 4) ? 0 : direct_pass(MP, XS);
     static_assert(KS == 64 || CC > 1 || XS / 2 + 1 <= kPass, "slots of 32 k come in one pass of whole lines");
     const int region = max(kPass * MP * 128, PARS * C * NB * 1024);
     unsigned char *own = lds + w * region;
@@ -146,9 +147,14 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     };
     // through LDS: slots at .. at + kPass - 1, each instruction 128 bytes of eight tokens' rows, piece c of token t at
     // position c ^ (t & 7) of its 128 bytes (the lanes that read one column of pieces meet different banks)
+    constexpr bool RANGE = CH == 0 && KS == 64;      // the wave's slots are one range of K: fetch_rows
     [[maybe_unused]] auto fetch_x = [&](int at) {
         const unsigned int base = lds_address_of(lds) + (unsigned int)(w * region);
         const unsigned long long xa = reinterpret_cast<unsigned long long>(p.x);
+        if constexpr (RANGE) {
+            fetch_rows<MP, 128>(p.x, p.ldx, p.M, first + at, p.S - 1, min(kPass, XS - at), base, lane);
+            return;
+        }
 #pragma unroll
         for (int t8 = 0; t8 < MP / 8; ++t8) {
             const int t = (lane >> 3) + 8 * t8;
@@ -183,8 +189,9 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                     for (int q = 0; q < XP; ++q) {
                         const int t = tok + 16 * nb, half = MP == 8 ? mcol >> 3 : q;
                         const int c = W16 ? 4 * half + g : 2 * g + half;
-                        xr[at + i][nb * XP + q] = *reinterpret_cast<const u32x4 *>(
-                            own + (i * (MP / 8) + (t >> 3)) * 1024 + (t & 7) * 128 + ((c ^ (t & 7)) * 16));
+                        const int where = RANGE ? row_piece<MP, 128>(t, i, c, min(kPass, XS - at))
+                                                : (i * (MP / 8) + (t >> 3)) * 1024 + (t & 7) * 128 + ((c ^ (t & 7)) * 16);
+                        xr[at + i][nb * XP + q] = *reinterpret_cast<const u32x4 *>(own + where);
                     }
     };
     if constexpr (kPass > 0) {

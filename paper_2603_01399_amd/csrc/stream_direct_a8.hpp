@@ -63,9 +63,10 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
 
     const int first = (p.S * w) / NW;
     const int n = (p.S * (w + 1)) / NW - first;
+    const int last = n > 0 ? first + n - 1 : first;     // (slots beyond the share repeat its last step)
     int step[XS];
 #pragma unroll
-    for (int i = 0; i < XS; ++i) step[i] = i < n ? first + i : min(first, p.S - 1);
+    for (int i = 0; i < XS; ++i) step[i] = min(first + i, last);
 
     // ---- requests: smoothing factors (each wave's own, into LDS), activations, row scales, weight ring
     if constexpr (SMOOTH) {
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
 #pragma unroll
         for (int j = 0; j < (XS + 3) / 4; ++j) {
             const int i = 4 * j + (lane >> 4);
-            const int st = i < n ? first + i : min(first, p.S - 1);
+            const int st = min(first + i, last);
             if (4 * j + 3 < XS || i < XS)
                 load_to_lds_16(reinterpret_cast<unsigned long long>(p.smooth), (unsigned int)st * 256u + 16u * (lane & 15), base + 1024 * j);
         }
@@ -88,17 +89,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     static_assert(HOLD || kPass == 0, "activations that are read twice come straight from memory");
     // through LDS in whole cache lines, as in stream_direct.hpp
     [[maybe_unused]] auto fetch_x = [&](int at) {
-        const unsigned int base = lds_address_of(lds) + (unsigned int)(w * region);
-#pragma unroll
-        for (int t8 = 0; t8 < MP / 8; ++t8) {
-            const int t = (lane >> 3) + 8 * t8;
-            const unsigned int off = (unsigned int)min(t, p.M - 1) * (unsigned int)(2 * p.ldx) + (unsigned int)(((lane & 7) ^ (t & 7)) * 16);
-#pragma unroll
-            for (int i = 0; i < kPass; ++i)
-                if (at + i < XS)
-                    load_to_lds_16(reinterpret_cast<unsigned long long>(p.x) + 128ull * (unsigned int)step[at + i], off,
-                                   base + (i * (MP / 8) + t8) * 1024);
-        }
+        fetch_rows<MP, 128>(p.x, p.ldx, p.M, first + at, last, min(kPass, XS - at), lds_address_of(lds) + (unsigned int)(w * region), lane);
     };
     [[maybe_unused]] auto read_x = [&](int at) {
 #pragma unroll
@@ -107,8 +98,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
 #pragma unroll
                 for (int j = 0; j < NB * XP; ++j) {
                     const int t = tok + 16 * (j / XP), c = 2 * g + half8 + j % XP;
-                    raw[HOLD ? at + i : 0][j] =
-                        *reinterpret_cast<const u32x4 *>(own + (i * (MP / 8) + (t >> 3)) * 1024 + (t & 7) * 128 + ((c ^ (t & 7)) * 16));
+                    raw[HOLD ? at + i : 0][j] = *reinterpret_cast<const u32x4 *>(own + row_piece<MP, 128>(t, i, c, min(kPass, XS - at)));
                 }
     };
     if constexpr (kPass > 0) fetch_x(0);
@@ -178,7 +168,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
             else v = load_x(i, j);
             smoothed(v, i, j, xt);
             const float a = piece_amax(xt);
-            amax[j / XP] = fmaxf(amax[j / XP], a);      // (slots beyond the share repeat its first step)
+            amax[j / XP] = fmaxf(amax[j / XP], a);      // (slots beyond the share repeat its last step)
             if (!HOLD && (i * NB * XP + j) % 8 == 7) __builtin_amdgcn_sched_barrier(0);     // (bounds the registers of the pass)
         }
 #pragma unroll

@@ -52,19 +52,9 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
     const int tok = (MP == 8) ? (mcol & 7) : mcol;
     const int half = (MP == 8) ? (mcol >> 3) : 0;
     u32x4 xr[XS][NB * XP];
-    // through LDS in whole cache lines: an instruction fetches 256 bytes (a slot) of four tokens, 16-byte piece c of token t at
-    // position c ^ (t & 7) of its 256 bytes
+    // through LDS in whole cache lines, as in stream_direct.hpp
     auto fetch_x = [&](int at) {
-        const unsigned int base = lds_address_of(lds) + (unsigned int)(w * region);
-        const unsigned long long xa = reinterpret_cast<unsigned long long>(p.x);
-#pragma unroll
-        for (int t4 = 0; t4 < MP / 4; ++t4) {
-            const int t = (lane >> 4) + 4 * t4;
-            const unsigned int off = (unsigned int)min(t, p.M - 1) * (unsigned int)(2 * p.ldx) + (unsigned int)(((lane & 15) ^ (t & 7)) * 16);
-#pragma unroll
-            for (int i = 0; i < kPass; ++i)
-                if (at + i < XS) load_to_lds_16(xa + 256ull * (unsigned int)step[at + i], off, base + (i * (MP / 4) + t4) * 1024);
-        }
+        fetch_rows<MP, 256>(p.x, p.ldx, p.M, first + at, p.S - 1, min(kPass, XS - at), lds_address_of(lds) + (unsigned int)(w * region), lane);
     };
     auto read_x = [&](int at) {
 #pragma unroll
@@ -76,7 +66,7 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
                     for (int j = 0; j < XP; ++j) {
                         const int t = tok + 16 * nb;
                         const int c = MP == 8 ? 4 * (2 * j + half) + g : 4 * j + g;
-                        xr[at + i][nb * XP + j] = *reinterpret_cast<const u32x4 *>(own + (i * MP + t) * 256 + ((c ^ (t & 7)) * 16));
+                        xr[at + i][nb * XP + j] = *reinterpret_cast<const u32x4 *>(own + row_piece<MP, 256>(t, i, c, min(kPass, XS - at)));
                     }
     };
     if constexpr (kPass > 0) {
