@@ -298,15 +298,20 @@ int quasar_quantize_activations(const uint16_t *x, int64_t M, int64_t K, int64_t
 
 /* W8A8 linear layer: activation smoothing + quantisation, int8 x int8 matrix-core
  * contraction with int32 sums, dequantisation by (delta_w . delta_x) (Eq. 10).
- * Arguments as quasar_w8_linear plus `smooth`.  The workspace may be NULL.  Where M x K is large a workspace of
- * quasar_w8a8_workspace_bytes (0: none is used for this shape) lets the activations be quantised once, by a launch
- * of their own, instead of in every workgroup; the sums are integers, so no bit depends on it.  It is scratch:
- * undefined on entry and on exit. */
-size_t quasar_w8a8_workspace_bytes(int64_t M, int64_t N, int64_t K);
+ * Arguments as quasar_w8_linear plus `smooth`; workspace unused (may be NULL). */
 int quasar_w8a8_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const float *smooth,
                        const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N,
                        uint16_t *y, int64_t ldy,
                        void *workspace, size_t workspace_bytes, void *hip_stream);
+
+/* quasar_w8a8_linear that uses its workspace (may be NULL).  Where M x K is large, one of quasar_w8a8_workspace_bytes (0: none
+ * is used for this shape) lets the activations be quantised once, by a launch of their own, instead of in every workgroup;
+ * the sums are integers, so no bit depends on it.  It is scratch: undefined on entry and on exit. */
+size_t quasar_w8a8_workspace_bytes(int64_t M, int64_t N, int64_t K);
+int quasar_w8a8_linear_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const float *smooth,
+                             const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N,
+                             uint16_t *y, int64_t ldy,
+                             void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* W8A8 vocabulary projection fused with the acceptance decision (Eq. 10 logits kept in
  * fp32, then Eq. 2 at temperature 0 as in quasar_lmhead_verify).  Arguments as

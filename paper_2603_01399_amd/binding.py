@@ -28,7 +28,7 @@ EXPORTS = (
     "quasar_read_stream", "quasar_copy_stream",
     "quasar_sequence_plan_bytes", "quasar_sequence_workspace_bytes", "quasar_sequence_prepare",
     "quasar_sequence_run",
-    "quasar_quantize_weights_smoothed", "quasar_quantize_activations", "quasar_w8a8_linear", "quasar_w8a8_workspace_bytes",
+    "quasar_quantize_weights_smoothed", "quasar_quantize_activations", "quasar_w8a8_linear", "quasar_w8a8_workspace_bytes", "quasar_w8a8_linear_split",
     "quasar_w8a8_lmhead_verify", "quasar_sequence_prepare_w8a8",
     "quasar_sample_workspace_bytes", "quasar_lmhead_verify_sample",
     "quasar_w4_packed_bytes", "quasar_quantize_weights_w4", "quasar_unpack_weights_w4", "quasar_w4_linear",
@@ -144,6 +144,7 @@ def _load() -> ctypes.CDLL:
     lib.quasar_quantize_activations.argtypes = [vp, i64, i64, i64, vp, vp, vp, vp]
     lib.quasar_w8a8_workspace_bytes.argtypes = [i64, i64, i64]
     lib.quasar_w8a8_workspace_bytes.restype = sz
+    lib.quasar_w8a8_linear_split.argtypes = [vp, i64, i64, i64, vp, vp, vp, i64, vp, i64, vp, sz, vp]
     lib.quasar_w8a8_linear.argtypes = [vp, i64, i64, i64, vp, vp, vp, i64, vp, i64, vp, sz, vp]
     lib.quasar_w8a8_lmhead_verify.argtypes = [vp, i64, i64, i64, vp, vp, vp, i64, vp, i64, vp, vp, vp, sz, vp]
     return lib
@@ -312,8 +313,8 @@ def w8a8_linear(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, 
     need = _lib.quasar_w8a8_workspace_bytes(M, N, K) if M > 16 or K > (8192 if M <= 8 else 5120) else 0
     ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
     _check("quasar_w8a8_linear",
-           _lib.quasar_w8a8_linear(_ptr(x), M, K, x.stride(0), _smooth_arg(smooth, K), _ptr(wq_packed), _ptr(scales),
-                                   N, _ptr(y), y.stride(0), _ptr(ws), need, _stream()))
+           _lib.quasar_w8a8_linear_split(_ptr(x), M, K, x.stride(0), _smooth_arg(smooth, K), _ptr(wq_packed), _ptr(scales),
+                                         N, _ptr(y), y.stride(0), _ptr(ws), need, _stream()))
     return y
 
 

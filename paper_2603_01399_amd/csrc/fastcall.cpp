@@ -92,6 +92,15 @@ void *current_stream() {
     return s;
 }
 
+// The launch runs without the interpreter's lock, as under ctypes.
+template <typename Entry, typename... Args>
+int call(Entry entry, Args... args) {
+    PyThreadState *state = PyEval_SaveThread();
+    const int status = entry(args...);
+    PyEval_RestoreThread(state);
+    return status;
+}
+
 // Calls body(); whatever keeps it from an ordinary call - a tensor without storage among them, for which torch throws - is left
 // to binding.py.
 template <typename Body>
@@ -112,7 +121,7 @@ PyObject *w8_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const void *w = cuda_tensor(a[1], at::kChar).data_ptr(), *sc = cuda_tensor(a[2], at::kBFloat16).data_ptr();
         const Output y(a[4]);
         const Workspace ws(a[5]);
-        return p_w8_linear(x.x, x.M, x.K, x.ldx, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc), integer(a[3]), y.y,
+        return call(p_w8_linear, x.x, x.M, x.K, x.ldx, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc), integer(a[3]), y.y,
                            y.ldy, ws.p, ws.bytes, current_stream());
     });
 }
@@ -124,7 +133,7 @@ PyObject *bf16_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const void *w = cuda_tensor(a[1], at::kBFloat16).data_ptr();
         const Output y(a[3]);
         const Workspace ws(a[4]);
-        return p_bf16_linear(x.x, x.M, x.K, x.ldx, static_cast<const uint16_t *>(w), integer(a[2]), y.y, y.ldy, ws.p, ws.bytes,
+        return call(p_bf16_linear, x.x, x.M, x.K, x.ldx, static_cast<const uint16_t *>(w), integer(a[2]), y.y, y.ldy, ws.p, ws.bytes,
                              current_stream());
     });
 }
@@ -143,7 +152,7 @@ PyObject *w8a8_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
             smooth = static_cast<const float *>(s.data_ptr());
         }
         const Output y(a[5]);
-        return p_w8a8_linear(x.x, x.M, x.K, x.ldx, smooth, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc),
+        return call(p_w8a8_linear, x.x, x.M, x.K, x.ldx, smooth, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc),
                              N, y.y, y.ldy, nullptr, 0, current_stream());
     });
 }
@@ -156,7 +165,7 @@ PyObject *w4_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const int64_t N = integer(a[2]);
         if (w.numel() < (int64_t)p_w4_packed_bytes(N, x.K) || p_w4_workspace_bytes(x.M, N, x.K)) return -1;
         const Output y(a[3]);
-        return p_w4_linear(x.x, x.M, x.K, x.ldx, w.data_ptr(), N, y.y, y.ldy, current_stream());
+        return call(p_w4_linear, x.x, x.M, x.K, x.ldx, w.data_ptr(), N, y.y, y.ldy, current_stream());
     });
 }
 

@@ -1535,9 +1535,9 @@ size_t quasar_w8a8_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     return a8_code_bytes(MP, (int)(K / kStepK8)) + 128 + splitk_bytes((int)M, (int)N, d.ksplit);
 }
 
-int quasar_w8a8_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const float *smooth,
-                       const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, uint16_t *y, int64_t ldy,
-                       void *workspace, size_t workspace_bytes, void *hip_stream) {
+int quasar_w8a8_linear_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const float *smooth,
+                             const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, uint16_t *y, int64_t ldy,
+                             void *workspace, size_t workspace_bytes, void *hip_stream) {
     if (!x || !wq_packed || !scales_bf16 || !y) return QUASAR_ERR_NULL;
     if (const int e = check_mnk(M, N, K)) return e;
     if (ldx < K || ldy < N || ldx % 8 || ldy % 8) return QUASAR_ERR_SHAPE;
@@ -1565,6 +1565,13 @@ int quasar_w8a8_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, con
         return launch_splitk_finalize<FMT_A8>(p, d.ksplit, dx, st);
     }
     return launch_w8a8<EPI_LINEAR>(p, (int)M, static_cast<hipStream_t>(hip_stream), nullptr);
+}
+
+int quasar_w8a8_linear(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const float *smooth,
+                       const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, uint16_t *y, int64_t ldy,
+                       void *workspace, size_t workspace_bytes, void *hip_stream) {
+    (void)workspace; (void)workspace_bytes;
+    return quasar_w8a8_linear_split(x, M, K, ldx, smooth, wq_packed, scales_bf16, N, y, ldy, nullptr, 0, hip_stream);
 }
 
 int quasar_w8a8_lmhead_verify(const uint16_t *hidden, int64_t M, int64_t K, int64_t ldh, const float *smooth,
@@ -1837,6 +1844,7 @@ namespace {
 struct AttnShape {
     int NQT, groups, nblk, nsplit;       // query tiles of a workgroup, groups of query rows, cache blocks, splits
     size_t group_bytes;                  // partial sums of a row group
+    size_t least_bytes;                  // of a workspace: grows with M and L_total and holds a row group of any smaller call
 };
 bool attn_shape(int64_t M, int64_t Hq, int64_t Hkv, int64_t L_total, AttnShape &a) {
     if (M < 1 || M > 32 || Hkv < 1 || Hkv > 1024 || Hq < Hkv || Hq % Hkv || Hq > 4096) return false;
@@ -1852,6 +1860,8 @@ bool attn_shape(int64_t M, int64_t Hq, int64_t Hkv, int64_t L_total, AttnShape &
     if (ns < 1) ns = 1;
     a.nsplit = (int)(ns < cap ? ns : cap);
     a.group_bytes = (size_t)Hkv * a.nsplit * a.NQT * (8 * 64 * 16 + 16 * 2 * 4);
+    const int64_t all = (int64_t)device_cus() / Hkv, most = all < 1 ? 1 : all;
+    a.least_bytes = (size_t)Hkv * (size_t)(ns < most ? ns : most) * (R <= 32 ? 2 : 4) * (8 * 64 * 16 + 16 * 2 * 4);
     return true;
 }
 int64_t cache_blocks(int64_t max_len) { return (max_len + kKvBlock - 1) / kKvBlock; }
@@ -1899,7 +1909,7 @@ int quasar_attn_prepare(const uint16_t *qkv, int64_t M, int64_t ld, int64_t n_q_
 size_t quasar_attention_workspace_bytes(int64_t M, int64_t n_q_heads, int64_t n_kv_heads, int64_t L_total) {
     AttnShape a{};
     if (!attn_shape(M, n_q_heads, n_kv_heads, L_total, a)) return 0;
-    return a.groups * a.group_bytes;
+    return a.groups * a.group_bytes > a.least_bytes ? a.groups * a.group_bytes : a.least_bytes;
 }
 
 int quasar_verify_attention(const uint16_t *q, int64_t M, int64_t ldq, int64_t n_q_heads, int64_t n_kv_heads,
@@ -1911,7 +1921,7 @@ int quasar_verify_attention(const uint16_t *q, int64_t M, int64_t ldq, int64_t n
     if (!quasar_kv_cache_bytes(n_kv_heads, max_len) || L_total > max_len) return QUASAR_ERR_SHAPE;
     if (ldq < n_q_heads * kHeadDim || ldo < n_q_heads * kHeadDim || ldq % 8 || ldo % 4) return QUASAR_ERR_SHAPE;
     if (!aligned(q, 16) || !aligned(out, 8) || !aligned(kv_cache, 16)) return QUASAR_ERR_ALIGN;
-    if (!workspace || workspace_bytes < a.group_bytes) return QUASAR_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < a.least_bytes) return QUASAR_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return QUASAR_ERR_ALIGN;
     AttnParams p{};
     const long long head_stride = (long long)cache_blocks(max_len) * kKvBlockBytes;

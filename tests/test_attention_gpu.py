@@ -178,8 +178,8 @@ def test_attention_argument_errors(qb):
                                          (32, 16, 4, 300), (32, 8, 1, 4500), (31, 32, 2, 64)])
 def test_row_groups_and_workspace(qb, M, Hq, Hkv, Lt):
     """One to four query tiles a workgroup and up to eight groups of rows in one launch: outputs against a 64-bit softmax over
-    the same cache; a workspace that holds one group (the groups then run one after the other) gives the same bits, a smaller one
-    is refused, and none is written beyond its end."""
+    the same cache; the least workspace that is accepted (it may hold fewer groups, which then run one after the other) gives the
+    same bits, a smaller one is refused, and none is written beyond its end."""
     say("attention row groups", M, Hq, Hkv, Lt)
     gen = torch.Generator(device="cuda").manual_seed(M * 1000 + Lt)
     q = (torch.randn(M, Hq * D, generator=gen, device="cuda") * 1.5).bfloat16()
@@ -188,16 +188,17 @@ def test_row_groups_and_workspace(qb, M, Hq, Hkv, Lt):
     cache.buf.fill_(0xFF)                                          # NaN wherever nothing is written
     cache.fill(k, v)
     need = qb.lib().quasar_attention_workspace_bytes(M, Hq, Hkv, Lt)
-    groups = -(-M * (Hq // Hkv) // 64)
-    assert need % groups == 0
     G, outs = Hq // Hkv, []
-    for room in (need, need // groups):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    least = Hkv * min(max(-(-Lt // 32) // 4, 1), max(cus // Hkv, 1)) * (2 if M * G <= 32 else 4) * (8 * 64 * 16 + 16 * 2 * 4)
+    assert need >= least
+    for room in (need, least):
         ws = torch.full((room + 256,), 0xA5, dtype=torch.uint8, device="cuda")
         outs.append(qb.verify_attention(q, Hq, cache, Lt, workspace=ws[:room]).clone())
         assert bool((ws[room:] == 0xA5).all())
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
     with pytest.raises(qb.QuasarError):
-        qb.verify_attention(q, Hq, cache, Lt, workspace=ws[:need // groups - 16])
+        qb.verify_attention(q, Hq, cache, Lt, workspace=ws[:least - 16])
     qd = q.double().view(M, Hkv, G, D)
     hidden = torch.arange(Lt, device="cuda")[None] > torch.arange(Lt - M, Lt, device="cuda")[:, None]
     for h in range(Hkv):

@@ -52,8 +52,8 @@ def test_w8a8_apart(M, N, K, smoothed):
     for room in (need, head, head - 1):
         ws = torch.full((need + 256,), 0xA5, dtype=torch.uint8, device="cuda")
         y2 = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
-        qb._check("w8a8", qb.lib().quasar_w8a8_linear(x.data_ptr(), M, K, x.stride(0), None if smooth is None else smooth.data_ptr(),
-                                                      wq.data_ptr(), sc.data_ptr(), N, y2.data_ptr(), N, ws.data_ptr(), room, qb._stream()))
+        qb._check("w8a8", qb.lib().quasar_w8a8_linear_split(x.data_ptr(), M, K, x.stride(0), None if smooth is None else smooth.data_ptr(),
+                                                            wq.data_ptr(), sc.data_ptr(), N, y2.data_ptr(), N, ws.data_ptr(), room, qb._stream()))
         same = y2.view(torch.int16) == want.view(torch.int16)
         assert bool((same | (y2.isnan() & want.isnan())).all())
         assert bool((ws[room:] == 0xA5).all())
@@ -87,3 +87,34 @@ def test_w4_outer(M, N, K):
                                                         ws.data_ptr(), max(room, 0), qb._stream()))
         assert float((y2.double() - want).abs().max() / want.abs().max()) <= 4e-3
         assert bool((ws[max(room, 0):] == 0xA5).all())
+
+
+@pytest.mark.parametrize("kind", ["w8a8", "int4", "fused", "gated"])
+def test_scratch_routes_under_capture(kind):
+    """The routes that take scratch from torch's allocator, captured and replayed with new inputs and eager work in between."""
+    from paper_2603_01399_amd import binding as qb
+    M, N, K = 20, 16 * 40, 8192
+    print("capture", kind, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    w = torch.randn(N, K, generator=gen, device="cuda") * 0.02
+    wq, sc = qb.quantize_weights(w)
+    w4 = qb.quantize_weights_w4(w)
+    gamma = (1 + 0.2 * torch.randn(K, generator=gen, device="cuda")).bfloat16()
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    y = torch.empty((M, N // 2 if kind == "gated" else N), dtype=torch.bfloat16, device="cuda")
+    res = torch.randn(M, N, generator=gen, device="cuda").bfloat16()
+    call = {"w8a8": lambda y: qb.w8a8_linear(x, wq, sc, N, y=y), "int4": lambda y: qb.w4_linear(x, w4, N, y=y),
+            "fused": lambda y: qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, residual=res, y=y),
+            "gated": lambda y: qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, y=y)}[kind]
+    call(y)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(y)
+    for _ in range(4):
+        x.copy_(torch.randn(M, K, generator=gen, device="cuda"))
+        want = call(torch.empty_like(y))
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
