@@ -170,14 +170,15 @@ _current_raw_stream = torch._C._cuda_getCurrentRawStream
 _current_device = torch._C._cuda_getDevice
 
 # The ordinary call of a linear - plain tensors, an output given, no scratch of its own - is marshalled in native code
-# (csrc/fastcall.cpp): 6.1 -> 4.2 us of host time; it answers -1 for any other, which the functions below handle.
+# (csrc/fastcall.cpp): 6.1 -> 4.0 us of host time; it answers -1 for any other, which the functions below handle.
 if not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
     raise ImportError(f"{_HERE}/_fastcall.so is missing: build it with `python -m paper_2603_01399_amd.build`")
 from . import _fastcall as _fast  # noqa: E402
 
 _fast.bind(tuple(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value
                  for n in ("quasar_w8_linear", "quasar_bf16_linear", "quasar_w8a8_linear", "quasar_w4_linear", "quasar_w4_packed_bytes",
-                           "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes")),
+                           "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes", "quasar_w8_linear_fused", "quasar_w8_gateup_swiglu",
+                           "quasar_w8_fused_workspace_bytes")),
            _current_device, _current_raw_stream)
 
 
@@ -498,6 +499,11 @@ def _fused_scratch(x, M, N, K, gamma, residual):
 def w8_linear_fused(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, N: int, *, gamma: torch.Tensor = None,
                     eps: float = 1e-6, residual: torch.Tensor = None, y: torch.Tensor = None) -> torch.Tensor:
     """y = [residual +] W8([RMSNorm](x)); the normalisation (gamma, eps) and the residual are optional."""
+    if y is not None:
+        status = _fast.w8_linear_fused(x, wq_packed, scales, N, gamma, eps, residual, y)
+        if status >= 0:
+            _check("quasar_w8_linear_fused", status)
+            return y
     _dev(x, "x", torch.bfloat16)
     _dev(wq_packed, "wq_packed", torch.int8)
     _dev(scales, "scales", torch.bfloat16)
@@ -529,6 +535,11 @@ def interleave_gate_up(gate: torch.Tensor, up: torch.Tensor) -> torch.Tensor:
 def w8_gateup_swiglu(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, I: int, *, gamma: torch.Tensor = None,
                      eps: float = 1e-6, y: torch.Tensor = None) -> torch.Tensor:
     """y[M, I] = silu(gate) * up with both projections taken from the row-interleaved [2 I, K] int8 matrix."""
+    if y is not None:
+        status = _fast.w8_gateup_swiglu(x, wq_packed, scales, I, gamma, eps, y)
+        if status >= 0:
+            _check("quasar_w8_gateup_swiglu", status)
+            return y
     _dev(x, "x", torch.bfloat16)
     _dev(wq_packed, "wq_packed", torch.int8)
     _dev(scales, "scales", torch.bfloat16)

@@ -1,11 +1,11 @@
-// The linears' argument marshalling in native code: what binding.py does for an ordinary call - plain CUDA tensors, an output
+// The linears' and fused linears' argument marshalling in native code: what binding.py does for an ordinary call - plain CUDA tensors, an output
 // given, no scratch of the call's own - without its Python and ctypes steps.
 //
 // Every function returns the status of the C entry point it calls, or -1 for "not an ordinary call": binding.py then goes its
 // own way, which allocates what is missing and raises what is to be raised.  Nothing is kept from one call for the next.
 //
-// What it measured, one 1024 x 1024 linear of 8 tokens through the binding, us of host time: 6.1 -> 4.2, of which the launch
-// itself takes 2.9 (the kernel 3.4 on the GPU).
+// What it measured, one 1024 x 1024 linear of 8 tokens through the binding, us of host time: 6.1 -> 4.0, of which the launch
+// itself takes 2.9 (the kernel 3.4 on the GPU); a decoder block whose six calls are host-bound 40.9 -> 33.8.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -25,6 +25,9 @@ decltype(&quasar_w4_linear) p_w4_linear;
 decltype(&quasar_w4_packed_bytes) p_w4_packed_bytes;
 decltype(&quasar_w8a8_workspace_bytes) p_w8a8_workspace_bytes;
 decltype(&quasar_w4_workspace_bytes) p_w4_workspace_bytes;
+decltype(&quasar_w8_linear_fused) p_w8_linear_fused;
+decltype(&quasar_w8_gateup_swiglu) p_w8_gateup_swiglu;
+decltype(&quasar_w8_fused_workspace_bytes) p_w8_fused_workspace_bytes;
 PyObject *g_device, *g_stream;
 
 struct NotOrdinary {};
@@ -169,11 +172,62 @@ PyObject *w4_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
     });
 }
 
-// (addresses of the seven entry points, current device, current raw stream)
+struct Gamma {
+    const uint16_t *p = nullptr;
+    Gamma(PyObject *o, int64_t K) {
+        if (o == Py_None) return;
+        const at::Tensor &t = cuda_tensor(o, at::kBFloat16);
+        if (t.numel() != K || !t.is_contiguous()) throw NotOrdinary{};
+        p = static_cast<const uint16_t *>(t.data_ptr());
+    }
+};
+float real(PyObject *o) {
+    if (!PyFloat_CheckExact(o)) throw NotOrdinary{};
+    return static_cast<float>(PyFloat_AS_DOUBLE(o));
+}
+
+// (x, wq_packed, scales, N, gamma, eps, residual, y)
+PyObject *w8_linear_fused(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    return status_of(n, 8, [&] {
+        const Activations x(a[0]);
+        const void *w = cuda_tensor(a[1], at::kChar).data_ptr(), *sc = cuda_tensor(a[2], at::kBFloat16).data_ptr();
+        const int64_t N = integer(a[3]);
+        const Gamma gamma(a[4], x.K);
+        const uint16_t *residual = nullptr;
+        int64_t ldr = 0;
+        if (a[6] != Py_None) {
+            const at::Tensor &r = cuda_tensor(a[6], at::kBFloat16);
+            if (r.dim() != 2 || r.size(0) != x.M || r.size(1) != N || r.stride(1) != 1) throw NotOrdinary{};
+            residual = static_cast<const uint16_t *>(r.data_ptr());
+            ldr = r.stride(0);
+        }
+        if (p_w8_fused_workspace_bytes(x.M, N, x.K, gamma.p != nullptr, residual != nullptr)) return -1;
+        const Output y(a[7]);
+        return call(p_w8_linear_fused, x.x, x.M, x.K, x.ldx, gamma.p, real(a[5]), static_cast<const int8_t *>(w),
+                    static_cast<const uint16_t *>(sc), N, residual, ldr, y.y, y.ldy, current_stream());
+    });
+}
+
+// (x, wq_packed, scales, I, gamma, eps, y)
+PyObject *w8_gateup_swiglu(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    return status_of(n, 7, [&] {
+        const Activations x(a[0]);
+        const void *w = cuda_tensor(a[1], at::kChar).data_ptr(), *sc = cuda_tensor(a[2], at::kBFloat16).data_ptr();
+        const int64_t I = integer(a[3]);
+        if (I < 0 || I > (1 << 25)) throw NotOrdinary{};
+        const Gamma gamma(a[4], x.K);
+        if (p_w8_fused_workspace_bytes(x.M, 2 * I, x.K, gamma.p != nullptr, 0)) return -1;
+        const Output y(a[6]);
+        return call(p_w8_gateup_swiglu, x.x, x.M, x.K, x.ldx, gamma.p, real(a[5]), static_cast<const int8_t *>(w),
+                    static_cast<const uint16_t *>(sc), I, y.y, y.ldy, current_stream());
+    });
+}
+
+// (addresses of the ten entry points, current device, current raw stream)
 PyObject *bind(PyObject *, PyObject *args) {
-    unsigned long long f[7];
+    unsigned long long f[10];
     PyObject *device, *stream;
-    if (!PyArg_ParseTuple(args, "(KKKKKKK)OO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &device, &stream)) return nullptr;
+    if (!PyArg_ParseTuple(args, "(KKKKKKKKKK)OO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &f[7], &f[8], &f[9], &device, &stream)) return nullptr;
     p_w8_linear = reinterpret_cast<decltype(p_w8_linear)>(f[0]);
     p_bf16_linear = reinterpret_cast<decltype(p_bf16_linear)>(f[1]);
     p_w8a8_linear = reinterpret_cast<decltype(p_w8a8_linear)>(f[2]);
@@ -181,6 +235,9 @@ PyObject *bind(PyObject *, PyObject *args) {
     p_w4_packed_bytes = reinterpret_cast<decltype(p_w4_packed_bytes)>(f[4]);
     p_w8a8_workspace_bytes = reinterpret_cast<decltype(p_w8a8_workspace_bytes)>(f[5]);
     p_w4_workspace_bytes = reinterpret_cast<decltype(p_w4_workspace_bytes)>(f[6]);
+    p_w8_linear_fused = reinterpret_cast<decltype(p_w8_linear_fused)>(f[7]);
+    p_w8_gateup_swiglu = reinterpret_cast<decltype(p_w8_gateup_swiglu)>(f[8]);
+    p_w8_fused_workspace_bytes = reinterpret_cast<decltype(p_w8_fused_workspace_bytes)>(f[9]);
     Py_INCREF(device);
     Py_INCREF(stream);
     g_device = device;
@@ -190,6 +247,7 @@ PyObject *bind(PyObject *, PyObject *args) {
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(w8_linear), FAST(bf16_linear), FAST(w8a8_linear), FAST(w4_linear),
+                         FAST(w8_linear_fused), FAST(w8_gateup_swiglu),
                          {"bind", bind, METH_VARARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -23,6 +23,7 @@ def test_what_is_not_an_ordinary_call(qb):
     assert f.w8_linear(x.as_subclass(_Sub), w, s, 16, y, None) == -1
     assert f.bf16_linear(x, s, 2 ** 80, y, None) == -1 and f.bf16_linear(x, s, 16.0, y, None) == -1
     assert f.w8a8_linear(x, w, s, 16, None, y) == -1 and f.w4_linear(x, w, 16, y) == -1
+    assert f.w8_linear_fused(x, w, s, 16, None, 1e-6, None, y) == -1 and f.w8_gateup_swiglu(x, w, s, 16, None, 1e-6, y) == -1
     with pytest.raises(TypeError):
         qb.w8_linear(x, w, s, 16, y=y)                                           # what the Python path says of it
     with pytest.raises(TypeError):
@@ -30,18 +31,24 @@ def test_what_is_not_an_ordinary_call(qb):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind", ["int8", "bf16", "w8a8", "smoothed", "int4"])
+@pytest.mark.parametrize("kind", ["int8", "bf16", "w8a8", "smoothed", "int4", "fused", "residual", "gated"])
 def test_ordinary_calls(qb, kind):
     M, N, K = 5, 48, 256
     gen = torch.Generator(device="cuda").manual_seed(3)
     x = torch.randn(M, K + 8, generator=gen, device="cuda").bfloat16()[:, :K]
     w = torch.randn(N, K, generator=gen, device="cuda") * 0.02
     smooth = torch.rand(K, generator=gen, device="cuda") + 0.5
+    gamma = (torch.rand(K, generator=gen, device="cuda") + 0.5).bfloat16()
+    res = torch.randn(M, N + 8, generator=gen, device="cuda").bfloat16()
     wq, sc = qb.quantize_weights(w)
+    wq2, sc2 = qb.quantize_weights(torch.cat([w, w]))
     packed = {"bf16": qb.pack_bf16_weights(w), "int4": qb.quantize_weights_w4(w)}.get(kind, wq)
     calls = {"int8": lambda x, N, y: qb.w8_linear(x, wq, sc, N, y=y), "bf16": lambda x, N, y: qb.bf16_linear(x, packed, N, y=y),
              "w8a8": lambda x, N, y: qb.w8a8_linear(x, wq, sc, N, y=y), "smoothed": lambda x, N, y: qb.w8a8_linear(x, wq, sc, N, smooth=smooth, y=y),
-             "int4": lambda x, N, y: qb.w4_linear(x, packed, N, y=y)}
+             "int4": lambda x, N, y: qb.w4_linear(x, packed, N, y=y),
+             "fused": lambda x, N, y: qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, eps=1e-5, residual=res[:, :N], y=y),
+             "residual": lambda x, N, y: qb.w8_linear_fused(x, wq, sc, N, residual=res[:, :N], y=y),
+             "gated": lambda x, N, y: qb.w8_gateup_swiglu(x, wq2, sc2, N, gamma=gamma, y=y)}
     call = calls[kind]
     want = call(x, N, None)                                                      # without an output: the Python path
     y = torch.full((M, N + 16), 7.0, dtype=torch.bfloat16, device="cuda")
