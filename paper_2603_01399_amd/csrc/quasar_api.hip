@@ -834,13 +834,28 @@ bool plan_w8a8_apart(int M, int N, int K, size_t room, DirectPlan &d) {
 }
 
 template <int EPI>
-int launch_w8a8(const GemmParams &base, int M, hipStream_t stream, int *grid_out) {
+int launch_w8a8(const GemmParams &base, int M, hipStream_t stream, int *grid_out, void *workspace = nullptr, size_t workspace_bytes = 0) {
     GemmParams p = base;
     p.Srow = p.S;
     p.ksplit = 1;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     const int NB = MP == 32 ? 2 : 1;
     DirectPlan d{};
+    if (EPI == EPI_ARGMAX && MP == 32 && p.S >= 16) {
+        // the vocabulary of more than 16 tokens: codes from a launch of their own, behind the keys of the workgroups (us, M = 32, in
+        // every workgroup -> apart: 151936 x 4096 131.6 -> 103.5, 151936 x 5120 160.7 -> 128.1, 32000 x 1024 22.9 -> 20.0)
+        const size_t at = kMaxGrid * 4 * 32, head = at + a8_code_bytes(MP, p.S);
+        if (workspace_bytes >= head + 128 && plan_direct_w8a8(MP, p.T, p.S, false, d) && d.XS <= 6 && (size_t)d.groups * MP * 8 <= at) {
+            unsigned char *codes = static_cast<unsigned char *>(workspace) + at;
+            float *dx = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + head);
+            if (const int e = launch_quantize_operand(p, MP, codes, dx, stream)) return e;
+            p.x = reinterpret_cast<const uint16_t *>(codes);
+            p.dx = dx;
+            p.smooth = nullptr;
+            if (grid_out) *grid_out = d.groups;
+            return launch_direct_w8a8(EPI, p, MP, d, stream);
+        }
+    }
     if (direct_reach(M, p.ldx) && plan_direct_w8a8(MP, p.T, p.S, p.smooth != nullptr, d)) {
         if (grid_out) *grid_out = d.groups;
         return launch_direct_w8a8(EPI, p, MP, d, stream);
@@ -1596,7 +1611,7 @@ int quasar_w8a8_lmhead_verify(const uint16_t *hidden, int64_t M, int64_t K, int6
     p.S = (int)(K / kStepK8);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     int grid = 0;
-    if (const int e = launch_w8a8<EPI_ARGMAX>(p, (int)M, st, &grid)) return e;
+    if (const int e = launch_w8a8<EPI_ARGMAX>(p, (int)M, st, &grid, workspace, workspace_bytes)) return e;
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32);
     hipLaunchKernelGGL(verify_finalize_kernel, dim3(1), dim3(1024), 0, st, p.partial, grid, MP, (int)M, (int)V,
                        draft_ids, (int)n_draft, out_argmax, out_accept_len);

@@ -35,7 +35,8 @@ __device__ __forceinline__ unsigned int quantize_quad(float x0, float x1, float 
 // A slot is 64 k of one tile: one 1 KB load, one v_mfma_i32_16x16x64_i8 per 16 tokens.
 // LDS: [a region per wave: activations on their way in, then 2 x NB partial tiles of 1 KB][row scales][16 x MP maxima]
 //      [smoothing factors: 16 waves x XS x 256 B]
-template <int MP, int EPI, int XS, bool SMOOTH>
+// PREQ: p.x is the operand codes that quantize_operand_kernel made (at 32 tokens), p.dx their step sizes; nothing is quantised here.
+template <int MP, int EPI, int XS, bool SMOOTH, bool PREQ = false>
 __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams p) {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int NW = 16;
@@ -45,6 +46,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     constexpr int RD = XS * U <= 6 ? XS * U : (XS == 10 ? 5 : (XS == 8 && MP == 8 ? 8 : 4));
     static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
     constexpr bool HOLD = a8_hold(MP, XS);
+    static_assert(!PREQ || (MP == 32 && !SMOOTH && !HOLD), "operand codes are read where nothing else of x is");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -107,6 +109,13 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
         for (int i = 0; i < XS; ++i)
 #pragma unroll
             for (int j = 0; j < NB * XP; ++j) raw[i][j] = load_x(i, j);
+    i32x4 bq[XS][NB];
+    if constexpr (PREQ)
+#pragma unroll
+        for (int i = 0; i < XS; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                bq[i][nb] = *(reinterpret_cast<const i32x4 *>(p.x) + ((long long)step[i] * NB + nb) * 64 + lane);
     unsigned int sc_first = 0;
     if (2 * tid < ntiles * kTileRows)
         sc_first = *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + 2 * tid);
@@ -154,6 +163,11 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
         }
     };
 
+    float dx[NB];
+    if constexpr (PREQ) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) dx[nb] = p.dx[tok + 16 * nb];
+    } else {
     // ---- per-token maxima over the whole K, step sizes
     float amax[NB];
 #pragma unroll
@@ -180,8 +194,6 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
         if (lane < (MP == 8 ? 8 : 16)) maxima[w * MP + lane + 16 * nb] = a;
     }
     lds_barrier();
-    float dx[NB];
-    i32x4 bq[XS][NB];
     float inv[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -214,6 +226,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
             bq[i][nb] = i32x4{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
             if (HOLD ? XS >= 6 : (i * NB + nb) % 2 == 1) __builtin_amdgcn_sched_barrier(0);
         }
+    }
 
     i32x4 acc[NB];
 #pragma unroll
@@ -298,6 +311,12 @@ template <int MP, int EPI, bool SMOOTH, int... XS>
 int launch_a8_forms(int xs, int grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
     int rc = QUASAR_ERR_SHAPE;
     ((xs == XS ? (void)(rc = launch(stream_direct_a8_kernel<MP, EPI, XS, SMOOTH>, grid, 1024, lds_bytes, stream, p)) : (void)0), ...);
+    return rc;
+}
+template <int... XS>
+int launch_a8_codes(int xs, int grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
+    int rc = QUASAR_ERR_SHAPE;
+    ((xs == XS ? (void)(rc = launch(stream_direct_a8_kernel<32, EPI_ARGMAX, XS, false, true>, grid, 1024, lds_bytes, stream, p)) : (void)0), ...);
     return rc;
 }
 template <int EPI, bool SMOOTH>

@@ -118,3 +118,28 @@ def test_scratch_routes_under_capture(kind):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,V,K", [(17, 16, 1024), (32, 16 * 300, 1088), (24, 16 * 1100, 4096), (32, 16 * 257, 5120), (20, 16 * 40, 6144), (20, 16 * 40, 6208)])
+@pytest.mark.parametrize("smoothed", [False, True])
+def test_w8a8_vocabulary_of_many_tokens(M, V, K, smoothed):
+    """Codes from a launch of their own, then the argmax: bit for bit the stated arithmetic, ties to the lowest index."""
+    from paper_2603_01399_amd import binding as qb
+    print("w8a8 vocabulary", M, V, K, smoothed, flush=True)
+    x = _activations(M, K)
+    x[1] = 0.0                                                     # every logit equal: index 0
+    w = torch.randn(V, K, device="cuda", generator=torch.Generator("cuda").manual_seed(31 + K)) * 0.02
+    w[V // 2:] = w[:V - V // 2]                                    # every row twice
+    smooth = torch.exp2(torch.rand(K, device="cuda") * 4 - 2) if smoothed else None
+    wq, sc = qb.quantize_weights(w)
+    codes, dx = qb.quantize_activations(x, smooth)
+    acc = (codes.double() @ qb.unpack_weights(wq, V, K).double().t()).float()
+    want = (acc * (dx[:, None] * sc.float()[None])).double()
+    top = want.max(1, keepdim=True).values
+    want = torch.where(want == top, torch.arange(V, device="cuda")[None], V).min(1).values.int()
+    draft = want[:-1].clone()
+    draft[M // 2:] += 1
+    ws = qb.make_workspace(M, V, K)
+    room = torch.full((ws.nbytes + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    am, accepted = qb.w8a8_lmhead_verify(x, wq, sc, V, draft.contiguous(), room[:ws.nbytes], smooth=smooth)
+    assert torch.equal(am, want) and int(accepted) == M // 2 and bool((room[ws.nbytes:] == 0xA5).all())
