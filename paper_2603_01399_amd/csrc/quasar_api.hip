@@ -228,8 +228,8 @@ bool plan_direct(int MP, int T, int TU, int S, int SC, int C, int ksplit, bool w
 // How many slices a K that would otherwise be staged in chunks is split into: the cheapest of 1 .. 8 by what the busiest
 // compute unit does.  Fitted to the times of 676 shapes (M 1 .. 32, K 2048 .. 25600, N 256 .. 16384, both weight types) with every
 // number of slices: 62 KB/us of weights, half of that for the loads of slots that only fill a form, 60 KB/us of
-// activations; a split adds a second launch (2 us and 0.6 us a slice, which it reads one after the other) and 0.7 us per MB of
-// partial sums.  Over those shapes the choice is 1 % slower than the best one on average.  (Rates of 25 and 75 KB/us and 4 us for
+// activations; a split adds a second launch (2 us and 0.6 us a slice, which it read one after the other; it requests them together
+// now, 1 us less at four or five slices) and 0.7 us per MB of partial sums.  Over those shapes the choice is 1 % slower than the best one on average.  (Rates of 25 and 75 KB/us and 4 us for
 // a split, the first estimate, chose up to half too many or too few slices where tiles are few: M = 16, 1024 x 12288
 // 12.7 us, now 8.5.)
 bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t workspace_bytes, int most_slots, DirectPlan &best) {
