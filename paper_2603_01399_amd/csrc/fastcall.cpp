@@ -14,8 +14,12 @@
 #include <cstdint>
 
 #include "../../include/quasar.h"
+#include "unlocked.hpp"
 
 namespace {
+
+using quasar::call;
+using quasar::status_of;
 
 // entry points of the library that binding.py has loaded, and torch's own two functions for the current stream
 decltype(&quasar_w8_linear) p_w8_linear;
@@ -93,28 +97,6 @@ void *current_stream() {
     Py_DECREF(raw);
     if (PyErr_Occurred()) throw NotOrdinary{};
     return s;
-}
-
-// The launch runs without the interpreter's lock, as under ctypes.
-template <typename Entry, typename... Args>
-int call(Entry entry, Args... args) {
-    PyThreadState *state = PyEval_SaveThread();
-    const int status = entry(args...);
-    PyEval_RestoreThread(state);
-    return status;
-}
-
-// Calls body(); whatever keeps it from an ordinary call - a tensor without storage among them, for which torch throws - is left
-// to binding.py.
-template <typename Body>
-PyObject *status_of(Py_ssize_t got, Py_ssize_t want, Body body) {
-    long status = -1;
-    try {
-        if (got == want) status = body();
-    } catch (...) {
-    }
-    if (PyErr_Occurred()) PyErr_Clear();
-    return PyLong_FromLong(status);
 }
 
 // (x, wq_packed, scales, N, y, workspace)

@@ -1,5 +1,10 @@
 """The linears' native marshalling: only calls of plain CUDA tensors are taken, every other one is left to the Python path, which
 raises as it did (CPU), and the ordinary calls give the same bits and the same errors (GPU)."""
+import importlib.util
+import os
+import subprocess
+import sysconfig
+
 import pytest
 import torch
 
@@ -28,6 +33,34 @@ def test_what_is_not_an_ordinary_call(qb):
         qb.w8_linear(x, w, s, 16, y=y)                                           # what the Python path says of it
     with pytest.raises(TypeError):
         qb.w4_linear(x, w, 16, y=y)
+
+
+_THROWING = """
+#include "unlocked.hpp"
+#include <new>
+static int throws(int) { throw std::bad_alloc(); }
+static PyObject *run(PyObject *, PyObject *) {
+    PyObject *status = quasar::status_of(1, 1, [] { return quasar::call(throws, 0); });
+    const int held = PyGILState_Check();
+    if (!held) PyGILState_Ensure();
+    return Py_BuildValue("(iN)", held, status);
+}
+static PyMethodDef methods[] = {{"run", run, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+static PyModuleDef module = {PyModuleDef_HEAD_INIT, "throwing", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+PyMODINIT_FUNC PyInit_throwing(void) { return PyModule_Create(&module); }
+"""
+
+
+def test_lock_after_an_exception(tmp_path):
+    """An entry point that throws leaves the interpreter's lock held by the caller, and the call is not an ordinary one."""
+    src, so = tmp_path / "throwing.cpp", tmp_path / "throwing.so"
+    src.write_text(_THROWING)
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_01399_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-fPIC", "-shared", "-I" + csrc, "-I" + sysconfig.get_paths()["include"], "-o", str(so), str(src)], check=True)
+    spec = importlib.util.spec_from_file_location("throwing", so)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module.run() == (1, -1)
 
 
 @pytest.mark.gpu
