@@ -186,6 +186,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _scratch(nbytes, device):
+    """Scratch of a call, from the allocator of the stream it runs on.  It makes a call faster and no call needs it: where memory is
+    short the call runs without."""
+    if nbytes:
+        try:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
+        except torch.OutOfMemoryError:
+            pass
+    return None, 0
+
+
 def _stream():
     return _current_raw_stream(_current_device())
 
@@ -310,9 +321,8 @@ def w8a8_linear(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, 
     M, K = x.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    # scratch of the call, from the allocator of the stream it runs on (small shapes never use any: not asked for)
-    need = _lib.quasar_w8a8_workspace_bytes(M, N, K) if M > 16 or K > (8192 if M <= 8 else 5120) else 0
-    ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
+    # (small shapes never use any scratch: not asked for)
+    ws, need = _scratch(_lib.quasar_w8a8_workspace_bytes(M, N, K) if M > 16 or K > (8192 if M <= 8 else 5120) else 0, x.device)
     _check("quasar_w8a8_linear",
            _lib.quasar_w8a8_linear_split(_ptr(x), M, K, x.stride(0), _smooth_arg(smooth, K), _ptr(wq_packed), _ptr(scales),
                                          N, _ptr(y), y.stride(0), _ptr(ws), need, _stream()))
@@ -448,9 +458,8 @@ def w4_linear(x: torch.Tensor, w4_packed: torch.Tensor, N: int, y: torch.Tensor 
         raise ValueError("w4_packed is smaller than quasar_w4_packed_bytes(N, K)")
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    # scratch of the call, from the allocator of the stream it runs on (small shapes never use any: not asked for)
-    need = _lib.quasar_w4_workspace_bytes(M, N, K) if K > (12288 if M <= 8 else 8192 if M <= 16 else 4096) else 0
-    ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
+    # (small shapes never use any scratch: not asked for)
+    ws, need = _scratch(_lib.quasar_w4_workspace_bytes(M, N, K) if K > (12288 if M <= 8 else 8192 if M <= 16 else 4096) else 0, x.device)
     _check("quasar_w4_linear",
            _lib.quasar_w4_linear_split(_ptr(x), M, K, x.stride(0), _ptr(w4_packed), N, _ptr(y), y.stride(0), _ptr(ws), need,
                                        _stream()))
@@ -489,11 +498,10 @@ def _gamma_arg(gamma, K):
 
 
 def _fused_scratch(x, M, N, K, gamma, residual):
-    """Scratch of a fused call, from the allocator of the stream it runs on (small shapes never use any: not asked for)."""
+    """Scratch of a fused call (small shapes never use any: not asked for)."""
     if K <= (8192 if M <= 8 else 4096 if M <= 16 else 2048):
         return None, 0
-    need = _lib.quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None)
-    return (torch.empty(need, dtype=torch.uint8, device=x.device) if need else None), need
+    return _scratch(_lib.quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None), x.device)
 
 
 def w8_linear_fused(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, N: int, *, gamma: torch.Tensor = None,

@@ -54,3 +54,42 @@ def test_fused_with_scratch(M, N, K, kind):
     again = qb.w8_gateup_swiglu(x, wq, sc, out, gamma=gamma) if kind == "gated" else \
         qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, residual=residual)
     assert float((again.double() - want.double()).abs().max() / want.double().abs().max()) <= 6e-3
+
+
+@pytest.mark.parametrize("kind", ["w8a8", "int4", "residual", "norm", "gated"])
+def test_without_memory_for_scratch(kind):
+    """Calls whose scratch does not fit the memory that is left run without it, as the entry points do that take none."""
+    from paper_2603_01399_amd import binding as qb
+    print("no memory for scratch", kind, flush=True)
+    M, N, K = 32, 16 * 320, 8192
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    w = torch.randn(N, K, generator=gen, device="cuda") * 0.02
+    packed = (qb.quantize_weights_w4(w),) if kind == "int4" else qb.quantize_weights(w)
+    gamma = (1 + 0.2 * torch.randn(K, generator=gen, device="cuda")).bfloat16()
+    x, res = torch.randn(M, K, generator=gen, device="cuda").bfloat16(), torch.randn(M, N, generator=gen, device="cuda").bfloat16()
+    y = torch.empty((M, N // 2 if kind == "gated" else N), dtype=torch.bfloat16, device="cuda")
+    call = {"w8a8": lambda: qb.w8a8_linear(x, *packed, N, y=y), "int4": lambda: qb.w4_linear(x, *packed, N, y=y),
+            "residual": lambda: qb.w8_linear_fused(x, *packed, N, residual=res, y=y),
+            "norm": lambda: qb.w8_linear_fused(x, *packed, N, gamma=gamma, y=y),
+            "gated": lambda: qb.w8_gateup_swiglu(x, *packed, N // 2, gamma=gamma, y=y)}[kind]
+    want = call().clone()
+    got = torch.empty_like(want)
+    del w
+    torch.cuda.empty_cache()
+    total, hold = torch.cuda.get_device_properties(0).total_memory, []
+    torch.cuda.set_per_process_memory_fraction(min(1.0, (torch.cuda.memory_reserved() + (64 << 20)) / total))
+    try:
+        for size in (1 << 24, 1 << 21, (1 << 20) + 512, 1 << 20, 1 << 14):      # both of the pools: what is left is less than any scratch
+            with pytest.raises(torch.OutOfMemoryError):
+                for _ in range(1 << 14):
+                    hold.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        y.fill_(7.0)
+        call()
+        got.copy_(y)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+        hold.clear()
+        torch.cuda.empty_cache()
+    # (another order of the sums: the bound above; W8A8: integers, the same bits)
+    assert float((got.double() - want.double()).abs().max() / want.double().abs().max()) <= (0.0 if kind == "w8a8" else 6e-3)
