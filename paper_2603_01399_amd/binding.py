@@ -169,16 +169,16 @@ _Tensor = torch.Tensor
 _current_raw_stream = torch._C._cuda_getCurrentRawStream
 _current_device = torch._C._cuda_getDevice
 
-# The ordinary call of a linear - plain tensors, an output given, no scratch of its own - is marshalled in native code
-# (csrc/fastcall.cpp): 6.1 -> 4.0 us of host time; it answers -1 for any other, which the functions below handle.
+# The ordinary call of a linear - plain tensors, an output given - is marshalled in native code (csrc/fastcall.cpp), scratch
+# included: 6.1 -> 4.0 us of host time; it answers -1 for any other, which the functions below handle.
 if not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
     raise ImportError(f"{_HERE}/_fastcall.so is missing: build it with `python -m paper_2603_01399_amd.build`")
 from . import _fastcall as _fast  # noqa: E402
 
 _fast.bind(tuple(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value
-                 for n in ("quasar_w8_linear", "quasar_bf16_linear", "quasar_w8a8_linear", "quasar_w4_linear", "quasar_w4_packed_bytes",
-                           "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes", "quasar_w8_linear_fused", "quasar_w8_gateup_swiglu",
-                           "quasar_w8_fused_workspace_bytes")),
+                 for n in ("quasar_w8_linear", "quasar_bf16_linear", "quasar_w8a8_linear_split", "quasar_w4_linear_split", "quasar_w4_packed_bytes",
+                           "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes", "quasar_w8_linear_fused_split",
+                           "quasar_w8_gateup_swiglu_split", "quasar_w8_fused_workspace_bytes")),
            _current_device, _current_raw_stream)
 
 
@@ -320,9 +320,8 @@ def w8a8_linear(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, 
     _dev(scales, "scales", torch.bfloat16)
     M, K = x.shape
     if y is None:
-        y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    # (small shapes never use any scratch: not asked for)
-    ws, need = _scratch(_lib.quasar_w8a8_workspace_bytes(M, N, K) if M > 16 or K > (8192 if M <= 8 else 5120) else 0, x.device)
+        return w8a8_linear(x, wq_packed, scales, N, smooth, torch.empty((M, N), dtype=torch.bfloat16, device=x.device))
+    ws, need = _scratch(_lib.quasar_w8a8_workspace_bytes(M, N, K), x.device)
     _check("quasar_w8a8_linear",
            _lib.quasar_w8a8_linear_split(_ptr(x), M, K, x.stride(0), _smooth_arg(smooth, K), _ptr(wq_packed), _ptr(scales),
                                          N, _ptr(y), y.stride(0), _ptr(ws), need, _stream()))
@@ -457,9 +456,8 @@ def w4_linear(x: torch.Tensor, w4_packed: torch.Tensor, N: int, y: torch.Tensor 
     if w4_packed.numel() < w4_packed_bytes(N, K):
         raise ValueError("w4_packed is smaller than quasar_w4_packed_bytes(N, K)")
     if y is None:
-        y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    # (small shapes never use any scratch: not asked for)
-    ws, need = _scratch(_lib.quasar_w4_workspace_bytes(M, N, K) if K > (12288 if M <= 8 else 8192 if M <= 16 else 4096) else 0, x.device)
+        return w4_linear(x, w4_packed, N, torch.empty((M, N), dtype=torch.bfloat16, device=x.device))
+    ws, need = _scratch(_lib.quasar_w4_workspace_bytes(M, N, K), x.device)
     _check("quasar_w4_linear",
            _lib.quasar_w4_linear_split(_ptr(x), M, K, x.stride(0), _ptr(w4_packed), N, _ptr(y), y.stride(0), _ptr(ws), need,
                                        _stream()))
@@ -497,13 +495,6 @@ def _gamma_arg(gamma, K):
     return gamma
 
 
-def _fused_scratch(x, M, N, K, gamma, residual):
-    """Scratch of a fused call (small shapes never use any: not asked for)."""
-    if K <= (8192 if M <= 8 else 4096 if M <= 16 else 2048):
-        return None, 0
-    return _scratch(_lib.quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None), x.device)
-
-
 def w8_linear_fused(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tensor, N: int, *, gamma: torch.Tensor = None,
                     eps: float = 1e-6, residual: torch.Tensor = None, y: torch.Tensor = None) -> torch.Tensor:
     """y = [residual +] W8([RMSNorm](x)); the normalisation (gamma, eps) and the residual are optional."""
@@ -522,8 +513,9 @@ def w8_linear_fused(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Tens
         if residual.shape != (M, N) or residual.stride(1) != 1:
             raise ValueError("residual must be [M, N] with a contiguous last dimension")
     if y is None:
-        y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    ws, need = _fused_scratch(x, M, N, K, gamma, residual)
+        return w8_linear_fused(x, wq_packed, scales, N, gamma=gamma, eps=eps, residual=residual,
+                               y=torch.empty((M, N), dtype=torch.bfloat16, device=x.device))
+    ws, need = _scratch(_lib.quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None), x.device)
     _check("quasar_w8_linear_fused",
            _lib.quasar_w8_linear_fused_split(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), N,
                                              _ptr(residual), 0 if residual is None else residual.stride(0),
@@ -554,8 +546,8 @@ def w8_gateup_swiglu(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Ten
     M, K = x.shape
     gamma = _gamma_arg(gamma, K)
     if y is None:
-        y = torch.empty((M, I), dtype=torch.bfloat16, device=x.device)
-    ws, need = _fused_scratch(x, M, 2 * I, K, gamma, None)
+        return w8_gateup_swiglu(x, wq_packed, scales, I, gamma=gamma, eps=eps, y=torch.empty((M, I), dtype=torch.bfloat16, device=x.device))
+    ws, need = _scratch(_lib.quasar_w8_fused_workspace_bytes(M, 2 * I, K, gamma is not None, False), x.device)
     _check("quasar_w8_gateup_swiglu",
            _lib.quasar_w8_gateup_swiglu_split(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), I,
                                               _ptr(y), y.stride(0), _ptr(ws), need, _stream()))

@@ -1,14 +1,17 @@
 // The linears' and fused linears' argument marshalling in native code: what binding.py does for an ordinary call - plain CUDA tensors, an output
-// given, no scratch of the call's own - without its Python and ctypes steps.
+// given - without its Python and ctypes steps.  Scratch that a call uses comes from torch's allocator, on the stream of the call.
 //
 // Every function returns the status of the C entry point it calls, or -1 for "not an ordinary call": binding.py then goes its
-// own way, which allocates what is missing and raises what is to be raised.  Nothing is kept from one call for the next.
+// own way, which raises what is to be raised.  Nothing is kept from one call for the next.
 //
 // What it measured, one 1024 x 1024 linear of 8 tokens through the binding, us of host time: 6.1 -> 4.0, of which the launch
-// itself takes 2.9 (the kernel 3.4 on the GPU); a decoder block whose six calls are host-bound 40.9 -> 33.8.
+// itself takes 2.9 (the kernel 3.4 on the GPU); a decoder block whose six calls are host-bound 40.9 -> 33.8.  A call with scratch and two
+// launches (1024 x 8256 with a residual, 9 tokens; 7.3 in a graph): 13.0 through Python, 7.9 so.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <c10/core/Allocator.h>
+#include <c10/util/Exception.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -24,13 +27,13 @@ using quasar::status_of;
 // entry points of the library that binding.py has loaded, and torch's own two functions for the current stream
 decltype(&quasar_w8_linear) p_w8_linear;
 decltype(&quasar_bf16_linear) p_bf16_linear;
-decltype(&quasar_w8a8_linear) p_w8a8_linear;
-decltype(&quasar_w4_linear) p_w4_linear;
+decltype(&quasar_w8a8_linear_split) p_w8a8_linear;
+decltype(&quasar_w4_linear_split) p_w4_linear;
 decltype(&quasar_w4_packed_bytes) p_w4_packed_bytes;
 decltype(&quasar_w8a8_workspace_bytes) p_w8a8_workspace_bytes;
 decltype(&quasar_w4_workspace_bytes) p_w4_workspace_bytes;
-decltype(&quasar_w8_linear_fused) p_w8_linear_fused;
-decltype(&quasar_w8_gateup_swiglu) p_w8_gateup_swiglu;
+decltype(&quasar_w8_linear_fused_split) p_w8_linear_fused;
+decltype(&quasar_w8_gateup_swiglu_split) p_w8_gateup_swiglu;
 decltype(&quasar_w8_fused_workspace_bytes) p_w8_fused_workspace_bytes;
 PyObject *g_device, *g_stream;
 
@@ -99,6 +102,21 @@ void *current_stream() {
     return s;
 }
 
+// A call with `need` bytes of scratch: entry(.., scratch, bytes, stream).  The scratch is given back behind the launch, for work that
+// follows on the same stream.  Scratch makes a call faster and no call needs it: where memory is short it runs without.
+template <typename Entry, typename... Args>
+int call_with_scratch(Entry entry, size_t need, void *stream, Args... args) {
+    quasar::Unlocked unlocked;
+    c10::DataPtr scratch;
+    if (need) {
+        try {
+            scratch = c10::GetAllocator(c10::DeviceType::CUDA)->allocate(need);
+        } catch (const c10::OutOfMemoryError &) {
+        }
+    }
+    return entry(args..., scratch.get(), scratch ? need : 0, stream);
+}
+
 // (x, wq_packed, scales, N, y, workspace)
 PyObject *w8_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return status_of(n, 6, [&] {
@@ -128,7 +146,6 @@ PyObject *w8a8_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return status_of(n, 6, [&] {
         const Activations x(a[0]);
         const int64_t N = integer(a[3]);
-        if (p_w8a8_workspace_bytes(x.M, N, x.K)) return -1;
         const void *w = cuda_tensor(a[1], at::kChar).data_ptr(), *sc = cuda_tensor(a[2], at::kBFloat16).data_ptr();
         const float *smooth = nullptr;
         if (a[4] != Py_None) {
@@ -137,8 +154,8 @@ PyObject *w8a8_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
             smooth = static_cast<const float *>(s.data_ptr());
         }
         const Output y(a[5]);
-        return call(p_w8a8_linear, x.x, x.M, x.K, x.ldx, smooth, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc),
-                             N, y.y, y.ldy, nullptr, 0, current_stream());
+        return call_with_scratch(p_w8a8_linear, p_w8a8_workspace_bytes(x.M, N, x.K), current_stream(), x.x, x.M, x.K, x.ldx, smooth,
+                                 static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc), N, y.y, y.ldy);
     });
 }
 
@@ -148,9 +165,10 @@ PyObject *w4_linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Activations x(a[0]);
         const at::Tensor &w = cuda_tensor(a[1], at::kByte);
         const int64_t N = integer(a[2]);
-        if (w.numel() < (int64_t)p_w4_packed_bytes(N, x.K) || p_w4_workspace_bytes(x.M, N, x.K)) return -1;
+        if (w.numel() < (int64_t)p_w4_packed_bytes(N, x.K)) throw NotOrdinary{};
         const Output y(a[3]);
-        return call(p_w4_linear, x.x, x.M, x.K, x.ldx, w.data_ptr(), N, y.y, y.ldy, current_stream());
+        return call_with_scratch(p_w4_linear, p_w4_workspace_bytes(x.M, N, x.K), current_stream(), x.x, x.M, x.K, x.ldx,
+                                 static_cast<const void *>(w.data_ptr()), N, y.y, y.ldy);
     });
 }
 
@@ -183,10 +201,11 @@ PyObject *w8_linear_fused(PyObject *, PyObject *const *a, Py_ssize_t n) {
             residual = static_cast<const uint16_t *>(r.data_ptr());
             ldr = r.stride(0);
         }
-        if (p_w8_fused_workspace_bytes(x.M, N, x.K, gamma.p != nullptr, residual != nullptr)) return -1;
+        const float eps = real(a[5]);
         const Output y(a[7]);
-        return call(p_w8_linear_fused, x.x, x.M, x.K, x.ldx, gamma.p, real(a[5]), static_cast<const int8_t *>(w),
-                    static_cast<const uint16_t *>(sc), N, residual, ldr, y.y, y.ldy, current_stream());
+        return call_with_scratch(p_w8_linear_fused, p_w8_fused_workspace_bytes(x.M, N, x.K, gamma.p != nullptr, residual != nullptr),
+                                 current_stream(), x.x, x.M, x.K, x.ldx, gamma.p, eps, static_cast<const int8_t *>(w),
+                                 static_cast<const uint16_t *>(sc), N, residual, ldr, y.y, y.ldy);
     });
 }
 
@@ -198,10 +217,11 @@ PyObject *w8_gateup_swiglu(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const int64_t I = integer(a[3]);
         if (I < 0 || I > (1 << 25)) throw NotOrdinary{};
         const Gamma gamma(a[4], x.K);
-        if (p_w8_fused_workspace_bytes(x.M, 2 * I, x.K, gamma.p != nullptr, 0)) return -1;
+        const float eps = real(a[5]);
         const Output y(a[6]);
-        return call(p_w8_gateup_swiglu, x.x, x.M, x.K, x.ldx, gamma.p, real(a[5]), static_cast<const int8_t *>(w),
-                    static_cast<const uint16_t *>(sc), I, y.y, y.ldy, current_stream());
+        return call_with_scratch(p_w8_gateup_swiglu, p_w8_fused_workspace_bytes(x.M, 2 * I, x.K, gamma.p != nullptr, 0), current_stream(),
+                                 x.x, x.M, x.K, x.ldx, gamma.p, eps, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc), I,
+                                 y.y, y.ldy);
     });
 }
 

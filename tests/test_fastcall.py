@@ -104,3 +104,35 @@ def test_ordinary_calls(qb, kind):
     meta = torch.empty(M, K, dtype=torch.bfloat16, device="meta")
     with pytest.raises(TypeError):
         call(meta, N, out)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["w8a8", "int4", "norm", "residual", "gated"])
+def test_calls_with_scratch(qb, kind):
+    """Calls that use scratch are ordinary ones: taken by the native side, and the bits are those of the Python path (to which a
+    subclass of Tensor goes)."""
+    M, N, K = 20, 16 * 40, 8192
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    w = torch.randn(N, K, generator=gen, device="cuda") * 0.02
+    wq, sc = qb.quantize_weights(w)
+    w4 = qb.quantize_weights_w4(w)
+    gamma = (torch.rand(K, generator=gen, device="cuda") + 0.5).bfloat16()
+    res = torch.randn(M, N, generator=gen, device="cuda").bfloat16()
+    y = torch.empty((M, N // 2 if kind == "gated" else N), dtype=torch.bfloat16, device="cuda")
+    native = {"w8a8": lambda: qb._fast.w8a8_linear(x, wq, sc, N, None, y), "int4": lambda: qb._fast.w4_linear(x, w4, N, y),
+              "norm": lambda: qb._fast.w8_linear_fused(x, wq, sc, N, gamma, 1e-6, None, y),
+              "residual": lambda: qb._fast.w8_linear_fused(x, wq, sc, N, None, 1e-6, res, y),
+              "gated": lambda: qb._fast.w8_gateup_swiglu(x, wq, sc, N // 2, gamma, 1e-6, y)}[kind]
+    call = {"w8a8": lambda x, y: qb.w8a8_linear(x, wq, sc, N, y=y), "int4": lambda x, y: qb.w4_linear(x, w4, N, y=y),
+            "norm": lambda x, y: qb.w8_linear_fused(x, wq, sc, N, gamma=gamma, y=y),
+            "residual": lambda x, y: qb.w8_linear_fused(x, wq, sc, N, residual=res, y=y),
+            "gated": lambda x, y: qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, y=y)}[kind]
+    lib = qb.lib()
+    assert {"w8a8": lib.quasar_w8a8_workspace_bytes(M, N, K), "int4": lib.quasar_w4_workspace_bytes(M, N, K)}.get(
+        kind, lib.quasar_w8_fused_workspace_bytes(M, N, K, kind != "residual", kind == "residual")) > 0
+    y.fill_(7.0)
+    assert native() == 0
+    want = call(x.as_subclass(_Sub), torch.empty_like(y))
+    for got in (y, call(x, torch.empty_like(y)), call(x, None)):
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
