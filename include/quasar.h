@@ -456,11 +456,12 @@ int quasar_w8_gateup_swiglu(const uint16_t *x, int64_t M, int64_t K, int64_t ldx
                             const int8_t *wq_packed_interleaved, const uint16_t *scales_bf16_interleaved,
                             int64_t I, uint16_t *y, int64_t ldy, void *hip_stream);
 
-/* The same with a workspace (may be NULL).  One of quasar_w8_fused_workspace_bytes (0: none is used for this shape; N is 2 I for
- * the gate/up form, which has no residual) lets the normalisation be a launch of its own where every workgroup's is dearer, and
- * K be split across workgroups through fp32 partial sums; sums are then taken in another order than without.  It is scratch:
- * undefined on entry and on exit. */
+/* The same with a workspace (may be NULL).  One of quasar_w8_fused_workspace_bytes, of quasar_w8_gateup_workspace_bytes for the
+ * gate/up form (0: none is used for this shape), lets the normalisation be a launch of its own where every workgroup's is dearer, and
+ * K of the linear be split across workgroups through fp32 partial sums; sums are then taken in another order than without.  It is
+ * scratch: undefined on entry and on exit. */
 size_t quasar_w8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int has_gamma, int has_residual);
+size_t quasar_w8_gateup_workspace_bytes(int64_t M, int64_t I, int64_t K, int has_gamma);
 int quasar_w8_linear_fused_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx,
                                  const uint16_t *gamma, float eps,
                                  const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N,

@@ -36,7 +36,7 @@ EXPORTS = (
     "quasar_drafter_create", "quasar_drafter_destroy", "quasar_drafter_append", "quasar_drafter_length",
     "quasar_drafter_propose",
     "quasar_w8_linear_fused", "quasar_w8_gateup_swiglu", "quasar_w8_fused_workspace_bytes", "quasar_w8_linear_fused_split",
-    "quasar_w8_gateup_swiglu_split",
+    "quasar_w8_gateup_workspace_bytes", "quasar_w8_gateup_swiglu_split",
     "quasar_kv_cache_bytes", "quasar_kv_cache_fill", "quasar_attn_prepare", "quasar_attention_workspace_bytes",
     "quasar_verify_attention",
 )
@@ -123,6 +123,8 @@ def _load() -> ctypes.CDLL:
     lib.quasar_w8_gateup_swiglu.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp]
     lib.quasar_w8_fused_workspace_bytes.argtypes = [i64, i64, i64, ci, ci]
     lib.quasar_w8_fused_workspace_bytes.restype = sz
+    lib.quasar_w8_gateup_workspace_bytes.argtypes = [i64, i64, i64, ci]
+    lib.quasar_w8_gateup_workspace_bytes.restype = sz
     lib.quasar_w8_linear_fused_split.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp, i64, vp, sz, vp]
     lib.quasar_w8_gateup_swiglu_split.argtypes = [vp, i64, i64, i64, vp, ctypes.c_float, vp, vp, i64, vp, i64, vp, sz, vp]
     lib.quasar_kv_cache_bytes.argtypes = [i64, i64]
@@ -178,7 +180,7 @@ from . import _fastcall as _fast  # noqa: E402
 _fast.bind(tuple(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value
                  for n in ("quasar_w8_linear", "quasar_bf16_linear", "quasar_w8a8_linear_split", "quasar_w4_linear_split", "quasar_w4_packed_bytes",
                            "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes", "quasar_w8_linear_fused_split",
-                           "quasar_w8_gateup_swiglu_split", "quasar_w8_fused_workspace_bytes")),
+                           "quasar_w8_gateup_swiglu_split", "quasar_w8_fused_workspace_bytes", "quasar_w8_gateup_workspace_bytes")),
            _current_device, _current_raw_stream)
 
 
@@ -547,7 +549,7 @@ def w8_gateup_swiglu(x: torch.Tensor, wq_packed: torch.Tensor, scales: torch.Ten
     gamma = _gamma_arg(gamma, K)
     if y is None:
         return w8_gateup_swiglu(x, wq_packed, scales, I, gamma=gamma, eps=eps, y=torch.empty((M, I), dtype=torch.bfloat16, device=x.device))
-    ws, need = _scratch(_lib.quasar_w8_fused_workspace_bytes(M, 2 * I, K, gamma is not None, False), x.device)
+    ws, need = _scratch(_lib.quasar_w8_gateup_workspace_bytes(M, I, K, gamma is not None), x.device)
     _check("quasar_w8_gateup_swiglu",
            _lib.quasar_w8_gateup_swiglu_split(_ptr(x), M, K, x.stride(0), _ptr(gamma), eps, _ptr(wq_packed), _ptr(scales), I,
                                               _ptr(y), y.stride(0), _ptr(ws), need, _stream()))

@@ -35,6 +35,7 @@ decltype(&quasar_w4_workspace_bytes) p_w4_workspace_bytes;
 decltype(&quasar_w8_linear_fused_split) p_w8_linear_fused;
 decltype(&quasar_w8_gateup_swiglu_split) p_w8_gateup_swiglu;
 decltype(&quasar_w8_fused_workspace_bytes) p_w8_fused_workspace_bytes;
+decltype(&quasar_w8_gateup_workspace_bytes) p_w8_gateup_workspace_bytes;
 PyObject *g_device, *g_stream;
 
 struct NotOrdinary {};
@@ -215,21 +216,20 @@ PyObject *w8_gateup_swiglu(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const Activations x(a[0]);
         const void *w = cuda_tensor(a[1], at::kChar).data_ptr(), *sc = cuda_tensor(a[2], at::kBFloat16).data_ptr();
         const int64_t I = integer(a[3]);
-        if (I < 0 || I > (1 << 25)) throw NotOrdinary{};
         const Gamma gamma(a[4], x.K);
         const float eps = real(a[5]);
         const Output y(a[6]);
-        return call_with_scratch(p_w8_gateup_swiglu, p_w8_fused_workspace_bytes(x.M, 2 * I, x.K, gamma.p != nullptr, 0), current_stream(),
+        return call_with_scratch(p_w8_gateup_swiglu, p_w8_gateup_workspace_bytes(x.M, I, x.K, gamma.p != nullptr), current_stream(),
                                  x.x, x.M, x.K, x.ldx, gamma.p, eps, static_cast<const int8_t *>(w), static_cast<const uint16_t *>(sc), I,
                                  y.y, y.ldy);
     });
 }
 
-// (addresses of the ten entry points, current device, current raw stream)
+// (addresses of the eleven entry points, current device, current raw stream)
 PyObject *bind(PyObject *, PyObject *args) {
-    unsigned long long f[10];
+    unsigned long long f[11];
     PyObject *device, *stream;
-    if (!PyArg_ParseTuple(args, "(KKKKKKKKKK)OO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &f[7], &f[8], &f[9], &device, &stream)) return nullptr;
+    if (!PyArg_ParseTuple(args, "(KKKKKKKKKKK)OO", &f[0], &f[1], &f[2], &f[3], &f[4], &f[5], &f[6], &f[7], &f[8], &f[9], &f[10], &device, &stream)) return nullptr;
     p_w8_linear = reinterpret_cast<decltype(p_w8_linear)>(f[0]);
     p_bf16_linear = reinterpret_cast<decltype(p_bf16_linear)>(f[1]);
     p_w8a8_linear = reinterpret_cast<decltype(p_w8a8_linear)>(f[2]);
@@ -240,6 +240,7 @@ PyObject *bind(PyObject *, PyObject *args) {
     p_w8_linear_fused = reinterpret_cast<decltype(p_w8_linear_fused)>(f[7]);
     p_w8_gateup_swiglu = reinterpret_cast<decltype(p_w8_gateup_swiglu)>(f[8]);
     p_w8_fused_workspace_bytes = reinterpret_cast<decltype(p_w8_fused_workspace_bytes)>(f[9]);
+    p_w8_gateup_workspace_bytes = reinterpret_cast<decltype(p_w8_gateup_workspace_bytes)>(f[10]);
     Py_INCREF(device);
     Py_INCREF(stream);
     g_device = device;

@@ -1788,6 +1788,12 @@ size_t quasar_w8_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int has_
     return norm + (norm || (has_residual && !has_gamma) ? free_split_bytes((int)M, (int)N, (int)K) : 0);
 }
 
+// (the gate/up form never splits K)
+size_t quasar_w8_gateup_workspace_bytes(int64_t M, int64_t I, int64_t K, int has_gamma) {
+    if (I < 16 || I % 16 || I > (1 << 25) || check_mnk(M, 2 * I, K)) return 0;
+    return fused_norm_bytes((int)M, (int)K, has_gamma != 0);
+}
+
 int quasar_w8_linear_fused_split(const uint16_t *x, int64_t M, int64_t K, int64_t ldx, const uint16_t *gamma, float eps,
                                  const int8_t *wq_packed, const uint16_t *scales_bf16, int64_t N, const uint16_t *residual,
                                  int64_t ldr, uint16_t *y, int64_t ldy, void *workspace, size_t workspace_bytes,

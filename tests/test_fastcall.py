@@ -129,8 +129,9 @@ def test_calls_with_scratch(qb, kind):
             "residual": lambda x, y: qb.w8_linear_fused(x, wq, sc, N, residual=res, y=y),
             "gated": lambda x, y: qb.w8_gateup_swiglu(x, wq, sc, N // 2, gamma=gamma, y=y)}[kind]
     lib = qb.lib()
-    assert {"w8a8": lib.quasar_w8a8_workspace_bytes(M, N, K), "int4": lib.quasar_w4_workspace_bytes(M, N, K)}.get(
-        kind, lib.quasar_w8_fused_workspace_bytes(M, N, K, kind != "residual", kind == "residual")) > 0
+    assert {"w8a8": lib.quasar_w8a8_workspace_bytes(M, N, K), "int4": lib.quasar_w4_workspace_bytes(M, N, K),
+            "gated": lib.quasar_w8_gateup_workspace_bytes(M, N // 2, K, 1)}.get(
+                kind, lib.quasar_w8_fused_workspace_bytes(M, N, K, kind != "residual", kind == "residual")) > 0
     y.fill_(7.0)
     assert native() == 0
     want = call(x.as_subclass(_Sub), torch.empty_like(y))

@@ -36,7 +36,8 @@ def test_fused_with_scratch(M, N, K, kind):
     gamma = (1 + 0.2 * torch.randn(K, generator=gen, device="cuda")).bfloat16() if kind != "residual" else None
     out = N // 2 if kind == "gated" else N
     residual = torch.randn(M, out, generator=gen, device="cuda").bfloat16() if kind in ("residual", "both") else None
-    need = qb.lib().quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None)
+    need = qb.lib().quasar_w8_gateup_workspace_bytes(M, N // 2, K, 1) if kind == "gated" else \
+        qb.lib().quasar_w8_fused_workspace_bytes(M, N, K, gamma is not None, residual is not None)
     want = torch.empty((M, out), dtype=torch.bfloat16, device="cuda")
     _call(qb, x, wq, sc, N, gamma, residual, want, kind == "gated", None, 0)
     for room in (need, need // 2, 15):

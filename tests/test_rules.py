@@ -15,3 +15,13 @@ def test_slices_of_a_long_k(lib, M, N, K, least, most):
     """Many slices where the second launch is cheap beside them; one where the kernel ends before the host has launched twice."""
     slices = lib.quasar_w8_fused_workspace_bytes(M, N, K, 0, 1) // (4 * M * N) or 1
     assert least <= slices <= most
+
+
+@pytest.mark.parametrize("M,I,K", [(32, 28672, 8192), (32, 16384, 6144), (9, 2048, 4160), (8, 2048, 8256), (32, 2048, 2112), (17, 16, 2112), (32, 2048, 2048)])
+def test_scratch_of_the_gateup_form(lib, M, I, K):
+    """Normalised activations and nothing else: the form never splits K."""
+    apart = K > (8192 if M <= 8 else 4096 if M <= 16 else 2048)
+    assert lib.quasar_w8_gateup_workspace_bytes(M, I, K, 1) == (2 * M * K if apart else 0)
+    assert lib.quasar_w8_gateup_workspace_bytes(M, I, K, 0) == 0
+    for bad in ((M, I + 8, K), (M, 0, K), (M, -16, K), (M, 1 << 26, K), (33, I, K), (M, I, K + 1), (M, 1 << 62, K)):
+        assert lib.quasar_w8_gateup_workspace_bytes(*bad, 1) == 0
