@@ -332,7 +332,9 @@ bool plan_outer(int fmt, int MP, int T, int S, int ksplit, DirectPlan &d) {
 // the average share, which all divisions have in common), its activations at 50, 2.8 us (W8A8; 4-bit 2.0) for a second launch
 // and 0.7 us per MB of partial sums.  Fitted to times of 1 to 8 slices; us:
 //   W8A8 (quantiser included), 1, 2, 3, 4 slices: 5120 x 25600, M = 32 46, 38, 35, 34.5 and M = 8 35, 33, 32, 33; 4096 x 12288, M = 32
-//     21.8, 20.3, 19.9, 18.9 and M = 8 15.8, 18.4, 18.4, 17.6; 12288 x 4096, M = 32 15.6, 19.9
+//     21.8, 20.3, 19.9, 18.9 and M = 8 15.8, 18.4, 18.4, 17.6; 12288 x 4096, M = 32 15.6, 19.9; up to 16 tokens an estimate of up to
+//     4.2 us (K up to 6336) stays in one piece, whose third launch takes the host 3.5 us (eagerly, 1, 8 slices: 1024 x 6144, M = 16
+//     10.0, 11.1 and 9.6, 10.6 in a graph; 16 x 5184, M = 9 8.6, 9.8 and 8.3, 8.1)
 //   4-bit, 1, 2, 3, 4, 6 slices: 5120 x 25600, M = 32 57, 39, 33, 31, 28; 4096 x 12288, M = 32 29, 20, 18, 17, 17 and M = 16 17.5, 15.3,
 //     14.5, 13.5, 16.3 (seven tiles); 25600 x 5120, M = 32 25.6
 bool plan_outer_split(int fmt, int MP, int M, int T, int S, int N, size_t room, DirectPlan &best) {
@@ -347,6 +349,7 @@ bool plan_outer_split(int fmt, int MP, int M, int T, int S, int N, size_t room, 
         double us = d.slice_steps * (d.XS / 45.0 + x_kb / 50.0);
         if (ks > 1) us += (fmt == FMT_W4 ? 2.0 : 2.8) + 0.7e-6 * (double)splitk_bytes(M, N, ks);
         if (!found || us < best_us) { best = d; best_us = us; found = true; }
+        if (fmt == FMT_A8 && MP < 32 && ks == 1 && us <= 4.2) break;
     }
     return found;
 }
@@ -824,13 +827,19 @@ bool plan_direct_w8a8(int MP, int T, int S, bool smooth, DirectPlan &d) {
 size_t a8_code_bytes(int MP, int S) { return (size_t)S * 64u * (size_t)MP; }
 
 // Whether that is the faster way, and its plan for a workspace of `room` bytes.  Quantising in every workgroup costs by M x K
-// (and by the registers that hold the codes), the launch 2.8 us; us of a call, in every workgroup -> apart:
-//   M <= 8:   4096 x 4096 7.9 -> 9.1, 12288 x 4096 12.5 -> 14.1, 5120 x 8192 14.1 -> 16.2, 4096 x 12288 19.0 -> 15.9
+// (and by the registers that hold the codes), the launch 2.8 us on the GPU and 3.5 us of the host; us of a call in a graph, in every
+// workgroup -> apart:
+//   M <= 8:   4096 x 4096 7.9 -> 9.1, 12288 x 4096 12.5 -> 14.1, 4096 x 12288 19.0 -> 15.9; ten slots (K up to 10240): 1024 x 8256
+//             10.0 -> 11.0, 4096 x 10240 12.4 -> 13.2, but slots that only fill the form cost at every tile: 8192 x 8256 (31 of 160)
+//             18.8 -> 17.9, 12288 x 9216 24.3 -> 23.4, 8192 x 9216 18.8 -> 19.0, 8192 x 10240 (none) 19.0 -> 20.2; few rows: 16 x 12288 12.3 ->
+//             9.3 though eagerly 10.2 -> 11.9 (three launches)
 //   M <= 16:  4096 x 4096 9.1 -> 9.6, 25600 x 5120 27.3 -> 28.2, 4096 x 6144 18.6 -> 13, 5120 x 8192 25.4 -> 17.2, 4096 x 12288 32.5 -> 16.7
-//   M <= 32:  1024 x 1024 7.9 -> 7.1, 4096 x 4096 22.5 -> 11.6, 12288 x 4096 29.7 -> 15.5, 25600 x 5120 56 -> 28.7
+//   M <= 32:  1024 x 1024 M = 17 / 24 / 32 6.9 / 7.5 / 8.1 -> 6.8 / 7.4 / 7.4 (eagerly 7.2 / 7.6 / 8.1, 7.8 apart), 4096 x 4096 22.5 -> 11.6,
+//             12288 x 4096 29.7 -> 15.5, 25600 x 5120 56 -> 28.7
 bool plan_w8a8_apart(int M, int N, int K, size_t room, DirectPlan &d) {
-    const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32), S = K / kStepK8;
-    if (S <= (MP == 8 ? 128 : (MP == 16 ? 80 : 15))) return false;
+    const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32), S = K / kStepK8, T = N / kTileRows;
+    if (S <= (MP == 8 ? 128 : (MP == 16 ? 80 : (M > 24 ? 15 : 16)))) return false;
+    if (MP == 8 && S <= 160 && (T < 2 * device_cus() || (160 - S) * ((T + device_cus() - 1) / device_cus()) < 48)) return false;
     const size_t head = a8_code_bytes(MP, S) + 128;
     return room >= head && plan_outer_split(FMT_A8, MP, M, N / kTileRows, S, N, room - head, d);
 }

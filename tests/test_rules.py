@@ -25,3 +25,18 @@ def test_scratch_of_the_gateup_form(lib, M, I, K):
     assert lib.quasar_w8_gateup_workspace_bytes(M, I, K, 0) == 0
     for bad in ((M, I + 8, K), (M, 0, K), (M, -16, K), (M, 1 << 26, K), (33, I, K), (M, I, K + 1), (M, 1 << 62, K)):
         assert lib.quasar_w8_gateup_workspace_bytes(*bad, 1) == 0
+
+
+# where a call is so short that it is the host that launches it which bounds it, and where the activations' registers do
+@pytest.mark.parametrize("M,N,K,apart", [(17, 16, 1024, False), (24, 4096, 1024, False), (25, 16, 1024, True), (32, 1024, 1024, True), (17, 16, 1088, True),
+                                         (9, 16, 5120, False), (9, 16, 5184, True), (8, 4096, 8192, False), (1, 4096, 8256, False),
+                                         (8, 1024, 10240, False), (8, 8192, 8256, True), (8, 8192, 9216, False), (8, 12288, 9216, True),
+                                         (8, 25600, 10240, False), (1, 16, 10304, True), (8, 4096, 12288, True)])
+def test_w8a8_quantised_apart(lib, M, N, K, apart):
+    assert (lib.quasar_w8a8_workspace_bytes(M, N, K) > 0) == apart
+
+
+@pytest.mark.parametrize("M,N,K,split", [(9, 16, 5184, False), (16, 1024, 6144, False), (16, 1024, 6400, True), (32, 256, 4096, True)])
+def test_w8a8_split(lib, M, N, K, split):
+    head = K // 64 * 64 * (8 if M <= 8 else 16 if M <= 16 else 32) + 128
+    assert (lib.quasar_w8a8_workspace_bytes(M, N, K) > head) == split
