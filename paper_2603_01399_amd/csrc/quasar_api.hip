@@ -854,9 +854,12 @@ int launch_w8a8(const GemmParams &base, int M, hipStream_t stream, int *grid_out
     DirectPlan d{};
     if (EPI == EPI_ARGMAX && MP == 32 && p.S >= 16) {
         // the vocabulary of more than 16 tokens: codes from a launch of their own, behind the keys of the workgroups (us, M = 32, in
-        // every workgroup -> apart: 151936 x 4096 131.6 -> 103.5, 151936 x 5120 160.7 -> 128.1, 32000 x 1024 22.9 -> 20.0)
+        // every workgroup -> apart: 151936 x 4096 131.6 -> 103.5, 151936 x 5120 160.7 -> 128.1, 32000 x 1024 22.9 -> 20.0).  Not where the
+        // call is short: a third launch takes the host longer than it saves (eagerly, M = 17 1024 x 1024 10.6 -> 12.9, 1024 x 2048
+        // 12.4 -> 12.7, M = 24 2048 x 1024 11.8 -> 12.9)
         const size_t at = kMaxGrid * 4 * 32, head = at + a8_code_bytes(MP, p.S);
-        if (workspace_bytes >= head + 128 && plan_direct_w8a8(MP, p.T, p.S, false, d) && d.XS <= 6 && (size_t)d.groups * MP * 8 <= at) {
+        const bool long_enough = p.T > 128 || (long long)M * p.K > 60000;
+        if (long_enough && workspace_bytes >= head + 128 && plan_direct_w8a8(MP, p.T, p.S, false, d) && d.XS <= 6 && (size_t)d.groups * MP * 8 <= at) {
             unsigned char *codes = static_cast<unsigned char *>(workspace) + at;
             float *dx = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + head);
             if (const int e = launch_quantize_operand(p, MP, codes, dx, stream)) return e;

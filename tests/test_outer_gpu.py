@@ -119,7 +119,7 @@ def test_scratch_routes_under_capture(kind):
         assert torch.equal(y.view(torch.int16), want.view(torch.int16))
 
 
-@pytest.mark.parametrize("M,V,K", [(17, 16, 1024), (32, 16 * 300, 1088), (24, 16 * 1100, 4096), (32, 16 * 257, 5120), (20, 16 * 40, 6144), (20, 16 * 40, 6208)])
+@pytest.mark.parametrize("M,V,K", [(17, 16, 1024), (24, 2048, 2048), (17, 2064, 1024), (32, 16 * 300, 1088), (24, 16 * 1100, 4096), (32, 16 * 257, 5120), (20, 16 * 40, 6144), (20, 16 * 40, 6208)])
 @pytest.mark.parametrize("smoothed", [False, True])
 def test_w8a8_vocabulary_of_many_tokens(M, V, K, smoothed):
     """Codes from a launch of their own, then the argmax: bit for bit the stated arithmetic, ties to the lowest index."""
@@ -142,3 +142,6 @@ def test_w8a8_vocabulary_of_many_tokens(M, V, K, smoothed):
     room = torch.full((ws.nbytes + 256,), 0xA5, dtype=torch.uint8, device="cuda")
     am, accepted = qb.w8a8_lmhead_verify(x, wq, sc, V, draft.contiguous(), room[:ws.nbytes], smooth=smooth)
     assert torch.equal(am, want) and int(accepted) == M // 2 and bool((room[ws.nbytes:] == 0xA5).all())
+    # the codes lie 512 KB behind the start; short calls make none
+    apart = (V > 2048 or M * K > 60000) and K <= 6144
+    assert bool((room[1 << 19:(1 << 19) + M * K // 2] != 0xA5).any()) == apart
