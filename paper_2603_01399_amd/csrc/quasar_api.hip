@@ -1086,11 +1086,14 @@ bool plan_direct_w4(int MP, int T, int S, DirectPlan &d) {
 //   M <= 8:   5120 x 25600 34.1 -> 22.6 (4096 x 12288, six slots: 10.0 -> 12.0)
 //   M <= 16:  4096 x 9216 16.9 -> 12.1, 4096 x 12288 18.8 -> 13.5, 5120 x 25600 50 -> 26 (5120 x 8192, four slots: 11.7 -> 12.5)
 //   M <= 32:  8192 x 5120 16.6 -> 14.9, 25600 x 5120 39.5 -> 25.6, 5120 x 8192 36.4 -> 15.1, 4096 x 12288 48.6 -> 17.2, 5120 x 25600
-//             101 -> 28.4 (12288 x 4096, four slots: 11.6 -> 14.9)
+//             101 -> 28.4 (12288 x 4096, four slots: 11.6 -> 14.9).  Five slots (K up to 5120) and one tile a compute unit: held, for a
+//             second launch costs what the split saves (4096 x 4224 10.4 -> 10.7, 256 x 4224 8.2 -> 8.3 and eagerly 8.0 -> 9.1) except for
+//             some 64 tiles (1024 x 5120 9.3 -> 8.5); more tiles: 5120 x 4224 15.3 -> 11.6
 bool plan_w4_outer(int M, int N, int K, size_t room, DirectPlan &d) {
     if (g_w4_nw.load() != 16 || g_w4_d.load() != 2) return false;            // launch shapes asked for by hand
     const int MP = M <= 8 ? 8 : (M <= 16 ? 16 : 32), S = K / kStepK4, T = N / kTileRows;
     if (S <= (MP == 8 ? 96 : (MP == 16 ? 64 : 32))) return false;
+    if (MP == 32 && S <= 40 && T <= device_cus() && !(S > 36 && T > 32 && T <= 64)) return false;
     if (!plan_outer_split(FMT_W4, MP, M, T, S, N, room, d)) return false;
     // (five slots, one tile a workgroup and K in one piece: 4096 x 5120 at M = 32 11.3 held, 14.9 so)
     return !(MP == 32 && S <= 40 && d.ksplit == 1 && d.XS == 1);

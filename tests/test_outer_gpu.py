@@ -60,7 +60,7 @@ def test_w8a8_apart(M, N, K, smoothed):
 
 @pytest.mark.parametrize("M,N,K", [(1, 16, 12416), (8, 16 * 320, 25600), (5, 16 * 1300, 12416), (8, 16 * 2049, 12416),
                                    (9, 16, 8320), (16, 16 * 256, 12288), (13, 16 * 700, 8320), (16, 16 * 1500, 8320), (16, 16 * 1537, 8320),
-                                   (17, 16 * 40, 5120), (32, 16 * 257, 5120), (24, 16 * 700, 4224), (32, 16 * 1000, 4224),
+                                   (17, 16 * 40, 5120), (32, 16 * 64, 4736), (32, 16 * 256, 4224), (17, 16, 5120), (32, 16 * 257, 5120), (24, 16 * 700, 4224), (32, 16 * 1000, 4224),
                                    (31, 16 * 1200, 4224), (32, 16 * 1600, 5120), (32, 16 * 2049, 4224), (32, 16 * 320, 25600), (20, 16 * 16, 33024)])
 def test_w4_outer(M, N, K):
     """Outputs against a 64-bit product with the dequantised codes: 4e-3 of max|y|, as for the kernel that holds x."""

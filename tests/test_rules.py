@@ -36,6 +36,12 @@ def test_w8a8_quantised_apart(lib, M, N, K, apart):
     assert (lib.quasar_w8a8_workspace_bytes(M, N, K) > 0) == apart
 
 
+@pytest.mark.parametrize("M,N,K,split", [(17, 16, 4224, False), (32, 256, 5120, False), (32, 1024, 4608, False), (32, 512, 5120, False), (32, 1024, 5120, True),
+                                         (32, 2048, 5120, False), (32, 4096, 5120, False), (32, 4112, 4224, True), (17, 16, 5248, True), (16, 256, 8320, True)])
+def test_w4_split(lib, M, N, K, split):
+    assert (lib.quasar_w4_workspace_bytes(M, N, K) > 0) == split
+
+
 @pytest.mark.parametrize("M,N,K,split", [(9, 16, 5184, False), (16, 1024, 6144, False), (16, 1024, 6400, True), (32, 256, 4096, True)])
 def test_w8a8_split(lib, M, N, K, split):
     head = K // 64 * 64 * (8 if M <= 8 else 16 if M <= 16 else 32) + 128
