@@ -104,8 +104,7 @@ def main() -> int:
     import torch
     from paper_2603_01399_amd import binding as qb, synth
     if os.environ.get("QUASAR_BENCH_LIB"):           # A/B runs of alternative builds of the library
-        qb.LIB_PATH = os.environ["QUASAR_BENCH_LIB"]
-        qb._lib = qb._load()
+        qb.use_library(os.environ["QUASAR_BENCH_LIB"])
 
     assert torch.cuda.is_available(), "bench.py needs the MI355X"
     torch.cuda.set_device(0)

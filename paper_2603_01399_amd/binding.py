@@ -177,11 +177,29 @@ if not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
     raise ImportError(f"{_HERE}/_fastcall.so is missing: build it with `python -m paper_2603_01399_amd.build`")
 from . import _fastcall as _fast  # noqa: E402
 
-_fast.bind(tuple(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value
-                 for n in ("quasar_w8_linear", "quasar_bf16_linear", "quasar_w8a8_linear_split", "quasar_w4_linear_split", "quasar_w4_packed_bytes",
-                           "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes", "quasar_w8_linear_fused_split",
-                           "quasar_w8_gateup_swiglu_split", "quasar_w8_fused_workspace_bytes", "quasar_w8_gateup_workspace_bytes")),
-           _current_device, _current_raw_stream)
+_NATIVE_ENTRIES = ("quasar_w8_linear", "quasar_bf16_linear", "quasar_w8a8_linear_split", "quasar_w4_linear_split", "quasar_w4_packed_bytes",
+                   "quasar_w8a8_workspace_bytes", "quasar_w4_workspace_bytes", "quasar_w8_linear_fused_split",
+                   "quasar_w8_gateup_swiglu_split", "quasar_w8_fused_workspace_bytes", "quasar_w8_gateup_workspace_bytes")
+
+
+def _native_addresses(lib):
+    return tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _NATIVE_ENTRIES)
+
+
+def use_library(path: str) -> None:
+    """Every call from here on goes to this build of the library (comparisons of builds; not while other threads make calls)."""
+    global LIB_PATH, _lib
+    before, LIB_PATH = LIB_PATH, path
+    try:
+        lib = _load()
+        _fast.bind(_native_addresses(lib), _current_device, _current_raw_stream)
+    except BaseException:
+        LIB_PATH = before
+        raise
+    _lib = lib
+
+
+_fast.bind(_native_addresses(_lib), _current_device, _current_raw_stream)
 
 
 def _ptr(t):

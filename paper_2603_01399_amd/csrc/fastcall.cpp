@@ -243,15 +243,23 @@ PyObject *bind(PyObject *, PyObject *args) {
     p_w8_gateup_workspace_bytes = reinterpret_cast<decltype(p_w8_gateup_workspace_bytes)>(f[10]);
     Py_INCREF(device);
     Py_INCREF(stream);
-    g_device = device;
-    g_stream = stream;
+    Py_XSETREF(g_device, device);
+    Py_XSETREF(g_stream, stream);
     Py_RETURN_NONE;
+}
+
+// the addresses that bind() was given
+PyObject *bound(PyObject *, PyObject *) {
+    auto at = [](auto *entry) { return static_cast<unsigned long long>(reinterpret_cast<uintptr_t>(entry)); };
+    return Py_BuildValue("(KKKKKKKKKKK)", at(p_w8_linear), at(p_bf16_linear), at(p_w8a8_linear), at(p_w4_linear), at(p_w4_packed_bytes),
+                         at(p_w8a8_workspace_bytes), at(p_w4_workspace_bytes), at(p_w8_linear_fused), at(p_w8_gateup_swiglu),
+                         at(p_w8_fused_workspace_bytes), at(p_w8_gateup_workspace_bytes));
 }
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(w8_linear), FAST(bf16_linear), FAST(w8a8_linear), FAST(w4_linear),
                          FAST(w8_linear_fused), FAST(w8_gateup_swiglu),
-                         {"bind", bind, METH_VARARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+                         {"bind", bind, METH_VARARGS, nullptr}, {"bound", bound, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -2,6 +2,7 @@
 raises as it did (CPU), and the ordinary calls give the same bits and the same errors (GPU)."""
 import importlib.util
 import os
+import shutil
 import subprocess
 import sysconfig
 
@@ -61,6 +62,24 @@ def test_lock_after_an_exception(tmp_path):
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
     assert module.run() == (1, -1)
+
+
+def test_another_build_of_the_library(qb, tmp_path):
+    """use_library: the native side calls the library that the ctypes calls go to; a file that cannot be loaded changes nothing."""
+    path, lib = qb.LIB_PATH, qb.lib()
+    assert qb._fast.bound() == qb._native_addresses(lib)
+    other = tmp_path / "other.so"
+    shutil.copy(path, other)
+    try:
+        qb.use_library(str(other))
+        assert qb.lib() is not lib and qb.LIB_PATH == str(other)
+        assert qb._fast.bound() == qb._native_addresses(qb.lib()) and not set(qb._fast.bound()) & set(qb._native_addresses(lib))
+        with pytest.raises(ImportError):
+            qb.use_library(str(tmp_path / "none.so"))
+        assert qb.LIB_PATH == str(other) and qb._fast.bound() == qb._native_addresses(qb.lib())
+    finally:
+        qb.use_library(path)
+    assert qb._fast.bound() == qb._native_addresses(lib)
 
 
 @pytest.mark.gpu
