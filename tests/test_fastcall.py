@@ -1,5 +1,6 @@
 """The linears' native marshalling: only calls of plain CUDA tensors are taken, every other one is left to the Python path, which
 raises as it did (CPU), and the ordinary calls give the same bits and the same errors (GPU)."""
+import ctypes
 import importlib.util
 import os
 import shutil
@@ -20,20 +21,73 @@ class _Sub(torch.Tensor):
     pass
 
 
-def test_what_is_not_an_ordinary_call(qb):
+def test_not_on_a_gpu_or_not_enough_arguments(qb):
     f = qb._fast
     x, w, s, y = torch.zeros(2, 128).bfloat16(), torch.zeros(4096, dtype=torch.int8), torch.zeros(16).bfloat16(), torch.zeros(2, 16).bfloat16()
-    assert f.w8_linear(x, w, s, 16, y, None) == -1                               # not on a GPU
-    assert f.w8_linear(x, w, s, 16, y) == -1 and f.w4_linear() == -1             # arguments missing
-    assert f.w8_linear(None, w, s, 16, y, None) == -1
-    assert f.w8_linear(x.as_subclass(_Sub), w, s, 16, y, None) == -1
-    assert f.bf16_linear(x, s, 2 ** 80, y, None) == -1 and f.bf16_linear(x, s, 16.0, y, None) == -1
-    assert f.w8a8_linear(x, w, s, 16, None, y) == -1 and f.w4_linear(x, w, 16, y) == -1
-    assert f.w8_linear_fused(x, w, s, 16, None, 1e-6, None, y) == -1 and f.w8_gateup_swiglu(x, w, s, 16, None, 1e-6, y) == -1
+    for call in (lambda: f.w8_linear(x, w, s, 16, y, None), lambda: f.bf16_linear(x, s, 16, y, None), lambda: f.w8a8_linear(x, w, s, 16, None, y),
+                 lambda: f.w4_linear(x, w, 16, y), lambda: f.w8_linear_fused(x, w, s, 16, None, 1e-6, None, y),
+                 lambda: f.w8_gateup_swiglu(x, w, s, 16, None, 1e-6, y), lambda: f.w8_linear(None, w, s, 16, y, None)):
+        assert call() == -1
+    assert f.w8_linear(x, w, s, 16, y) == -1 and f.w4_linear() == -1
     with pytest.raises(TypeError):
         qb.w8_linear(x, w, s, 16, y=y)                                           # what the Python path says of it
     with pytest.raises(TypeError):
         qb.w4_linear(x, w, 16, y=y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["int8", "bf16", "w8a8", "int4", "fused", "gated"])
+def test_what_is_not_an_ordinary_call(qb, kind):
+    """One thing wrong or unusual in a call that is ordinary otherwise: the native side leaves it, and the public function does what the
+    Python path does - raises (on the host, before any launch) or gives the ordinary call's bits."""
+    M, N, K = 3, 48, 256
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    w = torch.randn(N, K, generator=gen, device="cuda") * 0.02
+    wq, sc = qb.quantize_weights(torch.cat([w, w]) if kind == "gated" else w)
+    wp, w4 = qb.pack_bf16_weights(w), qb.quantize_weights_w4(w)
+    smooth = torch.rand(K, generator=gen, device="cuda") + 0.5
+    gamma = (torch.rand(K, generator=gen, device="cuda") + 0.5).bfloat16()
+    res = torch.randn(M, N, generator=gen, device="cuda").bfloat16()
+    y = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    good = {"int8": dict(x=x, wq_packed=wq, scales=sc, N=N, y=y, workspace=None), "bf16": dict(x=x, w_packed=wp, N=N, y=y, workspace=None),
+            "w8a8": dict(x=x, wq_packed=wq, scales=sc, N=N, smooth=smooth, y=y), "int4": dict(x=x, w4_packed=w4, N=N, y=y),
+            "fused": dict(x=x, wq_packed=wq, scales=sc, N=N, gamma=gamma, eps=0.0, residual=res, y=y),
+            "gated": dict(x=x, wq_packed=wq, scales=sc, I=N, gamma=gamma, eps=0.0, y=y)}[kind]
+    name = {"int8": "w8_linear", "bf16": "bf16_linear", "w8a8": "w8a8_linear", "int4": "w4_linear", "fused": "w8_linear_fused",
+            "gated": "w8_gateup_swiglu"}[kind]
+    native, public = getattr(qb._fast, name), getattr(qb, name)
+    assert native(*good.values()) == 0
+    want = y.clone()
+
+    rows = "I" if kind == "gated" else "N"
+    same = [("x", x.as_subclass(_Sub))]
+    wrong = [(rows, 2 ** 80), (rows, float(N)), (rows, True), (rows, None), ("x", x[0]), ("x", x.half()), ("x", None)]
+    weights = {"bf16": "w_packed", "int4": "w4_packed"}.get(kind, "wq_packed")
+    wrong += [(weights, good[weights].float()), (weights, good[weights].cpu())]
+    if "scales" in good:
+        wrong += [("scales", sc.float()), ("scales", None)]
+    if kind == "int4":
+        wrong += [("w4_packed", w4.flatten()[:-1])]
+    if kind == "w8a8":
+        wrong += [("smooth", smooth[:-1]), ("smooth", smooth.bfloat16()), ("smooth", torch.cat([smooth, smooth])[::2])]
+    if "gamma" in good:
+        wrong += [("gamma", gamma[:-1]), ("gamma", gamma.float()), ("gamma", torch.cat([gamma, gamma])[::2])]
+        same += [("eps", 0)]
+    if kind == "fused":
+        wrong += [("residual", torch.cat([res, res])[:M + 1]), ("residual", res[:, :-1]), ("residual", res.t().contiguous().t()), ("residual", res.float()),
+                  ("residual", res[0])]
+    for key, value in same + wrong:
+        print("not ordinary", kind, key, flush=True)
+        call = dict(good, **{key: value})
+        y.fill_(7.0)
+        assert native(*call.values()) == -1
+        if any(value is v for _, v in same):
+            assert torch.equal(public(**call).view(torch.int16), want.view(torch.int16))
+        else:
+            with pytest.raises((TypeError, ValueError, ctypes.ArgumentError, qb.QuasarError)):
+                public(**call)
+            assert bool((y == 7.0).all())
 
 
 _THROWING = """
