@@ -60,7 +60,7 @@ def _run(cmd, verbose):
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n{res.stdout}")
     lines = [l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l and l.strip()]
     if verbose and lines:
         print("\n".join(lines), flush=True)

@@ -109,3 +109,10 @@ def test_sizes_of_the_newer_formats(qb):
     assert lib.quasar_attention_workspace_bytes(8, 32, 8, 4104) > 0
     assert lib.quasar_attention_workspace_bytes(8, 30, 8, 4104) == 0 and lib.quasar_attention_workspace_bytes(8, 32, 8, 4) == 0
     assert lib.quasar_sample_workspace_bytes(8, 151936) >= 8 * 151936 * 4
+
+
+def test_a_failing_compiler_is_named():
+    """The library is built by hipcc and the argument marshalling by the host compiler: an error says whose it is."""
+    from paper_2603_01399_amd import build
+    with pytest.raises(RuntimeError, match=r"^g\+\+ failed:\n"):
+        build._run(["g++", "-fsyntax-only", "/nonexistent.cpp"], False)
