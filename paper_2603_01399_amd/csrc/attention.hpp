@@ -119,9 +119,11 @@ __global__ __launch_bounds__(256) void kv_cache_fill_kernel(const uint16_t *src,
 // ---------------------------------------------------------------------------------------------
 // Main kernel.  NQT = number of 16-row query tiles of one workgroup (rows r = m * G + g; rows at or
 // beyond M * G are padding): as many as the rows need, each costs its share of the arithmetic, of the merges and
-// 8 KB of partial sums a split.  More than 64 rows are several groups, side by side in the grid (SHARED): groups of the same
-// positions are a multiple of eight workgroups apart, so they meet in one XCD's L2 and the cache comes from memory once.
-// One launch a group, one after the other: 32 tokens of 32 / 8 heads over 4096 positions 33.8 us, now 19.9; 30011 70.3, now 52.
+// 8 KB of partial sums a split.  More than 64 rows are several groups, side by side in the grid (SHARED).  Groups of the same
+// positions are nsplit * Hkv workgroups apart: where that is a multiple of eight (any number of splits of 8 kv heads) they
+// meet in one XCD's L2 and the cache comes from memory once; else (4 kv heads and three groups: 84) they may read it more than once.
+// One launch a group, one after the other: 32 tokens of 32 / 8 heads over 4096 positions 33.7 us, now 18.9; 30011 71.6, now 48.4; three
+// groups, 17 tokens of 32 / 4 heads over 30011 78.1, now 40.5 (the merge included).
 // 1 to 4 tokens (one tile instead of two) over 4096 positions 12.4, now 9.8; 12 tokens (three instead of four) 17.5, now 14.4.
 // ---------------------------------------------------------------------------------------------
 template <int NQT, int NW, bool SHARED>
