@@ -110,8 +110,22 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
             read_x(at);
         }
     }
+    // two slots of 8 tokens: the rotated operands are kept, eight instructions a slot and tile less (25600 x 4096, M = 5 13.5 us, 13.1 so;
+    // forms of more slots have no registers for them)
+    constexpr bool KEEP = MP == 8 && XS == 2;
+    [[maybe_unused]] u32x4 xrot[XS][XP];
+    if constexpr (KEEP)
+#pragma unroll
+        for (int i = 0; i < XS; ++i)
+#pragma unroll
+            for (int j = 0; j < XP; ++j) {
+                xrot[i][j] = rotate_half_row(xr[i][j]);
+                asm volatile("" : "+v"(xrot[i][j].x), "+v"(xrot[i][j].y), "+v"(xrot[i][j].z), "+v"(xrot[i][j].w));
+            }
     auto operand = [&](int i, int nb, int j) {          // operand j (0 .. 3) of slot i
-        if constexpr (MP == 8) {
+        if constexpr (KEEP) {
+            return __builtin_bit_cast(bf16x8, (j & 1) ? xrot[i][j >> 1] : xr[i][j >> 1]);
+        } else if constexpr (MP == 8) {
             const u32x4 v = xr[i][j >> 1];
             return __builtin_bit_cast(bf16x8, (j & 1) ? rotate_half_row(v) : v);
         } else {
@@ -166,7 +180,10 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
             acc[nb].w = __builtin_fmaf(s3, grp[nb].w, acc[nb].w);
         }
     };
-    // tile end: cross-wave sum through LDS, fixed order
+    // tile end: cross-wave sum through LDS, fixed order, eight partial tiles requested together: left to itself the compiler read one after
+    // the other in most forms, 16 trips to LDS at every tile (us: 25600 x 2176, M = 1 11.4 so, 10.2 now; 25600 x 1024, M = 16 9.7, 8.4).
+    // Forms of more slots have no registers for eight (12288 x 4096 at M = 32, four slots: 10.8, 13.0 with them)
+    constexpr bool TOGETHER = XS <= (MP == 8 ? 4 : 3);
     auto tile_end = [&](int tl) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
@@ -181,9 +198,19 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
                 const unsigned char *st = lds + ((parity * NB + nb) * 64 + lane) * 16;
                 rsum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-                for (int w0 = 0; w0 < NW; w0 += 8)             // (a loop: bounds the registers of the reads in flight)
+                for (int w0 = 0; w0 < NW; w0 += 8) {           // (a loop: bounds the registers of the reads in flight)
+                    if constexpr (TOGETHER) {
+                        f32x4 v[8];
 #pragma unroll
-                    for (int ww = w0; ww < w0 + 8; ++ww) rsum[nb] += *reinterpret_cast<const f32x4 *>(st + ww * region);
+                        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4 *>(st + (w0 + j) * region);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) rsum[nb] += v[j];
+                    } else {
+#pragma unroll
+                        for (int ww = w0; ww < w0 + 8; ++ww) rsum[nb] += *reinterpret_cast<const f32x4 *>(st + ww * region);
+                    }
+                }
             }
             const u32x2 none[NB] = {};
             finish_tile<true, EPI, false, NB>(p, rsum, t0 + tl, nullptr, none, nullptr, 0, lane, bestv, besti);
