@@ -79,7 +79,9 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     const int C = PAIR ? CC : (CH ? p.C : 1);
 
     // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
-    // (bf16 weights keep the gather at four slots: seven linears of an 8B layer, 5 tokens, 79.4 us, 79.9 through LDS)
+    // (bf16 weights keep the gather at four slots, where LDS is as fast or faster call after call in a graph - 168 shapes of K 3328 to 4096
+    // 0.99 on average, 1024 x 4096 M = 8 6.2 -> 5.6 us - but slower eagerly up to five tokens: 4096 x 4096 M = 1 7.53, 7.69, M = 5 7.85,
+    // 7.95; seven linears of an 8B layer, M = 5 79.1, 79.6)
     constexpr int kPass = (KS == 32 && CC > 1) || (W16 && MP == 8 && XS == 4) ? 0 : direct_pass(MP, XS);
     static_assert(KS == 64 || CC > 1 || XS / 2 + 1 <= kPass, "slots of 32 k come in one pass of whole lines");
     const int region = max(kPass * MP * 128, PARS * C * NB * 1024);
