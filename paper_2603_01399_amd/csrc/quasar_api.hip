@@ -228,9 +228,10 @@ bool plan_direct(int MP, int T, int TU, int S, int SC, int C, int ksplit, bool w
 // How many slices a K that would otherwise be staged in chunks is split into: the cheapest of 1 .. 8 by what the busiest
 // compute unit does: 62 KB/us of weights, half of that for the loads of slots that only fill a form, 60 KB/us of activations
 // (fitted to 676 shapes, M 1 .. 32, K 2048 .. 25600, N 256 .. 16384, both weight types); a split adds a second launch, which requests all
-// slices together, 2.2 us and 0.25 us a slice, and 0.7 us per MB of partial sums.  The two figures were fitted to 540 shapes of the
-// same ranges at every number of slices: the choice is 1.3 % slower than the best one on average (2.0 and 0.6, which fitted a second launch
-// that read one slice after the other: 2.5 %; M = 16, 256 x 16384 int8 7.1 us in four slices, 6.4 in eight; 1024 x 25600 12.1, now 10.7).
+// slices together, 2.4 us and 0.4 us a slice, and 0.7 us per MB of partial sums.  The two figures were fitted to 1380 shapes of the same
+// ranges at every number of slices: the choice is 1.6 % slower than the best one on average (2.0 and 0.6, which fitted a second launch that
+// read one slice after the other: 2.2 %; int8, M = 8 3072 x 14336 14.3 us in two slices, 12.1 in four, M = 32 1024 x 16384 10.3 in four, 9.3 in eight).  2.2 and 0.25 are
+// 1.3 %, but split where one piece is better by up to 12 % (2048 x 8192 bf16, M = 1 9.0, 10.1).
 // Estimates of up to 6 us stay in one piece: the kernel is then done in 8 us, which is what a call of two launches takes the host (512 x
 // 9216, M = 1: 6.8 us, 5.6 in five slices, but 7.9 a call).
 bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t workspace_bytes, int most_slots, DirectPlan &best) {
@@ -242,7 +243,7 @@ bool plan_direct_split(int MP, int M, int T, int S, bool w16, int N, size_t work
         if (!plan_direct(MP, T, 1, S, S, 1, ks, !w16, most_slots, 0, false, d)) continue;
         const int tpw = (T + d.groups - 1) / d.groups, fill = d.XS * direct_waves(MP, d.XS) - d.slice_steps;
         double us = tpw * (w16 ? 2.0 : 1.0) * (d.slice_steps / 62.0 + fill / 30.0) + MP * 0.125 * d.slice_steps / 60.0;
-        if (ks > 1) us += 2.2 + 0.25 * ks + 0.7e-6 * (double)splitk_bytes(M, N, ks);
+        if (ks > 1) us += 2.4 + 0.4 * ks + 0.7e-6 * (double)splitk_bytes(M, N, ks);
         if (!found || us < best_us) { best = d; best_us = us; found = true; }
         if (ks == 1 && us <= 6.0) break;
     }
