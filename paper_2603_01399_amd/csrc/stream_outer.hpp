@@ -262,7 +262,8 @@ __global__ __launch_bounds__(outer_waves(MP) * 64) void stream_outer_kernel(cons
 
 // y[m, n] = bf16( (sum over K slices, in slice order, of part[slice][m][n]) * step size ): the second launch of a K split.
 // One thread per four consecutive outputs of a token; blockIdx.y is the token.  Launch-sized: what a thread waits for is one
-// trip to memory, so the slices are requested eight at a time and added in order (one after the other they cost 0.6 us each).
+// trip to memory, so the slices are requested together and added in order (one after the other they cost 0.6 us each); two, four or
+// eight of them, for requests that only repeat the last slice take their turn too (us a call, eight requested, two or four: bf16 2048 x 12288 M = 4, two slices 12.65, 12.3; int8 1024 x 12288 M = 16, four 8.1, 7.9).
 template <int FMT>
 __global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part, int ksplit, int M, int N, const uint16_t *scales,
                                                               const float *dx, const uint16_t *resid, long long ldr, uint16_t *y,
@@ -274,14 +275,19 @@ __global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part,
     u32x2 sb = {0u, 0u};
     if constexpr (FMT == FMT_INT8 || FMT == FMT_A8) sb = *reinterpret_cast<const u32x2 *>(scales + n0);
     sum_t acc = {};
-    for (int base = 0; base < ksplit; base += 8) {
-        sum_t v[8];
+    auto add = [&](int base, auto together) {
+        constexpr int R = decltype(together)::value;
+        sum_t v[R];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const sum_t *>(mine + (long long)min(base + j, ksplit - 1) * M * N);
+        for (int j = 0; j < R; ++j) v[j] = *reinterpret_cast<const sum_t *>(mine + (long long)min(base + j, ksplit - 1) * M * N);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = 0; j < R; ++j)
             if (base + j < ksplit) acc = base + j == 0 ? v[j] : acc + v[j];
-    }
+    };
+    if (ksplit <= 2) add(0, std::integral_constant<int, 2>{});
+    else if (ksplit <= 4) add(0, std::integral_constant<int, 4>{});
+    else
+        for (int base = 0; base < ksplit; base += 8) add(base, std::integral_constant<int, 8>{});
     u32x2 o;
     if constexpr (FMT == FMT_A8) {
         o = a8_outputs(acc, sb, dx[m]);

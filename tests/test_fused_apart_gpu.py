@@ -18,8 +18,8 @@ def _call(qb, x, wq, sc, N, gamma, residual, y, gated, ws, room):
         qb._check("fused", qb.lib().quasar_w8_linear_fused_split(*head, N, ptr(residual), 0 if residual is None else residual.stride(0), *tail))
 
 
-# K: first beyond each rule, ragged; the last two normalise in more than one round of registers or split K in eight
-@pytest.mark.parametrize("M,N,K", [(1, 16 * 22, 8256), (8, 16 * 258, 12288), (9, 16 * 258, 4160), (16, 16 * 40, 8256), (12, 16 * 320, 25600),
+# K: first beyond each rule, ragged, split in two to seven slices; the last two normalise in more than one round of registers or split K in eight
+@pytest.mark.parametrize("M,N,K", [(1, 16 * 22, 8256), (8, 16 * 258, 12288), (9, 16 * 258, 4160), (16, 16 * 40, 8256), (8, 16 * 128, 14336), (12, 16 * 320, 25600),
                                    (17, 16 * 258, 2112), (32, 16 * 700, 4096), (31, 16 * 40, 5184), (32, 16 * 320, 25600), (20, 16 * 16, 33024)])
 @pytest.mark.parametrize("kind", ["norm", "residual", "both", "gated"])
 def test_fused_with_scratch(M, N, K, kind):
