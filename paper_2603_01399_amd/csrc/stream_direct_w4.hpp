@@ -9,8 +9,8 @@
 //
 // What bounds it: per byte of weights twice the activations and conversions of the 8-bit kernel, so the activations' fetch
 // and, over many tiles, instruction issue.  Back to back, HBM-cold, us a launch, staged -> this:
-//     M = 8:  4096 x 4096 8.1 -> 5.7, 12288 x 4096 11.3 -> 9.7, 4096 x 12288 15.4 -> 9.2, 151936 x 4096 59.5 -> 55.7
-//     M = 16: 10.5 -> 6.0, 13.4 -> 10.4, 24.1 -> 18.4, 88.2 -> 58.8;  M = 32: 19.5 -> 7.2, 26.7 -> 11.2, 151936 x 4096 232 -> 70
+//     M = 8:  4096 x 4096 8.1 -> 5.1, 12288 x 4096 11.3 -> 9.0, 4096 x 12288 15.4 -> 9.9, 151936 x 4096 59.5 -> 55
+//     M = 16: 10.5 -> 5.8, 13.4 -> 10.0, 24.1 -> 18.4, 88.2 -> 57;  M = 32: 19.5 -> 7.1, 26.7 -> 11.2, 151936 x 4096 232 -> 66
 // Longer shares of K: linears in stream_outer.hpp (plan_w4_outer), argmax and other launch shapes in the staged kernel.
 #pragma once
 
