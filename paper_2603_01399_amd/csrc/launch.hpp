@@ -32,10 +32,10 @@ inline bool allow_large_lds(const void *fn) {
 }
 
 template <typename KernelT>
-int launch(KernelT kernel, int grid, int block, int lds_bytes, hipStream_t stream, const GemmParams &p) {
+int launch(KernelT kernel, dim3 grid, int block, int lds_bytes, hipStream_t stream, const GemmParams &p) {
     if (lds_bytes > kMaxLds) return QUASAR_ERR_SHAPE;
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return QUASAR_ERR_HIP;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds_bytes, stream, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(block), lds_bytes, stream, p);
     return hipGetLastError() == hipSuccess ? QUASAR_OK : QUASAR_ERR_HIP;
 }
 
@@ -136,6 +136,17 @@ constexpr int a8_region_bytes(int MP, int XS) {
     return 16 * (x > tiles ? x : tiles);
 }
 
+// What a kernel needs ahead of its first load, pinned so that it comes in one trip to the kernel arguments; the compiler otherwise loads
+// each value in front of its first use, up to four trips one after the other.  That, the divisions of the tile shares and those
+// of a K split (now a dimension of the grid) were why the last wave of a workgroup reached its first load 1.3 us after
+// the kernel began (the first one 0.2 us: the set-up runs side by side, four waves to a SIMD).  us a launch, HBM-cold, one after the other,
+// before -> so: int8, M = 8 1024 x 4096 4.89 -> 4.50, 4096 x 4096 5.69 -> 5.32, 12288 x 4096 10.54 -> 10.20; 4-bit 4096 x 4096 5.15 -> 4.87;
+// W8A8 4096 x 4096 6.86 -> 6.65; bf16 1024 x 4096 6.33 -> 6.21.
+template <typename... V>
+__device__ __forceinline__ void loaded_together(V... v) {
+    (..., ([](auto one) { asm volatile("" ::"s"(one)); }(v)));
+}
+
 // formats of weights and activations
 enum { FMT_INT8 = 0, FMT_BF16 = 1, FMT_W4 = 2, FMT_A8 = 3 };
 // ---- the kernel with K outermost (stream_outer.hpp): FMT_A8 and FMT_W4 ----
@@ -157,6 +168,13 @@ struct DirectPlan {
     int XS, SC, C, ksplit, slice_steps, groups, sc_bytes, lds_bytes;
     bool pair;       // 32 tokens in the order of sixteen waves
 };
+
+// units of TU tiles over the workgroups
+inline void share_tiles(GemmParams &p, const DirectPlan &d, int TU) {
+    p.groups = d.groups;
+    p.tq = p.T / TU / d.groups;
+    p.tr = p.T / TU % d.groups;
+}
 
 // p: as for the other kernels (its step counts are replaced by slots of 64 k).  epi, pre, resid: EPI_*, PRE_* and whether a
 // residual is added.

@@ -56,26 +56,24 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
     constexpr int kSlotBytes = WL * kStepBytes;
 
+    const int slice = blockIdx.x, b = blockIdx.y;
     GemmParams p = p0;
-    int G = gridDim.x, b = blockIdx.x, slice = 0;
-    if (p0.ksplit > 1) {
-        slice = b % p0.ksplit;
-        b = b / p0.ksplit;
-        G = G / p0.ksplit;
-        const int s0 = slice * p0.slice_steps;      // (all step counts here are in slots of 64 k)
-        p.S = min(p0.slice_steps, p0.S - s0);
-        p.w = p0.w + (long long)s0 * (64 * WL);
-        p.x = p0.x + (long long)s0 * 64;
-    }
+    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.Srow, p.slice_steps, p.sc_bytes, p.tq, p.tr);
+    if constexpr (CH) loaded_together(p.SC, p.C);
+    const int s0 = slice * p0.slice_steps;          // (all step counts here are in slots of 64 k; one slice: all of K)
+    p.S = min(p0.slice_steps, p0.S - s0);
+    p.w = p0.w + (long long)s0 * (64 * WL);
+    p.x = p0.x + (long long)s0 * 64;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
 
     constexpr int TU = EPI == EPI_SWIGLU ? 2 : 1;   // tiles are handed out in units of TU
-    const int t0 = TU * tile_split(p.T / TU, b, G);
-    const int t1 = TU * tile_split(p.T / TU, b + 1, G);
-    const int ntiles = t1 - t0;
+    // (vocabularies are cut as the sampler's blocks are; the cut is also the faster one there: V = 151936, M = 8 100 us, 102 to 108 with share_begin)
+    constexpr bool EVEN = EPI == EPI_ARGMAX || EPI == EPI_LOGITS;
+    const int t0 = EVEN ? tile_split(p.T, b, p.groups) : TU * share_begin(p.tq, p.tr, b);
+    const int ntiles = EVEN ? tile_split(p.T, b + 1, p.groups) - t0 : TU * share_count(p.tq, p.tr, b);
     const int C = PAIR ? CC : (CH ? p.C : 1);
 
     // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
@@ -445,8 +443,8 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
             if (tid < p.M) {
                 float m = red[2 * tid], s = red[2 * tid + 1];
                 for (int ww = 1; ww < NW; ++ww) softmax_merge(m, s, red[(ww * MP + tid) * 2], red[(ww * MP + tid) * 2 + 1]);
-                p.soft_stats[((long long)tid * G + b) * 2] = m;
-                p.soft_stats[((long long)tid * G + b) * 2 + 1] = s;
+                p.soft_stats[((long long)tid * p.groups + b) * 2] = m;
+                p.soft_stats[((long long)tid * p.groups + b) * 2 + 1] = s;
             }
         }
     }
@@ -455,7 +453,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
 // ---- dispatch over the built forms ----
 
 template <int MP, bool W16, int EPI, int CH, int PRE, bool RES, int... XS>
-int launch_direct_forms(int xs, int grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
+int launch_direct_forms(int xs, dim3 grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
     int rc = QUASAR_ERR_SHAPE;
     ((xs == XS ? (void)(rc = launch(stream_direct_kernel<MP, W16, EPI, XS, CH, PRE, RES>, grid, direct_waves(MP, XS) * 64, lds_bytes,
                                     stream, p))
@@ -469,15 +467,16 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
     p.SC = d.SC;
     p.C = d.C;
     p.ksplit = d.ksplit;
-    p.slice_steps = d.slice_steps;
+    p.slice_steps = d.ksplit > 1 ? d.slice_steps : p.S;
     p.sc_bytes = d.sc_bytes;
     p.xs_bytes = 0;
-    const int grid = d.groups * d.ksplit;
+    share_tiles(p, d, EPI == EPI_SWIGLU ? 2 : 1);
+    const dim3 grid((unsigned int)d.ksplit, (unsigned int)d.groups);
     if constexpr (PRE == PRE_NONE && !RES && (EPI == EPI_LINEAR || EPI == EPI_ARGMAX)) {
         // (CH: slots of a share)
         if (d.pair) {
             if constexpr (W16) {
-                p.S = p.Srow = p.K / 32;
+                p.S = p.Srow = p.slice_steps = p.K / 32;
                 if constexpr (EPI == EPI_ARGMAX)
                     if (d.C > 1) return launch_direct_forms<32, W16, EPI, 2, PRE, RES, 8, 12, 16, 20>(d.XS, grid, d.lds_bytes, stream, p);
                 if (d.XS == 2) return launch_direct_forms<32, W16, EPI, 1, PRE, RES, 2>(d.XS, grid, d.lds_bytes, stream, p);

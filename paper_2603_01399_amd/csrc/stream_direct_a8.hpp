@@ -52,9 +52,13 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
-    const int G = gridDim.x, b = blockIdx.x;
-    const int t0 = tile_split(p.T, b, G);
-    const int ntiles = tile_split(p.T, b + 1, G) - t0;
+    const int b = blockIdx.x;
+    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.sc_bytes, p.tq, p.tr);
+    if constexpr (SMOOTH) loaded_together(p.smooth);
+    if constexpr (PREQ) loaded_together(p.dx);
+    constexpr bool EVEN = EPI == EPI_ARGMAX;         // (stream_direct.hpp)
+    const int t0 = EVEN ? tile_split(p.T, b, p.groups) : share_begin(p.tq, p.tr, b);
+    const int ntiles = EVEN ? tile_split(p.T, b + 1, p.groups) - t0 : share_count(p.tq, p.tr, b);
 
     constexpr int kPass = a8_pass(MP, XS);
     constexpr int region = a8_region_bytes(MP, XS) / NW;

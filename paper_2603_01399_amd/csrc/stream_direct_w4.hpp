@@ -34,9 +34,11 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
-    const int G = gridDim.x, b = blockIdx.x;
-    const int t0 = tile_split(p.T, b, G);
-    const int ntiles = tile_split(p.T, b + 1, G) - t0;
+    const int b = blockIdx.x;
+    loaded_together(p.x, p.ldx, p.w, p.M, p.S, p.tq, p.tr);
+    constexpr bool EVEN = EPI == EPI_ARGMAX;         // (stream_direct.hpp)
+    const int t0 = EVEN ? tile_split(p.T, b, p.groups) : share_begin(p.tq, p.tr, b);
+    const int ntiles = EVEN ? tile_split(p.T, b + 1, p.groups) - t0 : share_count(p.tq, p.tr, b);
 
     const int first = (p.S * w) / NW;
     const int n = (p.S * (w + 1)) / NW - first;

@@ -46,6 +46,9 @@ struct GemmParams {
     float *soft_stats;
     float inv_t;
     const float *dx;           // step sizes of the activation codes (stream_outer.hpp), [M]
+    // the kernels of stream_direct*.hpp and stream_outer.hpp: workgroups that share the tiles, units of tiles of each, units left over
+    // (share_begin)
+    int groups, tq, tr;
 };
 
 // Operation applied to the activations while they are staged (the normalisation in front of

@@ -56,19 +56,19 @@ __global__ __launch_bounds__(outer_waves(MP) * 64) void stream_outer_kernel(cons
     constexpr int OPS = FMT == FMT_W4 ? 4 : 1;               // B operands a slot and 16 tokens
     typedef std::conditional_t<FMT == FMT_A8, i32x4, f32x4> sum_t;
 
-    const int slice = p0.ksplit > 1 ? blockIdx.x % p0.ksplit : 0;
-    const int b = p0.ksplit > 1 ? blockIdx.x / p0.ksplit : blockIdx.x;
-    const int G = p0.ksplit > 1 ? gridDim.x / p0.ksplit : gridDim.x;
-    const int s0 = slice * p0.slice_steps;
-    const int S = p0.ksplit > 1 ? min(p0.slice_steps, p0.S - s0) : p0.S;
+    const int slice = blockIdx.x, b = blockIdx.y;
     const GemmParams &p = p0;
+    loaded_together(p.x, p.w, p.S, p.Srow, p.slice_steps, p.tq, p.tr);
+    if constexpr (FMT == FMT_A8) loaded_together(p.scales);
+    else loaded_together(p.ldx, p.M);
+    const int s0 = slice * p.slice_steps;
+    const int S = min(p.slice_steps, p.S - s0);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
-    const int t0 = tile_split(p.T, b, G);
-    const int ntiles = tile_split(p.T, b + 1, G) - t0;       // <= NT
+    const int t0 = share_begin(p.tq, p.tr, b), ntiles = share_count(p.tq, p.tr, b);       // <= NT
     const int n = (S - w + NW - 1) / NW;                     // the wave's slots: w, w + NW, ..
 
     // ---- where the lane reads x
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) void splitk_finalize_kernel(const float *part,
 // ---- dispatch over the built forms ----
 
 template <int FMT, int MP, int... NT>
-int launch_outer_forms(int nt, int grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
+int launch_outer_forms(int nt, dim3 grid, int lds_bytes, hipStream_t stream, const GemmParams &p) {
     int rc = QUASAR_ERR_SHAPE;
     ((nt == NT ? (void)(rc = launch(stream_outer_kernel<FMT, MP, NT>, grid, outer_waves(MP) * 64, lds_bytes, stream, p)) : (void)0), ...);
     return rc;
@@ -329,8 +329,9 @@ int launch_outer_as(const GemmParams &base, int MP, const DirectPlan &d, hipStre
     GemmParams p = base;
     p.S = p.Srow = p.K / outer_slot_k(FMT);
     p.ksplit = d.ksplit;
-    p.slice_steps = d.slice_steps;
-    const int grid = d.groups * d.ksplit;
+    p.slice_steps = d.ksplit > 1 ? d.slice_steps : p.S;
+    share_tiles(p, d, 1);
+    const dim3 grid((unsigned int)d.ksplit, (unsigned int)d.groups);
     if (MP == 8) return launch_outer_forms<FMT, 8, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
     if (MP == 16) {
         if constexpr (outer_tiles(FMT, 16) == 6) return launch_outer_forms<FMT, 16, 1, 2, 3, 4, 5, 6>(d.XS, grid, d.lds_bytes, stream, p);
