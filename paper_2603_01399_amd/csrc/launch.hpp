@@ -142,13 +142,60 @@ constexpr int a8_region_bytes(int MP, int XS) {
 // the kernel began (the first one 0.2 us: the set-up runs side by side, four waves to a SIMD).  us a launch, HBM-cold, one after the other,
 // before -> so: int8, M = 8 1024 x 4096 4.89 -> 4.50, 4096 x 4096 5.69 -> 5.32, 12288 x 4096 10.54 -> 10.20; 4-bit 4096 x 4096 5.15 -> 4.87;
 // W8A8 4096 x 4096 6.86 -> 6.65; bf16 1024 x 4096 6.33 -> 6.21.
-template <typename... V>
-__device__ __forceinline__ void loaded_together(V... v) {
-    (..., ([](auto one) { asm volatile("" ::"s"(one)); }(v)));
+// (one statement: in several, the loads of the later ones wait for the first; constants need no register)
+template <class A, class B, class C, class D, class E = int, class F = int, class G = int, class H = int>
+__device__ __forceinline__ void loaded_together(A a, B b, C c, D d, E e = 0, F f = 0, G g = 0, H h = 0, int i = 0, int j = 0, int k = 0, int l = 0,
+                                                int m = 0, int n = 0, int o = 0, int q = 0) {
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "is"(e), "is"(f), "is"(g), "is"(h), "is"(i), "is"(j), "is"(k), "is"(l), "is"(m), "is"(n),
+                 "is"(o), "is"(q));
 }
 
 // formats of weights and activations
 enum { FMT_INT8 = 0, FMT_BF16 = 1, FMT_W4 = 2, FMT_A8 = 3 };
+
+// Whether the workgroups of a register-resident form (XS slots a wave of NW) are dealt their tiles (TileShare).  Contiguous shares keep
+// 256 streams some MB apart open, which costs address translation and leaves some XCDs behind the others by a tenth of a
+// long stream.  us, contiguous, dealt, M = 8 unless said: vocabulary of 151936, K = 4096, int8 99.9, 94.9, W8A8 103.5, 98.2, bf16 188,
+// 183, 4-bit 53.9, 52.9, K = 2560 int8 62.4, 60.7; int8 12288 x 4096 10.17, 10.03, 16384 x 8192 23.3, 22.6, 65536 x 3072 34.7, 31.4,
+// 25600 x 5120 M = 32 26.5, 25.8; bf16 12288 x 4096 17.6, 16.8, 10240 x 4096 15.5, 14.9, M = 32 18.0, 17.3.
+// Short K, where a tile is a slot or two a wave, stays contiguous: int8 16384 x 1024 6.75, 7.25, 20480 x 2048 9.27, 9.44 (a
+// vocabulary of 100000 38.6, 36.2), bf16 16384 x 1024 8.53, 8.81, 65536 x 2048 40.4, 42.1; 4-bit linears of three slots and more too, whose
+// tiles are no whole number of 4 KB pages: 8192 x 8192 9.8, 10.6, 16384 x 8192 14.4, 15.0 (but 25600 x 5120 15.5, 15.2).
+constexpr bool deal_tiles(int fmt, int NW, int XS, bool argmax) {
+    const int k = (fmt == FMT_W4 ? 128 : 64) * NW * XS;      // the longest K of the form
+    if (fmt == FMT_W4) return k > 2048 && (argmax || XS == 2 * 16 / NW);
+    return k > 2048 || (argmax && fmt != FMT_BF16 && k > 1024);
+}
+
+// The tiles of workgroup b, in units of TU: p.tq of them and one more in the first p.tr workgroups, which lie in all XCDs (b mod 8) alike.
+// DEAL: round by round, unit u in the u-th stretch of p.groups units, the workgroups of an XCD side by side in it, so that the chip
+// walks the matrix from front to back and an XCD reads a megabyte or two at a time (without regard to the XCDs 16384 x 8192, M = 32
+// is 29.1 us, so 27.3, contiguous 28.2).  Else contiguous: EVEN as tile_split cuts, or
+// share_begin.
+template <int TU, bool DEAL, bool EVEN>
+struct TileShare {
+    static constexpr bool kDeal = DEAL;
+    int first, step, rest, units, tq;   // unit u < tq begins at tile first + u * step, unit tq at tile `rest`; units in all
+    __device__ __forceinline__ TileShare(const GemmParams &p, int b) : tq(p.tq) {
+        units = share_count(p.tq, p.tr, b);
+        if constexpr (DEAL) {
+            first = TU * ((b & p.xcd_mask) * p.xcd_each + (b >> p.xcd_shift));
+            step = TU * p.groups;
+            rest = TU * (p.rest + b);
+        } else if constexpr (EVEN) {
+            first = TU * tile_split(p.T / TU, b, p.groups);
+            units = tile_split(p.T / TU, b + 1, p.groups) - first / TU;
+        } else {
+            first = TU * share_begin(p.tq, p.tr, b);
+        }
+    }
+    __device__ __forceinline__ int tile(int tl) const {
+        if constexpr (!DEAL) return first + tl;
+        const int u = TU == 2 ? tl >> 1 : tl;
+        return (u < tq ? first + u * step : rest) + (TU == 2 ? tl & 1 : 0);
+    }
+};
+
 // ---- the kernel with K outermost (stream_outer.hpp): FMT_A8 and FMT_W4 ----
 // tiles a workgroup walks side by side, at most (4-bit weights, 9 to 16 tokens: seven spill 44 registers)
 constexpr int outer_tiles(int fmt, int MP) { return fmt == FMT_W4 && MP == 16 ? 6 : 8; }
@@ -174,6 +221,13 @@ inline void share_tiles(GemmParams &p, const DirectPlan &d, int TU) {
     p.groups = d.groups;
     p.tq = p.T / TU / d.groups;
     p.tr = p.T / TU % d.groups;
+    p.rest = p.tq * d.groups;
+    // the workgroups of a slice lie in 8, 4, 2 or 1 XCDs by turns
+    const int shift = d.ksplit <= 1 ? 3 : (d.ksplit == 2 ? 2 : (d.ksplit == 4 ? 1 : 0));
+    const bool even = d.groups % (1 << shift) == 0;
+    p.xcd_shift = even ? shift : 0;
+    p.xcd_mask = even ? (1 << shift) - 1 : 0;
+    p.xcd_each = d.groups >> shift;
 }
 
 // p: as for the other kernels (its step counts are replaced by slots of 64 k).  epi, pre, resid: EPI_*, PRE_* and whether a

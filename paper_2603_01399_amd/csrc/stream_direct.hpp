@@ -56,11 +56,14 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     static_assert((XS * U) % RD == 0, "a round is whole turns of the ring");
     constexpr int kSlotBytes = WL * kStepBytes;
 
+    constexpr int TU = EPI == EPI_SWIGLU ? 2 : 1;   // tiles are handed out in units of TU
+    using Share = TileShare<TU, EPI != EPI_LOGITS && deal_tiles(W16 ? FMT_BF16 : FMT_INT8, NW, PAIR ? XS * KS / 64 : XS, EPI == EPI_ARGMAX),
+                            EPI == EPI_ARGMAX || EPI == EPI_LOGITS>;
     const int slice = blockIdx.x, b = blockIdx.y;
     GemmParams p = p0;
-    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.Srow, p.slice_steps, p.sc_bytes, p.tq, p.tr);
-    if constexpr (CH) loaded_together(p.SC, p.C);
-    const int s0 = slice * p0.slice_steps;          // (all step counts here are in slots of 64 k; one slice: all of K)
+    loaded_together(p.x, p.ldx, p.w, W16 ? 0 : p.scales, p.M, p.S, p.Srow, p.slice_steps, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0, Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0,
+                    Share::kDeal ? p.xcd_each : 0, CH ? p.SC : p.sc_bytes);
+    const int s0 = slice * p0.slice_steps;          // (all step counts here are in slots of 64 k)
     p.S = min(p0.slice_steps, p0.S - s0);
     p.w = p0.w + (long long)s0 * (64 * WL);
     p.x = p0.x + (long long)s0 * 64;
@@ -69,11 +72,8 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
 
-    constexpr int TU = EPI == EPI_SWIGLU ? 2 : 1;   // tiles are handed out in units of TU
-    // (vocabularies are cut as the sampler's blocks are; the cut is also the faster one there: V = 151936, M = 8 100 us, 102 to 108 with share_begin)
-    constexpr bool EVEN = EPI == EPI_ARGMAX || EPI == EPI_LOGITS;
-    const int t0 = EVEN ? tile_split(p.T, b, p.groups) : TU * share_begin(p.tq, p.tr, b);
-    const int ntiles = EVEN ? tile_split(p.T, b + 1, p.groups) - t0 : TU * share_count(p.tq, p.tr, b);
+    const Share share(p, b);
+    const int ntiles = TU * share.units;
     const int C = PAIR ? CC : (CH ? p.C : 1);
 
     // per wave: [2][C][NB][64] partial tiles, over the activations' way into the registers
@@ -214,19 +214,19 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     [[maybe_unused]] unsigned int sc_first = 0;
     if constexpr (!W16) {
         if (2 * tid < ntiles * kTileRows)
-            sc_first = *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + 2 * tid);
+            sc_first = *reinterpret_cast<const unsigned int *>(p.scales + (long long)share.tile(tid >> 3) * kTileRows + 2 * (tid & 7));
     }
     u32x2 resid[NB];
-    load_residual<RES, NB>(p, t0 + min(w, ntiles - 1), lane, resid);
+    load_residual<RES, NB>(p, share.tile(min(w, ntiles - 1)), lane, resid);
 
-    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w) + (unsigned long long)t0 * p.Srow * kSlotBytes;
+    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w);
     const unsigned int tile_bytes = (unsigned int)p.Srow * (unsigned int)kSlotBytes;
     auto mine = [&](int i) { return PAIR ? (have >> i & 1u) != 0u : i < n; };
     u32x4 ring[RD][WL];
     // refill of ring entry d with slot i of tile tl; beyond the workgroup's last tile every lane reads the same 16 bytes
     auto refill = [&](int d, int tl, int i) {
         const bool real = tl < ntiles && (CC == 1 || mine(i));
-        const unsigned long long a = real ? wbase + (unsigned long long)tl * tile_bytes + (unsigned int)step[i] * (unsigned int)kSlotBytes
+        const unsigned long long a = real ? wbase + (unsigned long long)(unsigned int)share.tile(tl) * tile_bytes + (unsigned int)step[i] * (unsigned int)kSlotBytes
                                           : reinterpret_cast<unsigned long long>(p.x);
         unsigned int off = real ? 16u * lane : 0u;
 #pragma unroll
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
         if (2 * tid < ntiles * kTileRows) reinterpret_cast<unsigned int *>(sc_lds)[tid] = sc_first;
         for (int i = 2 * (tid + NW * 64); i < ntiles * kTileRows; i += 2 * NW * 64)
             reinterpret_cast<unsigned int *>(sc_lds)[i >> 1] =
-                *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + i);
+                *reinterpret_cast<const unsigned int *>(p.scales + (long long)share.tile(i >> 4) * kTileRows + (i & 15));
     }
     if constexpr (PRE == PRE_RMSNORM) {
         // sum of squares per token: this lane's values, the lanes of the token, then the waves in order
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                 }
             }
             if constexpr (PARS == 1) lds_barrier();          // (the others wait below: the one set of partial tiles is free again)
-            finish_tile<W16, EPI, RES, NB>(p, rsum, t0 + tl, sc_lds + tl * kTileRows, resid, gate_keep, slice, lane, bestv, besti);
+            finish_tile<W16, EPI, RES, NB>(p, rsum, share.tile(tl), sc_lds + tl * kTileRows, resid, gate_keep, slice, lane, bestv, besti);
             if constexpr (EPI == EPI_LOGITS) {
                 if (p.soft_stats) {
                     // the logits of finish_tile once more: a running (max, sum) per lane and token
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                                     rsum[nb].w * bf16_bits_to_float(sb.y >> 16) * p.inv_t);
                 }
             }
-            if (RES) load_residual<RES, NB>(p, t0 + min(tl + NW, ntiles - 1), lane, resid);      // of this wave's next tile
+            if (RES) load_residual<RES, NB>(p, share.tile(min(tl + NW, ntiles - 1)), lane, resid);      // of this wave's next tile
         } else if constexpr (PARS == 1) {
             lds_barrier();
         }

@@ -53,12 +53,11 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
     const int b = blockIdx.x;
-    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.sc_bytes, p.tq, p.tr);
-    if constexpr (SMOOTH) loaded_together(p.smooth);
-    if constexpr (PREQ) loaded_together(p.dx);
-    constexpr bool EVEN = EPI == EPI_ARGMAX;         // (stream_direct.hpp)
-    const int t0 = EVEN ? tile_split(p.T, b, p.groups) : share_begin(p.tq, p.tr, b);
-    const int ntiles = EVEN ? tile_split(p.T, b + 1, p.groups) - t0 : share_count(p.tq, p.tr, b);
+    using Share = TileShare<1, deal_tiles(FMT_A8, NW, XS, EPI == EPI_ARGMAX), EPI == EPI_ARGMAX>;
+    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.smooth, p.dx, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0, Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0,
+                    Share::kDeal ? p.xcd_each : 0, p.sc_bytes);
+    const Share share(p, b);
+    const int ntiles = share.units;
 
     constexpr int kPass = a8_pass(MP, XS);
     constexpr int region = a8_region_bytes(MP, XS) / NW;
@@ -122,14 +121,14 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
                 bq[i][nb] = *(reinterpret_cast<const i32x4 *>(p.x) + ((long long)step[i] * NB + nb) * 64 + lane);
     unsigned int sc_first = 0;
     if (2 * tid < ntiles * kTileRows)
-        sc_first = *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + 2 * tid);
+        sc_first = *reinterpret_cast<const unsigned int *>(p.scales + (long long)share.tile(tid >> 3) * kTileRows + 2 * (tid & 7));
 
-    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w) + (unsigned long long)t0 * p.S * kStepBytes;
+    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w);
     const unsigned int tile_bytes = (unsigned int)p.S * (unsigned int)kStepBytes;
     u32x4 ring[RD];
     auto refill = [&](int d, int tl, int i) {
         const bool real = tl < ntiles;
-        const unsigned long long a = real ? wbase + (unsigned long long)tl * tile_bytes + (unsigned int)step[i] * (unsigned int)kStepBytes
+        const unsigned long long a = real ? wbase + (unsigned long long)(unsigned int)share.tile(tl) * tile_bytes + (unsigned int)step[i] * (unsigned int)kStepBytes
                                           : reinterpret_cast<unsigned long long>(p.x);
         unsigned int off = real ? 16u * lane : 0u;
         ring[d] = ring_refill_at(a, off, ring[d]);
@@ -142,7 +141,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     if (2 * tid < ntiles * kTileRows) reinterpret_cast<unsigned int *>(sc_lds)[tid] = sc_first;
     for (int i = 2 * (tid + NW * 64); i < ntiles * kTileRows; i += 2 * NW * 64)
         reinterpret_cast<unsigned int *>(sc_lds)[i >> 1] =
-            *reinterpret_cast<const unsigned int *>(p.scales + (long long)t0 * kTileRows + i);
+            *reinterpret_cast<const unsigned int *>(p.scales + (long long)share.tile(i >> 4) * kTileRows + (i & 15));
     // (the loads into LDS are older than the ring's and loads return in order)
     if constexpr (SMOOTH || kPass > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RD) : "memory");
     if constexpr (kPass > 0) {
@@ -251,7 +250,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
         }
         lds_barrier();
         if (w == (tl % NW)) {
-            const int n0 = (t0 + tl) * kTileRows + 4 * g;
+            const int n0 = share.tile(tl) * kTileRows + 4 * g;
             const u32x2 sb = *reinterpret_cast<const u32x2 *>(sc_lds + tl * kTileRows + 4 * g);
             const float dw0 = bf16_bits_to_float(sb.x & 0xFFFFu), dw1 = bf16_bits_to_float(sb.x >> 16);
             const float dw2 = bf16_bits_to_float(sb.y & 0xFFFFu), dw3 = bf16_bits_to_float(sb.y >> 16);

@@ -35,10 +35,11 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, mcol = lane & 15;
     const int b = blockIdx.x;
-    loaded_together(p.x, p.ldx, p.w, p.M, p.S, p.tq, p.tr);
-    constexpr bool EVEN = EPI == EPI_ARGMAX;         // (stream_direct.hpp)
-    const int t0 = EVEN ? tile_split(p.T, b, p.groups) : share_begin(p.tq, p.tr, b);
-    const int ntiles = EVEN ? tile_split(p.T, b + 1, p.groups) - t0 : share_count(p.tq, p.tr, b);
+    using Share = TileShare<1, deal_tiles(FMT_W4, NW, XS, EPI == EPI_ARGMAX), EPI == EPI_ARGMAX>;
+    loaded_together(p.x, p.ldx, p.w, p.M, p.S, 0, 0, 0, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0, Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0,
+                    Share::kDeal ? p.xcd_each : 0);
+    const Share share(p, b);
+    const int ntiles = share.units;
 
     const int first = (p.S * w) / NW;
     const int n = (p.S * (w + 1)) / NW - first;
@@ -82,13 +83,13 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
     }
 
     // ---- weight ring: codes and the rows' step sizes of a slot
-    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w) + (unsigned long long)t0 * p.S * kStepBytes4;
+    const unsigned long long wbase = reinterpret_cast<unsigned long long>(p.w);
     const unsigned int tile_bytes = (unsigned int)p.S * (unsigned int)kStepBytes4;
     u32x4 ring[RD];
     u32x2 scl[RD];
     auto refill = [&](int d, int tl, int i) {
         const bool real = tl < ntiles;
-        const unsigned long long a = real ? wbase + (unsigned long long)tl * tile_bytes + (unsigned int)step[i] * (unsigned int)kStepBytes4
+        const unsigned long long a = real ? wbase + (unsigned long long)(unsigned int)share.tile(tl) * tile_bytes + (unsigned int)step[i] * (unsigned int)kStepBytes4
                                           : reinterpret_cast<unsigned long long>(p.x);
         unsigned int oc = real ? 16u * lane : 0u, os = real ? 1024u + 8u * g : 0u;
         ring[d] = ring_refill_at(a, oc, ring[d]);
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
                 }
             }
             const u32x2 none[NB] = {};
-            finish_tile<true, EPI, false, NB>(p, rsum, t0 + tl, nullptr, none, nullptr, 0, lane, bestv, besti);
+            finish_tile<true, EPI, false, NB>(p, rsum, share.tile(tl), nullptr, none, nullptr, 0, lane, bestv, besti);
         }
         parity ^= 1;
     };

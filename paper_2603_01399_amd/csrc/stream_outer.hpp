@@ -58,9 +58,7 @@ __global__ __launch_bounds__(outer_waves(MP) * 64) void stream_outer_kernel(cons
 
     const int slice = blockIdx.x, b = blockIdx.y;
     const GemmParams &p = p0;
-    loaded_together(p.x, p.w, p.S, p.Srow, p.slice_steps, p.tq, p.tr);
-    if constexpr (FMT == FMT_A8) loaded_together(p.scales);
-    else loaded_together(p.ldx, p.M);
+    loaded_together(p.x, p.w, p.scales, p.ldx, p.S, p.Srow, p.slice_steps, p.M, p.tq, p.tr);
     const int s0 = slice * p.slice_steps;
     const int S = min(p.slice_steps, p.S - s0);
 
