@@ -748,7 +748,7 @@ constexpr unsigned int kSeqSpinLimit = 20000000u;
 
 struct SeqHandle {   // lives in quasar_sequence::words
     int magic, nphases, M, MP, w16, xs_bytes, sc_bytes, lds_bytes, grid, has_verify, n_linears, a8;
-    int n_barriers, n_flag_waits, roles;
+    int n_barriers, n_flag_waits, roles, deals;
 };
 static_assert(sizeof(SeqHandle) <= sizeof(quasar_sequence), "handle must fit");
 
@@ -797,6 +797,13 @@ int launch_logits(const GemmParams &base, int M, float inv_t, float *stats, size
     if (MP == 16) return launch(stream_mfma_kernel<16, false, EPI_LOGITS, 16, 4>, pl.grid, 1024, pl.lds_bytes, stream, p);
     return launch(stream_mfma_kernel<32, false, EPI_LOGITS, 16, 4>, pl.grid, 1024, pl.lds_bytes, stream, p);
 }
+
+// Whether the G workgroups of a whole-step phase are dealt its T tiles (stream_sequence.hpp).  us a step, contiguous, dealt: Qwen3-8B layers,
+// M = 8, 36 int8 1854, 1804, 9 W8A8 784, 752, 9 bf16 851, 812; nine Qwen3-32B layers int8 1149, 1119.  Phases of one or two tiles a
+// workgroup stay contiguous: of q|k|v (384 tiles) the workgroups with two are then those of every second XCD, whose stores are
+// acknowledged in 0.9 us; beside workgroups that already poll for the next phase the last one takes 2.3 (o's share of a layer 5.5 us,
+// 7.2).  Short K too, as in deal_tiles (nine layers of K = 1536, M = 3 315, 327; K = 2560, M = 5 456, 462).
+int deal_phase(int T, int K, int G) { return T >= 3 * G && (K >= 3072 || (K >= 2048 && T >= 8 * G)); }
 
 // Plan of the W8A8 kernel that keeps its activation codes in registers (stream_direct_a8.hpp): integer sums, so no order to
 // keep; 16 waves, the smallest built form that holds a wave's slots.
@@ -1130,10 +1137,12 @@ int launch_w4(const GemmParams &base, int M, hipStream_t stream, int *grid_out) 
 #undef QUASAR_LAUNCH_W4
 }
 
-template <int MP, bool W16, bool A8, int ROLES>
+// Built with and without dealt phases (M = 3, nine int8 layers of K = 1536 317 us without, 325 with the code that none uses); int8
+// weights of more than 8 tokens without (two chunks of K gain nothing from it: nine Qwen3-8B layers, M = 16 747, 752 us).
+template <int MP, bool W16, bool A8, int ROLES, bool DEAL = false>
 int launch_sequence(const SeqHandle &h, const SeqParams &sp, hipStream_t st) {
     constexpr int NW = ROLES == 2 ? kSeqWaves2 : kSeqWaves;
-    auto kernel = stream_sequence_kernel<MP, W16, A8, NW, (ROLES == 2 ? kSeqDepth2 : kSeqDepth), ROLES>;
+    auto kernel = stream_sequence_kernel<MP, W16, A8, NW, (ROLES == 2 ? kSeqDepth2 : kSeqDepth), ROLES, DEAL>;
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return QUASAR_ERR_HIP;
     hipLaunchKernelGGL(sequence_reset_kernel, dim3(1), dim3(256), 0, st, sp.sync);
     // Plain launch: every workgroup is resident by construction (grid = ROLES workgroups per compute
@@ -1144,10 +1153,10 @@ int launch_sequence(const SeqHandle &h, const SeqParams &sp, hipStream_t st) {
 }
 
 // Workgroups of this kernel shape that fit one compute unit (0 on error).
-template <int MP, bool W16, bool A8, int ROLES>
+template <int MP, bool W16, bool A8, int ROLES, bool DEAL = false>
 int sequence_residency(int lds_bytes) {
     constexpr int NW = ROLES == 2 ? kSeqWaves2 : kSeqWaves;
-    auto kernel = stream_sequence_kernel<MP, W16, A8, NW, (ROLES == 2 ? kSeqDepth2 : kSeqDepth), ROLES>;
+    auto kernel = stream_sequence_kernel<MP, W16, A8, NW, (ROLES == 2 ? kSeqDepth2 : kSeqDepth), ROLES, DEAL>;
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return 0;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, NW * 64, (size_t)lds_bytes) != hipSuccess) {
@@ -1157,17 +1166,18 @@ int sequence_residency(int lds_bytes) {
     return per_cu;
 }
 template <int ROLES>
-int sequence_residency_of(int MP, bool w16, bool a8, int lds_bytes) {
+int sequence_residency_of(int MP, bool w16, bool a8, bool deals, int lds_bytes) {
     if constexpr (ROLES == 2) {
         if (MP != 8) return 0;
         return w16 ? sequence_residency<8, true, false, 2>(lds_bytes)
                    : (a8 ? sequence_residency<8, false, true, 2>(lds_bytes) : sequence_residency<8, false, false, 2>(lds_bytes));
     } else {
-        if (w16) return MP == 8 ? sequence_residency<8, true, false, 1>(lds_bytes)
-                                : (MP == 16 ? sequence_residency<16, true, false, 1>(lds_bytes) : sequence_residency<32, true, false, 1>(lds_bytes));
-        if (a8) return MP == 8 ? sequence_residency<8, false, true, 1>(lds_bytes)
-                               : (MP == 16 ? sequence_residency<16, false, true, 1>(lds_bytes) : sequence_residency<32, false, true, 1>(lds_bytes));
-        return MP == 8 ? sequence_residency<8, false, false, 1>(lds_bytes)
+#define QUASAR_RESIDENCY(MPV, W16V, A8V) \
+    (deals ? sequence_residency<MPV, W16V, A8V, 1, true>(lds_bytes) : sequence_residency<MPV, W16V, A8V, 1>(lds_bytes))
+        if (w16) return MP == 8 ? QUASAR_RESIDENCY(8, true, false) : (MP == 16 ? QUASAR_RESIDENCY(16, true, false) : QUASAR_RESIDENCY(32, true, false));
+        if (a8) return MP == 8 ? QUASAR_RESIDENCY(8, false, true) : (MP == 16 ? QUASAR_RESIDENCY(16, false, true) : QUASAR_RESIDENCY(32, false, true));
+        return MP == 8 ? QUASAR_RESIDENCY(8, false, false)
+#undef QUASAR_RESIDENCY
                        : (MP == 16 ? sequence_residency<16, false, false, 1>(lds_bytes) : sequence_residency<32, false, false, 1>(lds_bytes));
     }
 }
@@ -1389,6 +1399,7 @@ static int sequence_prepare_impl(const quasar_linear_desc *linears, int64_t n_li
     for (size_t i = 0; i < phases.size(); ++i) {
         SeqPhase &p = phases[i];
         if ((long long)p.T * (G + 1) >= (1ll << 31)) return QUASAR_ERR_SHAPE;   // the kernel splits tiles in 32 bits
+        p.deal = deal_phase(p.T, p.K, G);
         int xs, sc, ac;
         plan_phase(p, MP, w16, a8, G, xs, sc, ac);
         p.xs_bytes = xs;
@@ -1428,7 +1439,7 @@ static int sequence_prepare_impl(const quasar_linear_desc *linears, int64_t n_li
     if (MP == 8 && want2) {
         int lds2 = lds_need(stage2);
         if (lds2 < kSeqMinLds2) lds2 = kSeqMinLds2;
-        if (lds2 <= kSeqMaxLds2 && sequence_residency_of<2>(MP, w16, a8, lds2) >= 2) {
+        if (lds2 <= kSeqMaxLds2 && sequence_residency_of<2>(MP, w16, a8, false, lds2) >= 2) {
             roles = 2;
             lds = lds2;
         } else if (form == 2) {
@@ -1452,13 +1463,14 @@ static int sequence_prepare_impl(const quasar_linear_desc *linears, int64_t n_li
     h.lds_bytes = (roles == 1 && lds < kMinLds) ? kMinLds : lds;
     h.grid = G * roles; h.roles = roles;
     h.has_verify = verify ? 1 : 0; h.n_linears = (int)n_linears; h.a8 = a8 ? 1 : 0;
-    h.n_barriers = 0; h.n_flag_waits = 0;
+    h.n_barriers = 0; h.n_flag_waits = 0; h.deals = 0;
     for (const SeqPhase &p : phases) {
+        if (p.deal) h.deals = 1;
         if (p.wait == SEQ_WAIT_BARRIER) ++h.n_barriers;
         if (p.wait == SEQ_WAIT_FLAGS) ++h.n_flag_waits;
     }
     // The launch relies on every workgroup being resident at once (they wait for each other).
-    if (roles == 1 && sequence_residency_of<1>(MP, w16, a8, h.lds_bytes) < 1) return QUASAR_ERR_HIP;
+    if (roles == 1 && sequence_residency_of<1>(MP, w16, a8, h.deals, h.lds_bytes) < 1) return QUASAR_ERR_HIP;
     std::memset(seq, 0, sizeof(*seq));
     std::memcpy(seq, &h, sizeof(h));
     return QUASAR_OK;
@@ -1510,17 +1522,20 @@ static int sequence_run_impl(const quasar_sequence *seq, const void *plan_device
         if (h.a8) return launch_sequence<8, false, true, 2>(h, sp, st);
         return launch_sequence<8, false, false, 2>(h, sp, st);
     }
+#define QUASAR_SEQUENCE(MPV, W16V, A8V) \
+    (h.deals ? launch_sequence<MPV, W16V, A8V, 1, true>(h, sp, st) : launch_sequence<MPV, W16V, A8V, 1>(h, sp, st))
     if (h.w16) {
-        if (h.MP == 8) return launch_sequence<8, true, false, 1>(h, sp, st);
-        if (h.MP == 16) return launch_sequence<16, true, false, 1>(h, sp, st);
-        return launch_sequence<32, true, false, 1>(h, sp, st);
+        if (h.MP == 8) return QUASAR_SEQUENCE(8, true, false);
+        if (h.MP == 16) return QUASAR_SEQUENCE(16, true, false);
+        return QUASAR_SEQUENCE(32, true, false);
     }
     if (h.a8) {
-        if (h.MP == 8) return launch_sequence<8, false, true, 1>(h, sp, st);
-        if (h.MP == 16) return launch_sequence<16, false, true, 1>(h, sp, st);
-        return launch_sequence<32, false, true, 1>(h, sp, st);
+        if (h.MP == 8) return QUASAR_SEQUENCE(8, false, true);
+        if (h.MP == 16) return QUASAR_SEQUENCE(16, false, true);
+        return QUASAR_SEQUENCE(32, false, true);
     }
-    if (h.MP == 8) return launch_sequence<8, false, false, 1>(h, sp, st);
+    if (h.MP == 8) return QUASAR_SEQUENCE(8, false, false);
+#undef QUASAR_SEQUENCE
     if (h.MP == 16) return launch_sequence<16, false, false, 1>(h, sp, st);
     return launch_sequence<32, false, false, 1>(h, sp, st);
 }

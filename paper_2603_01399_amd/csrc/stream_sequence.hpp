@@ -48,6 +48,7 @@ struct SeqPhase {
     SeqSeg seg[kMaxSeg];
     int nseg;
     int T;                   // tiles over all segments
+    int deal;                // tiles dealt to the workgroups round by round (share_of; rule: deal_phase)
     int K, S, SC, C;         // as in GemmParams
     int kind;                // EPI_LINEAR or EPI_ARGMAX (argmax: one segment)
     int wait;                // SEQ_WAIT_*: how the input becomes available
@@ -154,7 +155,7 @@ constexpr int kSeqRefillGroup = 4;
 // the same bits.
 constexpr int kSeqCuSlots = 2048;     // distinct compute-unit ids (XCC, shader engine, unit)
 
-template <int MP, bool W16, bool A8, int NW, int D, int ROLES>
+template <int MP, bool W16, bool A8, int NW, int D, int ROLES, bool DEAL>
 __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_kernel(const SeqParams sp) {
     extern __shared__ __align__(16) unsigned char lds[];
     static_assert(!(W16 && A8), "the W8A8 form needs int8 weights");
@@ -220,6 +221,19 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
         rk = __builtin_amdgcn_readfirstlane((int)box[1]);
         lds_barrier();
     }
+    // The workgroup's tiles of a phase, t0 + i * step for i < n: contiguous, or dealt round by round, in each round the workgroups of an
+    // XCD (rk mod 8) side by side (TileShare in launch.hpp).  DEAL: some phase is dealt (the code costs a sequence without one 1 to 3 %).
+    auto share_of = [&](const auto &P, int &t0, int &step, int &n) {
+        if (DEAL && P.deal) {
+            t0 = ROLES == 1 && (GW & 7) == 0 ? (rk & 7) * (GW >> 3) + (rk >> 3) : rk;
+            step = GW;
+            n = (P.T - t0 + GW - 1) / GW;
+        } else {
+            t0 = (int)(((unsigned int)P.T * (unsigned int)rk) / (unsigned int)GW);   // the host checks T * G < 2^31
+            step = 1;
+            n = (int)(((unsigned int)P.T * (unsigned int)(rk + 1)) / (unsigned int)GW) - t0;
+        }
+    };
     auto mine = [&](int ph) -> bool { return ROLES == 1 || (ph & 1) == role; };
     auto stamp = [&](int ph, int what) {
         if (sp.stamps && tid == 0)
@@ -247,7 +261,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     // block of zeros, so such a slot contributes nothing without any masking.
     constexpr int kForever = 0x7FFFFFFF;
     const unsigned long long zeros = reinterpret_cast<unsigned long long>(sp.zeros);
-    int l_ph = 0, l_c = -1, l_tl = 0, l_spw = 0, l_ntiles = 0, l_t0 = 0, l_seg_end = 0, l_s_lo = 0;
+    int l_ph = 0, l_c = -1, l_tl = 0, l_spw = 0, l_ntiles = 0, l_t0 = 0, l_step = 1, l_seg_end = 0, l_s_lo = 0;
     unsigned long long l_stride = 0;   // bytes from one tile to the next
     unsigned long long l_wt = 0;       // this wave's first step in the current tile
     unsigned long long l_base = zeros; // the next slot to load
@@ -255,10 +269,10 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     int l_left = 1;
     auto l_retile = [&]() {
         const auto &P = phases[l_ph];
-        const int t = l_t0 + l_tl;
+        const int t = l_t0 + l_tl * l_step;
         const int s = seg_of(P, t);
         l_seg_end = (s + 1 < P.nseg) ? P.seg[s + 1].tile_begin : P.T;
-        l_stride = (unsigned long long)P.S * 1024ull;
+        l_stride = (unsigned long long)((unsigned int)P.S * 1024u) * (unsigned int)l_step;
         l_wt = reinterpret_cast<unsigned long long>(P.seg[s].w) +
                ((unsigned long long)(t - P.seg[s].tile_begin) * P.S + (unsigned long long)l_c * P.SC + l_s_lo) * 1024ull;
     };
@@ -269,8 +283,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
             if (l_ph < nph && l_c >= phases[l_ph].C) { ++l_ph; l_c = 0; }
             if (l_ph >= nph) { l_ntiles = 0; l_spw = 0; return; }
             const auto &P = phases[l_ph];
-            l_t0 = (int)(((unsigned int)P.T * (unsigned int)rk) / (unsigned int)GW);   // the host checks T * G < 2^31
-            l_ntiles = (int)(((unsigned int)P.T * (unsigned int)(rk + 1)) / (unsigned int)GW) - l_t0;
+            share_of(P, l_t0, l_step, l_ntiles);
             if (l_ntiles == 0 || !mine(l_ph)) { l_c = P.C - 1; continue; }
             const int scc = min(P.SC, P.S - l_c * P.SC);
             l_s_lo = (scc * w) / NW;
@@ -290,7 +303,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     auto l_event = [&]() {
         if (l_ph < nph) {
             if (!l_in_pad && ++l_tl < l_ntiles) {
-                if (l_t0 + l_tl == l_seg_end) l_retile(); else l_wt += l_stride;
+                if (l_t0 + l_tl * l_step >= l_seg_end) l_retile(); else l_wt += l_stride;
             } else {
                 const int pad = l_in_pad ? 0 : (-(l_ntiles * max(l_spw, 1))) & (GR - 1);
 
@@ -320,7 +333,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     }
 
     // ------------------------------------------------------------------ compute front
-    int c_ph = 0, c_c = -1, c_tl = 0, c_nsl = 1, c_ntiles = 0, c_t0 = 0;
+    int c_ph = 0, c_c = -1, c_tl = 0, c_nsl = 1, c_ntiles = 0, c_t0 = 0, c_step = 1;
     int c_C = 1, c_kind = EPI_LINEAR;
     int c_left = kForever;             // slots to the end of the current tile
     unsigned int c_x0 = 0, c_xinc = 0; // LDS offset of this wave's first step in the chunk; bytes per step
@@ -332,7 +345,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     int c_tb = 0, c_seg_end = 0;
     auto c_reseg = [&]() {
         const auto &P = phases[c_ph];
-        const int s = seg_of(P, c_t0 + c_tl);
+        const int s = seg_of(P, c_t0 + c_tl * c_step);
         c_y = P.seg[s].y;
         c_ldy = P.seg[s].ldy;
         c_tb = P.seg[s].tile_begin - P.tile_shift;
@@ -596,7 +609,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     auto scale_stage = [&](const auto &P, int t0, int ntiles) {
         if constexpr (!W16) {
             for (int i = 2 * tid; i < ntiles * kTileRows; i += 2 * nthreads) {
-                const int t = t0 + (i >> 4);
+                const int t = t0 + (i >> 4) * c_step;
                 const int s = seg_of(P, t);
                 const long long n = (long long)(t - P.seg[s].tile_begin) * kTileRows + (i & 15);
                 reinterpret_cast<unsigned int *>(sc_lds)[i >> 1] =
@@ -612,7 +625,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
         unsigned int v = 0u;
         if constexpr (!W16) {
             if (i >= 0 && i < ntiles * (kTileRows / 2)) {
-                const int t = t0 + (i >> 3);
+                const int t = t0 + (i >> 3) * c_step;
                 const uint16_t *base = P.seg[0].scales;
                 int tb = 0;
                 if (P.nseg > 1 && t >= P.seg[1].tile_begin) { base = P.seg[1].scales; tb = P.seg[1].tile_begin; }
@@ -766,8 +779,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
             if (c_c == 0) {
                 c_C = P.C;
                 c_kind = P.kind;
-                c_t0 = (int)(((unsigned int)P.T * (unsigned int)rk) / (unsigned int)GW);
-                c_ntiles = (int)(((unsigned int)P.T * (unsigned int)(rk + 1)) / (unsigned int)GW) - c_t0;
+                share_of(P, c_t0, c_step, c_ntiles);
                 if (P.wait == SEQ_WAIT_BARRIER) {
                     ++barriers_done;
                     grid_barrier(sp.sync, barriers_done * (unsigned int)G, sp.spin_limit);
@@ -976,7 +988,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
                         }
                     }
                     if (c_c == c_C - 1) {
-                        const int n0 = (c_t0 + c_tl - c_tb) * kTileRows + 4 * g;
+                        const int n0 = (c_t0 + c_tl * c_step - c_tb) * kTileRows + 4 * g;
                         float s4[4] = {1.f, 1.f, 1.f, 1.f};
                         if constexpr (!W16) {
                             const u32x2 sb = *reinterpret_cast<const u32x2 *>(sc_lds + c_tl * kTileRows + 4 * g);
@@ -1026,7 +1038,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
                     nocomp = true;
                     c_leave();
                 } else {
-                    if (__builtin_expect(c_t0 + c_tl == c_seg_end, 0)) c_reseg();
+                    if (__builtin_expect(c_t0 + c_tl * c_step >= c_seg_end, 0)) c_reseg();
                     c_left = c_nsl;
                     c_xoff = c_x0;
                 }
