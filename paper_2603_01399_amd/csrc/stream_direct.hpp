@@ -13,9 +13,9 @@
 // What bounds it: a launch whose compute units read nothing but the 16 MB of a 4096 x 4096 matrix takes 3.9 us back to
 // back (48 MB: 8.6 us); the rest is the fetch of x (as many bytes per compute unit as its weights at M = 8) and the
 // tile end.  Back to back, HBM-cold, int8, us a launch, staged kernel -> this one:
-//     M = 8:  1024 x 1024 5.1 -> 3.5, 4096 x 4096 7.2 -> 5.2, 12288 x 4096 11.7 -> 10.2, 4096 x 12288 13.9 -> 11.5
+//     M = 8:  1024 x 1024 5.1 -> 3.2, 4096 x 4096 7.2 -> 5.3, 12288 x 4096 11.7 -> 10.0, 4096 x 12288 13.9 -> 11.1
 //     M = 16: 4096 x 4096 9.4 -> 6.5, 12288 x 4096 14.8 -> 11.3, 4096 x 8192 14.3 -> 9.9
-//     M = 32: 4096 x 4096 13.0 -> 7.9, 12288 x 4096 22.9 -> 12.6
+//     M = 32: 4096 x 4096 13.0 -> 7.9, 12288 x 4096 22.9 -> 12.5
 // Fetching x: straight into the registers, or, for more of it, in whole cache lines through the wave's own piece of LDS
 // (direct_pass).  Weights requested before x: 0.4 us slower; workgroups that start at different K slices, rows of x at
 // other strides: no difference.
@@ -61,8 +61,8 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                             EPI == EPI_ARGMAX || EPI == EPI_LOGITS>;
     const int slice = blockIdx.x, b = blockIdx.y;
     GemmParams p = p0;
-    loaded_together(p.x, p.ldx, p.w, W16 ? 0 : p.scales, p.M, p.S, p.Srow, p.slice_steps, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0, Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0,
-                    Share::kDeal ? p.xcd_each : 0, CH ? p.SC : p.sc_bytes);
+    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.Srow, p.slice_steps, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0,
+                    Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0, Share::kDeal ? p.xcd_each : 0, CH ? p.SC : p.sc_bytes);
     const int s0 = slice * p0.slice_steps;          // (all step counts here are in slots of 64 k)
     p.S = min(p0.slice_steps, p0.S - s0);
     p.w = p0.w + (long long)s0 * (64 * WL);

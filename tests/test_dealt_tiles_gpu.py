@@ -13,7 +13,7 @@ def _weights(n, k, seed):
 
 
 # workgroups are at most as many as compute units (256): one to ten tiles each, 1, 7, 8, 255 and 0 left over
-@pytest.mark.parametrize("tiles", [256 + 1, 2 * 256 + 7, 2 * 256 + 255, 5 * 256 + 8, 10 * 256, 264, 200])
+@pytest.mark.parametrize("tiles", [256 + 1, 2 * 256 + 7, 2 * 256 + 255, 5 * 256 + 8, 10 * 256, 264, 200, 101])
 @pytest.mark.parametrize("fmt", ["int8", "w8a8", "int4", "bf16"])
 def test_every_tile_once(fmt, tiles):
     from paper_2603_01399_amd import binding as qb
@@ -43,6 +43,23 @@ def test_every_tile_once(fmt, tiles):
     want = xd @ wd.t()
     # a bf16 rounding (2^-9) and fp32 sums of k terms of the size of the row's norm product
     bound = want.abs() * 2.0 ** -8 + 1e-5 * xd.norm(dim=1)[:, None] * wd.norm(dim=1)[None]
+    torch.cuda.synchronize()
+    assert bool(((y.double() - want).abs() <= bound).all())
+
+
+# K in two to eight slices, whose workgroups lie in four, two or all XCDs by turns
+@pytest.mark.parametrize("m,tiles,k", [(8, 67, 14336), (8, 320, 25600), (32, 131, 8192), (32, 323, 16384), (16, 517, 13312)])
+def test_every_tile_of_every_slice(m, tiles, k):
+    from paper_2603_01399_amd import binding as qb
+    n = 16 * tiles
+    w = _weights(n, k, tiles)
+    x = (torch.randn((m, k), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))).to(torch.bfloat16)
+    q, s = qb.quantize_weights(w)
+    y = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    qb.w8_linear(x, q, s, n, y=y, workspace=qb.make_workspace(m, n, k))
+    wd = qb.unpack_weights(q, n, k).double() * s.double()[:, None]
+    want = x.double() @ wd.t()
+    bound = want.abs() * 2.0 ** -8 + 1e-5 * x.double().norm(dim=1)[:, None] * wd.norm(dim=1)[None]      # as above
     torch.cuda.synchronize()
     assert bool(((y.double() - want).abs() <= bound).all())
 
