@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libquasar.so")
 FAST = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["quasar_api.hip", "direct_int8.hip", "direct_bf16.hip", "direct_w8a8.hip", "direct_w4.hip",
            "outer_w8a8.hip", "outer_w4.hip"]
-HEADERS = ["quasar_device.hpp", "launch.hpp", "stream_gemm.hpp", "stream_direct.hpp", "stream_direct_a8.hpp", "stream_direct_w4.hpp", "stream_outer.hpp", "norm.hpp", "stream_sequence.hpp", "stream_w8a8.hpp", "stream_w4.hpp", "drafter.hpp", "attention.hpp", "sample.hpp", "draw.hpp", "pack.hpp", "probe.hpp", "unlocked.hpp"]
+HEADERS = ["quasar_device.hpp", "launch.hpp", "shares.hpp", "stream_gemm.hpp", "stream_direct.hpp", "stream_direct_a8.hpp", "stream_direct_w4.hpp", "stream_outer.hpp", "norm.hpp", "stream_sequence.hpp", "stream_w8a8.hpp", "stream_w4.hpp", "drafter.hpp", "attention.hpp", "sample.hpp", "draw.hpp", "pack.hpp", "probe.hpp", "unlocked.hpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -7,7 +7,7 @@ int launch_direct_w4(int epi, const GemmParams &base, int MP, const DirectPlan &
     GemmParams p = base;
     p.S = p.K / kStepK4;
     p.ksplit = 1;
-    share_tiles(p, d, 1);
+    share_tiles(p, d.groups, 1, 1);
     return epi == EPI_ARGMAX ? launch_w4_as<EPI_ARGMAX>(p, MP, d, stream) : launch_w4_as<EPI_LINEAR>(p, MP, d, stream);
 }
 

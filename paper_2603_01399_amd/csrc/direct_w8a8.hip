@@ -7,7 +7,7 @@ int launch_direct_w8a8(int epi, const GemmParams &base, int MP, const DirectPlan
     GemmParams p = base;
     p.S = p.K / 64;
     p.sc_bytes = d.sc_bytes;
-    share_tiles(p, d, 1);
+    share_tiles(p, d.groups, 1, 1);
     if (epi == EPI_ARGMAX && p.dx) return launch_a8_codes<1, 2, 3, 4, 5, 6>(d.XS, d.groups, d.lds_bytes, stream, p);
     if (epi == EPI_ARGMAX)
         return p.smooth ? launch_a8_as<EPI_ARGMAX, true>(p, MP, d, stream) : launch_a8_as<EPI_ARGMAX, false>(p, MP, d, stream);

@@ -167,35 +167,6 @@ constexpr bool deal_tiles(int fmt, int NW, int XS, bool argmax) {
     return k > 2048 || (argmax && fmt != FMT_BF16 && k > 1024);
 }
 
-// The tiles of workgroup b, in units of TU: p.tq of them and one more in the first p.tr workgroups, which lie in all XCDs (b mod 8) alike.
-// DEAL: round by round, unit u in the u-th stretch of p.groups units, the workgroups of an XCD side by side in it, so that the chip
-// walks the matrix from front to back and an XCD reads a megabyte or two at a time (without regard to the XCDs 16384 x 8192, M = 32
-// is 29.1 us, so 27.3, contiguous 28.2).  Else contiguous: EVEN as tile_split cuts, or
-// share_begin.
-template <int TU, bool DEAL, bool EVEN>
-struct TileShare {
-    static constexpr bool kDeal = DEAL;
-    int first, step, rest, units, tq;   // unit u < tq begins at tile first + u * step, unit tq at tile `rest`; units in all
-    __device__ __forceinline__ TileShare(const GemmParams &p, int b) : tq(p.tq) {
-        units = share_count(p.tq, p.tr, b);
-        if constexpr (DEAL) {
-            first = TU * ((b & p.xcd_mask) * p.xcd_each + (b >> p.xcd_shift));
-            step = TU * p.groups;
-            rest = TU * (p.rest + b);
-        } else if constexpr (EVEN) {
-            first = TU * tile_split(p.T / TU, b, p.groups);
-            units = tile_split(p.T / TU, b + 1, p.groups) - first / TU;
-        } else {
-            first = TU * share_begin(p.tq, p.tr, b);
-        }
-    }
-    __device__ __forceinline__ int tile(int tl) const {
-        if constexpr (!DEAL) return first + tl;
-        const int u = TU == 2 ? tl >> 1 : tl;
-        return (u < tq ? first + u * step : rest) + (TU == 2 ? tl & 1 : 0);
-    }
-};
-
 // ---- the kernel with K outermost (stream_outer.hpp): FMT_A8 and FMT_W4 ----
 // tiles a workgroup walks side by side, at most (4-bit weights, 9 to 16 tokens: seven spill 44 registers)
 constexpr int outer_tiles(int fmt, int MP) { return fmt == FMT_W4 && MP == 16 ? 6 : 8; }
@@ -215,20 +186,6 @@ struct DirectPlan {
     int XS, SC, C, ksplit, slice_steps, groups, sc_bytes, lds_bytes;
     bool pair;       // 32 tokens in the order of sixteen waves
 };
-
-// units of TU tiles over the workgroups
-inline void share_tiles(GemmParams &p, const DirectPlan &d, int TU) {
-    p.groups = d.groups;
-    p.tq = p.T / TU / d.groups;
-    p.tr = p.T / TU % d.groups;
-    p.rest = p.tq * d.groups;
-    // the workgroups of a slice lie in 8, 4, 2 or 1 XCDs by turns
-    const int shift = d.ksplit <= 1 ? 3 : (d.ksplit == 2 ? 2 : (d.ksplit == 4 ? 1 : 0));
-    const bool even = d.groups % (1 << shift) == 0;
-    p.xcd_shift = even ? shift : 0;
-    p.xcd_mask = even ? (1 << shift) - 1 : 0;
-    p.xcd_each = d.groups >> shift;
-}
 
 // p: as for the other kernels (its step counts are replaced by slots of 64 k).  epi, pre, resid: EPI_*, PRE_* and whether a
 // residual is added.

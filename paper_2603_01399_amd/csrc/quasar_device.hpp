@@ -86,19 +86,6 @@ __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v,
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// floor(T * b / G) for wave-uniform non-negative operands: where a workgroup's share of T tiles
-// begins.  The 64-bit division is a long software routine; it runs only when the product does
-// not fit 32 bits.
-__device__ __forceinline__ int tile_split(int T, int b, int G) {
-    const unsigned long long prod = (unsigned long long)(unsigned int)T * (unsigned int)b;
-    if (prod <= 0xFFFFFFFFull) return (int)((unsigned int)prod / (unsigned int)G);
-    return (int)(prod / (unsigned long long)(unsigned int)G);
-}
-
-// The same shares without a division: of G workgroups each has q tiles and the first r one more (q = T / G, r = T % G).
-__device__ __forceinline__ int share_begin(int q, int r, int b) { return b * q + min(b, r); }
-__device__ __forceinline__ int share_count(int q, int r, int b) { return q + (b < r ? 1 : 0); }
-
 // 16 bytes per lane from gbase + lane_offset (gbase wave-uniform) straight into LDS at lds_addr + 16 * lane,
 // without passing through registers.  Inline assembly on purpose: when the compiler sees a direct-to-LDS
 // load anywhere in a kernel it makes every LDS read wait for ALL outstanding vector memory loads (it

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     const int slice = blockIdx.x, b = blockIdx.y;
     GemmParams p = p0;
     loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.Srow, p.slice_steps, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0,
-                    Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0, Share::kDeal ? p.xcd_each : 0, CH ? p.SC : p.sc_bytes);
+                    Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0, CH ? p.SC : p.sc_bytes);
     const int s0 = slice * p0.slice_steps;          // (all step counts here are in slots of 64 k)
     p.S = min(p0.slice_steps, p0.S - s0);
     p.w = p0.w + (long long)s0 * (64 * WL);
@@ -470,7 +470,7 @@ int launch_direct_as(const GemmParams &base, int MP, const DirectPlan &d, hipStr
     p.slice_steps = d.ksplit > 1 ? d.slice_steps : p.S;
     p.sc_bytes = d.sc_bytes;
     p.xs_bytes = 0;
-    share_tiles(p, d, EPI == EPI_SWIGLU ? 2 : 1);
+    share_tiles(p, d.groups, d.ksplit, EPI == EPI_SWIGLU ? 2 : 1);
     const dim3 grid((unsigned int)d.ksplit, (unsigned int)d.groups);
     if constexpr (PRE == PRE_NONE && !RES && (EPI == EPI_LINEAR || EPI == EPI_ARGMAX)) {
         // (CH: slots of a share)

@@ -11,6 +11,7 @@
 #pragma once
 
 #include "quasar_device.hpp"
+#include "shares.hpp"
 
 namespace quasar {
 
@@ -26,7 +27,7 @@ struct GemmParams {
     int slice_steps;         // of a K slice, see ksplit
     // the kernels of stream_direct*.hpp and stream_outer.hpp: units of tiles of a workgroup, units left over, workgroups that share the
     // tiles, the first unit left over, and how workgroups lie in the XCDs (TileShare)
-    int tq, tr, groups, rest, xcd_mask, xcd_shift, xcd_each;
+    int tq, tr, groups, rest, xcd_mask, xcd_shift;
     int sc_bytes;   // LDS bytes reserved for the workgroup's row scales
     int SC;         // steps per K chunk (activations of one chunk fit in LDS)
     int C;          // number of K chunks

@@ -328,7 +328,7 @@ int launch_outer_as(const GemmParams &base, int MP, const DirectPlan &d, hipStre
     p.S = p.Srow = p.K / outer_slot_k(FMT);
     p.ksplit = d.ksplit;
     p.slice_steps = d.ksplit > 1 ? d.slice_steps : p.S;
-    share_tiles(p, d, 1);
+    share_tiles(p, d.groups, d.ksplit, 1);
     const dim3 grid((unsigned int)d.ksplit, (unsigned int)d.groups);
     if (MP == 8) return launch_outer_forms<FMT, 8, 1, 2, 3, 4, 5, 6, 7, 8>(d.XS, grid, d.lds_bytes, stream, p);
     if (MP == 16) {
