@@ -798,12 +798,20 @@ int launch_logits(const GemmParams &base, int M, float inv_t, float *stats, size
     return launch(stream_mfma_kernel<32, false, EPI_LOGITS, 16, 4>, pl.grid, 1024, pl.lds_bytes, stream, p);
 }
 
-// Whether the G workgroups of a whole-step phase are dealt its T tiles (stream_sequence.hpp).  us a step, contiguous, dealt: Qwen3-8B layers,
-// M = 8, 36 int8 1854, 1804, 9 W8A8 784, 752, 9 bf16 851, 812; nine Qwen3-32B layers int8 1149, 1119.  Phases of one or two tiles a
-// workgroup stay contiguous: of q|k|v (384 tiles) the workgroups with two are then those of every second XCD, whose stores are
-// acknowledged in 0.9 us; beside workgroups that already poll for the next phase the last one takes 2.3 (o's share of a layer 5.5 us,
-// 7.2).  Short K too, as in deal_tiles (nine layers of K = 1536, M = 3 315, 327; K = 2560, M = 5 456, 462).
-int deal_phase(int T, int K, int G) { return T >= 3 * G && (K >= 3072 || (K >= 2048 && T >= 8 * G)); }
+// Whether the G workgroups of a whole-step phase are dealt its T tiles (stream_sequence.hpp).  us a step, contiguous, dealt, means of four
+// plans and more (where a plan lies moves a step by 2 %): five Qwen3-8B layers and the vocabulary, M = 8 int8 357, 345, W8A8 485, 469, bf16
+// 569, 541, M = 16 W8A8 708, 692, bf16 630, 615; four Qwen3-32B layers, M = 8 int8 589, 577, W8A8 762, 740, bf16 971, 945.  Contiguous stay
+//   more than 16 tokens (five 8B layers W8A8 1254, 1267, bf16 1017, 1047; four 32B layers 1903, 1948 and 1711, 1760) and int8 of more than
+//     8 (two chunks of K gain nothing: nine 8B layers, M = 16 747, 752);
+//   phases of one or two tiles a workgroup: of q|k|v (384 tiles) the workgroups with two are then those of every second XCD, whose stores
+//     are acknowledged in 0.9 us; beside workgroups that already poll for the next phase the last one takes 2.3 (o's share of a
+//     layer 5.5 us, 7.2);
+//   8-bit weights of K below 3072, where a step without a dealt phase runs the shorter code (five layers of K = 2560 and 12288, M = 8 int8
+//     290, 296, W8A8 M = 16 506, 518) - bf16 only below 2048 or eight tiles (K = 2048 and 10240, M = 8 320, 312; K = 2304 285, 284).
+int deal_phase(int MP, bool w16, bool a8, int T, int K, int G) {
+    if (MP > (w16 || a8 ? 16 : 8) || T < 3 * G) return 0;
+    return K >= 3072 || (w16 && K >= 2048 && T >= 8 * G);
+}
 
 // Plan of the W8A8 kernel that keeps its activation codes in registers (stream_direct_a8.hpp): integer sums, so no order to
 // keep; 16 waves, the smallest built form that holds a wave's slots.
@@ -1137,8 +1145,8 @@ int launch_w4(const GemmParams &base, int M, hipStream_t stream, int *grid_out) 
 #undef QUASAR_LAUNCH_W4
 }
 
-// Built with and without dealt phases (M = 3, nine int8 layers of K = 1536 317 us without, 325 with the code that none uses); int8
-// weights of more than 8 tokens without (two chunks of K gain nothing from it: nine Qwen3-8B layers, M = 16 747, 752 us).
+// Built with dealt phases where deal_phase has some, and without (M = 3, nine int8 layers of K = 1536 317 us without, 325 with the code that
+// none uses).
 template <int MP, bool W16, bool A8, int ROLES, bool DEAL = false>
 int launch_sequence(const SeqHandle &h, const SeqParams &sp, hipStream_t st) {
     constexpr int NW = ROLES == 2 ? kSeqWaves2 : kSeqWaves;
@@ -1174,8 +1182,8 @@ int sequence_residency_of(int MP, bool w16, bool a8, bool deals, int lds_bytes) 
     } else {
 #define QUASAR_RESIDENCY(MPV, W16V, A8V) \
     (deals ? sequence_residency<MPV, W16V, A8V, 1, true>(lds_bytes) : sequence_residency<MPV, W16V, A8V, 1>(lds_bytes))
-        if (w16) return MP == 8 ? QUASAR_RESIDENCY(8, true, false) : (MP == 16 ? QUASAR_RESIDENCY(16, true, false) : QUASAR_RESIDENCY(32, true, false));
-        if (a8) return MP == 8 ? QUASAR_RESIDENCY(8, false, true) : (MP == 16 ? QUASAR_RESIDENCY(16, false, true) : QUASAR_RESIDENCY(32, false, true));
+        if (w16) return MP == 8 ? QUASAR_RESIDENCY(8, true, false) : (MP == 16 ? QUASAR_RESIDENCY(16, true, false) : sequence_residency<32, true, false, 1>(lds_bytes));
+        if (a8) return MP == 8 ? QUASAR_RESIDENCY(8, false, true) : (MP == 16 ? QUASAR_RESIDENCY(16, false, true) : sequence_residency<32, false, true, 1>(lds_bytes));
         return MP == 8 ? QUASAR_RESIDENCY(8, false, false)
 #undef QUASAR_RESIDENCY
                        : (MP == 16 ? sequence_residency<16, false, false, 1>(lds_bytes) : sequence_residency<32, false, false, 1>(lds_bytes));
@@ -1399,7 +1407,7 @@ static int sequence_prepare_impl(const quasar_linear_desc *linears, int64_t n_li
     for (size_t i = 0; i < phases.size(); ++i) {
         SeqPhase &p = phases[i];
         if ((long long)p.T * (G + 1) >= (1ll << 31)) return QUASAR_ERR_SHAPE;   // the kernel splits tiles in 32 bits
-        p.deal = deal_phase(p.T, p.K, G);
+        p.deal = deal_phase(MP, w16, a8, p.T, p.K, G);
         int xs, sc, ac;
         plan_phase(p, MP, w16, a8, G, xs, sc, ac);
         p.xs_bytes = xs;
@@ -1465,7 +1473,7 @@ static int sequence_prepare_impl(const quasar_linear_desc *linears, int64_t n_li
     h.has_verify = verify ? 1 : 0; h.n_linears = (int)n_linears; h.a8 = a8 ? 1 : 0;
     h.n_barriers = 0; h.n_flag_waits = 0; h.deals = 0;
     for (const SeqPhase &p : phases) {
-        if (p.deal) h.deals = 1;
+        if (p.deal && roles == 1) h.deals = 1;
         if (p.wait == SEQ_WAIT_BARRIER) ++h.n_barriers;
         if (p.wait == SEQ_WAIT_FLAGS) ++h.n_flag_waits;
     }
@@ -1527,12 +1535,12 @@ static int sequence_run_impl(const quasar_sequence *seq, const void *plan_device
     if (h.w16) {
         if (h.MP == 8) return QUASAR_SEQUENCE(8, true, false);
         if (h.MP == 16) return QUASAR_SEQUENCE(16, true, false);
-        return QUASAR_SEQUENCE(32, true, false);
+        return launch_sequence<32, true, false, 1>(h, sp, st);
     }
     if (h.a8) {
         if (h.MP == 8) return QUASAR_SEQUENCE(8, false, true);
         if (h.MP == 16) return QUASAR_SEQUENCE(16, false, true);
-        return QUASAR_SEQUENCE(32, false, true);
+        return launch_sequence<32, false, true, 1>(h, sp, st);
     }
     if (h.MP == 8) return QUASAR_SEQUENCE(8, false, false);
 #undef QUASAR_SEQUENCE

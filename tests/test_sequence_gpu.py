@@ -456,3 +456,69 @@ def test_sequence_of_independent_linears_takes_the_alternating_form(qb):
             assert torch.equal(one.view(torch.int16), ys[i].view(torch.int16)), (w8a8, i)
             if w8a8:
                 assert np.array_equal(bf16_to_host(ys[i]), a8.w8a8_linear(bf16_to_host(xs[i]), ws[i][0][0], ws[i][0][1])), i
+
+
+# (tiles of gate and up are no multiple of the workgroups: up begins inside a round, the last round is not full; so does the vocabulary's)
+@pytest.mark.parametrize("fmt,M,hidden,inter,vocab,dealt", [
+    ("int8", 5, 3072, 6208, 869, True),
+    ("bf16", 3, 3072, 6208, 869, True),
+    ("bf16", 16, 3072, 6208, 869, True),
+    ("w8a8", 8, 3072, 6208, 869, True),
+    ("w8a8", 13, 3072, 6208, 869, True),
+    ("bf16", 4, 2048, 2112, 2053, True),      # the vocabulary alone
+    ("int8", 8, 2048, 2112, 2053, False),     # (and where contiguous shares are faster)
+    ("int8", 16, 3072, 6208, 869, False),
+    ("bf16", 32, 3072, 6208, 869, False),
+    ("w8a8", 17, 3072, 6208, 869, False),
+])
+def test_sequence_of_dealt_phases_same_bits(qb, fmt, M, hidden, inter, vocab, dealt):
+    """Phases whose tiles are dealt round by round, against the single calls: identical bits, on 256 compute units."""
+    print("sequence dealt", fmt, M, hidden, inter, vocab, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(9500 + M)
+    V, n_layers = 16 * vocab, 2
+
+    def packed(N, K):
+        w = torch.randn((N, K), generator=gen, device="cuda") / K ** 0.5
+        return (qb.pack_bf16_weights(w), None) if fmt == "bf16" else qb.quantize_weights(w)
+
+    layers = [{name: (*packed(N, K), N) for name, K, N in layer_shapes(hidden, 512, inter)} for _ in range(n_layers)]
+    head = packed(V, hidden)
+    x0 = torch.randn((M, hidden), generator=gen, device="cuda").to(torch.bfloat16)
+    draft = torch.arange(M - 1, dtype=torch.int32, device="cuda")
+
+    def chain():
+        h, linears = x0, []
+        for lin in layers:
+            y = {n: torch.full((M, lin[n][2]), float("nan"), dtype=torch.bfloat16, device="cuda") for n in lin}
+            for n, x in (("q", h), ("k", h), ("v", h), ("o", y["q"]), ("gate", y["o"]), ("up", y["o"]), ("down", y["gate"])):
+                linears.append((x, *lin[n], y[n]))
+            h = y["down"]
+        return linears, h
+
+    linears, h = chain()
+    am = torch.full((M,), -1, dtype=torch.int32, device="cuda")
+    acc = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    seq = qb.Sequence(linears, verify=(h, *head, V, draft, am, acc), w8a8=fmt == "w8a8")
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert seq.handle.words[15] == dealt
+    for _ in range(3):                        # (the second and third run reuse the flags of new epochs)
+        for lin in linears:
+            lin[4].fill_(float("nan"))
+        seq.run()
+    torch.cuda.synchronize()
+    assert not seq.timed_out()
+    single, h1 = chain()
+    for x, wp, sc, N, y in single:
+        if fmt == "bf16":
+            qb.bf16_linear(x, wp, N, y)
+        else:
+            (qb.w8a8_linear if fmt == "w8a8" else qb.w8_linear)(x, wp, sc, N, y=y)
+    ws = qb.make_workspace(M, V, hidden)
+    if fmt == "bf16":
+        am1, acc1 = qb.bf16_lmhead_verify(h1, head[0], V, draft, ws)
+    else:
+        am1, acc1 = (qb.w8a8_lmhead_verify if fmt == "w8a8" else qb.lmhead_verify)(h1, *head, V, draft, ws)
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(linears, single)):
+        assert not torch.isnan(b[4]).any() and torch.equal(a[4].view(torch.int16), b[4].view(torch.int16)), i
+    assert torch.equal(am, am1) and torch.equal(acc, acc1)
