@@ -16,31 +16,29 @@
 namespace quasar {
 
 struct GemmParams {
-    // (what the register-resident kernels read ahead of their first load comes first, side by side: loaded_together)
+    // (what the staged kernels read ahead of their first load lies in the first 128 bytes, in this order: with the shares of the kernels
+    // below in among it a staged call took 0.15 us longer eagerly - bf16, M = 8 1024 x 192 4.47, 4.64, 4096 x 2560 7.77, 7.92,
+    // 12288 x 3584 16.9, 17.1; the others are the same either way)
     const uint16_t *x;       // [M, K] bf16, row stride ldx
     long long ldx;
     const u32x4 *w;          // packed weights, 64 x 16 B per step, steps of a tile contiguous
     const uint16_t *scales;  // [N] bf16 step sizes (nullptr for bf16 weights)
-    int M;
-    int S;          // steps per tile (K/64 for int8, K/32 for bf16 weights)
-    int Srow;       // steps per tile in memory (= S unless the workgroup works on a K slice)
-    int slice_steps;         // of a K slice, see ksplit
-    // the kernels of stream_direct*.hpp and stream_outer.hpp: units of tiles of a workgroup, units left over, workgroups that share the
-    // tiles, the first unit left over, and how workgroups lie in the XCDs (TileShare)
-    int tq, tr, groups, rest, xcd_mask, xcd_shift;
-    int sc_bytes;   // LDS bytes reserved for the workgroup's row scales
-    int SC;         // steps per K chunk (activations of one chunk fit in LDS)
-    int C;          // number of K chunks
-    int T;          // number of 16-row tiles
-    int N, K;
-    int xs_bytes;   // LDS bytes reserved for the activation chunk
     uint16_t *y;             // [M, N] bf16, row stride ldy          (linear epilogue)
     long long ldy;
-    unsigned long long *partial;  // [gridDim.x][MP] packed (logit, index) keys  (argmax epilogue)
+    unsigned long long *partial;  // [workgroups][MP] packed (logit, index) keys  (argmax epilogue)
+    int M, N, K;
+    int T;          // number of 16-row tiles
+    int S;          // steps per tile (K/64 for int8, K/32 for bf16 weights)
+    int SC;         // steps per K chunk (activations of one chunk fit in LDS)
+    int C;          // number of K chunks
+    int xs_bytes;   // LDS bytes reserved for the activation chunk
+    int sc_bytes;   // LDS bytes reserved for the workgroup's row scales
     const float *smooth;   // [K] per-channel smoothing factors of the W8A8 path (nullptr: none)
+    int Srow;       // steps per tile in memory (= S unless the workgroup works on a K slice)
     // K split across workgroups (linears only): slice_steps of K for each of ksplit groups of workgroups, which write fp32 partial
     // sums, part32[slice][m][n]
     int ksplit;
+    int slice_steps;
     float *part32;
     // fused operations around the linear (stream_mfma_kernel with PRE / RES):
     const uint16_t *pre_arg;   // PRE_RMSNORM: gamma [K] bf16
@@ -52,6 +50,9 @@ struct GemmParams {
     float *soft_stats;
     float inv_t;
     const float *dx;           // step sizes of the activation codes (stream_outer.hpp), [M]
+    // the kernels of stream_direct*.hpp and stream_outer.hpp: units of tiles of a workgroup, units left over, workgroups that share the
+    // tiles, the first unit left over, and how workgroups lie in the XCDs (TileShare)
+    int tq, tr, groups, rest, xcd_mask, xcd_shift;
 };
 
 // Operation applied to the activations while they are staged (the normalisation in front of
