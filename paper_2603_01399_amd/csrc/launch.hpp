@@ -155,15 +155,18 @@ enum { FMT_INT8 = 0, FMT_BF16 = 1, FMT_W4 = 2, FMT_A8 = 3 };
 
 // Whether the workgroups of a register-resident form (XS slots a wave of NW) are dealt their tiles (TileShare).  Contiguous shares keep
 // 256 streams some MB apart open, which costs address translation and leaves some XCDs behind the others by a tenth of a
-// long stream.  us, contiguous, dealt, M = 8 unless said: vocabulary of 151936, K = 4096, int8 99.9, 94.9, W8A8 103.5, 98.2, bf16 188,
-// 183, 4-bit 53.9, 52.9, K = 2560 int8 62.4, 60.7; int8 12288 x 4096 10.17, 10.03, 16384 x 8192 23.3, 22.6, 65536 x 3072 34.7, 31.4,
-// 25600 x 5120 M = 32 26.5, 25.8; bf16 12288 x 4096 17.6, 16.8, 10240 x 4096 15.5, 14.9, M = 32 18.0, 17.3.
+// long stream.  us, contiguous, dealt, M = 8 unless said: vocabulary of 151936, K = 4096, int8 104.0, 98.5, W8A8 104.5, 97.9, bf16 195.6,
+// 187.2, 4-bit 56.7, 53.6, K = 2560 int8 67.7, 62.2, 4-bit 43.7, 44.4 (K = 3072 50.0, 46.3); int8 12288 x 4096 10.24, 10.03, 65536 x 3072 34.7,
+// 31.4, 25600 x 5120 22.6, 22.1, M = 32 26.6, 26.2, 16384 x 8192 23.4, 23.8, M = 32 28.9, 27.5; bf16 12288 x 4096 17.6, 16.9, 16384 x 8192
+// 42.6, 41.4, 12288 x 4096 M = 32 19.5, 19.0.  One or two tiles a workgroup are the same either way (int8 4096 x 4096 5.35, 5.36), but int8
+// and W8A8 of K just over 2048, up to 8 tokens: 8192 x 2112 6.26, 6.28, M = 1 5.36, 5.58, 16384 x 2112 W8A8 9.4, 9.9.
 // Short K, where a tile is a slot or two a wave, stays contiguous: int8 16384 x 1024 6.75, 7.25, 20480 x 2048 9.27, 9.44 (a
-// vocabulary of 100000 38.6, 36.2), bf16 16384 x 1024 8.53, 8.81, 65536 x 2048 40.4, 42.1; 4-bit linears of three slots and more too, whose
-// tiles are no whole number of 4 KB pages: 8192 x 8192 9.8, 10.6, 16384 x 8192 14.4, 15.0 (but 25600 x 5120 15.5, 15.2).
-constexpr bool deal_tiles(int fmt, int NW, int XS, bool argmax) {
+// vocabulary of 100000 38.6, 36.2), bf16 16384 x 1024 8.53, 8.81, 65536 x 2048 40.4, 42.1.  4-bit linears too, but those of 9 to 16 tokens and two
+// slots (25600 x 4096 13.25, 13.14, 10240 x 3072 7.95, 7.88): M = 1 12288 x 4096 7.98, 8.21, 25600 x 4096 11.83, 12.07, M = 8 12.15, 12.25, M = 32
+// 16.1, 16.1, and of three slots and more 8192 x 8192 9.8, 10.6, 16384 x 8192 14.6, 15.1, 25600 x 5120 15.8, 15.4.
+constexpr bool deal_tiles(int fmt, int MP, int NW, int XS, bool argmax) {
     const int k = (fmt == FMT_W4 ? 128 : 64) * NW * XS;      // the longest K of the form
-    if (fmt == FMT_W4) return k > 2048 && (argmax || XS == 2 * 16 / NW);
+    if (fmt == FMT_W4) return k > 2048 && (argmax || (MP == 16 && XS == 2));
     return k > 2048 || (argmax && fmt != FMT_BF16 && k > 1024);
 }
 

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
     constexpr int kSlotBytes = WL * kStepBytes;
 
     constexpr int TU = EPI == EPI_SWIGLU ? 2 : 1;   // tiles are handed out in units of TU
-    using Share = TileShare<TU, EPI != EPI_LOGITS && deal_tiles(W16 ? FMT_BF16 : FMT_INT8, NW, PAIR ? XS * KS / 64 : XS, EPI == EPI_ARGMAX),
+    using Share = TileShare<TU, EPI != EPI_LOGITS && deal_tiles(W16 ? FMT_BF16 : FMT_INT8, MP, NW, PAIR ? XS * KS / 64 : XS, EPI == EPI_ARGMAX),
                             EPI == EPI_ARGMAX || EPI == EPI_LOGITS>;
     const int slice = blockIdx.x, b = blockIdx.y;
     GemmParams p = p0;
