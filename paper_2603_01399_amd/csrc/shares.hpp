@@ -15,7 +15,9 @@ QUASAR_BOTH int tile_split(int T, int b, int G) {
     return (int)(prod / (unsigned long long)(unsigned int)G);
 }
 
-// The same shares without a division: of G workgroups each has q tiles and the first r one more (q = T / G, r = T % G).
+// Contiguous shares without a division: of G workgroups each has q tiles and the FIRST r one more (q = T / G, r = T % G), where
+// tile_split spreads those over all of them.  The two are not interchangeable: what reads by the cuts of tile_split (the sampler's
+// blocks, sample.hpp) needs them, and a vocabulary of 151936 takes 108 us cut like this and 99.9 like that.
 QUASAR_BOTH int share_begin(int q, int r, int b) { return b * q + (b < r ? b : r); }
 QUASAR_BOTH int share_count(int q, int r, int b) { return q + (b < r ? 1 : 0); }
 
