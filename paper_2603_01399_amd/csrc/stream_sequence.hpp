@@ -168,6 +168,7 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
     constexpr int XB = kSeqStageBatch;
     constexpr int NPAR = ROLES == 2 ? 1 : 2;   // copies of the cross-wave staging area
     static_assert(ROLES == 1 || ROLES == 2, "one workgroup per compute unit, or two that alternate");
+    static_assert(!DEAL || ROLES == 1, "ranks are places in the launch, and so in the XCDs, with one workgroup per compute unit only");
     static_assert((ROLES == 1 && NW == 16) || (ROLES == 2 && NW == 8), "wave count of each form");
     constexpr int GR = kSeqRefillGroup;
     static_assert(GR >= 1 && (GR & (GR - 1)) == 0 && D % GR == 0, "refill groups tile the ring");
@@ -222,10 +223,10 @@ __global__ __launch_bounds__(NW * 64, ROLES == 2 ? 4 : 1) void stream_sequence_k
         lds_barrier();
     }
     // The workgroup's tiles of a phase, t0 + i * step for i < n: contiguous, or dealt round by round, in each round the workgroups of an
-    // XCD (rk mod 8) side by side (TileShare in launch.hpp).  DEAL: some phase is dealt (the code costs a sequence without one 1 to 3 %).
+    // XCD (rk mod 8) side by side (TileShare in shares.hpp).  DEAL: some phase is dealt (the code costs a sequence without one 1 to 3 %).
     auto share_of = [&](const auto &P, int &t0, int &step, int &n) {
         if (DEAL && P.deal) {
-            t0 = ROLES == 1 && (GW & 7) == 0 ? (rk & 7) * (GW >> 3) + (rk >> 3) : rk;
+            t0 = (GW & 7) == 0 ? (rk & 7) * (GW >> 3) + (rk >> 3) : rk;
             step = GW;
             n = (P.T - t0 + GW - 1) / GW;
         } else {
