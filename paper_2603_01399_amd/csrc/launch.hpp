@@ -142,12 +142,13 @@ constexpr int a8_region_bytes(int MP, int XS) {
 // the kernel began (the first one 0.2 us: the set-up runs side by side, four waves to a SIMD).  us a launch, HBM-cold, one after the other,
 // before -> so: int8, M = 8 1024 x 4096 4.89 -> 4.50, 4096 x 4096 5.69 -> 5.32, 12288 x 4096 10.54 -> 10.20; 4-bit 4096 x 4096 5.15 -> 4.87;
 // W8A8 4096 x 4096 6.86 -> 6.65; bf16 1024 x 4096 6.33 -> 6.21.
-// (one statement: in several, the loads of the later ones wait for the first; constants need no register)
-template <class A, class B, class C, class D, class E = int, class F = int, class G = int, class H = int>
-__device__ __forceinline__ void loaded_together(A a, B b, C c, D d, E e = 0, F f = 0, G g = 0, H h = 0, int i = 0, int j = 0, int k = 0, int l = 0,
-                                                int m = 0, int n = 0, int o = 0, int q = 0) {
-    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "is"(e), "is"(f), "is"(g), "is"(h), "is"(i), "is"(j), "is"(k), "is"(l), "is"(m), "is"(n),
-                 "is"(o), "is"(q));
+// (one statement: in several, the loads of the later ones wait for the first.  What the kernel itself needs, then what its tile
+// share does; constants need no register)
+template <class Share, class A, class B, class C, class D, class E, class F = int, class G = int, class H = int, class I = int>
+__device__ __forceinline__ void loaded_together(const GemmParams &p, A a, B b, C c, D d, E e, F f = 0, G g = 0, H h = 0, I i = 0) {
+    constexpr bool deal = Share::kDeal;
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "is"(f), "is"(g), "is"(h), "is"(i), "s"(p.tq), "s"(p.tr), "is"(deal ? p.groups : 0),
+                 "is"(deal ? p.rest : 0), "is"(deal ? p.xcd_mask : 0), "is"(deal ? p.xcd_shift : 0));
 }
 
 // formats of weights and activations

@@ -61,8 +61,7 @@ __global__ __launch_bounds__(direct_waves(MP, XS) * 64) void stream_direct_kerne
                             EPI == EPI_ARGMAX || EPI == EPI_LOGITS>;
     const int slice = blockIdx.x, b = blockIdx.y;
     GemmParams p = p0;
-    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.Srow, p.slice_steps, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0,
-                    Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0, CH ? p.SC : p.sc_bytes);
+    loaded_together<Share>(p, p.x, p.ldx, p.w, p.scales, p.M, p.S, p.Srow, p.slice_steps, CH ? p.SC : p.sc_bytes);
     const int s0 = slice * p0.slice_steps;          // (all step counts here are in slots of 64 k)
     p.S = min(p0.slice_steps, p0.S - s0);
     p.w = p0.w + (long long)s0 * (64 * WL);

@@ -54,8 +54,7 @@ __global__ __launch_bounds__(1024) void stream_direct_a8_kernel(const GemmParams
     const int g = lane >> 4, mcol = lane & 15;
     const int b = blockIdx.x;
     using Share = TileShare<1, deal_tiles(FMT_A8, MP, NW, XS, EPI == EPI_ARGMAX), EPI == EPI_ARGMAX>;
-    loaded_together(p.x, p.ldx, p.w, p.scales, p.M, p.S, p.smooth, p.dx, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0, Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0,
-                    p.sc_bytes);
+    loaded_together<Share>(p, p.x, p.ldx, p.w, p.scales, p.M, p.S, p.smooth, p.dx, p.sc_bytes);
     const Share share(p, b);
     const int ntiles = share.units;
 

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(w4_waves(MP, XS) * 64) void stream_direct_w4_kernel
     const int g = lane >> 4, mcol = lane & 15;
     const int b = blockIdx.x;
     using Share = TileShare<1, deal_tiles(FMT_W4, MP, NW, XS, EPI == EPI_ARGMAX), EPI == EPI_ARGMAX>;
-    loaded_together(p.x, p.ldx, p.w, p.M, p.S, 0, 0, 0, p.tq, p.tr, Share::kDeal ? p.groups : 0, Share::kDeal ? p.rest : 0, Share::kDeal ? p.xcd_mask : 0, Share::kDeal ? p.xcd_shift : 0);
+    loaded_together<Share>(p, p.x, p.ldx, p.w, p.M, p.S);
     const Share share(p, b);
     const int ntiles = share.units;
 

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(outer_waves(MP) * 64) void stream_outer_kernel(cons
 
     const int slice = blockIdx.x, b = blockIdx.y;
     const GemmParams &p = p0;
-    loaded_together(p.x, p.w, p.scales, p.ldx, p.S, p.Srow, p.slice_steps, p.M, p.tq, p.tr);
+    loaded_together<TileShare<1, false, false>>(p, p.x, p.w, p.scales, p.ldx, p.S, p.Srow, p.slice_steps, p.M);
     const int s0 = slice * p.slice_steps;
     const int S = min(p.slice_steps, p.S - s0);
 
