@@ -740,7 +740,10 @@ constexpr int kSeqDepth2 = 12;
 constexpr int kSeqMaxLds2 = 80 * 1024 - 1280;
 constexpr int kSeqMinLds2 = 56 * 1024;
 std::atomic<int> g_seq_form{0};          // 0: choose; 1 or 2: workgroups per compute unit wanted
-constexpr int kSeqMagic = 0x51534551;   // "QSEQ"
+// "QSE" and the version of the phase table and the handle: raised whenever either or what their values mean changes, so that a plan
+// which another build of the library has prepared (a process may hold several) is refused instead of misread on the GPU.
+constexpr int kSeqMagic = 0x51534503;
+static_assert(sizeof(SeqPhase) == 288, "another table: another version in kSeqMagic");
 // Bound on any single wait inside the whole-step launch: 200 ms of the 100 MHz constant clock.  A step takes
 // about 2 ms; a wait that long means a workgroup is not running at all, and the launch then ends with the
 // error word set instead of holding the device.

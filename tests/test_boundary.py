@@ -88,6 +88,18 @@ def test_argument_validation_without_launch(qb):
     assert L.quasar_copy_stream(a, None, 1024, None) == ERR_NULL
 
 
+def test_plan_of_another_build_is_refused(qb):
+    """The phase table changes with the library; a handle names the version of its table (before there were versions: 0x51534551)."""
+    L, a = qb.lib(), ctypes.c_void_p(0x1000)          # (never dereferenced: no room is given either)
+    h = qb.SequenceHandle()
+    hp = ctypes.cast(ctypes.pointer(h), ctypes.c_void_p)
+    for magic in (0, 0x51534551):
+        # (phases, M, MP, .., grid, .., workgroups per compute unit)
+        h.words[0], h.words[1], h.words[2], h.words[3], h.words[8], h.words[10], h.words[14] = magic, 4, 8, 8, 256, 7, 1
+        assert L.quasar_sequence_run(hp, a, a, 0, None) == 2                   # QUASAR_ERR_SHAPE, not the workspace's error
+        assert L.quasar_sequence_stamps_bytes(hp) == 0
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU; asking for more exits with a message instead of running."""
     import subprocess
