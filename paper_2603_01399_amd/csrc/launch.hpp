@@ -148,7 +148,7 @@ template <class Share, class A, class B, class C, class D, class E, class F = in
 __device__ __forceinline__ void loaded_together(const GemmParams &p, A a, B b, C c, D d, E e, F f = 0, G g = 0, H h = 0, I i = 0) {
     constexpr bool deal = Share::kDeal;
     asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "is"(f), "is"(g), "is"(h), "is"(i), "s"(p.tq), "s"(p.tr), "is"(deal ? p.groups : 0),
-                 "is"(deal ? p.rest : 0), "is"(deal ? p.xcd_mask : 0), "is"(deal ? p.xcd_shift : 0));
+                 "is"(deal ? p.xcd_shift : 0));
 }
 
 // formats of weights and activations

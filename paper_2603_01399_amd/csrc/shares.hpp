@@ -35,10 +35,10 @@ struct TileShare {
         units = share_count(p.tq, p.tr, b);
         if constexpr (DEAL) {
             // behind the workgroups of the XCDs in front of its own, which have groups >> shift or one more
-            const int more = p.groups & p.xcd_mask;
-            first = TU * (share_begin(p.groups >> p.xcd_shift, more, b & p.xcd_mask) + (b >> p.xcd_shift));
+            const int mask = (1 << p.xcd_shift) - 1;
+            first = TU * (share_begin(p.groups >> p.xcd_shift, p.groups & mask, b & mask) + (b >> p.xcd_shift));
             step = TU * p.groups;
-            rest = TU * (p.rest + b);
+            rest = tq * step + TU * b;
         } else if constexpr (EVEN) {
             first = TU * tile_split(p.T / TU, b, p.groups);
             units = tile_split(p.T / TU, b + 1, p.groups) - first / TU;
@@ -59,14 +59,12 @@ inline void share_tiles(P &p, int groups, int ksplit, int TU) {
     p.groups = groups;
     p.tq = p.T / TU / groups;
     p.tr = p.T / TU % groups;
-    p.rest = p.tq * groups;
     // Workgroup b of slice s is the launch's (s + ksplit * b)th, and workgroup i of a launch lies in XCD i mod 8: those of a slice lie by turns
     // in 8 XCDs, 4 (two or six slices), 2 (four) or 1 (eight).  us, int8, shares of three, five, six and seven slices dealt without regard to
     // that, so: 16384 x 14336 M = 12 42.4, 41.4, 8192 x 25600 M = 32 42.5, 41.8, 16384 x 17408 M = 24 56.2, 54.3, 5120 x 14336 M = 24 18.0,
     // 18.0 (contiguous 42.2, 42.2, 56.1, 18.0).
     const int common = ksplit & -ksplit;     // the power of two in it
     p.xcd_shift = common >= 8 ? 0 : (common == 4 ? 1 : (common == 2 ? 2 : 3));
-    p.xcd_mask = (1 << p.xcd_shift) - 1;
 }
 
 }  // namespace quasar

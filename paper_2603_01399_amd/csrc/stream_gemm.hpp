@@ -10,15 +10,17 @@
 // one contiguous address range.
 #pragma once
 
+#include <cstddef>
+
 #include "quasar_device.hpp"
 #include "shares.hpp"
 
 namespace quasar {
 
 struct GemmParams {
-    // (what the staged kernels read ahead of their first load lies in the first 128 bytes, in this order: with the shares of the kernels
-    // below in among it a staged call took 0.15 us longer eagerly - bf16, M = 8 1024 x 192 4.47, 4.64, 4096 x 2560 7.77, 7.92,
-    // 12288 x 3584 16.9, 17.1; the others are the same either way)
+    // (What kernels read ahead of their first load, and what the staged ones read at all, lies in the first 128 bytes: each further
+    // cache line of the arguments is a trip to memory, 0.15-0.2 us of an eager call, whose arguments no cache holds yet.  us, eager, with
+    // the shares first and the rest up to 0x98, so: bf16, M = 8 1024 x 192 4.64, 4.47, 4096 x 2560 7.92, 7.75, 12288 x 3584 17.1, 16.9.)
     const uint16_t *x;       // [M, K] bf16, row stride ldx
     long long ldx;
     const u32x4 *w;          // packed weights, 64 x 16 B per step, steps of a tile contiguous
@@ -33,13 +35,17 @@ struct GemmParams {
     int C;          // number of K chunks
     int xs_bytes;   // LDS bytes reserved for the activation chunk
     int sc_bytes;   // LDS bytes reserved for the workgroup's row scales
-    const float *smooth;   // [K] per-channel smoothing factors of the W8A8 path (nullptr: none)
     int Srow;       // steps per tile in memory (= S unless the workgroup works on a K slice)
     // K split across workgroups (linears only): slice_steps of K for each of ksplit groups of workgroups, which write fp32 partial
     // sums, part32[slice][m][n]
     int ksplit;
     int slice_steps;
     float *part32;
+    // the kernels of stream_direct*.hpp and stream_outer.hpp: units of tiles of a workgroup, units left over, workgroups that share the
+    // tiles, and how workgroups lie in the XCDs (TileShare)
+    int tq, tr, groups, xcd_shift;
+    // ---- from here on beyond the first 128 bytes
+    const float *smooth;   // [K] per-channel smoothing factors of the W8A8 path (nullptr: none)
     // fused operations around the linear (stream_mfma_kernel with PRE / RES):
     const uint16_t *pre_arg;   // PRE_RMSNORM: gamma [K] bf16
     float eps;                 // PRE_RMSNORM
@@ -50,10 +56,8 @@ struct GemmParams {
     float *soft_stats;
     float inv_t;
     const float *dx;           // step sizes of the activation codes (stream_outer.hpp), [M]
-    // the kernels of stream_direct*.hpp and stream_outer.hpp: units of tiles of a workgroup, units left over, workgroups that share the
-    // tiles, the first unit left over, and how workgroups lie in the XCDs (TileShare)
-    int tq, tr, groups, rest, xcd_mask, xcd_shift;
 };
+static_assert(offsetof(GemmParams, smooth) == 128, "two cache lines of arguments (above)");
 
 // Operation applied to the activations while they are staged (the normalisation in front of
 // the linears of a decoder block, fused into the linear that consumes its result):

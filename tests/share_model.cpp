@@ -4,7 +4,7 @@
 using namespace quasar;
 
 struct Params {
-    int T, tq, tr, groups, rest, xcd_mask, xcd_shift;
+    int T, tq, tr, groups, xcd_shift;
 };
 
 template <int TU, bool DEAL, bool EVEN>
