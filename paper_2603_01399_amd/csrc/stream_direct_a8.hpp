@@ -9,9 +9,9 @@
 //
 // What bounds it: the quantiser's vector instructions (about eight per element and workgroup, 1.3 us at M = 8, K = 4096)
 // while the first weights are on their way; then the weight stream.  Back to back, HBM-cold, us a launch, staged -> this:
-//     M = 8:  4096 x 4096 11.8 -> 7.1, 12288 x 4096 17.2 -> 11.4, 4096 x 12288 28.4 -> 17.9 (12 slots: every workgroup
-//             quantises 98304 values; 20.7 with x gathered);  M = 16: 17.8 -> 8.7, 23.1 -> 12.5, 45.2 -> 29.3;  M = 32: 31.6 -> 21.5,
-//             36.0 -> 27.6.  Linears of large M x K with a workspace: stream_outer.hpp
+//     M = 8:  4096 x 4096 11.8 -> 6.4, 12288 x 4096 17.2 -> 10.4, 4096 x 12288 28.4 -> 17.9 (12 slots: every workgroup
+//             quantises 98304 values; 20.7 with x gathered);  M = 16: 17.8 -> 8.4, 23.1 -> 11.9, 45.2 -> 29.3;  M = 32: 31.6 -> 21.5,
+//             36.0 -> 27.6.  Linears of large M x K with a workspace: stream_outer.hpp (4096 x 4096, M = 32 10.1)
 #pragma once
 
 #include "launch.hpp"
